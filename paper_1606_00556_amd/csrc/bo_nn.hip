@@ -6,18 +6,18 @@
 // lane l holding A[l % 16][8 (l / 16) + j], B[8 (l / 16) + j][l % 16] for
 // j < 8, and receiving C[4 (l / 16) + j][l % 16] for j < 4).
 //
-// Convolution as an implicit GEMM.  A workgroup owns an output tile of
-// 16 (x) by 4 (y) by 4 (z) voxels = 16 rows of 16 voxels; its four wavefronts
-// take four rows each.  The input halo (18 x 6 x 6 voxels, channel-last BF16)
-// and the layer's weights are staged in LDS.  For one row and one tap the
-// product is D[n][i] = sum_k W[t][n][k] X[i + off(t)][k] with n the output
-// channel, i the voxel of the row and k the input channel, with the weights
-// as the A operand and the shifted row as the B operand, so that lane l ends
-// with output channels 4(l/16)..4(l/16)+3 of voxel l%16 and stores them as one
-// 8-byte write.  One 16x16x32 MFMA covers two taps of 16 input channels (lane
-// groups 0-1 the first tap, 2-3 the second; 27 taps padded to 28 with a zero
-// one): 14 per row.  The first layer has 2 input channels (padded to 4): one
-// MFMA covers eight taps, each lane group two of them (27 taps padded to 32).
+// Convolution as an implicit GEMM.  A workgroup owns output tiles of 16 (x) by
+// 4 (y) by 4 (z) voxels = 16 rows of 16 voxels; its four wavefronts take four
+// rows each.  The input halo (18 x 6 x 6 voxels, BF16) is staged in LDS, the
+// layer's weights stay in registers.  For one row and one tap the product is
+// D[n][i] = sum_k W[t][n][k] X[i + off(t)][k] with n the output channel, i the
+// voxel of the row and k the input channel, with the weights as the A operand
+// and the shifted row as the B operand, so that lane l ends with output
+// channels 4(l/16)..4(l/16)+3 of voxel l%16 and stores them as one 8-byte
+// write.  One 16x16x32 MFMA covers two taps of 16 input channels (lane groups
+// 0-1 the first tap, 2-3 the second; 27 taps padded to 28 with a zero one): 14
+// per row.  The first layer has 2 input channels (padded to 4): one MFMA covers
+// eight taps, each lane group two of them (27 taps padded to 32).
 //
 // Backward: the input gradient of a layer is the same convolution with the
 // kernel flipped and transposed (dX[u][c] = sum_t sum_o dZ[u - off(t)][o]
@@ -25,6 +25,8 @@
 // dW[t][c][o] = sum_v X[v + off(t)][c] dZ[v][o] is an MFMA reduction over the
 // voxels of each tile (32 voxels, two rows, per MFMA), combined across
 // workgroups in a fixed order.
+#include <cstring>
+#include <type_traits>
 #include "bo_nn.hpp"
 #include "bo_cpr.hpp"
 
@@ -36,7 +38,6 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 // eight BF16 values (16 bytes) as an MFMA operand
 __device__ __forceinline__ v8bf bf8(uint4 u) { return __builtin_bit_cast(v8bf, u); }
-__device__ __forceinline__ v8bf lds8(const uint16_t *p) { return bf8(*(const uint4 *)p); }
 
 constexpr int TX = 16, TY = 4, TZ = 4;
 constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
@@ -73,190 +74,330 @@ __device__ __forceinline__ long long voxel(const Vol &V, int b, int z, int y, in
     return (((long long)b * V.nz + z) * V.ny + y) * V.nx + x;
 }
 
-// halo of a C-channel BF16 tensor into LDS (zero outside the volume)
-template <int C>
-__device__ __forceinline__ void load_halo(const uint16_t *__restrict__ act, const Vol &V, const TileXY &T,
-                                          uint16_t *lds) {
-    constexpr int CH = C / 4;
-    for (int q = threadIdx.x; q < HV * CH; q += blockDim.x) {
-        int hv = q / CH, c4 = q % CH;
-        int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
-        int x = T.x0 + hx - 1, y = T.y0 + hy - 1, z = T.z0 + hz - 1;
-        uint2 val = make_uint2(0u, 0u);
-        if (x >= 0 && x < V.nx && y >= 0 && y < V.ny && z >= 0 && z < V.nz)
-            val = *(const uint2 *)(act + voxel(V, T.b, z, y, x) * C + 4 * c4);
-        *(uint2 *)(lds + hv * C + 4 * c4) = val;
-    }
-}
-
 __device__ __forceinline__ int halo_index(int z, int y, int x) { return (z * HY + y) * HX + x; }
+
+// The tiles a workgroup visits: each XCD owns one contiguous range of tiles
+// (workgroups are dealt to the eight XCDs round-robin), so the halos that
+// neighbouring tiles share are read from that XCD's L2.  The grid is a
+// multiple of 8.
+struct TileRange {
+    int first, last, step;
+};
+__device__ __forceinline__ TileRange tiles_of_block(int ntiles) {
+    const int x = blockIdx.x % 8, q = blockIdx.x / 8;
+    const int per = ntiles / 8, rem = ntiles % 8;
+    const int base = x * per + min(x, rem);
+    return {base + q, base + per + (x < rem ? 1 : 0), (int)gridDim.x / 8};
+}
 
 // Convolution of a CIN-channel input to 16 output channels.  W: [taps][16][CIN]
 // BF16 (27 taps and zero ones up to 28 (CIN = 16) or 32 (CIN = 4)).
 //   MODE_ACT:  out = BF16(ReLU(acc + bias))              -> act_out [v][16]
-//   MODE_OUT:  y = acc[channel 0] + bias[0]              -> y_out [v] (FP32)
+//   MODE_OUT:  y = acc[channel 0] + bias[0]              -> y_out [v] (FP32), and y_copy [v] unless NULL
 //   MODE_GRAD: out = BF16(acc) where mask[v][n] > 0, else 0 -> act_out [v][16]
+// Bound by LDS reads (14 KB per row of 16 voxels, 22 us for 2M voxels) and by
+// the activations' traffic (64 B per voxel, 25 us), not by the matrix cores
+// (11 us).  The weights therefore stay in registers over all tiles of a
+// workgroup, the halo is kept as two planes of 8 channels (16 B per voxel: the
+// 16 lanes of a row read 256 contiguous bytes, no bank conflict), the tap
+// offsets are four registers and constants, and four rows' accumulators run
+// interleaved; registers stay at 128, four workgroups per CU.  16 -> 16
+// channels over 2M voxels: 132 us with weights and offsets taken per row from
+// LDS, 49 us now (2.6 TB/s of the 128 B per voxel).
 template <int CIN, int MODE>
-__global__ void __launch_bounds__(256) k_nn_conv(Vol V, const uint16_t *__restrict__ in,
+__global__ void __launch_bounds__(256, 4) k_nn_conv(Vol V, int ntiles, const uint16_t *__restrict__ in,
                                                  const uint16_t *__restrict__ W, const float *__restrict__ bias,
                                                  const uint16_t *__restrict__ mask, uint16_t *__restrict__ act_out,
-                                                 float *__restrict__ y_out) {
-    constexpr int NT = CIN == 4 ? 32 : 28;
-    __shared__ __align__(16) uint16_t xs[HV * CIN];
-    __shared__ __align__(16) uint16_t ws[NT * 16 * CIN];
-    const TileXY T = tile_of(V, blockIdx.x);
-    load_halo<CIN>(in, V, T, xs);
-    for (int q = threadIdx.x; q < NT * 16 * CIN / 4; q += blockDim.x)
-        *(uint2 *)(ws + 4 * q) = *(const uint2 *)(W + 4 * q);
-    __syncthreads();
+                                                 float *__restrict__ y_out, float *__restrict__ y_copy) {
+    typedef typename std::conditional<CIN == 16, uint4, uint2>::type Vec;  // one plane's part of a voxel
+    constexpr int NP = CIN == 16 ? 2 : 1;                                  // planes
+    constexpr int NLD = (HV * NP + 255) / 256;
+    constexpr int NOP = CIN == 16 ? 14 : 4;                                // MFMAs per row
+    __shared__ __align__(16) Vec xs[NP * HV];
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const int i = lane % 16, g = lane / 16;
+    // A operands and LDS offsets of the taps.  CIN = 16: k = 8g + j is tap
+    // 2 tp + g / 2, input channel 8 (g % 2) + j.  CIN = 4: k = 8g + 4h + j is
+    // tap 8q + 2g + h, input channel j.  Taps past 26 have zero weights.
+    // For CIN = 16 the second tap of a pair is 1 voxel, one row less 2 or one
+    // plane less 2 rows and 2 voxels further on (0 for the padding tap): four
+    // lane offsets, the rest are constants.
+    v8bf wa[NOP];
+    int off[NOP], off2[NOP], base[4];
+    base[0] = wave * HY * HX + i + (g & 1) * HV;
+    base[1] = base[0] + (g >> 1);
+    base[2] = base[0] + (g >> 1) * (HX - 2);
+    base[3] = base[0] + (g >> 1) * (HX * HY - 2 * HX - 2);
+#pragma unroll
+    for (int q = 0; q < NOP; q++) {
+        const int t0 = CIN == 16 ? 2 * q + (g >> 1) : 8 * q + 2 * g;
+        const int ta = min(t0, 26), tb = min(t0 + 1, 26);
+        const int row0 = wave * HY * HX + i;
+        if (CIN == 16) {
+            wa[q] = bf8(*(const uint4 *)(W + (t0 * 16 + i) * 16 + 8 * (g & 1)));
+        } else {
+            off[q] = row0 + halo_index(ta / 9, (ta / 3) % 3, ta % 3);
+            off2[q] = row0 + halo_index(tb / 9, (tb / 3) % 3, tb % 3);
+            const uint2 a = *(const uint2 *)(W + (t0 * 16 + i) * 4), b = *(const uint2 *)(W + ((t0 + 1) * 16 + i) * 4);
+            wa[q] = bf8(make_uint4(a.x, a.y, b.x, b.y));
+        }
+    }
     float bv[4] = {0.f, 0.f, 0.f, 0.f};
     if (MODE != MODE_GRAD)
         for (int j = 0; j < 4; j++) bv[j] = (MODE == MODE_OUT && 4 * g + j > 0) ? 0.f : bias[4 * g + j];
-    for (int rr = 0; rr < 4; rr++) {
-        const int r = wave * 4 + rr;
-        const int ry = r % TY, rz = r / TY;
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        if (CIN == 16) {
-            // k = 8g + j: tap 2 tp + g / 2, input channel 8 (g % 2) + j
-            const int ko = 8 * (g & 1);
-#pragma unroll 2
-            for (int tp = 0; tp < 14; tp++) {
-                const int t = 2 * tp + (g >> 1);
-                const int tt = t < 27 ? t : 26;        // tap 27 has zero weights
-                const int dz = tt / 9 - 1, dy = (tt / 3) % 3 - 1, dx = tt % 3 - 1;
-                v8bf a = lds8(ws + (t * 16 + i) * 16 + ko);
-                v8bf b = lds8(xs + halo_index(rz + 1 + dz, ry + 1 + dy, i + 1 + dx) * 16 + ko);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-            }
-        } else {
-            // k = 8g + 4h + j: tap 8q + 2g + h, input channel j
+    const TileRange R = tiles_of_block(ntiles);
+    for (int tile = R.first; tile < R.last; tile += R.step) {
+        const TileXY T = tile_of(V, tile);
+        // the halo (zero outside the volume), every load in flight at once; the
+        // other workgroups of the CU cover the wait (keeping the next tile's
+        // halo in registers during the products costs more occupancy than it
+        // hides: 72 against 49 us at 2M voxels)
+        Vec ld[NLD];
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                uint2 wa[2], xb[2];
-#pragma unroll
-                for (int h = 0; h < 2; h++) {
-                    const int t = 8 * q + 2 * g + h;
-                    const int tt = t < 27 ? t : 26;    // taps 27..31 have zero weights
-                    const int dz = tt / 9 - 1, dy = (tt / 3) % 3 - 1, dx = tt % 3 - 1;
-                    wa[h] = *(const uint2 *)(ws + (t * 16 + i) * 4);
-                    xb[h] = *(const uint2 *)(xs + halo_index(rz + 1 + dz, ry + 1 + dy, i + 1 + dx) * 4);
-                }
-                v8bf a = bf8(make_uint4(wa[0].x, wa[0].y, wa[1].x, wa[1].y));
-                v8bf b = bf8(make_uint4(xb[0].x, xb[0].y, xb[1].x, xb[1].y));
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-            }
+        for (int u = 0; u < NLD; u++) {
+            const int q = threadIdx.x + 256 * u;
+            const int hv = q / NP, p = q % NP;
+            const int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
+            const int x = T.x0 + hx - 1, y = T.y0 + hy - 1, z = T.z0 + hz - 1;
+            Vec val = {};
+            if (q < NP * HV && x >= 0 && x < V.nx && y >= 0 && y < V.ny && z >= 0 && z < V.nz)
+                val = ((const Vec *)in)[voxel(V, T.b, z, y, x) * NP + p];
+            ld[u] = val;
         }
-        const int x = T.x0 + i, y = T.y0 + ry, z = T.z0 + rz;
-        if (x >= V.nx || y >= V.ny || z >= V.nz) continue;
-        const long long v = voxel(V, T.b, z, y, x);
-        if (MODE == MODE_OUT) {
-            if (g == 0) y_out[v] = acc[0] + bv[0];
-        } else {
-            uint16_t o[4];
-            if (MODE == MODE_ACT) {
-                for (int j = 0; j < 4; j++) o[j] = to_bf16(fmaxf(acc[j] + bv[j], 0.f));
-            } else {
-                uint2 mk = *(const uint2 *)(mask + v * 16 + 4 * g);
-                uint32_t mw[4] = {mk.x & 0xFFFFu, mk.x >> 16, mk.y & 0xFFFFu, mk.y >> 16};
-                for (int j = 0; j < 4; j++) o[j] = (mw[j] & 0x7FFFu) ? to_bf16(acc[j]) : (uint16_t)0;
+        __syncthreads();  // the previous tile's reads
+#pragma unroll
+        for (int u = 0; u < NLD; u++) {
+            const int q = threadIdx.x + 256 * u;
+            if (q < NP * HV) xs[(q % NP) * HV + q / NP] = ld[u];
+        }
+        __syncthreads();
+        v4f acc[4];
+#pragma unroll
+        for (int rr = 0; rr < 4; rr++) acc[rr] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < NOP; q++)
+#pragma unroll
+            for (int rr = 0; rr < 4; rr++) {
+                v8bf b;
+                if constexpr (CIN == 16) {
+                    constexpr int ahead[14] = {1, 2, 1, 1, 3, 1, 1, 2, 1, 1, 2, 1, 1, 0};
+                    const int t = 2 * q;
+                    b = bf8(xs[base[ahead[q]] + halo_index(t / 9, (t / 3) % 3, t % 3) + rr * HX]);
+                } else {
+                    const uint2 u = xs[off[q] + rr * HX], w = xs[off2[q] + rr * HX];
+                    b = bf8(make_uint4(u.x, u.y, w.x, w.y));
+                }
+                acc[rr] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[q], b, acc[rr], 0, 0, 0);
             }
-            *(uint2 *)(act_out + v * 16 + 4 * g) =
-                make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+        const int x = T.x0 + i, z = T.z0 + wave;
+        if (x >= V.nx || z >= V.nz) continue;
+        const long long v0 = voxel(V, T.b, z, T.y0, x);
+#pragma unroll
+        for (int rr = 0; rr < 4; rr++) {
+            if (T.y0 + rr >= V.ny) break;
+            const long long v = v0 + (long long)rr * V.nx;
+            if (MODE == MODE_OUT) {
+                if (g == 0) {
+                    const float y = acc[rr][0] + bv[0];
+                    y_out[v] = y;
+                    if (y_copy) y_copy[v] = y;
+                }
+            } else {
+                uint16_t o[4];
+                if (MODE == MODE_ACT) {
+                    for (int j = 0; j < 4; j++) o[j] = to_bf16(fmaxf(acc[rr][j] + bv[j], 0.f));
+                } else {
+                    uint2 mk = *(const uint2 *)(mask + v * 16 + 4 * g);
+                    uint32_t mw[4] = {mk.x & 0xFFFFu, mk.x >> 16, mk.y & 0xFFFFu, mk.y >> 16};
+                    for (int j = 0; j < 4; j++) o[j] = (mw[j] & 0x7FFFu) ? to_bf16(acc[rr][j]) : (uint16_t)0;
+                }
+                *(uint2 *)(act_out + v * 16 + 4 * g) =
+                    make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+            }
         }
     }
+}
+
+// two voxels' channel pairs (a: channels c, c+1 of the first voxel, b: of the
+// second) as one word per channel
+__device__ __forceinline__ uint32_t chan_lo(uint32_t a, uint32_t b) { return (a & 0xFFFFu) | (b << 16); }
+__device__ __forceinline__ uint32_t chan_hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xFFFF0000u); }
+
+// voxel pair (a, b) into one plane per channel (S 16-bit words apart): eight
+// channels, or the N used ones of a 4-channel voxel
+template <int S, int N>
+__device__ __forceinline__ void put_pair(uint32_t *o, const uint4 &a, const uint4 &b) {
+    constexpr int P = S / 2;
+    o[0 * P] = chan_lo(a.x, b.x); o[1 * P] = chan_hi(a.x, b.x);
+    o[2 * P] = chan_lo(a.y, b.y); o[3 * P] = chan_hi(a.y, b.y);
+    o[4 * P] = chan_lo(a.z, b.z); o[5 * P] = chan_hi(a.z, b.z);
+    o[6 * P] = chan_lo(a.w, b.w); o[7 * P] = chan_hi(a.w, b.w);
+}
+template <int S, int N>
+__device__ __forceinline__ void put_pair(uint32_t *o, const uint2 &a, const uint2 &b) {
+    o[0] = chan_lo(a.x, b.x);
+    if (N > 1) o[S / 2] = chan_hi(a.x, b.x);
 }
 
 // Weight and bias gradients of one layer: dW[t][c][o] = sum_v X[v+off(t)][c]
-// dZ[v][o], db[o] = sum_v dZ[v][o], with X the layer's CIN-channel input and
-// dZ its COUT-channel (4 or 16, zero padded) output gradient.  Each wavefront
-// accumulates 27 16x16 tiles D_t[o][c] over its rows of every tile it visits
-// and writes them to part[(block*4 + wave)][27*256 + 16].
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) k_nn_wgrad(Vol V, long long ntiles, const uint16_t *__restrict__ X,
+// dZ[v][o], db[o] = sum_v dZ[v][o], with X the layer's input (CIN channels
+// stored, CI used) and dZ its output gradient (COUT stored, CO used; channels
+// past CO are zero).  The products reduce over voxels, so both operands need 8
+// consecutive voxels of one channel per lane: the tile is transposed to one
+// plane per channel on its way into LDS (two voxels per 32-bit word).  A lane
+// then reads the ten voxels its three x-shifts cover as one 16-byte and one
+// 4-byte read and forms the middle shift with four funnel shifts; the plane
+// strides (1744 and 528 bytes) put the 16 channels of a read in distinct
+// banks.  Six wavefronts: z-shift (3) x half of the tile's rows (2), nine
+// 16x16 accumulators each; the halves meet in LDS once per workgroup, which
+// writes its sums to part[workgroup][gradient layout] (kNnPartStride apart).
+// Bound by the staging (LDS writes and the loads' latency; the next tile's
+// loads are in flight during the products).  16 -> 16 channels at 524288
+// voxels: 78 us with 16-bit LDS gathers and 27 accumulators per wavefront,
+// 18 us now.
+template <int CIN, int CI, int COUT, int CO>
+__global__ void __launch_bounds__(384) k_nn_wgrad(Vol V, int ntiles, const uint16_t *__restrict__ X,
                                                   const uint16_t *__restrict__ dZ, float *__restrict__ part) {
-    __shared__ __align__(16) uint16_t xs[HV * CIN];
-    __shared__ __align__(16) uint16_t ds[TV * COUT];
+    constexpr int PX = 24;            // halo row pitch, 16-bit words
+    constexpr int XS = 872;           // plane strides, 16-bit words
+    constexpr int DS = 264;
+    constexpr int XW = 16 * XS / 2, DW = 16 * DS / 2;
+    constexpr int CMB = 3 * 40 * 64;  // the combination at the end, 32-bit words
+    __shared__ __align__(16) uint32_t sm[XW + DW > CMB ? XW + DW : CMB];
+    uint16_t *xs = (uint16_t *)sm, *ds = (uint16_t *)(sm + XW);
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const int c = lane % 16, g = lane / 16;   // A: output channel o = c; B: input channel = c
-    v4f acc[27];
+    const int dzi = wave % 3, half = wave / 3;
+    // lanes past the used channels repeat a used one; their sums are dropped
+    const uint16_t *xb = xs + (c < CI ? c : 0) * XS + 8 * (g & 1);
+    const uint16_t *db = ds + (c < CO ? c : 0) * DS + 8 * (g & 1);
+    v4f acc[9], accb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 27; t++) acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
-    float db = 0.f;
-    for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const TileXY T = tile_of(V, (int)tile);
-        __syncthreads();  // LDS reuse
-        load_halo<CIN>(X, V, T, xs);
-        for (int q = threadIdx.x; q < TV * COUT / 4; q += blockDim.x) {
-            int tv = q / (COUT / 4), c4 = q % (COUT / 4);
-            int tx = tv % TX, ty = (tv / TX) % TY, tz = tv / (TX * TY);
-            int x = T.x0 + tx, y = T.y0 + ty, z = T.z0 + tz;
-            uint2 val = make_uint2(0u, 0u);
-            if (x < V.nx && y < V.ny && z < V.nz) val = *(const uint2 *)(dZ + voxel(V, T.b, z, y, x) * COUT + 4 * c4);
-            *(uint2 *)(ds + tv * COUT + 4 * c4) = val;
+    for (int t = 0; t < 9; t++) acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
+    const v8bf ones = bf8(make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+    const TileRange R = tiles_of_block(ntiles);
+    // voxel pairs of the X halo and of dZ per thread: (pair, group of 8 (16
+    // stored channels) or 2 channels); the next tile's are in flight while the
+    // current one is worked on
+    typedef typename std::conditional<CIN == 16, uint4, uint2>::type XVec;
+    typedef typename std::conditional<COUT == 16, uint4, uint2>::type DVec;
+    constexpr int XG = CIN == 16 ? 2 : 1, DG = COUT == 16 ? 2 : 1;
+    constexpr int NX = (HV / 2 * XG + 383) / 384, ND = (TV / 2 * DG + 383) / 384;
+    XVec xa[NX], xc[NX];
+    DVec da[ND], dc[ND];
+    auto load = [&](const TileXY &T) {
+#pragma unroll
+        for (int u = 0; u < NX; u++) {
+            const int q = threadIdx.x + 384 * u;
+            const int h = q % XG, pr = q / XG;
+            const int px = pr % (HX / 2), hy = (pr / (HX / 2)) % HY, hz = pr / (HX / 2 * HY);
+            const int x = T.x0 + 2 * px - 1, y = T.y0 + hy - 1, z = T.z0 + hz - 1;
+            const bool in = q < HV / 2 * XG && y >= 0 && y < V.ny && z >= 0 && z < V.nz;
+            const long long v = voxel(V, T.b, z, y, x);
+            XVec a = {}, b = {};
+            if (in && x >= 0 && x < V.nx) a = ((const XVec *)X)[XG * v + h];
+            if (in && x + 1 < V.nx) b = ((const XVec *)X)[XG * (v + 1) + h];
+            xa[u] = a;
+            xc[u] = b;
+        }
+#pragma unroll
+        for (int u = 0; u < ND; u++) {
+            const int q = threadIdx.x + 384 * u;
+            const int h = q % DG, pr = q / DG;
+            const int px = pr % (TX / 2), ty = (pr / (TX / 2)) % TY, tz = pr / (TX / 2 * TY);
+            const int x = T.x0 + 2 * px, y = T.y0 + ty, z = T.z0 + tz;
+            const bool in = q < TV / 2 * DG && y < V.ny && z < V.nz;
+            const long long v = voxel(V, T.b, z, y, x);
+            DVec a = {}, b = {};
+            if (in && x < V.nx) a = ((const DVec *)dZ)[DG * v + h];
+            if (in && x + 1 < V.nx) b = ((const DVec *)dZ)[DG * (v + 1) + h];
+            da[u] = a;
+            dc[u] = b;
+        }
+    };
+    if (R.first < R.last) load(tile_of(V, R.first));
+    for (int tile = R.first; tile < R.last; tile += R.step) {
+        __syncthreads();  // the previous tile's reads
+#pragma unroll
+        for (int u = 0; u < NX; u++) {
+            const int q = threadIdx.x + 384 * u;
+            const int h = q % XG, pr = q / XG;
+            const int px = pr % (HX / 2), row = pr / (HX / 2);
+            if (q < HV / 2 * XG) put_pair<XS, 2>((uint32_t *)xs + row * (PX / 2) + px + 8 * h * (XS / 2), xa[u], xc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < ND; u++) {
+            const int q = threadIdx.x + 384 * u;
+            const int h = q % DG, pr = q / DG;
+            if (q < TV / 2 * DG) put_pair<DS, 1>((uint32_t *)ds + pr + 8 * h * (DS / 2), da[u], dc[u]);
         }
         __syncthreads();
+        if (tile + R.step < R.last) load(tile_of(V, tile + R.step));
         // two rows of 16 voxels per MFMA: k = 8g + j is voxel 8 (g % 2) + j of
-        // row r0 + g / 2
-        for (int rp = 0; rp < 2; rp++) {
-            const int r = wave * 4 + 2 * rp + (g >> 1);
+        // row 2s + g / 2
+#pragma unroll
+        for (int ss = 0; ss < 4; ss++) {
+            const int r = 2 * (4 * half + ss) + (g >> 1);
             const int ry = r % TY, rz = r / TY;
-            const int vo = 8 * (g & 1);
-            // A[o = c][k]
-            uint16_t ha[8];
+            const v8bf a = bf8(*(const uint4 *)(db + r * TX));
+            if (dzi == 1) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, accb, 0, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
-                uint16_t h = c < COUT ? ds[(r * TX + vo + j) * COUT + c] : (uint16_t)0;
-                ha[j] = h;
-                db += from_bf16(h);
-            }
-            const v8bf a = bf8(make_uint4(ha[0] | ((uint32_t)ha[1] << 16), ha[2] | ((uint32_t)ha[3] << 16),
-                                          ha[4] | ((uint32_t)ha[5] << 16), ha[6] | ((uint32_t)ha[7] << 16)));
-            // fully unrolled: the 27 accumulators stay in registers
-#pragma unroll
-            for (int t = 0; t < 27; t++) {
-                const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-                uint16_t hb[8];
-#pragma unroll
-                for (int j = 0; j < 8; j++) {
-                    int hv = halo_index(rz + 1 + dz, ry + 1 + dy, vo + j + 1 + dx);
-                    hb[j] = c < CIN ? xs[hv * CIN + c] : (uint16_t)0;
-                }
-                const v8bf b = bf8(make_uint4(hb[0] | ((uint32_t)hb[1] << 16), hb[2] | ((uint32_t)hb[3] << 16),
-                                              hb[4] | ((uint32_t)hb[5] << 16), hb[6] | ((uint32_t)hb[7] << 16)));
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t], 0, 0, 0);
+            for (int dy = 0; dy < 3; dy++) {
+                const uint16_t *p = xb + ((rz + dzi) * HY + ry + dy) * PX;
+                const uint4 w = *(const uint4 *)p;
+                const uint32_t w4 = *(const uint32_t *)(p + 8);
+                const uint4 m = make_uint4(__builtin_amdgcn_alignbit(w.y, w.x, 16), __builtin_amdgcn_alignbit(w.z, w.y, 16),
+                                           __builtin_amdgcn_alignbit(w.w, w.z, 16), __builtin_amdgcn_alignbit(w4, w.w, 16));
+                acc[3 * dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf8(w), acc[3 * dy], 0, 0, 0);
+                acc[3 * dy + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf8(m), acc[3 * dy + 1], 0, 0, 0);
+                acc[3 * dy + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf8(make_uint4(w.y, w.z, w.w, w4)),
+                                                                          acc[3 * dy + 2], 0, 0, 0);
             }
         }
     }
-    // D_t[o = 4g+j][c]
-    float *out = part + (size_t)(blockIdx.x * 4 + wave) * (27 * 256 + 16);
+    // the two halves of the rows
+    __syncthreads();
+    float *cmb = (float *)sm + dzi * 40 * 64 + lane;
+    if (half == 1) {
 #pragma unroll
-    for (int t = 0; t < 27; t++)
-        for (int j = 0; j < 4; j++) out[t * 256 + (4 * g + j) * 16 + c] = acc[t][j];
-    // bias: lanes with the same c hold partial sums over different voxels
-    db += __shfl_xor(db, 16, 64);
-    db += __shfl_xor(db, 32, 64);
-    if (g == 0) out[27 * 256 + c] = db;
+        for (int t = 0; t < 9; t++)
+            for (int j = 0; j < 4; j++) cmb[(4 * t + j) * 64] = acc[t][j];
+        for (int j = 0; j < 4; j++) cmb[(36 + j) * 64] = accb[j];
+    }
+    __syncthreads();
+    if (half == 1) return;
+    // D_t[o = 4g+j][c]
+    float *out = part + (size_t)blockIdx.x * kNnPartStride;
+#pragma unroll
+    for (int t = 0; t < 9; t++)
+        for (int j = 0; j < 4; j++) {
+            const int o = 4 * g + j;
+            if (c < CI && o < CO) out[((dzi * 9 + t) * CI + c) * CO + o] = acc[t][j] + cmb[(4 * t + j) * 64];
+        }
+    if (dzi == 1 && c == 0)   // every column holds the same sum
+        for (int j = 0; j < 4; j++)
+            if (4 * g + j < CO) out[27 * CI * CO + 4 * g + j] = accb[j] + cmb[(36 + j) * 64];
 }
 
-// sum the partials in a fixed order into the flat gradient of one layer
-__global__ void k_nn_wgrad_reduce(int nparts, const float *__restrict__ part, int cin, int cout,
-                                  float *__restrict__ gW, float *__restrict__ gb) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    int nw = 27 * cin * cout;
-    if (e >= nw + cout) return;
-    int src;
-    if (e < nw) {
-        int t = e / (cin * cout), ci = (e / cout) % cin, co = e % cout;
-        src = t * 256 + co * 16 + ci;
-    } else {
-        src = 27 * 256 + (e - nw);
-    }
-    float s = 0.f;
-    for (int p = 0; p < nparts; p++) s += part[(size_t)p * (27 * 256 + 16) + src];
-    if (e < nw) gW[e] = s;
-    else gb[e - nw] = s;
+// The workgroups' gradients summed in a fixed order, all layers at once: 64
+// parameters per workgroup, eight wavefronts taking every eighth part each.
+// Bound by reading the parts once (15169 floats per workgroup of k_nn_wgrad);
+// one thread per parameter over 1024 parts took 271 us per layer, all four
+// layers take 7 us now.
+__global__ void __launch_bounds__(512) k_nn_wgrad_reduce(int nparts, const float *__restrict__ part,
+                                                         float *__restrict__ grad) {
+    __shared__ double red[8][64];
+    const int l = threadIdx.x % 64, w = threadIdx.x / 64;
+    const int e = blockIdx.x * 64 + l;
+    double s = 0.0;
+    if (e < kNnParams)
+#pragma unroll 8
+        for (int p = w; p < nparts; p += 8) s += (double)part[(size_t)p * kNnPartStride + e];
+    red[w][l] = s;
+    __syncthreads();
+    if (w != 0 || e >= kNnParams) return;
+    for (int q = 1; q < 8; q++) s += red[q][l];
+    grad[e] = (float)s;
 }
 
 // network input from FP32 pairs of channels [v][2] -> BF16 [v][4]
@@ -289,11 +430,16 @@ __global__ void __launch_bounds__(256) k_nn_loss(long long nv, const float *__re
     if (threadIdx.x == 0) lpart[blockIdx.x] = red[0];
 }
 
-__global__ void k_nn_loss_final(int nparts, const double *__restrict__ lpart, double inv_m, double *__restrict__ loss) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// the partial sums of the loss in a fixed order, one workgroup (118 us for
+// 2048 partial sums by one thread)
+__global__ void __launch_bounds__(kBlock) k_nn_loss_final(int nparts, const double *__restrict__ lpart, double inv_m,
+                                                          double *__restrict__ loss) {
+    __shared__ double red[kBlock];
     double s = 0.0;
-    for (int p = 0; p < nparts; p++) s += lpart[p];
-    *loss = s * inv_m;
+#pragma unroll 4
+    for (int p = threadIdx.x; p < nparts; p += kBlock) s += lpart[p];
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) *loss = s * inv_m;
 }
 
 // A_pp-weighted loss: R = A (y - t) on the voxels whose six neighbours lie in
@@ -348,8 +494,16 @@ __global__ void k_nn_wout(Vol V, const float *__restrict__ coef, const float *__
     *(uint2 *)(dz + 4 * j) = make_uint2((uint32_t)to_bf16((float)(scale * g)), 0u);
 }
 
+// where parameter e of the flat layout stands in the packed BF16 weights
+struct PackedNet {
+    uint16_t *wf[kNnLayers], *wb[kNnLayers];
+};
+
+// Adam, and the BF16 copies of the updated weights in the layouts of k_nn_pack
+// (each weight has one place in either; the padding stays zero)
 __global__ void k_nn_adam(int n, float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m,
-                          float *__restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2) {
+                          float *__restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2,
+                          PackedNet P) {
     int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
     float gi = g[e];
@@ -357,7 +511,23 @@ __global__ void k_nn_adam(int n, float *__restrict__ w, const float *__restrict_
     float vi = b2 * v[e] + (1.f - b2) * gi * gi;
     m[e] = mi;
     v[e] = vi;
-    w[e] = w[e] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    const float wn = w[e] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    w[e] = wn;
+    const uint16_t h = to_bf16(wn);
+    int off = 0;
+#pragma unroll
+    for (int l = 0; l < kNnLayers; l++) {
+        constexpr int chan[kNnLayers + 1] = {2, 16, 16, 16, 1};
+        const int ci = chan[l], co = chan[l + 1], nw = 27 * ci * co;
+        const int q = e - off;
+        if (q >= 0 && q < nw) {
+            const int t = q / (ci * co), k = (q / co) % ci, o = q % co;
+            const int kf = l == 0 ? 4 : 16, kb = l == kNnLayers - 1 ? 4 : 16;
+            P.wf[l][(t * 16 + o) * kf + k] = h;
+            if (l > 0) P.wb[l][((26 - t) * 16 + k) * kb + o] = h;
+        }
+        off += nw + co;
+    }
 }
 
 // BF16 weight layouts from the FP32 master W[t][ci][co] of one layer:
@@ -422,19 +592,27 @@ static bo_status nn_buffers(bo_nn *nn, const Vol &V) {
     return BO_OK;
 }
 
+// workgroups of a pass over nt tiles: a multiple of 8, at most what the chip
+// holds at once (256 CUs, four workgroups each)
+static unsigned conv_grid(long long nt, long long most = 1024) {
+    return (unsigned)(std::min<long long>((nt + 7) / 8 * 8, most));
+}
+
 // forward pass of the network on x1 (already filled); the output lands in nn->y
-bo_status nn_forward_x1(bo_nn *nn, const Vol &V, hipStream_t s) {
-    long long nt = tiles_of(V);
+// and, unless out is NULL, in out
+static bo_status nn_forward_x1(bo_nn *nn, const Vol &V, float *out, hipStream_t s) {
+    const long long nt = tiles_of(V);
     if (nt <= 0) return BO_OK;
     const float *w = nn->w.p;
-    k_nn_conv<4, MODE_ACT><<<(unsigned)nt, 256, 0, s>>>(V, nn->x1.p, nn->wf[0].p, w + layer_off(0) + 27 * 2 * 16,
-                                                        nullptr, nn->a1.p, nullptr);
-    k_nn_conv<16, MODE_ACT><<<(unsigned)nt, 256, 0, s>>>(V, nn->a1.p, nn->wf[1].p, w + layer_off(1) + 27 * 16 * 16,
-                                                         nullptr, nn->a2.p, nullptr);
-    k_nn_conv<16, MODE_ACT><<<(unsigned)nt, 256, 0, s>>>(V, nn->a2.p, nn->wf[2].p, w + layer_off(2) + 27 * 16 * 16,
-                                                         nullptr, nn->a3.p, nullptr);
-    k_nn_conv<16, MODE_OUT><<<(unsigned)nt, 256, 0, s>>>(V, nn->a3.p, nn->wf[3].p, w + layer_off(3) + 27 * 16,
-                                                         nullptr, nullptr, nn->y.p);
+    const unsigned nb = conv_grid(nt);
+    k_nn_conv<4, MODE_ACT><<<nb, 256, 0, s>>>(V, (int)nt, nn->x1.p, nn->wf[0].p, w + layer_off(0) + 27 * 2 * 16,
+                                              nullptr, nn->a1.p, nullptr, nullptr);
+    k_nn_conv<16, MODE_ACT><<<nb, 256, 0, s>>>(V, (int)nt, nn->a1.p, nn->wf[1].p, w + layer_off(1) + 27 * 16 * 16,
+                                               nullptr, nn->a2.p, nullptr, nullptr);
+    k_nn_conv<16, MODE_ACT><<<nb, 256, 0, s>>>(V, (int)nt, nn->a2.p, nn->wf[2].p, w + layer_off(2) + 27 * 16 * 16,
+                                               nullptr, nn->a3.p, nullptr, nullptr);
+    k_nn_conv<16, MODE_OUT><<<nb, 256, 0, s>>>(V, (int)nt, nn->a3.p, nn->wf[3].p, w + layer_off(3) + 27 * 16,
+                                               nullptr, nullptr, nn->y.p, out);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
@@ -464,7 +642,7 @@ bo_status nn_input_cpr(bo_nn *nn, const Grid &g, const void *rp, bool fp32, cons
     if (fp32) k_nn_input_cpr<float><<<grid_for(n), kBlock, 0, s>>>(n, (const float *)rp, s2, z, nn->x1.p);
     else k_nn_input_cpr<double><<<grid_for(n), kBlock, 0, s>>>(n, (const double *)rp, s2, z, nn->x1.p);
     BO_HIP(hipGetLastError());
-    return nn_forward_x1(nn, V, s);
+    return nn_forward_x1(nn, V, nullptr, s);
 }
 
 }  // namespace bo
@@ -520,9 +698,20 @@ extern "C" bo_status bo_nn_set_params(bo_nn *nn, const float *params, void *stre
 extern "C" bo_status bo_nn_get_params(bo_nn *nn, float *params, float *grads, void *stream) {
     if (!nn) return fail(BO_ERR_INVALID_ARG, "bo_nn_get_params: NULL handle");
     hipStream_t s = (hipStream_t)stream;
-    if (params) BO_HIP(hipMemcpyAsync(params, nn->w.p, sizeof(float) * kNnParams, hipMemcpyDeviceToHost, s));
-    if (grads) BO_HIP(hipMemcpyAsync(grads, nn->g.p, sizeof(float) * kNnParams, hipMemcpyDeviceToHost, s));
+    // through pinned memory: both copies are asynchronous and share one wait
+    constexpr size_t bytes = sizeof(float) * kNnParams;
+    if (!nn->pin) {
+        const hipError_t e = hipHostMalloc((void **)&nn->pin, 2 * bytes, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            nn->pin = nullptr;
+            return fail(BO_ERR_ALLOC, std::string("bo_nn_get_params: hipHostMalloc failed: ") + hipGetErrorString(e));
+        }
+    }
+    if (params) BO_HIP(hipMemcpyAsync(nn->pin, nn->w.p, bytes, hipMemcpyDeviceToHost, s));
+    if (grads) BO_HIP(hipMemcpyAsync(nn->pin + kNnParams, nn->g.p, bytes, hipMemcpyDeviceToHost, s));
     BO_HIP(hipStreamSynchronize(s));
+    if (params) std::memcpy(params, nn->pin, bytes);
+    if (grads) std::memcpy(grads, nn->pin + kNnParams, bytes);
     return BO_OK;
 }
 
@@ -539,45 +728,38 @@ extern "C" bo_status bo_nn_forward(bo_nn *nn, const float *in, float *out, int32
     long long nv = V.voxels();
     k_nn_input<<<grid_for(nv), kBlock, 0, s>>>(nv, in, nn->x1.p);
     BO_HIP(hipGetLastError());
-    BO_TRY(nn_forward_x1(nn, V, s));
-    BO_HIP(hipMemcpyAsync(out, nn->y.p, sizeof(float) * nv, hipMemcpyDeviceToDevice, s));
-    return BO_OK;
+    return nn_forward_x1(nn, V, out, s);
 }
 
 namespace {
 // gradients of every layer from the output gradient in nn->dz4; the loss in
 // nn->loss is copied to *loss (may be NULL); synchronises the stream
 bo_status nn_backprop(bo_nn *nn, const Vol &V, double *loss, hipStream_t s) {
-    long long nt = tiles_of(V);
-    int wblocks = (int)std::min<long long>(nt, kNnWgradBlocks);
-    BO_TRY(nn->part.alloc((size_t)wblocks * 4 * (27 * 256 + 16)));
-    float *gw = nn->g.p;
-    auto reduce = [&](int l) {
-        int ci = kNnChan[l], co = kNnChan[l + 1];
-        int n = 27 * ci * co + co;
-        k_nn_wgrad_reduce<<<grid_for(n), kBlock, 0, s>>>(wblocks * 4, nn->part.p, ci, co, gw + layer_off(l),
-                                                          gw + layer_off(l) + 27 * ci * co);
-    };
+    const long long nt = tiles_of(V);
+    const unsigned nb = conv_grid(nt), wb = conv_grid(nt, kNnWgradBlocks);
+    BO_TRY(nn->part.alloc((size_t)wb * kNnPartStride));
+    float *pt = nn->part.p;
+    const int n = (int)nt;
     // layer 4 (A3 -> y)
-    k_nn_wgrad<16, 4><<<wblocks, 256, 0, s>>>(V, nt, nn->a3.p, nn->dz4.p, nn->part.p);
-    reduce(3);
-    k_nn_conv<4, MODE_GRAD><<<(unsigned)nt, 256, 0, s>>>(V, nn->dz4.p, nn->wb[3].p, nullptr, nn->a3.p, nn->dz.p,
-                                                         nullptr);
+    k_nn_wgrad<16, 16, 4, 1><<<wb, 384, 0, s>>>(V, n, nn->a3.p, nn->dz4.p, pt + layer_off(3));
+    k_nn_conv<4, MODE_GRAD><<<nb, 256, 0, s>>>(V, n, nn->dz4.p, nn->wb[3].p, nullptr, nn->a3.p, nn->dz.p, nullptr,
+                                               nullptr);
     // layer 3 (A2 -> A3)
-    k_nn_wgrad<16, 16><<<wblocks, 256, 0, s>>>(V, nt, nn->a2.p, nn->dz.p, nn->part.p);
-    reduce(2);
-    k_nn_conv<16, MODE_GRAD><<<(unsigned)nt, 256, 0, s>>>(V, nn->dz.p, nn->wb[2].p, nullptr, nn->a2.p, nn->dzb.p,
-                                                          nullptr);
+    k_nn_wgrad<16, 16, 16, 16><<<wb, 384, 0, s>>>(V, n, nn->a2.p, nn->dz.p, pt + layer_off(2));
+    k_nn_conv<16, MODE_GRAD><<<nb, 256, 0, s>>>(V, n, nn->dz.p, nn->wb[2].p, nullptr, nn->a2.p, nn->dzb.p, nullptr,
+                                                nullptr);
     // layer 2 (A1 -> A2)
-    k_nn_wgrad<16, 16><<<wblocks, 256, 0, s>>>(V, nt, nn->a1.p, nn->dzb.p, nn->part.p);
-    reduce(1);
-    k_nn_conv<16, MODE_GRAD><<<(unsigned)nt, 256, 0, s>>>(V, nn->dzb.p, nn->wb[1].p, nullptr, nn->a1.p, nn->dz.p,
-                                                          nullptr);
+    k_nn_wgrad<16, 16, 16, 16><<<wb, 384, 0, s>>>(V, n, nn->a1.p, nn->dzb.p, pt + layer_off(1));
+    k_nn_conv<16, MODE_GRAD><<<nb, 256, 0, s>>>(V, n, nn->dzb.p, nn->wb[1].p, nullptr, nn->a1.p, nn->dz.p, nullptr,
+                                                nullptr);
     // layer 1 (X1 -> A1)
-    k_nn_wgrad<4, 16><<<wblocks, 256, 0, s>>>(V, nt, nn->x1.p, nn->dz.p, nn->part.p);
-    reduce(0);
+    k_nn_wgrad<4, 2, 16, 16><<<wb, 384, 0, s>>>(V, n, nn->x1.p, nn->dz.p, pt + layer_off(0));
+    k_nn_wgrad_reduce<<<grid_for(kNnParams, 64), 512, 0, s>>>((int)wb, pt, nn->g.p);
     BO_HIP(hipGetLastError());
-    if (loss) BO_HIP(hipMemcpyAsync(loss, nn->loss.p, sizeof(double), hipMemcpyDeviceToHost, s));
+    if (loss) {
+        const HostRead rd{nn->loss.p, sizeof(double), loss};
+        return host_reads(&rd, 1, s);
+    }
     BO_HIP(hipStreamSynchronize(s));
     return BO_OK;
 }
@@ -602,7 +784,7 @@ extern "C" bo_status bo_nn_backward(bo_nn *nn, const float *target, double *loss
     hipStream_t s = (hipStream_t)stream;
     unsigned nlb = grid_for(nv);
     k_nn_loss<<<nlb, 256, 0, s>>>(nv, nn->y.p, target, (float)(2.0 / (double)nv), nn->dz4.p, nn->lpart.p);
-    k_nn_loss_final<<<1, 64, 0, s>>>((int)nlb, nn->lpart.p, 1.0 / (double)nv, nn->loss.p);
+    k_nn_loss_final<<<1, kBlock, 0, s>>>((int)nlb, nn->lpart.p, 1.0 / (double)nv, nn->loss.p);
     return nn_backprop(nn, V, loss, s);
 }
 
@@ -619,7 +801,7 @@ extern "C" bo_status bo_nn_backward_weighted(bo_nn *nn, const float *coef, const
     unsigned nlb = grid_for(nv);
     BO_TRY(nn->wres.alloc((size_t)nv));
     k_nn_wres<<<nlb, 256, 0, s>>>(V, coef, nn->y.p, target, nn->wres.p, nn->lpart.p);
-    k_nn_loss_final<<<1, 64, 0, s>>>((int)nlb, nn->lpart.p, 1.0 / (double)interior, nn->loss.p);
+    k_nn_loss_final<<<1, kBlock, 0, s>>>((int)nlb, nn->lpart.p, 1.0 / (double)interior, nn->loss.p);
     k_nn_wout<<<nlb, kBlock, 0, s>>>(V, coef, nn->wres.p, (float)(2.0 / (double)interior), nn->dz4.p);
     return nn_backprop(nn, V, loss, s);
 }
@@ -632,8 +814,13 @@ extern "C" bo_status bo_nn_adam_step(bo_nn *nn, float lr, void *stream) {
     const float b1 = 0.9f, b2 = 0.999f;
     float c1 = (float)(1.0 - std::pow(0.9, (double)nn->step));
     float c2 = (float)(1.0 - std::pow(0.999, (double)nn->step));
+    PackedNet P;
+    for (int l = 0; l < kNnLayers; l++) {
+        P.wf[l] = nn->wf[l].p;
+        P.wb[l] = nn->wb[l].p;
+    }
     k_nn_adam<<<grid_for(kNnParams), kBlock, 0, s>>>(kNnParams, nn->w.p, nn->g.p, nn->m.p, nn->v.p, lr, b1, b2,
-                                                     1e-8f, c1, c2);
+                                                     1e-8f, c1, c2, P);
     BO_HIP(hipGetLastError());
-    return nn_pack(nn, s);
+    return BO_OK;
 }

@@ -13,7 +13,8 @@ struct Vol {
 constexpr int kNnLayers = 4;
 constexpr int kNnChan[kNnLayers + 1] = {2, 16, 16, 16, 1};
 constexpr int kNnParams = 15169;  // sum over layers of 27 c_in c_out + c_out
-constexpr int kNnWgradBlocks = 256;
+constexpr int kNnPartStride = 15184;  // one workgroup's weight-gradient sums (kNnParams, padded)
+constexpr int kNnWgradBlocks = 512;
 
 }  // namespace bo
 
@@ -36,4 +37,8 @@ struct bo_nn {
     bo::DBuf<double> lpart;                       // loss partial sums
     bo::DBuf<double> loss;                        // last loss (device)
     bo::DBuf<float> wres;                         // weighted loss: the residual A (y - t) per voxel
+    float *pin = nullptr;                         // pinned staging of bo_nn_get_params (2 kNnParams floats)
+    ~bo_nn() {
+        if (pin) (void)hipHostFree(pin);
+    }
 };

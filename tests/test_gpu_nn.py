@@ -149,6 +149,39 @@ def test_weighted_backward_matches_oracle(B):
             assert np.linalg.norm(a - e) <= 1e-2 * np.linalg.norm(e), (l, q)
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 4, 4, 16), (3, 5, 3, 17), (1, 9, 21, 33), (2, 25, 61, 83)])
+def test_passes_over_tile_edges_and_many_tiles(B, shape):
+    """Forward output and every gradient at sizes where the tiling can go wrong:
+    one voxel, one full tile, single voxels past a tile's edge, and more tiles
+    (1344) than workgroups in either pass (1024 and 512, which then take
+    several tiles each), to the bounds of the tests above; Adam's own BF16
+    copies of the weights equal a fresh packing, bit for bit."""
+    rng = np.random.default_rng(31)
+    params = cg.cnn_init(27, last_scale=1.0)
+    params = [(W, rng.standard_normal(b.shape).astype(np.float32) * 0.1) for W, b in params]
+    X = rng.standard_normal(shape + (2,))
+    T = rng.standard_normal(shape)
+    nn = B.Nn(params)
+    Y = gpu_forward(B, nn, X)
+    loss = nn.backward(to_dev(T.astype(np.float32)))
+    gl = B.nn_unflatten(nn.get()[1])
+    ge, lref = None, 0.0
+    for v in range(shape[0]):
+        ye, cache = N.forward(f64(params), X[v], emulate_bf16=True)
+        assert np.linalg.norm(Y[v] - ye[..., 0]) <= 1e-3 * np.linalg.norm(ye)
+        gv = [(a / shape[0], b / shape[0]) for a, b in N.backward(f64(params), cache, ye, T[v][..., None],
+                                                                  emulate_bf16=True)]
+        ge = gv if ge is None else [(A + a, Bb + b) for (A, Bb), (a, b) in zip(ge, gv)]
+        lref += N.mse(ye, T[v][..., None]) / shape[0]
+    assert abs(loss - lref) <= 1e-3 * lref
+    for l in range(4):
+        for q in range(2):
+            a, e = np.asarray(gl[l][q], np.float64), ge[l][q]
+            assert np.linalg.norm(a - e) <= 1e-2 * np.linalg.norm(e), (l, q)
+    nn.adam_step(1e-3)
+    assert np.array_equal(gpu_forward(B, nn, X), gpu_forward(B, B.Nn(nn.get()[0]), X))
+
+
 def test_pressure_stencil_export(B, O):
     """bo_cpr_pressure_stencil: the decoupled level-0 pressure matrix of the
     oracle (its entries in slot order, zero outside the grid), rounded to
