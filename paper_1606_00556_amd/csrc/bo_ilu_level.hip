@@ -12,13 +12,22 @@
 //
 // Schedule: in natural order (x fastest, then y, then z) a grid cell's lower
 // entries are its -x, -y and -z neighbours, all on the hyperplane i+j+k-1, so
-// the cells of one hyperplane depend only on earlier hyperplanes.  The
-// factorisation and each sweep take the nx+ny+nz-2 hyperplanes one launch at
-// a time, one thread per cell.  Rows after the grid's cells (fixed-rate
-// wells) come after every cell in natural order and may couple to each
-// other: one thread takes them in order after the last hyperplane (before
-// the first one in the backward sweep).  Each thread reads its own row's
-// blocks (72 contiguous bytes each) and writes its own row only.
+// the cells of one hyperplane depend only on earlier hyperplanes.
+//
+// Plain grid: the grid is cut into tiles of 8x8 columns, one wavefront each;
+// lane (a, b) handles layer k = s - a - b at step s, so inside a tile the
+// hyperplanes advance in registers, and the values that cross a tile edge are
+// handed over through memory as soon as they exist (see Handover below).  The
+// whole sweep is one launch whose critical path is the nx+ny+nz-2
+// hyperplanes at the latency of a step, not of a launch.
+//
+// Grid with further rows (fixed-rate wells): these come after every cell in
+// natural order and may couple to each other, and a cell row may hold blocks
+// towards them.  The factorisation and each sweep take the hyperplanes one
+// launch at a time, one thread per cell, and one thread takes the further rows
+// in order after the last hyperplane (before the first one in the backward
+// sweep).  Each thread reads its own row's blocks (72 contiguous bytes each)
+// and writes its own row only.
 #include "bo_cpr.hpp"
 
 namespace bo {
@@ -206,6 +215,497 @@ __global__ void k_nat_add_p(int npr, const double *__restrict__ dp, double *out)
     if (r < npr) out[3 * (size_t)r] = dp[r] + out[3 * (size_t)r];
 }
 
+// ---- plain grid: tiles of 8x8 columns with handed-over edges ----------------------
+constexpr int kNt = 8;                    // columns of a tile in x and in y
+constexpr int kCPairs = 32, kFPairs = 14, kBPairs = 19;
+struct NatGeom {
+    int nx, ny, nz, ntx, nty, ns, M;
+    __host__ __device__ int tiles() const { return ntx * nty; }
+    __host__ __device__ size_t slots() const { return (size_t)ntx * nty * ns * 64; }
+    __host__ __device__ size_t hand() const { return (size_t)ntx * nty * M * kNt; }  // cells per direction
+};
+// Packed blocks, as double2 pairs in (tile, step, pair, lane) order (1 KB per
+// wavefront load).  C, 32 pairs a slot: [A_ii | A_i,-z | A_i,-y | A_i,-x |
+// A_-z,i | A_-y,i | A_-x,i], the factorisation's input; it leaves the unit-lower
+// factors [L_-z | L_-y | L_-x] in the first 14 pairs.  Bp, 19 pairs:
+// [E^-1, pad | A_i,+x | A_i,+y | A_i,+z], blocks outside the grid zero.
+__device__ __forceinline__ size_t c_index(const NatGeom &G, int tile, int s, int lane) {
+    return ((size_t)tile * G.ns + s) * kCPairs * 64 + lane;
+}
+__device__ __forceinline__ size_t b_index(const NatGeom &G, int tile, int s, int lane) {
+    return ((size_t)tile * G.ns + s) * kBPairs * 64 + lane;
+}
+
+__global__ void __launch_bounds__(kBlock) k_nat_pack(NatGeom G, const double *__restrict__ A, double2 *__restrict__ C,
+                                                     double2 *__restrict__ Bp) {
+    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= G.slots()) return;
+    const int t = (int)(q % 64);
+    const int s = (int)((q / 64) % G.ns), tile = (int)(q / 64 / G.ns);
+    const int a = t % kNt, b = t / kNt;
+    const int i = tile % G.ntx * kNt + a, j = tile / G.ntx * kNt + b, k = s - a - b;
+    if (i >= G.nx || j >= G.ny || k < 0 || k >= G.nz) return;  // idle slot, never read
+    const size_t N = (size_t)G.nx * G.ny * G.nz;
+    const int nxy = G.nx * G.ny, g = i + G.nx * j + nxy * k;
+    double v[64], u[38];
+    auto blk = [&](bool have, int slot, int row, double *o) {
+        const double *p = A + (size_t)slot * 9 * N + (have ? row : g);
+#pragma unroll
+        for (int z = 0; z < 9; z++) o[z] = have ? p[z * N] : 0.0;
+    };
+    blk(true, S_D, g, v);
+    blk(k > 0, S_MZ, g, v + 9);
+    blk(j > 0, S_MY, g, v + 18);
+    blk(i > 0, S_MX, g, v + 27);
+    blk(k > 0, S_PZ, g - nxy, v + 36);
+    blk(j > 0, S_PY, g - G.nx, v + 45);
+    blk(i > 0, S_PX, g - 1, v + 54);
+    v[63] = 0.0;
+    blk(i + 1 < G.nx, S_PX, g, u + 10);
+    blk(j + 1 < G.ny, S_PY, g, u + 19);
+    blk(k + 1 < G.nz, S_PZ, g, u + 28);
+    u[37] = 0.0;
+    double2 *c = C + c_index(G, tile, s, t), *d = Bp + b_index(G, tile, s, t);
+#pragma unroll
+    for (int p = 0; p < kCPairs; p++) c[p * 64] = make_double2(v[2 * p], v[2 * p + 1]);
+#pragma unroll
+    for (int p = 5; p < kBPairs; p++) d[p * 64] = make_double2(u[2 * p], u[2 * p + 1]);
+}
+
+// order[q]: the tiles by ascending I + J, then I (each tile after the ones its
+// forward dependences reach)
+__global__ void k_nat_order(int ntx, int nty, int32_t *__restrict__ order) {
+    const int tile = blockIdx.x * blockDim.x + threadIdx.x;
+    if (tile >= ntx * nty) return;
+    const int I = tile % ntx, J = tile / ntx, d = I + J;
+    int pos = 0;
+    for (int q = 0; q < d; q++) pos += min(q, ntx - 1) - max(q - (nty - 1), 0) + 1;
+    order[pos + I - max(d - (nty - 1), 0)] = tile;
+}
+
+__global__ void k_nat_hand_init(size_t n, unsigned long long *__restrict__ H, unsigned long long *__restrict__ ctl,
+                                unsigned long long empty) {
+    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q < n) H[q] = empty;
+    if (q < 2) ctl[q] = 0;
+}
+
+// Handover of the values at a tile's edge.  Every edge cell has a place of its
+// own in H (the x direction first, then the y direction), written by one
+// lane and read by one lane.  A place is empty while it holds kEmpty (a
+// signalling NaN with a payload no arithmetic produces); the reader polls
+// until it holds something else and puts kEmpty back, so every sweep leaves
+// all places empty for the next one.  All accesses are relaxed 64-bit atomics
+// at agent scope (the tiles' L2s are not coherent with each other otherwise);
+// the value is its own flag, so no ordering between accesses is needed.
+// Tiles are taken from a ticket in dependence order, so a tile only ever
+// waits for tiles that workgroups already running hold.  Waiting is bounded:
+// a wavefront polls at most kSpin times in all, then goes on with what it has
+// (NaN) and marks ctl[1], which stops every later wait of this handle until
+// its next setup: the results are NaN, never a hang.
+constexpr unsigned long long kEmpty = 0x7FF4A3C15E2D9B87ull;
+constexpr int kSpin = 1 << 21;
+__device__ __forceinline__ unsigned long long hand_get(const unsigned long long *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void hand_put(unsigned long long *p, unsigned long long v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long hand_bits(double v) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    return u == kEmpty ? 0x7FF8000000000000ull : u;  // an input with kEmpty's bits passes on as another NaN
+}
+
+// one lane's view of its tile's edges: in the forward direction it takes from
+// the tiles at -x and -y and gives to +x and +y, backward the other way round
+struct NatLane {
+    int t, a, b, tile;
+    bool col;                      // a column of the grid
+    bool tx, ty, gx, gy;           // takes / gives in x / y
+    unsigned long long *Hx_t, *Hy_t, *Hx_g, *Hy_g;  // place of (step offset 0) in each role
+    int st, sg;                    // step offsets of taking and giving
+    size_t pitch;                  // words between consecutive steps
+};
+template <int K, bool FWD>
+__device__ __forceinline__ NatLane nat_lane(const NatGeom &G, const int32_t *__restrict__ order,
+                                            unsigned long long *__restrict__ H, unsigned long long *__restrict__ ctl) {
+    NatLane L;
+    L.t = threadIdx.x;
+    unsigned q = 0;
+    if (L.t == 0) q = (unsigned)(atomicAdd(ctl, 1ull) % (unsigned long long)G.tiles());
+    q = __builtin_amdgcn_readfirstlane(q);
+    L.tile = order[FWD ? q : G.tiles() - 1 - q];
+    L.a = L.t % kNt;
+    L.b = L.t / kNt;
+    const int I = L.tile % G.ntx, J = L.tile / G.ntx;
+    L.col = I * kNt + L.a < G.nx && J * kNt + L.b < G.ny;
+    const bool mx = I > 0 && L.a == 0, my = J > 0 && L.b == 0;                       // edges towards -x, -y
+    const bool px = I + 1 < G.ntx && L.a == kNt - 1, py = J + 1 < G.nty && L.b == kNt - 1;
+    L.tx = L.col && (FWD ? mx : px);
+    L.ty = L.col && (FWD ? my : py);
+    L.gx = L.col && (FWD ? px : mx);
+    L.gy = L.col && (FWD ? py : my);
+    // an edge's places belong to the tile on its lower side; cell (k, b) of an
+    // x edge stands at step m = k + b, lane b, cell (k, a) of a y edge at m =
+    // k + a, lane a
+    unsigned long long *Hy = H + G.hand() * 9;
+    L.pitch = (size_t)kNt * K;
+    auto place = [&](unsigned long long *base, int tile, int lane) { return base + ((size_t)tile * G.M * kNt + lane) * K; };
+    unsigned long long *own_x = place(H, L.tile, L.b), *own_y = place(Hy, L.tile, L.a);
+    unsigned long long *low_x = place(H, I > 0 ? L.tile - 1 : L.tile, L.b), *low_y = place(Hy, J > 0 ? L.tile - G.ntx : L.tile, L.a);
+    L.Hx_t = FWD ? low_x : own_x;
+    L.Hy_t = FWD ? low_y : own_y;
+    L.Hx_g = FWD ? own_x : low_x;
+    L.Hy_g = FWD ? own_y : low_y;
+    L.st = FWD ? 0 : kNt - 1;      // m = s - st when taking, s - sg when giving
+    L.sg = FWD ? kNt - 1 : 0;
+    return L;
+}
+__device__ __forceinline__ bool nat_active(const NatGeom &G, const NatLane &L, int s) {
+    const int k = s - L.a - L.b;
+    return L.col && k >= 0 && k < G.nz;
+}
+template <int K>
+struct Hand {
+    unsigned long long x[K], y[K];
+};
+// first look at the places of step s (lanes that take nothing look at place 0)
+template <int K>
+__device__ __forceinline__ void hand_look(const NatGeom &G, const NatLane &L, int s, Hand<K> &h) {
+    const bool act = nat_active(G, L, s);
+    const size_t o = act ? (size_t)(s - L.st) * L.pitch : 0;
+    const unsigned long long *px = L.Hx_t + (L.tx ? o : 0), *py = L.Hy_t + (L.ty ? o : 0);
+#pragma unroll
+    for (int z = 0; z < K; z++) {
+        h.x[z] = hand_get(px + z);
+        h.y[z] = hand_get(py + z);
+    }
+}
+// wait until every value the wavefront takes at step s is there, empty the
+// places, and leave zeros in the lanes that take nothing
+template <int K>
+__device__ __forceinline__ void hand_take(const NatGeom &G, const NatLane &L, int s, Hand<K> &h, int &spin,
+                                          unsigned long long *__restrict__ ctl) {
+    const bool act = nat_active(G, L, s);
+    const bool tx = act && L.tx, ty = act && L.ty;
+    auto missing = [&]() {
+        bool m = false;
+#pragma unroll
+        for (int z = 0; z < K; z++) m = m || (tx && h.x[z] == kEmpty) || (ty && h.y[z] == kEmpty);
+        return m;
+    };
+    while (__any(missing())) {
+        if (spin <= 0) {
+            if (L.t == 0) hand_put(ctl + 1, 1ull);
+            break;
+        }
+        spin--;
+        hand_look<K>(G, L, s, h);
+    }
+    const size_t o = act ? (size_t)(s - L.st) * L.pitch : 0;
+    if (tx)
+#pragma unroll
+        for (int z = 0; z < K; z++) hand_put(L.Hx_t + o + z, kEmpty);
+    if (ty)
+#pragma unroll
+        for (int z = 0; z < K; z++) hand_put(L.Hy_t + o + z, kEmpty);
+#pragma unroll
+    for (int z = 0; z < K; z++) {
+        h.x[z] = tx ? h.x[z] : 0ull;
+        h.y[z] = ty ? h.y[z] : 0ull;
+    }
+}
+template <int K>
+__device__ __forceinline__ void hand_give(const NatLane &L, int s, const double *v) {
+    const size_t o = (size_t)(s - L.sg) * L.pitch;
+    if (L.gx)
+#pragma unroll
+        for (int z = 0; z < K; z++) hand_put(L.Hx_g + o + z, hand_bits(v[z]));
+    if (L.gy)
+#pragma unroll
+        for (int z = 0; z < K; z++) hand_put(L.Hy_g + o + z, hand_bits(v[z]));
+}
+__device__ __forceinline__ double hand_val(unsigned long long u) { return __longlong_as_double((long long)u); }
+
+// Factorisation: E_i = A_ii - sum over -z, -y, -x of (A_ik E_k^-1) A_ki, one
+// wavefront per tile, the neighbours' E^-1 from the lanes of the previous step
+// or handed over.  Bound by the arithmetic of a step (six 3x3 products and an
+// inverse, FP64 without contraction) times the hyperplanes.
+__global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int32_t *__restrict__ order,
+                                                           double2 *__restrict__ C, double2 *__restrict__ Bp,
+                                                           unsigned long long *__restrict__ H,
+                                                           unsigned long long *__restrict__ ctl,
+                                                           int32_t *__restrict__ bad) {
+    const NatLane L = nat_lane<9, true>(G, order, H, ctl);
+    const int t = L.t;
+    int spin = hand_get(ctl + 1) ? 0 : kSpin;
+    struct Slot {
+        double v[64];
+    } R0, R1;
+    Hand<9> h;
+    double Ep[9];
+#pragma unroll
+    for (int z = 0; z < 9; z++) Ep[z] = 0.0;
+    auto fetch = [&](int s, Slot &S) {
+        const int sc = min(s, G.ns - 1);
+        // (idle lanes read a lane of the same step that is in the grid's first
+        // column or, where that is idle too, memory of the slot array: unused)
+        const double2 *c = C + c_index(G, L.tile, sc, nat_active(G, L, sc) ? t : 0);
+#pragma unroll
+        for (int p = 0; p < kCPairs; p++) {
+            const double2 d = c[p * 64];
+            S.v[2 * p] = d.x;
+            S.v[2 * p + 1] = d.y;
+        }
+    };
+    auto step = [&](int s, const Slot &S) {
+        double Ex[9], Ey[9];
+#pragma unroll
+        for (int z = 0; z < 9; z++) {
+            Ex[z] = __shfl(Ep[z], L.a > 0 ? t - 1 : t, 64);
+            Ey[z] = __shfl(Ep[z], L.b > 0 ? t - kNt : t, 64);
+        }
+        hand_take<9>(G, L, s, h, spin, ctl);
+#pragma unroll
+        for (int z = 0; z < 9; z++) {
+            Ex[z] = L.a > 0 ? Ex[z] : hand_val(h.x[z]);
+            Ey[z] = L.b > 0 ? Ey[z] : hand_val(h.y[z]);
+        }
+        if (s + 1 < G.ns) hand_look<9>(G, L, s + 1, h);
+        if (!nat_active(G, L, s)) return;
+        const double *v = S.v;
+        double E[9], lw[28], tmp[9];
+#pragma unroll
+        for (int z = 0; z < 9; z++) E[z] = v[z];
+        // absent neighbours have zero blocks and zero (never NaN) values
+        mul3(v + 9, Ep, lw);
+        mul3(lw, v + 36, tmp);
+#pragma unroll
+        for (int z = 0; z < 9; z++) E[z] = E[z] - tmp[z];
+        mul3(v + 18, Ey, lw + 9);
+        mul3(lw + 9, v + 45, tmp);
+#pragma unroll
+        for (int z = 0; z < 9; z++) E[z] = E[z] - tmp[z];
+        mul3(v + 27, Ex, lw + 18);
+        mul3(lw + 18, v + 54, tmp);
+#pragma unroll
+        for (int z = 0; z < 9; z++) E[z] = E[z] - tmp[z];
+        lw[27] = 0.0;
+        double Ei[10];
+        if (!inv3_gj(E, Ei)) {
+            atomicOr(bad, 1);
+#pragma unroll
+            for (int z = 0; z < 9; z++) Ei[z] = 0.0;
+        }
+        Ei[9] = 0.0;
+        hand_give<9>(L, s, Ei);
+        double2 *c = C + c_index(G, L.tile, s, t), *d = Bp + b_index(G, L.tile, s, t);
+#pragma unroll
+        for (int p = 0; p < kFPairs; p++) c[p * 64] = make_double2(lw[2 * p], lw[2 * p + 1]);
+#pragma unroll
+        for (int p = 0; p < 5; p++) d[p * 64] = make_double2(Ei[2 * p], Ei[2 * p + 1]);
+#pragma unroll
+        for (int z = 0; z < 9; z++) Ep[z] = Ei[z];
+    };
+    hand_look<9>(G, L, 0, h);
+    fetch(0, R0);
+    int s0 = 0;
+    for (; s0 + 2 <= G.ns; s0 += 2) {
+        fetch(s0 + 1, R1);
+        step(s0, R0);
+        fetch(s0 + 2, R0);
+        step(s0 + 1, R1);
+    }
+    if (s0 < G.ns) step(s0, R0);
+}
+
+// The sweeps: one wavefront per tile without barriers, the neighbours' values
+// by lane shuffles, the factors, the operand and a first look at the handed-over
+// values of kNatAhead steps in flight.  Sums in the row's column order.
+// Bound by the latency of a step (its products and shuffles, and a poll of
+// the other XCD's memory where the neighbour tile is not ahead) times the
+// nx+ny+nz-2 hyperplanes; one launch per hyperplane took 9.4 us each.
+constexpr int kNatAhead = 3;
+
+// forward: y_i = r_i - sum_{-z,-y,-x} L y, into yq[3][slot]
+__global__ void __launch_bounds__(64, 1) k_nat_tile_forward(NatGeom G, const int32_t *__restrict__ order,
+                                                            const double2 *__restrict__ C,
+                                                            const double *__restrict__ r, double *__restrict__ yq,
+                                                            unsigned long long *__restrict__ H,
+                                                            unsigned long long *__restrict__ ctl) {
+    const NatLane L = nat_lane<3, true>(G, order, H, ctl);
+    const int t = L.t;
+    int spin = hand_get(ctl + 1) ? 0 : kSpin;
+    const size_t S = G.slots();
+    const size_t g0 = (size_t)(L.tile % G.ntx * kNt + L.a) + (size_t)G.nx * (L.tile / G.ntx * kNt + L.b);
+    struct Slot {
+        double f[28], r[3];
+        Hand<3> h;
+    } ring[kNatAhead];
+    auto fetch = [&](int s, Slot &Q) {
+        const int sc = min(s, G.ns - 1);
+        const bool act = nat_active(G, L, sc);
+        const double2 *c = C + c_index(G, L.tile, sc, act ? t : 0);
+#pragma unroll
+        for (int p = 0; p < kFPairs; p++) {
+            const double2 d = c[p * 64];
+            Q.f[2 * p] = d.x;
+            Q.f[2 * p + 1] = d.y;
+        }
+        const double *rg = r + 3 * (act ? g0 + (size_t)(sc - L.a - L.b) * G.nx * G.ny : 0);
+        Q.r[0] = rg[0]; Q.r[1] = rg[1]; Q.r[2] = rg[2];
+        hand_look<3>(G, L, sc, Q.h);
+    };
+    double yp[3] = {0.0, 0.0, 0.0};
+    auto step = [&](int s, Slot &Q) {
+        double yx[3], yy[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            yx[c] = __shfl(yp[c], L.a > 0 ? t - 1 : t, 64);
+            yy[c] = __shfl(yp[c], L.b > 0 ? t - kNt : t, 64);
+        }
+        hand_take<3>(G, L, s, Q.h, spin, ctl);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            yx[c] = L.a > 0 ? yx[c] : hand_val(Q.h.x[c]);
+            yy[c] = L.b > 0 ? yy[c] : hand_val(Q.h.y[c]);
+        }
+        if (nat_active(G, L, s)) {
+            double u[3], v[3] = {Q.r[0], Q.r[1], Q.r[2]};
+            if (s - L.a - L.b > 0) {
+                mv3d(Q.f, yp, u);
+                for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+            }
+            mv3d(Q.f + 9, yy, u);
+            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+            mv3d(Q.f + 18, yx, u);
+            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+            for (int c = 0; c < 3; c++) yp[c] = v[c];
+            hand_give<3>(L, s, v);
+            const size_t q = ((size_t)L.tile * G.ns + s) * 64 + t;
+            yq[q] = v[0]; yq[S + q] = v[1]; yq[2 * S + q] = v[2];
+        }
+        fetch(s + kNatAhead, Q);
+    };
+#pragma unroll
+    for (int u = 0; u < kNatAhead; u++) fetch(u, ring[u]);
+    for (int s0 = 0; s0 < G.ns; s0 += kNatAhead)
+#pragma unroll
+        for (int u = 0; u < kNatAhead; u++)
+            if (s0 + u < G.ns) step(s0 + u, ring[u]);
+}
+
+// backward: x_i = E_i^-1 (y_i - sum_{+x,+y,+z} A x), out = x + (dp, 0, 0) in
+// natural order (dp may be NULL)
+__global__ void __launch_bounds__(64, 1) k_nat_tile_backward(NatGeom G, const int32_t *__restrict__ order,
+                                                             const double2 *__restrict__ Bp,
+                                                             const double *__restrict__ yq,
+                                                             const double *__restrict__ dp, double *__restrict__ out,
+                                                             unsigned long long *__restrict__ H,
+                                                             unsigned long long *__restrict__ ctl) {
+    const NatLane L = nat_lane<3, false>(G, order, H, ctl);
+    const int t = L.t;
+    int spin = hand_get(ctl + 1) ? 0 : kSpin;
+    const size_t S = G.slots();
+    const size_t g0 = (size_t)(L.tile % G.ntx * kNt + L.a) + (size_t)G.nx * (L.tile / G.ntx * kNt + L.b);
+    const bool last_x = L.a == kNt - 1, last_y = L.b == kNt - 1;
+    struct Slot {
+        double f[38], y[3], d;
+        Hand<3> h;
+    } ring[kNatAhead];
+    auto fetch = [&](int s, Slot &Q) {
+        const int sc = max(s, 0);
+        const bool act = nat_active(G, L, sc);
+        const int tl = act ? t : 0;
+        const double2 *c = Bp + b_index(G, L.tile, sc, tl);
+#pragma unroll
+        for (int p = 0; p < kBPairs; p++) {
+            const double2 d = c[p * 64];
+            Q.f[2 * p] = d.x;
+            Q.f[2 * p + 1] = d.y;
+        }
+        const size_t q = ((size_t)L.tile * G.ns + sc) * 64 + tl;
+        Q.y[0] = yq[q]; Q.y[1] = yq[S + q]; Q.y[2] = yq[2 * S + q];
+        Q.d = dp ? dp[act ? g0 + (size_t)(sc - L.a - L.b) * G.nx * G.ny : 0] : 0.0;
+        hand_look<3>(G, L, sc, Q.h);
+    };
+    double xp[3] = {0.0, 0.0, 0.0};
+    auto step = [&](int s, Slot &Q) {
+        double xx[3], xy[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            xx[c] = __shfl(xp[c], last_x ? t : t + 1, 64);
+            xy[c] = __shfl(xp[c], last_y ? t : t + kNt, 64);
+        }
+        hand_take<3>(G, L, s, Q.h, spin, ctl);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            xx[c] = last_x ? hand_val(Q.h.x[c]) : xx[c];
+            xy[c] = last_y ? hand_val(Q.h.y[c]) : xy[c];
+        }
+        if (nat_active(G, L, s)) {
+            double u[3], v[3] = {Q.y[0], Q.y[1], Q.y[2]};
+            mv3d(Q.f + 10, xx, u);
+            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+            mv3d(Q.f + 19, xy, u);
+            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+            mv3d(Q.f + 28, xp, u);
+            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+            mv3d(Q.f, v, xp);
+            hand_give<3>(L, s, xp);
+            double *o = out + 3 * (g0 + (size_t)(s - L.a - L.b) * G.nx * G.ny);
+            o[0] = dp ? Q.d + xp[0] : xp[0];
+            o[1] = xp[1];
+            o[2] = xp[2];
+        }
+        fetch(s - kNatAhead, Q);
+    };
+    const int e = G.ns - 1;
+#pragma unroll
+    for (int u = 0; u < kNatAhead; u++) fetch(e - u, ring[u]);
+    for (int s0 = e; s0 >= 0; s0 -= kNatAhead)
+#pragma unroll
+        for (int u = 0; u < kNatAhead; u++)
+            if (s0 - u >= 0) step(s0 - u, ring[u]);
+}
+
+NatGeom nat_geom(const Grid &g) {
+    NatGeom G;
+    G.nx = g.nx; G.ny = g.ny; G.nz = g.nz;
+    G.ntx = (g.nx + kNt - 1) / kNt;
+    G.nty = (g.ny + kNt - 1) / kNt;
+    G.ns = g.nz + 2 * (kNt - 1);
+    G.M = g.nz + kNt - 1;
+    return G;
+}
+
+// factorisation of a plain grid from the operator's slot arrays
+bo_status nat_tile_launch(bo_cpr *pc, hipStream_t s) {
+    const NatGeom G = nat_geom(pc->g);
+    const size_t S = G.slots(), nh = 2 * 9 * G.hand();
+    BO_TRY(pc->nat_c.alloc(S * kCPairs));
+    BO_TRY(pc->nat_b.alloc(S * kBPairs));
+    BO_TRY(pc->nat_y.alloc(3 * S));
+    BO_TRY(pc->nat_hand.alloc(nh + 2));
+    BO_TRY(pc->nat_perm.alloc(G.tiles()));
+    unsigned long long *H = pc->nat_hand.p, *ctl = H + nh;
+    k_nat_pack<<<grid_for((long long)S), kBlock, 0, s>>>(G, pc->A.p, pc->nat_c.p, pc->nat_b.p);
+    k_nat_order<<<grid_for(G.tiles()), kBlock, 0, s>>>(G.ntx, G.nty, pc->nat_perm.p);
+    k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty);
+    k_nat_tile_factor<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, H, ctl, pc->fflag.p);
+    BO_HIP(hipGetLastError());
+    return BO_OK;
+}
+
+bo_status nat_tile_apply(bo_cpr *pc, const double *r, const double *dp, double *out, hipStream_t s) {
+    const NatGeom G = nat_geom(pc->g);
+    unsigned long long *H = pc->nat_hand.p, *ctl = H + 2 * 9 * G.hand();
+    k_nat_tile_forward<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, r, pc->nat_y.p, H, ctl);
+    k_nat_tile_backward<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_b.p, pc->nat_y.p, dp, out, H, ctl);
+    BO_HIP(hipGetLastError());
+    return BO_OK;
+}
+
 }  // namespace
 
 // Factorisation on stream s over the handle's BSR copy (Arp, Aci, Aval); it
@@ -217,6 +717,7 @@ bo_status nat_launch(bo_cpr *pc, hipStream_t s) {
     const int n = pc->n, N = (int)g.n();
     if (!pc->has_grid || pc->ncell != N || n < N)
         return fail(BO_ERR_UNSUPPORTED, "F stage: the natural-order ILU needs a grid without matrix cells");
+    if (!pc->general) return nat_tile_launch(pc, s);
     const int nl = g.nx + g.ny + g.nz - 2;
     pc->nat_lptr.assign(nl + 1, 0);
     for (int l = 0; l < nl; l++) {
@@ -251,6 +752,7 @@ bo_status nat_launch(bo_cpr *pc, hipStream_t s) {
 
 // out = F(r) (+ (dp, 0, 0) on the pressure rows when dp != NULL); out may be r
 bo_status nat_apply(bo_cpr *pc, const double *r, const double *dp, double *out, hipStream_t s) {
+    if (!pc->general) return nat_tile_apply(pc, r, dp, out, s);
     const int n = pc->n, N = (int)pc->g.n();
     const int nl = (int)pc->nat_lptr.size() - 1;
     const int32_t *rp = pc->Arp.p, *ci = pc->Aci.p, *perm = pc->nat_perm.p;

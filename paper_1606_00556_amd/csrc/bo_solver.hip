@@ -259,8 +259,8 @@ bo_status bo::cpr_setup_impl(const bo_bsr *A, const bo_grid *grid, const bo_cpr_
     HostRead rd{pc->flag.p, sizeof bad, &bad};
     BO_TRY(host_reads(&rd, 1, s));
     if (bad) return fail(BO_ERR_NONFINITE, "bo_cpr_setup: the matrix holds NaN or Inf");
-    // the BSR copy: the general form's operator, and the natural-order ILU's pattern
-    if (pc->general || pc->o.ftype == BO_F_ILU_NATURAL) {
+    // the BSR copy: the general form's operator (and the pattern of its natural-order ILU)
+    if (pc->general) {
         BO_TRY(pc->Arp.alloc(n + 1));
         BO_TRY(pc->Aci.alloc(A->nnzb));
         BO_TRY(pc->Aval.alloc(9 * (size_t)A->nnzb));

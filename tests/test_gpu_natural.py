@@ -193,3 +193,42 @@ def test_natural_refusals(B, O):
     with pytest.raises(B.BoError):  # the extended form: matrix cells
         B.bo_cpr_setup(device_bsr(B, drp, dci, dval), (d.nx, d.ny, d.nz, 1),
                        B.bo_cpr_default_opts(ftype=B.BO_F_ILU_NATURAL, smoother=B.BO_SMOOTH_L1))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 7), (8, 8, 3), (9, 17, 1), (17, 3, 4), (33, 25, 9), (403, 405, 2)])
+def test_natural_tiles_hand_over_every_edge(B, O, shape):
+    """The plain grid's sweeps run tile by tile (8x8 columns) with the edge
+    values handed over: one column, one full tile, single columns past a tile's
+    edge, several tiles each way, and 2601 tiles (more than the chip holds at
+    once); repeated applications, also through a captured graph's replay in a
+    solve, give the same bits, and a rebuilt handle those of a fresh one."""
+    import torch
+    nx, ny, nz = shape
+    mats = []
+    for seed in (41, 42):
+        case = cg.tiny_case(nx, ny, nz, seed=seed, step=0.01, wells=[cg.Well(0, 0, 0, nz - 1, "inj", "bhp", 3500.0)])
+        P = O.Problem(case)
+        rp, ci, val, R = O.jacobian(P)
+        mats.append((P, rp, ci, val, device_bsr(B, rp, ci, val)))
+    P, rp, ci, val, A = mats[0]
+    opc = O.Cpr(P, rp, ci, val, ftype=O.F_ILU_NATURAL, use_amg=0)
+    opts = B.bo_cpr_default_opts(ftype=B.BO_F_ILU_NATURAL, use_amg=0)
+    gpc = B.bo_cpr_setup(A, (nx, ny, nz), opts)
+    v = np.random.default_rng(8).standard_normal(3 * case.n)
+    ref = opc.fstage(v)
+    first = None
+    for _ in range(3):
+        got = run_stage(B, gpc, B.bo_cpr_fstage, v, 3 * case.n)
+        assert rel_err_parts(got, ref) <= 1e-10
+        first = got if first is None else first
+        assert np.array_equal(got, first)
+    xs = []
+    for graph in (0, 1):
+        x = torch.zeros(3 * case.n, dtype=torch.float64, device="cuda")
+        B.bo_fgmres_solve(gpc, A, to_dev(v), x, B.bo_fgmres_default_opts(graph=graph, maxit=5))
+        xs.append(to_host(x))
+    assert np.array_equal(xs[0], xs[1])
+    B.bo_cpr_update(gpc, mats[1][4])
+    fresh = B.bo_cpr_setup(mats[1][4], (nx, ny, nz), opts)
+    assert np.array_equal(run_stage(B, gpc, B.bo_cpr_fstage, v, 3 * case.n),
+                          run_stage(B, fresh, B.bo_cpr_fstage, v, 3 * case.n))
