@@ -27,6 +27,7 @@
 #include <type_traits>
 #include "bo_cpr.hpp"
 
+
 namespace bo {
 namespace {
 
@@ -356,358 +357,297 @@ __global__ void __launch_bounds__(64) k_ilu_chain(TileGeom T, double2 *__restric
     if (s0 < T.ns) step(s0, R0);
 }
 
-// One half of a slot's 36 factor values: half 0 = values 0..17 (E^{-1} and
-// the first block), half 1 = values 18..35 (the other two blocks).  In the
-// FP32 / BF16 forms the quad holding values 16..19 is read by both halves.
-template <typename T>
-struct Half {
-    T v[18];
-};
-template <int St, typename T, int H>
-__device__ __forceinline__ void load_half(const void *__restrict__ F, int tile, int ns, int s, int t, Half<T> &p) {
-    // (callers pass lane 0 for idle slots: all idle lanes of a load then hit
-    // one cache line)
-    if constexpr (St == ST_F64) {
-        const double2 *D = (const double2 *)F;
+// One slot's factors as loaded, for one sweep: FP64 forward 14 pairs (4..17:
+// a pad and the unit-lower factors -z, -y, -x), FP64 backward 18 pairs (E^-1,
+// +z, +x, +y), FP32 / BF16 9 quads (E^-1 and three blocks).
+template <int St, bool FWD>
+struct Factors {
+    typedef typename std::conditional<St == ST_F64, double2,
+                                      typename std::conditional<St == ST_F32, float4, uint2>::type>::type Raw;
+    static constexpr int kFirst = St == ST_F64 && FWD ? 4 : 0;
+    static constexpr int kCount = St == ST_F64 ? kPairs - kFirst : kQuads;
+    static constexpr int kStride = St == ST_F64 ? kPairs : kQuads;
+    Raw raw[kCount];
+    __device__ __forceinline__ void load(const Raw *__restrict__ p) {
 #pragma unroll
-        for (int i = 0; i < 9; i++) {
-            double2 d = D[pk_index(tile, ns, s, 9 * H + i, t)];
-            p.v[2 * i] = d.x;
-            p.v[2 * i + 1] = d.y;
-        }
-    } else {
-        T u[20];
+        for (int i = 0; i < kCount; i++) raw[i] = p[(kFirst + i) * 64];
+    }
+    // values 9 q .. 9 q + 8 of the slot's 36 (q = 1..3 in the FP64 forward form)
+    template <typename T>
+    __device__ __forceinline__ void block(int q, T *o) const {
 #pragma unroll
-        for (int i = 0; i < 5; i++) {
-            int qd = 4 * H + i;
-            if constexpr (St == ST_F32) {
-                float4 f = ((const float4 *)F)[pq_index(tile, ns, s, qd, t)];
-                u[4 * i] = f.x; u[4 * i + 1] = f.y; u[4 * i + 2] = f.z; u[4 * i + 3] = f.w;
+        for (int z = 0; z < 9; z++) {
+            const int v = 9 * q + z;
+            if constexpr (St == ST_F64) {
+                const int w = v - 2 * kFirst;
+                o[z] = w % 2 ? raw[w / 2].y : raw[w / 2].x;
+            } else if constexpr (St == ST_F32) {
+                const float4 f = raw[v / 4];
+                o[z] = v % 4 == 0 ? f.x : v % 4 == 1 ? f.y : v % 4 == 2 ? f.z : f.w;
             } else {
-                uint2 b = ((const uint2 *)F)[pq_index(tile, ns, s, qd, t)];
-                u[4 * i] = bf16_value(b.x & 0xFFFFu); u[4 * i + 1] = bf16_value(b.x >> 16);
-                u[4 * i + 2] = bf16_value(b.y & 0xFFFFu); u[4 * i + 3] = bf16_value(b.y >> 16);
+                const uint32_t h = v % 4 < 2 ? raw[v / 4].x : raw[v / 4].y;
+                o[z] = bf16_value(v % 2 ? h >> 16 : h & 0xFFFFu);
             }
         }
-        // half 0: values 0..17 = u[0..17]; half 1: values 18..35 = u[2..19]
-#pragma unroll
-        for (int i = 0; i < 18; i++) p.v[i] = u[i + 2 * H];
     }
-}
+};
 
-// the FP64 forward slot's -z factor (values 9..17, with value 8) into
-// p.v[8..17]: pairs 4..8 only
-__device__ __forceinline__ void load_lz(const void *__restrict__ F, int tile, int ns, int s, int t,
-                                        Half<double> &p) {
-    const double2 *D = (const double2 *)F;
-#pragma unroll
-    for (int i = 4; i < 9; i++) {
-        double2 d = D[pk_index(tile, ns, s, i, t)];
-        p.v[2 * i] = d.x;
-        p.v[2 * i + 1] = d.y;
-    }
-}
-
-// the sweep's vector operand at one slot (three arrays S apart)
-template <typename T>
-__device__ __forceinline__ void load_vec(const T *__restrict__ vec, size_t S, size_t q, T *w) {
-    w[0] = vec[q]; w[1] = vec[S + q]; w[2] = vec[2 * S + q];
-}
-
-// Sweeps: two wavefronts per tile.  Wavefront 0 loads the first half of each
-// slot's factors (E^{-1} and the -z block forward, only the -z factor in the
-// FP64 form; E^{-1} and the +z block backward) with the vector operand,
-// wavefront 1 the second half (the -y and
-// -x blocks; the +x and +y blocks), so each keeps its own steps of loads in
-// flight.  Per step, wavefront 1 multiplies its
-// blocks with the neighbours' values of the previous step (read from LDS) and
-// hands the products to wavefront 0 through LDS; wavefront 0 completes the
-// step and hands the new values back.  The products are combined in the
-// order of the one-wavefront formula, so the results do not change.  Idle
-// slots (column outside the tile or grid, layer outside 0..nz-1) load
-// nothing.
+// The sweeps: one wavefront per tile, no barrier.  Lane t = a + tile_x*b owns
+// grid column (i0+a, j0+b) and at step s handles layer k = s - a - b; the
+// neighbours' values of the previous step come by lane shuffles.  The loads of
+// AH steps are in flight: a ring of register buffers, the step loop unrolled by
+// its length, so a buffer is refilled in place once its step is done and no
+// register with a load in flight is ever copied (a copy would wait for it).
+// Every load and store is issued on every path (idle slots read lane 0's data
+// of the step, stores that have nothing to do repeat a value): the hardware
+// returns vector memory operations in order and the compiler counts them
+// statically, so one that some paths skip makes later waits take in the next
+// steps' loads too.  (With conditional output stores and two wavefronts
+// joined by two barriers a step took 1.2 us backward and 0.6 us forward,
+// one memory latency, whatever the ring's length.)
 struct SweepLane {
-    int t, a, b;
-    bool col_ok;
+    int t, a, b, ab;  // ab: first step of the column, out of reach for a lane without one
+    size_t c0;        // the column's cell in layer 0
     __device__ SweepLane(const TileGeom &G, int tile, int lane) : t(lane) {
         a = lane % G.tx;
         b = lane / G.tx;
-        int ti = tile % G.ntx, tj = tile / G.ntx;
-        col_ok = lane < G.tx * G.ty && ti * G.tx + a < G.nx && tj * G.ty + b < G.ny;
+        const int i = (tile % G.ntx) * G.tx + a, j = (tile / G.ntx) * G.ty + b;
+        const bool col_ok = lane < G.tx * G.ty && i < G.nx && j < G.ny;
+        ab = col_ok ? a + b : 1 << 30;
+        c0 = (size_t)i + (size_t)G.nx * j;
     }
-    __device__ bool active(const TileGeom &G, int s) const {
-        int k = s - a - b;
-        return col_ok && k >= 0 && k < G.nz;
+    __device__ __forceinline__ bool active(const TileGeom &G, int s) const {
+        return (unsigned)(s - ab) < (unsigned)G.nz;
     }
-    // the grid cell of an active slot (the factorisation's cell index)
-    __device__ size_t cell(const TileGeom &G, int tile, int s) const {
-        int i = (tile % G.ntx) * G.tx + a, j = (tile / G.ntx) * G.ty + b, k = s - a - b;
-        return (size_t)i + (size_t)G.nx * ((size_t)j + (size_t)G.ny * k);
+    // the grid cell of a slot (cell 0 for an idle one)
+    __device__ __forceinline__ size_t cell(const TileGeom &G, int s) const {
+        return active(G, s) ? c0 + (size_t)(s - ab) * ((size_t)G.nx * G.ny) : 0;
     }
 };
-
-// Each wavefront keeps a ring of register buffers, one per step in flight;
-// the step loop is unrolled by the ring length, so a buffer is refilled in
-// place once its step is done and no register holding a load in flight is
-// ever copied (a copy would have to wait for the load).  Every lane loads at
-// every step (idle slots and steps past the end read lane 0's data of a
-// valid step of the tile and ignore it, so the idle lanes of a load share one
-// cache line): loads that some paths skip would make the compiler wait for
-// all outstanding loads before using any of them.
-// Two steps ahead in both wavefronts: the sweeps then take about 140
-// registers and three tiles' wavefronts share a SIMD (with rings of four and
-// six steps, 248 registers and two), and the extra tiles in flight hide the
-// latency better than longer rings (measured on the 32M-cell workload, same
-// on the 500k- and 2M-cell ones).  A ring of one step (64 and 78 registers,
-// every tile of a 400x400 grid resident at once) measured the same as two.
-constexpr int kAhead0 = 2;  // wavefront 0: its factor and vector loads per step
-constexpr int kAhead1 = 2;  // wavefront 1: 9 factor loads per step
 
 // forward sweep: FP64: y = r - sum_lower L y_lower with the unit-lower
 // factors L_ik = A_ik E_k^{-1}; FP32 / BF16: w = E^{-1}(r - sum_lower A w_lower)
 // (w = E^{-1} y).  r (FP64) in natural order, read at the slot's cell and
 // rounded to T; the result in (tile, step, lane) order
-template <int St, typename T>
-__global__ void __launch_bounds__(128) k_ilu_forward(TileGeom G, const void *__restrict__ F,
-                                                     const double *__restrict__ r,
-                                                     T *__restrict__ wq) {
-    __shared__ T wsh[2][3][64];  // w of a step, by step parity
-    __shared__ T ysh[2][6][64];  // wavefront 1's products L_y w_y and L_x w_x
-    const int wv = threadIdx.x / 64;
-    const int tile = blockIdx.x;
-    const SweepLane L(G, tile, threadIdx.x % 64);
+template <int St, typename T, int AH>
+__global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__restrict__ F,
+                                                    const double *__restrict__ r, T *__restrict__ wq) {
+    typedef Factors<St, true> Fac;
+    const int tile = blockIdx.x, ns = G.ns;
+    const SweepLane L(G, tile, threadIdx.x);
     const int t = L.t;
     const size_t S = (size_t)G.slots();
-    const int ns = G.ns;
-    if (wv == 1) {
-        const int lx = L.a > 0 ? t - 1 : t, ly = L.b > 0 ? t - G.tx : t;
-        Half<T> buf[kAhead1];
-        auto fetch = [&](int s, Half<T> &h) {
-            const int sc = min(s, ns - 1);
-            load_half<St, T, 1>(F, tile, ns, sc, L.active(G, sc) ? t : 0, h);
-        };
-        auto step = [&](int s, Half<T> &h) {
-            T wy[3] = {0, 0, 0}, wx[3] = {0, 0, 0};
-            if (s > 0) {
-                const int p = (s - 1) & 1;
-                for (int c = 0; c < 3; c++) { wy[c] = wsh[p][c][ly]; wx[c] = wsh[p][c][lx]; }
-            }
-            T ya[3] = {0, 0, 0}, yb[3] = {0, 0, 0};
-            if (L.active(G, s)) {
-                mv3(h.v, wy, ya);
-                mv3(h.v + 9, wx, yb);
-            }
-            fetch(s + kAhead1, h);
-            for (int c = 0; c < 3; c++) { ysh[s & 1][c][t] = ya[c]; ysh[s & 1][3 + c][t] = yb[c]; }
-            __syncthreads();  // products of step s published
-            __syncthreads();  // w of step s published
-        };
+    const typename Fac::Raw *Ft = (const typename Fac::Raw *)F + (size_t)tile * ns * Fac::kStride * 64;
+    T *wt = wq + (size_t)tile * ns * 64 + t;
+    const int lx = L.a > 0 ? t - 1 : t, ly = L.b > 0 ? t - G.tx : t;
+    struct Slot {
+        Fac f;
+        double r[3];
+    } ring[AH];
+    auto fetch = [&](int s, Slot &Q) {
+        const int sc = min(s, ns - 1);
+        Q.f.load(Ft + (size_t)sc * Fac::kStride * 64 + (L.active(G, sc) ? t : 0));
+        const double *rg = r + 3 * L.cell(G, sc);
+        Q.r[0] = rg[0]; Q.r[1] = rg[1]; Q.r[2] = rg[2];
+    };
+    T wp[3] = {0, 0, 0};
+    auto step = [&](int s, Slot &Q) {
+        T wx[3], wy[3];
 #pragma unroll
-        for (int u = 0; u < kAhead1; u++) fetch(u, buf[u]);
-        int s0 = 0;
-        for (; s0 + kAhead1 <= ns; s0 += kAhead1) {
-#pragma unroll
-            for (int u = 0; u < kAhead1; u++) step(s0 + u, buf[u]);
+        for (int c = 0; c < 3; c++) {
+            wx[c] = __shfl(wp[c], lx, 64);
+            wy[c] = __shfl(wp[c], ly, 64);
         }
-#pragma unroll
-        for (int u = 0; u < kAhead1; u++)
-            if (s0 + u < ns) step(s0 + u, buf[u]);
-    } else {
-        T wp[3] = {0, 0, 0};
-        Half<T> buf[kAhead0];
-        T vec[kAhead0][3];
-        auto fetch = [&](int s, Half<T> &h, T *w) {
-            const int sc = min(s, ns - 1);
-            const bool act = L.active(G, sc);
-            if constexpr (St == ST_F64) load_lz(F, tile, ns, sc, act ? t : 0, h);
-            else load_half<St, T, 0>(F, tile, ns, sc, act ? t : 0, h);
-            const double *rg = r + 3 * (act ? L.cell(G, tile, sc) : 0);
-            w[0] = (T)rg[0]; w[1] = (T)rg[1]; w[2] = (T)rg[2];
-        };
-        auto step = [&](int s, Half<T> &h, T *w) {
-            __syncthreads();  // products of step s published
-            if (L.active(G, s)) {
-                T v[3] = {w[0], w[1], w[2]};
-                T y[3];
-                // zero blocks stand for missing neighbours
-                mv3(h.v + 9, wp, y); v[0] = v[0] - y[0]; v[1] = v[1] - y[1]; v[2] = v[2] - y[2];
-                v[0] = v[0] - ysh[s & 1][0][t]; v[1] = v[1] - ysh[s & 1][1][t]; v[2] = v[2] - ysh[s & 1][2][t];
-                v[0] = v[0] - ysh[s & 1][3][t]; v[1] = v[1] - ysh[s & 1][4][t]; v[2] = v[2] - ysh[s & 1][5][t];
-                if constexpr (St == ST_F64) {
-                    wp[0] = v[0]; wp[1] = v[1]; wp[2] = v[2];
-                } else {
-                    mv3(h.v, v, wp);
-                }
-            } else {
-                wp[0] = wp[1] = wp[2] = 0;
-            }
-            for (int c = 0; c < 3; c++) wsh[s & 1][c][t] = wp[c];
-            {  // idle slots store 0
-                size_t q = ((size_t)tile * ns + s) * 64 + t;
-                wq[q] = wp[0]; wq[S + q] = wp[1]; wq[2 * S + q] = wp[2];
-            }
-            fetch(s + kAhead0, h, w);
-            __syncthreads();  // w of step s published
-        };
-#pragma unroll
-        for (int u = 0; u < kAhead0; u++) fetch(u, buf[u], vec[u]);
-        int s0 = 0;
-        for (; s0 + kAhead0 <= ns; s0 += kAhead0) {
-#pragma unroll
-            for (int u = 0; u < kAhead0; u++) step(s0 + u, buf[u], vec[u]);
+        // zero blocks stand for missing neighbours
+        T A[9], y[3], v[3] = {(T)Q.r[0], (T)Q.r[1], (T)Q.r[2]};
+        Q.f.block(1, A);
+        mv3(A, wp, y); v[0] = v[0] - y[0]; v[1] = v[1] - y[1]; v[2] = v[2] - y[2];
+        Q.f.block(2, A);
+        mv3(A, wy, y); v[0] = v[0] - y[0]; v[1] = v[1] - y[1]; v[2] = v[2] - y[2];
+        Q.f.block(3, A);
+        mv3(A, wx, y); v[0] = v[0] - y[0]; v[1] = v[1] - y[1]; v[2] = v[2] - y[2];
+        if constexpr (St != ST_F64) {
+            Q.f.block(0, A);
+            mv3(A, v, y);
+            v[0] = y[0]; v[1] = y[1]; v[2] = y[2];
         }
+        const bool act = L.active(G, s);
+        T *w = wt + (size_t)s * 64;  // idle slots store 0
 #pragma unroll
-        for (int u = 0; u < kAhead0; u++)
-            if (s0 + u < ns) step(s0 + u, buf[u], vec[u]);
-    }
+        for (int c = 0; c < 3; c++) {
+            wp[c] = act ? v[c] : (T)0;
+            w[c * S] = wp[c];
+        }
+        fetch(s + AH, Q);
+    };
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(u, ring[u]);
+    for (int s0 = 0; s0 < ns; s0 += AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {
+            if (s0 + u >= ns) return;
+            step(s0 + u, ring[u]);
+        }
 }
 
 // backward sweep: FP64: x_i = E_i^{-1}(y_i - sum_{upper} A_ij x_j); FP32 /
 // BF16: x_i = w_i - E_i^{-1} sum_{upper} A_ij x_j; written in natural order as
-// out = x + (dp, 0, 0) in FP64 (dp may be NULL).
-// Output staging (D > 0, D = tile_x + tile_y - 1 layers of 64 x 3 doubles in
-// dynamic LDS): lane (a, b) finishes layer k at step k + a + b, so the layers
-// in flight at step s are s .. s + D - 1 and layer s is complete once step s
-// is.  Wavefront 0 puts each result into the layer's ring slot (k mod D);
-// wavefront 1, at the start of step s - 1 (after step s's last barrier),
-// writes layer s of the tile to HBM as tile_y rows of 3 tile_x contiguous
-// doubles, and layer 0 after the last step.  A slot is next written at step
-// s - 1 after that step's first barrier, which orders it after the write-out.
-// Without staging (D == 0) every lane writes its 24 bytes at its cell, and the
-// partial lines cost HBM writes of more than twice the output's size.
-// With zin != NULL the result is added to it: out = zin + (x + (dp, 0, 0))
-// (zin may be out itself: each cell is read and written by one thread).
-template <int St, typename T, typename TD>
-__global__ void __launch_bounds__(128) k_ilu_backward(TileGeom G, const void *__restrict__ F,
-                                                      const T *__restrict__ wq,
-                                                      const TD *__restrict__ dp, double *out,
-                                                      int D, const double *zin) {
-    __shared__ T xsh[2][3][64];  // x of a step, by step parity
-    __shared__ T ash[2][3][64];  // wavefront 1's U_x x_x + U_y x_y
+// out = x + (dp, 0, 0) in FP64 (dp may be NULL), or with ZIN added to zin: out
+// = zin + (x + (dp, 0, 0)) (zin may be out itself: each value is read and
+// written by one wavefront, the read AH steps before).
+// Output staging: lane (a, b) finishes layer k at step k + a + b, so the layers
+// in flight at step s are s .. s + D - 1 (D = tile_x + tile_y - 1) and layer s
+// is complete once step s is.  Each result goes into the layer's LDS slot (k
+// mod D, 64 x 3 doubles); step s writes layer s + 1 to HBM as tile_y rows of 3
+// tile_x contiguous doubles, three values per lane (lanes beyond the tile's or
+// the grid's columns repeat the tile's first value; up to AH - 1 steps before
+// the first finished layer write the last layer's places, in the ZIN form with
+// the values they hold).  Without staging (STAGE false, where D layers do not fit) every lane
+// writes its 24 bytes at its cell, and the partial lines cost HBM writes of more than twice the output's size.
+template <int St, typename T, typename TD, int AH, bool ZIN, bool STAGE>
+__global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__restrict__ F, T *__restrict__ wq,
+                                                     const TD *__restrict__ dp, double *out, int D,
+                                                     const double *zin) {
     extern __shared__ double obuf[];  // D slots of [lane][3]
-    const int wv = threadIdx.x / 64;
-    const int tile = blockIdx.x;
-    const SweepLane L(G, tile, threadIdx.x % 64);
+    typedef Factors<St, false> Fac;
+    const int tile = blockIdx.x, ns = G.ns, e = G.ns - 1;
+    const SweepLane L(G, tile, threadIdx.x);
     const int t = L.t;
-    const size_t S = (size_t)G.slots();
-    const int ns = G.ns, e = G.ns - 1;
-    if (wv == 1) {
-        const int px = L.a + 1 < G.tx && t + 1 < 64 ? t + 1 : t;
-        const int py = L.b + 1 < G.ty && t + G.tx < 64 ? t + G.tx : t;
-        Half<T> buf[kAhead1];
-        auto fetch = [&](int s, Half<T> &h) {
-            const int sc = max(s, 0);
-            load_half<St, T, 1>(F, tile, ns, sc, L.active(G, sc) ? t : 0, h);
-        };
-        // layer k of the tile from its ring slot to HBM
+    const size_t S = (size_t)G.slots(), nxy3 = 3 * (size_t)G.nx * G.ny;
+    const typename Fac::Raw *Ft = (const typename Fac::Raw *)F + (size_t)tile * ns * Fac::kStride * 64;
+    T *wt = wq + (size_t)tile * ns * 64;
+    const int px = L.a + 1 < G.tx && t + 1 < 64 ? t + 1 : t;
+    const int py = L.b + 1 < G.ty && t + G.tx < 64 ? t + G.tx : t;
+    // the three values of a finished layer this lane writes: place in the LDS
+    // slot and in the layer
+    int lo[3];
+    size_t go[3];
+    if constexpr (STAGE) {
         const int i0 = (tile % G.ntx) * G.tx, j0 = (tile / G.ntx) * G.ty;
-        const int rowlen = 3 * G.tx, tot = rowlen * G.ty;
-        auto flush = [&](int k) {
-            if (D == 0 || k >= G.nz) return;
-            const double *ob = obuf + (size_t)(k % D) * 192;
-            for (int q = t; q < tot; q += 64) {
-                const int b = q / rowlen, rem = q - b * rowlen, a = rem / 3;
-                if (i0 + a < G.nx && j0 + b < G.ny) {
-                    const size_t g0 = (size_t)i0 + (size_t)G.nx * ((size_t)(j0 + b) + (size_t)G.ny * k);
-                    const double o = ob[3 * (a + G.tx * b) + (rem - 3 * a)];
-                    out[3 * g0 + rem] = zin ? zin[3 * g0 + rem] + o : o;
-                }
-            }
-        };
-        auto step = [&](int s, Half<T> &h) {
-            flush(s + 1);
-            T xx[3] = {0, 0, 0}, xy[3] = {0, 0, 0};
-            if (s < e) {
-                const int p = (s + 1) & 1;
-                for (int c = 0; c < 3; c++) { xx[c] = xsh[p][c][px]; xy[c] = xsh[p][c][py]; }
-            }
-            T acc[3] = {0, 0, 0};
-            if (L.active(G, s)) {
-                T y[3];
-                mv3(h.v, xx, acc);
-                mv3(h.v + 9, xy, y); acc[0] = acc[0] + y[0]; acc[1] = acc[1] + y[1]; acc[2] = acc[2] + y[2];
-            }
-            fetch(s - kAhead1, h);
-            for (int c = 0; c < 3; c++) ash[s & 1][c][t] = acc[c];
-            __syncthreads();  // products of step s published
-            __syncthreads();  // x of step s published
-        };
 #pragma unroll
-        for (int u = 0; u < kAhead1; u++) fetch(e - u, buf[u]);
-        int s0 = e;
-        for (; s0 - kAhead1 + 1 >= 0; s0 -= kAhead1) {
-#pragma unroll
-            for (int u = 0; u < kAhead1; u++) step(s0 - u, buf[u]);
+        for (int u = 0; u < 3; u++) {
+            const int q = t + 64 * u, b = q / (3 * G.tx), rem = q - b * 3 * G.tx, a = rem / 3;
+            const bool in = b < G.ty && i0 + a < G.nx && j0 + b < G.ny;
+            lo[u] = in ? 3 * (a + G.tx * b) + (rem - 3 * a) : 0;
+            go[u] = 3 * ((size_t)i0 + (size_t)G.nx * (in ? j0 + b : j0)) + (in ? rem : 0);
         }
+    }
+    struct Slot {
+        Fac f;
+        T w[3];
+        TD d;
+        double z[3];
+    } ring[AH];
+    const TD *dpl = dp ? dp : (const TD *)wq;  // without dp a load that is not used
+    auto fetch = [&](int s, Slot &Q) {
+        const int sc = max(s, 0);
+        const bool act = L.active(G, sc);
+        const int tl = act ? t : 0;
+        Q.f.load(Ft + (size_t)sc * Fac::kStride * 64 + tl);
+        const T *w = wt + (size_t)sc * 64 + tl;
+        Q.w[0] = w[0]; Q.w[1] = w[S]; Q.w[2] = w[2 * S];
+        const size_t g = L.cell(G, sc);
+        Q.d = dpl[dp ? g : 0];
+        if constexpr (ZIN && STAGE) {
+            const double *zl = zin + (size_t)min(s + 1 < 0 ? 0 : s + 1, G.nz - 1) * nxy3;  // layer s + 1
 #pragma unroll
-        for (int u = 0; u < kAhead1; u++)
-            if (s0 - u >= 0) step(s0 - u, buf[u]);
-        flush(0);
-    } else {
-        T xp[3] = {0, 0, 0};
-        Half<T> buf[kAhead0];
-        T vec[kAhead0][3];
-        TD dpv[kAhead0];
-        // dp of the slot's cell is loaded with the slot (a load waited for
-        // inside the step would wait for every load in flight)
-        auto fetch = [&](int s, Half<T> &h, T *w, TD &d) {
-            const int sc = max(s, 0);
-            const bool act = L.active(G, sc);
-            const int tl = act ? t : 0;
-            load_half<St, T, 0>(F, tile, ns, sc, tl, h);
-            load_vec(wq, S, ((size_t)tile * ns + sc) * 64 + tl, w);
-            if (dp) d = dp[act ? L.cell(G, tile, sc) : 0];
-        };
-        auto step = [&](int s, Half<T> &h, T *w, TD &d) {
-            __syncthreads();  // products of step s published
-            if (L.active(G, s)) {
-                T acc[3], y[3];
-                acc[0] = ash[s & 1][0][t]; acc[1] = ash[s & 1][1][t]; acc[2] = ash[s & 1][2][t];
-                mv3(h.v + 9, xp, y); acc[0] = acc[0] + y[0]; acc[1] = acc[1] + y[1]; acc[2] = acc[2] + y[2];
-                if constexpr (St == ST_F64) {
-                    y[0] = w[0] - acc[0]; y[1] = w[1] - acc[1]; y[2] = w[2] - acc[2];
-                    mv3(h.v, y, xp);
-                } else {
-                    mv3(h.v, acc, y);
-                    xp[0] = w[0] - y[0]; xp[1] = w[1] - y[1]; xp[2] = w[2] - y[2];
-                }
-            } else {
-                xp[0] = xp[1] = xp[2] = 0;
-            }
-            for (int c = 0; c < 3; c++) xsh[s & 1][c][t] = xp[c];
-            if (L.active(G, s)) {
-                const double o0 = dp ? (double)d + (double)xp[0] : (double)xp[0];
-                if (D > 0) {
-                    double *ob = obuf + (size_t)((s - L.a - L.b) % D) * 192 + 3 * t;
-                    ob[0] = o0;
-                    ob[1] = (double)xp[1];
-                    ob[2] = (double)xp[2];
-                } else {
-                    size_t g = L.cell(G, tile, s);
-                    if (zin) {
-                        out[3 * g] = zin[3 * g] + o0;
-                        out[3 * g + 1] = zin[3 * g + 1] + (double)xp[1];
-                        out[3 * g + 2] = zin[3 * g + 2] + (double)xp[2];
-                    } else {
-                        out[3 * g] = o0;
-                        out[3 * g + 1] = (double)xp[1];
-                        out[3 * g + 2] = (double)xp[2];
-                    }
-                }
-            }
-            fetch(s - kAhead0, h, w, d);
-            __syncthreads();  // x of step s published
-        };
+            for (int u = 0; u < 3; u++) Q.z[u] = zl[go[u]];
+        } else if constexpr (ZIN) {
 #pragma unroll
-        for (int u = 0; u < kAhead0; u++) fetch(e - u, buf[u], vec[u], dpv[u]);
-        int s0 = e;
-        for (; s0 - kAhead0 + 1 >= 0; s0 -= kAhead0) {
-#pragma unroll
-            for (int u = 0; u < kAhead0; u++) step(s0 - u, buf[u], vec[u], dpv[u]);
+            for (int u = 0; u < 3; u++) Q.z[u] = zin[3 * g + u];
         }
+    };
+    T xp[3] = {0, 0, 0};
+    // slots of this lane's layer and of the layer written, both falling by one a step
+    int ks = 0, kf = 0;
+    if constexpr (STAGE) {
+        ks = ((e - L.a - L.b) % D + D) % D;
+        kf = (e + 1) % D;
+    }
+    auto flush = [&](int k, const double *o, const double *z) {
+        double *ol = out + (size_t)min(k, G.nz - 1) * nxy3;
+        const bool done = k < G.nz;
 #pragma unroll
-        for (int u = 0; u < kAhead0; u++)
-            if (s0 - u >= 0) step(s0 - u, buf[u], vec[u], dpv[u]);
+        for (int u = 0; u < 3; u++) {
+            if constexpr (ZIN) ol[go[u]] = done ? z[u] + o[u] : z[u];
+            else ol[go[u]] = o[u];
+        }
+    };
+    // fl (a constant at each call): write layer s + 1 out
+    auto step = [&](int s, Slot &Q, bool fl) {
+        T xx[3], xy[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            xx[c] = __shfl(xp[c], px, 64);
+            xy[c] = __shfl(xp[c], py, 64);
+        }
+        double o[3];
+        if (STAGE && fl) {
+#pragma unroll
+            for (int u = 0; u < 3; u++) o[u] = obuf[kf * 192 + lo[u]];
+        }
+        T A[9], acc[3], y[3], x[3];
+        Q.f.block(2, A);
+        mv3(A, xx, acc);
+        Q.f.block(3, A);
+        mv3(A, xy, y); acc[0] = acc[0] + y[0]; acc[1] = acc[1] + y[1]; acc[2] = acc[2] + y[2];
+        Q.f.block(1, A);
+        mv3(A, xp, y); acc[0] = acc[0] + y[0]; acc[1] = acc[1] + y[1]; acc[2] = acc[2] + y[2];
+        Q.f.block(0, A);
+        if constexpr (St == ST_F64) {
+            y[0] = Q.w[0] - acc[0]; y[1] = Q.w[1] - acc[1]; y[2] = Q.w[2] - acc[2];
+            mv3(A, y, x);
+        } else {
+            mv3(A, acc, y);
+            x[0] = Q.w[0] - y[0]; x[1] = Q.w[1] - y[1]; x[2] = Q.w[2] - y[2];
+        }
+        const bool act = L.active(G, s);
+#pragma unroll
+        for (int c = 0; c < 3; c++) xp[c] = act ? x[c] : (T)0;
+        const double o0 = dp ? (double)Q.d + (double)xp[0] : (double)xp[0];
+        if constexpr (STAGE) {
+            // (an idle lane's layer k, below 0 or past nz - 1, shares its slot
+            // with layer k +- D, which is written out already or still to come)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            double *ob = obuf + ks * 192 + 3 * t;
+            ob[0] = o0;
+            ob[1] = (double)xp[1];
+            ob[2] = (double)xp[2];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (fl) flush(s + 1, o, Q.z);
+            ks = ks == 0 ? D - 1 : ks - 1;
+            kf = kf == 0 ? D - 1 : kf - 1;
+        } else {
+            if (act) {
+                double *p = out + 3 * L.cell(G, s);
+                p[0] = ZIN ? Q.z[0] + o0 : o0;
+                p[1] = ZIN ? Q.z[1] + (double)xp[1] : (double)xp[1];
+                p[2] = ZIN ? Q.z[2] + (double)xp[2] : (double)xp[2];
+            }
+        }
+        fetch(s - AH, Q);
+    };
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(e - u, ring[u]);
+    int s0 = e;
+    for (; s0 - AH >= G.nz - 2; s0 -= AH)  // no layer finished yet
+#pragma unroll
+        for (int u = 0; u < AH; u++) step(s0 - u, ring[u], false);
+    for (; s0 >= 0; s0 -= AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {
+            if (s0 - u < 0) break;
+            step(s0 - u, ring[u], true);
+        }
+    if constexpr (STAGE) {
+        // layer 0; its zin values were loaded by the fetch for step -1
+        double o[3], z[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 3; u++) {
+            o[u] = obuf[kf * 192 + lo[u]];
+            if constexpr (ZIN) z[u] = zin[go[u]];
+        }
+        flush(0, o, z);
     }
 }
 
@@ -904,6 +844,34 @@ inline int stage_layers(const TileGeom &G) {
     return D * kStageBytes <= 32768 ? D : 0;
 }
 
+// One wavefront per tile: up to one per SIMD (1024 tiles) a longer ring of
+// loads pays for its registers (104x104x31, both sweeps: 54.4 us with 4 and 3
+// steps, 58.4 us with 2 and 2, 64.0 us with 6 and 4), beyond that more
+// tiles per SIMD do (400x400x100: 2.16 ms either way, HBM bound).
+constexpr int kFewTiles = 1024, kAheadF = 4, kAheadB = 3;
+template <int St, typename T>
+void launch_forward(const TileGeom &G, const void *F, const double *r, T *wq, hipStream_t s) {
+    const int nb = G.ntx * G.nty;
+    if (nb <= kFewTiles) k_ilu_forward<St, T, kAheadF><<<nb, 64, 0, s>>>(G, F, r, wq);
+    else k_ilu_forward<St, T, 2><<<nb, 64, 0, s>>>(G, F, r, wq);
+}
+template <int St, typename T, typename TD, int AH, bool ZIN>
+void launch_backward_ah(const TileGeom &G, const void *F, T *wq, const TD *dp, double *out, const double *zin,
+                        hipStream_t s) {
+    const int nb = G.ntx * G.nty, D = stage_layers(G);
+    if (D > 0) k_ilu_backward<St, T, TD, AH, ZIN, true><<<nb, 64, D * kStageBytes, s>>>(G, F, wq, dp, out, D, zin);
+    else k_ilu_backward<St, T, TD, AH, ZIN, false><<<nb, 64, 0, s>>>(G, F, wq, dp, out, D, zin);
+}
+template <int St, typename T, typename TD>
+void launch_backward(const TileGeom &G, const void *F, T *wq, const TD *dp, double *out, const double *zin,
+                     hipStream_t s) {
+    const bool few = G.ntx * G.nty <= kFewTiles;
+    if (zin && few) launch_backward_ah<St, T, TD, kAheadB, true>(G, F, wq, dp, out, zin, s);
+    else if (zin) launch_backward_ah<St, T, TD, 2, true>(G, F, wq, dp, out, zin, s);
+    else if (few) launch_backward_ah<St, T, TD, kAheadB, false>(G, F, wq, dp, out, zin, s);
+    else launch_backward_ah<St, T, TD, 2, false>(G, F, wq, dp, out, zin, s);
+}
+
 TileGeom geom(const bo_cpr *pc) {
     TileGeom T;
     T.nx = pc->g.nx; T.ny = pc->g.ny; T.nz = pc->g.nz;
@@ -1017,10 +985,8 @@ bo_status fstage_run(bo_cpr *pc, const double *r, const TD *dp, double *out, T *
         k_bj_apply<St, T, TD><<<grid_for(n), kBlock, 0, s>>>(n, pc->einv.p, r, dp, out);
     } else {
         TileGeom G = geom(pc);
-        k_ilu_forward<St, T><<<G.ntx * G.nty, 128, 0, s>>>(G, pc->ilu_f.p, r, wq);
-        const int D = stage_layers(G);
-        k_ilu_backward<St, T, TD><<<G.ntx * G.nty, 128, D * kStageBytes, s>>>(G, pc->ilu_b.p, wq, dp, out, D,
-                                                                                 zin);
+        launch_forward<St, T>(G, pc->ilu_f.p, r, wq, s);
+        launch_backward<St, T, TD>(G, pc->ilu_b.p, wq, dp, out, zin, s);
     }
     BO_HIP(hipGetLastError());
     return BO_OK;
@@ -1040,25 +1006,20 @@ bo_status fstage_apply(bo_cpr *pc, const double *r, const double *dp, double *ou
         const long long N = pc->g.n();
         const int st = store_of(pc);
         if (st != ST_F64) {
-            if (st == ST_F32) k_ilu_forward<ST_F32, float><<<G.ntx * G.nty, 128, 0, s>>>(G, pc->ilu_f.p, r,
-                                                                                          pc->ilu_w32.p);
-            else k_ilu_forward<ST_BF16, float><<<G.ntx * G.nty, 128, 0, s>>>(G, pc->ilu_f.p, r, pc->ilu_w32.p);
+            if (st == ST_F32) launch_forward<ST_F32, float>(G, pc->ilu_f.p, r, pc->ilu_w32.p, s);
+            else launch_forward<ST_BF16, float>(G, pc->ilu_f.p, r, pc->ilu_w32.p, s);
             if (pc->n > pc->ncell) {
                 int cnt = pc->n - pc->ncell;
                 k_rows_apply<double><<<grid_for(cnt), kBlock, 0, s>>>(pc->ncell, cnt, pc->x_einv_w.p, r, out, nullptr,
                                                                       nullptr);
             }
-            const int D = stage_layers(G);
             if (st == ST_F32)
-                k_ilu_backward<ST_F32, float, double><<<G.ntx * G.nty, 128, D * kStageBytes, s>>>(
-                    G, pc->ilu_b.p, pc->ilu_w32.p, nullptr, out, D, nullptr);
-            else
-                k_ilu_backward<ST_BF16, float, double><<<G.ntx * G.nty, 128, D * kStageBytes, s>>>(
-                    G, pc->ilu_b.p, pc->ilu_w32.p, nullptr, out, D, nullptr);
+                launch_backward<ST_F32, float, double>(G, pc->ilu_b.p, pc->ilu_w32.p, nullptr, out, nullptr, s);
+            else launch_backward<ST_BF16, float, double>(G, pc->ilu_b.p, pc->ilu_w32.p, nullptr, out, nullptr, s);
             BO_HIP(hipGetLastError());
             return BO_OK;
         }
-        k_ilu_forward<ST_F64, double><<<G.ntx * G.nty, 128, 0, s>>>(G, pc->ilu_f.p, r, pc->ilu_w.p);
+        launch_forward<ST_F64, double>(G, pc->ilu_f.p, r, pc->ilu_w.p, s);
         if (pc->ncell > N)
             k_dual_forward<<<grid_for(N), kBlock, 0, s>>>((int)N, pc->ilu_slot.p, S, r, pc->x_einv_m.p, pc->x_amf.p,
                                                           pc->x_afm.p, pc->x_einv_f.p, pc->ilu_w.p, out);
@@ -1067,9 +1028,7 @@ bo_status fstage_apply(bo_cpr *pc, const double *r, const double *dp, double *ou
             k_rows_apply<double><<<grid_for(cnt), kBlock, 0, s>>>(pc->ncell, cnt, pc->x_einv_w.p, r, out, nullptr,
                                                                   nullptr);
         }
-        const int D = stage_layers(G);
-        k_ilu_backward<ST_F64, double, double><<<G.ntx * G.nty, 128, D * kStageBytes, s>>>(
-            G, pc->ilu_b.p, pc->ilu_w.p, nullptr, out, D, nullptr);
+        launch_backward<ST_F64, double, double>(G, pc->ilu_b.p, pc->ilu_w.p, nullptr, out, nullptr, s);
         BO_HIP(hipGetLastError());
         return BO_OK;
     }

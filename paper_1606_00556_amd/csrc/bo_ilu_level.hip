@@ -222,7 +222,6 @@ struct NatGeom {
     int nx, ny, nz, ntx, nty, ns, M;
     __host__ __device__ int tiles() const { return ntx * nty; }
     __host__ __device__ size_t slots() const { return (size_t)ntx * nty * ns * 64; }
-    __host__ __device__ size_t hand() const { return (size_t)ntx * nty * M * kNt; }  // cells per direction
 };
 // Packed blocks, as double2 pairs in (tile, step, pair, lane) order (1 KB per
 // wavefront load).  C, 32 pairs a slot: [A_ii | A_i,-z | A_i,-y | A_i,-x |
@@ -290,14 +289,22 @@ __global__ void k_nat_hand_init(size_t n, unsigned long long *__restrict__ H, un
     if (q < 2) ctl[q] = 0;
 }
 
-// Handover of the values at a tile's edge.  Every edge cell has a place of its
-// own in H (the x direction first, then the y direction), written by one
-// lane and read by one lane.  A place is empty while it holds kEmpty (a
-// signalling NaN with a payload no arithmetic produces); the reader polls
-// until it holds something else and puts kEmpty back, so every sweep leaves
-// all places empty for the next one.  All accesses are relaxed 64-bit atomics
-// at agent scope (the tiles' L2s are not coherent with each other otherwise);
-// the value is its own flag, so no ordering between accesses is needed.
+// Handover of the values at a tile's edge.  The sweeps run in steps u with
+// mirrored lane coordinates: p = a, q = b, u = s forward, p = 7 - a, q = 7 - b,
+// u = ns - 1 - s backward, so that a tile always takes from the sides p = 0 and
+// q = 0 and gives from p = 7 and q = 7.  What a tile takes at step u stands in
+// row u of its own places: K values of each of the 8 edge cells of the x side,
+// then of the y side, then padding up to NW * 64 words, so that a wavefront
+// looks at the whole row with NW loads.  A place is written by one lane of the
+// neighbour and read by one lane.  It is empty while it holds kEmpty (a
+// signalling NaN with a payload no arithmetic produces); the reader polls until
+// it holds something else.  The forward and the backward sweep have their own
+// places, and each empties the other's behind its own steps (the factorisation
+// has the backward sweep's ones emptied by a launch of its own).  Accesses are
+// relaxed 64-bit atomics at agent scope (the XCDs' L2s are not coherent with
+// each other otherwise); a value is its own flag, so no ordering between
+// accesses is needed.  Row M takes the writes of lanes that have nothing to
+// give or to empty.
 // Tiles are taken from a ticket in dependence order, so a tile only ever
 // waits for tiles that workgroups already running hold.  Waiting is bounded:
 // a wavefront polls at most kSpin times in all, then goes on with what it has
@@ -315,164 +322,158 @@ __device__ __forceinline__ unsigned long long hand_bits(double v) {
     const unsigned long long u = (unsigned long long)__double_as_longlong(v);
     return u == kEmpty ? 0x7FF8000000000000ull : u;  // an input with kEmpty's bits passes on as another NaN
 }
+constexpr int hand_words(int K) { return (16 * K + 63) / 64; }  // loads per row
 
-// one lane's view of its tile's edges: in the forward direction it takes from
-// the tiles at -x and -y and gives to +x and +y, backward the other way round
-struct NatLane {
-    int t, a, b, tile;
-    bool col;                      // a column of the grid
-    bool tx, ty, gx, gy;           // takes / gives in x / y
-    unsigned long long *Hx_t, *Hy_t, *Hx_g, *Hy_g;  // place of (step offset 0) in each role
-    int st, sg;                    // step offsets of taking and giving
-    size_t pitch;                  // words between consecutive steps
-};
+// One wavefront's tile and edges, K values per cell.  The cells' values of the
+// last step are kept in LDS, [lane][K] with the taken row behind them, so a
+// lane reads its x and y neighbours from places found once.
 template <int K, bool FWD>
-__device__ __forceinline__ NatLane nat_lane(const NatGeom &G, const int32_t *__restrict__ order,
-                                            unsigned long long *__restrict__ H, unsigned long long *__restrict__ ctl) {
-    NatLane L;
-    L.t = threadIdx.x;
-    unsigned q = 0;
-    if (L.t == 0) q = (unsigned)(atomicAdd(ctl, 1ull) % (unsigned long long)G.tiles());
-    q = __builtin_amdgcn_readfirstlane(q);
-    L.tile = order[FWD ? q : G.tiles() - 1 - q];
-    L.a = L.t % kNt;
-    L.b = L.t / kNt;
-    const int I = L.tile % G.ntx, J = L.tile / G.ntx;
-    L.col = I * kNt + L.a < G.nx && J * kNt + L.b < G.ny;
-    const bool mx = I > 0 && L.a == 0, my = J > 0 && L.b == 0;                       // edges towards -x, -y
-    const bool px = I + 1 < G.ntx && L.a == kNt - 1, py = J + 1 < G.nty && L.b == kNt - 1;
-    L.tx = L.col && (FWD ? mx : px);
-    L.ty = L.col && (FWD ? my : py);
-    L.gx = L.col && (FWD ? px : mx);
-    L.gy = L.col && (FWD ? py : my);
-    // an edge's places belong to the tile on its lower side; cell (k, b) of an
-    // x edge stands at step m = k + b, lane b, cell (k, a) of a y edge at m =
-    // k + a, lane a
-    unsigned long long *Hy = H + G.hand() * 9;
-    L.pitch = (size_t)kNt * K;
-    auto place = [&](unsigned long long *base, int tile, int lane) { return base + ((size_t)tile * G.M * kNt + lane) * K; };
-    unsigned long long *own_x = place(H, L.tile, L.b), *own_y = place(Hy, L.tile, L.a);
-    unsigned long long *low_x = place(H, I > 0 ? L.tile - 1 : L.tile, L.b), *low_y = place(Hy, J > 0 ? L.tile - G.ntx : L.tile, L.a);
-    L.Hx_t = FWD ? low_x : own_x;
-    L.Hy_t = FWD ? low_y : own_y;
-    L.Hx_g = FWD ? own_x : low_x;
-    L.Hy_g = FWD ? own_y : low_y;
-    L.st = FWD ? 0 : kNt - 1;      // m = s - st when taking, s - sg when giving
-    L.sg = FWD ? kNt - 1 : 0;
-    return L;
-}
-__device__ __forceinline__ bool nat_active(const NatGeom &G, const NatLane &L, int s) {
-    const int k = s - L.a - L.b;
-    return L.col && k >= 0 && k < G.nz;
-}
-template <int K>
-struct Hand {
-    unsigned long long x[K], y[K];
-};
-// first look at the places of step s (lanes that take nothing look at place 0)
-template <int K>
-__device__ __forceinline__ void hand_look(const NatGeom &G, const NatLane &L, int s, Hand<K> &h) {
-    const bool act = nat_active(G, L, s);
-    const size_t o = act ? (size_t)(s - L.st) * L.pitch : 0;
-    const unsigned long long *px = L.Hx_t + (L.tx ? o : 0), *py = L.Hy_t + (L.ty ? o : 0);
+struct NatLane {
+    static constexpr int NW = hand_words(K);
+    static constexpr int kLds = 64 * K + NW * 64;  // doubles
+    int t, a, b, ab, tile;          // ab: first step (in u) of the lane's column, out of reach without one
+    size_t g0;                      // the column's cell in layer 0
+    int rx, ry;                     // LDS places of the -/+x and y neighbours' values
+    int take[NW], give[NW], gsrc[NW];  // first steps of taking and giving a word (out of reach: never), its LDS source
+    unsigned long long *row, *clr;  // this lane's word in row 0 of the own and of the other sweep's places
+    unsigned long long *dst[NW];    // this lane's words in the taking tile's row 0
+    unsigned long long *ctl, *sink; // sink: this lane's word of the own row M
+    int spin;
+    static constexpr int kNever = 1 << 30;
+    __device__ NatLane(const NatGeom &G, const int32_t *__restrict__ order, unsigned long long *H,
+                       unsigned long long *other, unsigned long long *ctl_)
+        : t(threadIdx.x), ctl(ctl_) {
+        unsigned qt = 0;
+        if (t == 0) qt = (unsigned)(atomicAdd(ctl, 1ull) % (unsigned long long)G.tiles());
+        qt = __builtin_amdgcn_readfirstlane(qt);
+        tile = order[FWD ? qt : G.tiles() - 1 - qt];
+        a = t % kNt;
+        b = t / kNt;
+        const int I = tile % G.ntx, J = tile / G.ntx;
+        const int p = FWD ? a : kNt - 1 - a, q = FWD ? b : kNt - 1 - b;
+        auto col = [&](int pp, int qq) {  // a column of the grid, by mirrored coordinates
+            return I * kNt + (FWD ? pp : kNt - 1 - pp) < G.nx && J * kNt + (FWD ? qq : kNt - 1 - qq) < G.ny;
+        };
+        ab = col(p, q) ? p + q : kNever;
+        g0 = (size_t)(I * kNt + a) + (size_t)G.nx * (J * kNt + b);
+        rx = p > 0 ? (FWD ? t - 1 : t + 1) * K : 64 * K + q * K;
+        ry = q > 0 ? (FWD ? t - kNt : t + kNt) * K : 64 * K + (8 + p) * K;
+        const bool has_tx = FWD ? I > 0 : I + 1 < G.ntx, has_ty = FWD ? J > 0 : J + 1 < G.nty;
+        const bool has_gx = FWD ? I + 1 < G.ntx : I > 0, has_gy = FWD ? J + 1 < G.nty : J > 0;
+        const int nx_tile = FWD ? tile + 1 : tile - 1, ny_tile = FWD ? tile + G.ntx : tile - G.ntx;
+        const size_t pitch = NW * 64;
+        auto place = [&](unsigned long long *set, int tl) { return set + (size_t)tl * (G.M + 1) * pitch + t; };
+        row = place(H, tile);
+        clr = place(other, tile);
+        sink = row + (size_t)G.M * pitch;
 #pragma unroll
-    for (int z = 0; z < K; z++) {
-        h.x[z] = hand_get(px + z);
-        h.y[z] = hand_get(py + z);
-    }
-}
-// wait until every value the wavefront takes at step s is there, empty the
-// places, and leave zeros in the lanes that take nothing
-template <int K>
-__device__ __forceinline__ void hand_take(const NatGeom &G, const NatLane &L, int s, Hand<K> &h, int &spin,
-                                          unsigned long long *__restrict__ ctl) {
-    const bool act = nat_active(G, L, s);
-    const bool tx = act && L.tx, ty = act && L.ty;
-    auto missing = [&]() {
-        bool m = false;
-#pragma unroll
-        for (int z = 0; z < K; z++) m = m || (tx && h.x[z] == kEmpty) || (ty && h.y[z] == kEmpty);
-        return m;
-    };
-    while (__any(missing())) {
-        if (spin <= 0) {
-            if (L.t == 0) hand_put(ctl + 1, 1ull);
-            break;
+        for (int w = 0; w < NW; w++) {
+            const int l = t + 64 * w, e = l / (8 * K), o = l / K % 8, z = l % K;  // side, cell, value
+            const bool y = e == 1, edge = e < 2;
+            take[w] = edge && (y ? has_ty && col(o, 0) : has_tx && col(0, o)) ? o : kNever;
+            const int gp = y ? o : kNt - 1, gq = y ? kNt - 1 : o;
+            const bool g = edge && (y ? has_gy : has_gx) && col(gp, gq);
+            give[w] = g ? o + kNt - 1 : kNever;
+            gsrc[w] = (edge ? (FWD ? gp + kNt * gq : kNt - 1 - gp + kNt * (kNt - 1 - gq)) : t) * K + z;
+            dst[w] = g ? place(H, y ? ny_tile : nx_tile) + 64 * w : sink + 64 * w;
         }
-        spin--;
-        hand_look<K>(G, L, s, h);
+        spin = hand_get(ctl + 1) ? 0 : kSpin;
     }
-    const size_t o = act ? (size_t)(s - L.st) * L.pitch : 0;
-    if (tx)
-#pragma unroll
-        for (int z = 0; z < K; z++) hand_put(L.Hx_t + o + z, kEmpty);
-    if (ty)
-#pragma unroll
-        for (int z = 0; z < K; z++) hand_put(L.Hy_t + o + z, kEmpty);
-#pragma unroll
-    for (int z = 0; z < K; z++) {
-        h.x[z] = tx ? h.x[z] : 0ull;
-        h.y[z] = ty ? h.y[z] : 0ull;
+    __device__ __forceinline__ bool active(const NatGeom &G, int u) const { return (unsigned)(u - ab) < (unsigned)G.nz; }
+    // the cell of an active step (cell 0 otherwise)
+    __device__ __forceinline__ size_t cell(const NatGeom &G, int u) const {
+        const int k = FWD ? u - ab : G.nz - 1 - (u - ab);
+        return active(G, u) ? g0 + (size_t)k * ((size_t)G.nx * G.ny) : 0;
     }
-}
-template <int K>
-__device__ __forceinline__ void hand_give(const NatLane &L, int s, const double *v) {
-    const size_t o = (size_t)(s - L.sg) * L.pitch;
-    if (L.gx)
+    // first look at the row of step u
+    __device__ __forceinline__ void look(const NatGeom &G, int u, unsigned long long *h) const {
+        const unsigned long long *r = row + (size_t)min(u, G.M) * (NW * 64);
 #pragma unroll
-        for (int z = 0; z < K; z++) hand_put(L.Hx_g + o + z, hand_bits(v[z]));
-    if (L.gy)
+        for (int w = 0; w < NW; w++) h[w] = hand_get(r + 64 * w);
+    }
+    // wait for the row of step u, put it behind the lanes' values in LDS (0
+    // where nothing is taken) and empty the other sweep's row u
+    __device__ __forceinline__ void taken(const NatGeom &G, int u, unsigned long long *h, double *lds) {
+        bool need[NW], miss = false;
 #pragma unroll
-        for (int z = 0; z < K; z++) hand_put(L.Hy_g + o + z, hand_bits(v[z]));
-}
-__device__ __forceinline__ double hand_val(unsigned long long u) { return __longlong_as_double((long long)u); }
+        for (int w = 0; w < NW; w++) {
+            need[w] = (unsigned)(u - take[w]) < (unsigned)G.nz;
+            miss = miss || (need[w] && h[w] == kEmpty);
+        }
+        if (__any(miss)) {
+            do {
+                if (spin <= 0) {
+                    if (t == 0) hand_put(ctl + 1, 1ull);
+                    break;
+                }
+                spin--;
+                look(G, u, h);
+                miss = false;
+#pragma unroll
+                for (int w = 0; w < NW; w++) miss = miss || (need[w] && h[w] == kEmpty);
+            } while (__any(miss));
+        }
+        const size_t o = (size_t)min(u, G.M) * (NW * 64);
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            lds[64 * K + t + 64 * w] = need[w] ? __longlong_as_double((long long)h[w]) : 0.0;
+            if (K == 3) hand_put(clr + o + 64 * w, kEmpty);
+        }
+    }
+    // after the lanes' values of step u are in LDS: hand the edges over
+    __device__ __forceinline__ void given(const NatGeom &G, int u, const double *lds) const {
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            const bool g = (unsigned)(u - give[w]) < (unsigned)G.nz;
+            unsigned long long *d = g ? dst[w] + (size_t)(u - (kNt - 1)) * (NW * 64) : sink + 64 * w;
+            hand_put(d, hand_bits(lds[gsrc[w]]));
+        }
+    }
+};
+#define WAVE_FENCE() __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront")
 
 // Factorisation: E_i = A_ii - sum over -z, -y, -x of (A_ik E_k^-1) A_ki, one
-// wavefront per tile, the neighbours' E^-1 from the lanes of the previous step
-// or handed over.  Bound by the arithmetic of a step (six 3x3 products and an
-// inverse, FP64 without contraction) times the hyperplanes.
+// wavefront per tile.  Bound by the arithmetic of a step (six 3x3 products and
+// an inverse, FP64 without contraction) times the hyperplanes; a launch per
+// hyperplane took 38 us each (8.8 ms on 99x101x31).
 __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int32_t *__restrict__ order,
                                                            double2 *__restrict__ C, double2 *__restrict__ Bp,
                                                            unsigned long long *__restrict__ H,
                                                            unsigned long long *__restrict__ ctl,
                                                            int32_t *__restrict__ bad) {
-    const NatLane L = nat_lane<9, true>(G, order, H, ctl);
+    typedef NatLane<9, true> Lane;
+    __shared__ double lds[Lane::kLds];
+    Lane L(G, order, H, H, ctl);
     const int t = L.t;
-    int spin = hand_get(ctl + 1) ? 0 : kSpin;
+#pragma unroll
+    for (int z = 0; z < 9; z++) lds[9 * t + z] = 0.0;
     struct Slot {
         double v[64];
+        unsigned long long h[Lane::NW];
     } R0, R1;
-    Hand<9> h;
     double Ep[9];
 #pragma unroll
     for (int z = 0; z < 9; z++) Ep[z] = 0.0;
     auto fetch = [&](int s, Slot &S) {
         const int sc = min(s, G.ns - 1);
-        // (idle lanes read a lane of the same step that is in the grid's first
-        // column or, where that is idle too, memory of the slot array: unused)
-        const double2 *c = C + c_index(G, L.tile, sc, nat_active(G, L, sc) ? t : 0);
+        const double2 *c = C + c_index(G, L.tile, sc, L.active(G, sc) ? t : 0);
 #pragma unroll
         for (int p = 0; p < kCPairs; p++) {
             const double2 d = c[p * 64];
             S.v[2 * p] = d.x;
             S.v[2 * p + 1] = d.y;
         }
+        L.look(G, sc, S.h);
     };
-    auto step = [&](int s, const Slot &S) {
+    auto step = [&](int s, Slot &S) {
+        L.taken(G, s, S.h, lds);
+        WAVE_FENCE();
         double Ex[9], Ey[9];
 #pragma unroll
         for (int z = 0; z < 9; z++) {
-            Ex[z] = __shfl(Ep[z], L.a > 0 ? t - 1 : t, 64);
-            Ey[z] = __shfl(Ep[z], L.b > 0 ? t - kNt : t, 64);
+            Ex[z] = lds[L.rx + z];
+            Ey[z] = lds[L.ry + z];
         }
-        hand_take<9>(G, L, s, h, spin, ctl);
-#pragma unroll
-        for (int z = 0; z < 9; z++) {
-            Ex[z] = L.a > 0 ? Ex[z] : hand_val(h.x[z]);
-            Ey[z] = L.b > 0 ? Ey[z] : hand_val(h.y[z]);
-        }
-        if (s + 1 < G.ns) hand_look<9>(G, L, s + 1, h);
-        if (!nat_active(G, L, s)) return;
         const double *v = S.v;
         double E[9], lw[28], tmp[9];
 #pragma unroll
@@ -492,182 +493,206 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int3
         for (int z = 0; z < 9; z++) E[z] = E[z] - tmp[z];
         lw[27] = 0.0;
         double Ei[10];
+        const bool act = L.active(G, s);
         if (!inv3_gj(E, Ei)) {
-            atomicOr(bad, 1);
+            if (act) atomicOr(bad, 1);
 #pragma unroll
             for (int z = 0; z < 9; z++) Ei[z] = 0.0;
         }
         Ei[9] = 0.0;
-        hand_give<9>(L, s, Ei);
+#pragma unroll
+        for (int z = 0; z < 9; z++) {
+            Ep[z] = act ? Ei[z] : Ep[z];
+            lds[9 * t + z] = Ep[z];
+        }
+        WAVE_FENCE();
+        L.given(G, s, lds);
+        // (an idle lane's results go to its idle slot)
         double2 *c = C + c_index(G, L.tile, s, t), *d = Bp + b_index(G, L.tile, s, t);
 #pragma unroll
         for (int p = 0; p < kFPairs; p++) c[p * 64] = make_double2(lw[2 * p], lw[2 * p + 1]);
 #pragma unroll
         for (int p = 0; p < 5; p++) d[p * 64] = make_double2(Ei[2 * p], Ei[2 * p + 1]);
-#pragma unroll
-        for (int z = 0; z < 9; z++) Ep[z] = Ei[z];
+        fetch(s + 2, S);
     };
-    hand_look<9>(G, L, 0, h);
     fetch(0, R0);
-    int s0 = 0;
-    for (; s0 + 2 <= G.ns; s0 += 2) {
-        fetch(s0 + 1, R1);
+    fetch(1, R1);
+    for (int s0 = 0; s0 < G.ns; s0 += 2) {
         step(s0, R0);
-        fetch(s0 + 2, R0);
+        if (s0 + 1 >= G.ns) break;
         step(s0 + 1, R1);
     }
-    if (s0 < G.ns) step(s0, R0);
 }
 
-// The sweeps: one wavefront per tile without barriers, the neighbours' values
-// by lane shuffles, the factors, the operand and a first look at the handed-over
-// values of kNatAhead steps in flight.  Sums in the row's column order.
-// Bound by the latency of a step (its products and shuffles, and a poll of
-// the other XCD's memory where the neighbour tile is not ahead) times the
-// nx+ny+nz-2 hyperplanes; one launch per hyperplane took 9.4 us each.
-constexpr int kNatAhead = 3;
+// The sweeps: one wavefront per tile without barriers, the factors, the operand
+// and a first look at the handed-over values of AH steps in flight, and
+// every load and store issued on every path but the poll that follows a look
+// that came too early (vector memory operations return in order and are
+// counted statically: a store some paths skip, or the poll as a loop around
+// the first look, makes each step wait for the loads of the steps ahead too).
+// Sums in the row's column order.  Bound by the latency of a step (0.62 us)
+// times the nx+ny+nz-2 hyperplanes and the handovers between tiles (3.3 us
+// each): 104x104x31, both sweeps, 464 us (4.3 ms with a launch per hyperplane).
+// A look AH steps ahead needs the neighbour that much further ahead, so a short
+// ring wins while every tile has a SIMD of its own (464 / 499 / 565 us with 2 /
+// 3 / 4 steps); with more tiles the HBM bandwidth does (400x400x100: 4.43 / 4.09
+// / 4.35 ms).
 
 // forward: y_i = r_i - sum_{-z,-y,-x} L y, into yq[3][slot]
+template <int AH>
 __global__ void __launch_bounds__(64, 1) k_nat_tile_forward(NatGeom G, const int32_t *__restrict__ order,
                                                             const double2 *__restrict__ C,
                                                             const double *__restrict__ r, double *__restrict__ yq,
                                                             unsigned long long *__restrict__ H,
+                                                            unsigned long long *__restrict__ other,
                                                             unsigned long long *__restrict__ ctl) {
-    const NatLane L = nat_lane<3, true>(G, order, H, ctl);
+    typedef NatLane<3, true> Lane;
+    __shared__ double lds[Lane::kLds];
+    Lane L(G, order, H, other, ctl);
     const int t = L.t;
-    int spin = hand_get(ctl + 1) ? 0 : kSpin;
     const size_t S = G.slots();
-    const size_t g0 = (size_t)(L.tile % G.ntx * kNt + L.a) + (size_t)G.nx * (L.tile / G.ntx * kNt + L.b);
+    const double2 *Ct = C + c_index(G, L.tile, 0, 0);
+    double *yt = yq + (size_t)L.tile * G.ns * 64 + t;
+#pragma unroll
+    for (int c = 0; c < 3; c++) lds[3 * t + c] = 0.0;
     struct Slot {
         double f[28], r[3];
-        Hand<3> h;
-    } ring[kNatAhead];
+        unsigned long long h[1];
+    } ring[AH];
     auto fetch = [&](int s, Slot &Q) {
         const int sc = min(s, G.ns - 1);
-        const bool act = nat_active(G, L, sc);
-        const double2 *c = C + c_index(G, L.tile, sc, act ? t : 0);
+        const double2 *c = Ct + (size_t)sc * kCPairs * 64 + (L.active(G, sc) ? t : 0);
 #pragma unroll
         for (int p = 0; p < kFPairs; p++) {
             const double2 d = c[p * 64];
             Q.f[2 * p] = d.x;
             Q.f[2 * p + 1] = d.y;
         }
-        const double *rg = r + 3 * (act ? g0 + (size_t)(sc - L.a - L.b) * G.nx * G.ny : 0);
+        const double *rg = r + 3 * L.cell(G, sc);
         Q.r[0] = rg[0]; Q.r[1] = rg[1]; Q.r[2] = rg[2];
-        hand_look<3>(G, L, sc, Q.h);
+        L.look(G, sc, Q.h);
     };
     double yp[3] = {0.0, 0.0, 0.0};
     auto step = [&](int s, Slot &Q) {
-        double yx[3], yy[3];
+        L.taken(G, s, Q.h, lds);
+        WAVE_FENCE();
+        double yx[3], yy[3], u[3], v[3] = {Q.r[0], Q.r[1], Q.r[2]};
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-            yx[c] = __shfl(yp[c], L.a > 0 ? t - 1 : t, 64);
-            yy[c] = __shfl(yp[c], L.b > 0 ? t - kNt : t, 64);
+            yx[c] = lds[L.rx + c];
+            yy[c] = lds[L.ry + c];
         }
-        hand_take<3>(G, L, s, Q.h, spin, ctl);
+        mv3d(Q.f, yp, u);
+        for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+        mv3d(Q.f + 9, yy, u);
+        for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+        mv3d(Q.f + 18, yx, u);
+        for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
+        const bool act = L.active(G, s);
+        double *y = yt + (size_t)s * 64;  // (an idle lane's value goes to its idle slot)
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-            yx[c] = L.a > 0 ? yx[c] : hand_val(Q.h.x[c]);
-            yy[c] = L.b > 0 ? yy[c] : hand_val(Q.h.y[c]);
+            yp[c] = act ? v[c] : 0.0;
+            lds[3 * t + c] = yp[c];
+            y[c * S] = yp[c];
         }
-        if (nat_active(G, L, s)) {
-            double u[3], v[3] = {Q.r[0], Q.r[1], Q.r[2]};
-            if (s - L.a - L.b > 0) {
-                mv3d(Q.f, yp, u);
-                for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
-            }
-            mv3d(Q.f + 9, yy, u);
-            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
-            mv3d(Q.f + 18, yx, u);
-            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
-            for (int c = 0; c < 3; c++) yp[c] = v[c];
-            hand_give<3>(L, s, v);
-            const size_t q = ((size_t)L.tile * G.ns + s) * 64 + t;
-            yq[q] = v[0]; yq[S + q] = v[1]; yq[2 * S + q] = v[2];
-        }
-        fetch(s + kNatAhead, Q);
+        WAVE_FENCE();
+        L.given(G, s, lds);
+        fetch(s + AH, Q);
     };
 #pragma unroll
-    for (int u = 0; u < kNatAhead; u++) fetch(u, ring[u]);
-    for (int s0 = 0; s0 < G.ns; s0 += kNatAhead)
+    for (int u = 0; u < AH; u++) fetch(u, ring[u]);
+    for (int s0 = 0; s0 < G.ns; s0 += AH)
 #pragma unroll
-        for (int u = 0; u < kNatAhead; u++)
-            if (s0 + u < G.ns) step(s0 + u, ring[u]);
+        for (int u = 0; u < AH; u++) {
+            if (s0 + u >= G.ns) return;
+            step(s0 + u, ring[u]);
+        }
 }
 
 // backward: x_i = E_i^-1 (y_i - sum_{+x,+y,+z} A x), out = x + (dp, 0, 0) in
 // natural order (dp may be NULL)
+template <int AH>
 __global__ void __launch_bounds__(64, 1) k_nat_tile_backward(NatGeom G, const int32_t *__restrict__ order,
-                                                             const double2 *__restrict__ Bp,
-                                                             const double *__restrict__ yq,
+                                                             const double2 *__restrict__ Bp, double *__restrict__ yq,
                                                              const double *__restrict__ dp, double *__restrict__ out,
                                                              unsigned long long *__restrict__ H,
+                                                             unsigned long long *__restrict__ other,
                                                              unsigned long long *__restrict__ ctl) {
-    const NatLane L = nat_lane<3, false>(G, order, H, ctl);
-    const int t = L.t;
-    int spin = hand_get(ctl + 1) ? 0 : kSpin;
+    typedef NatLane<3, false> Lane;
+    __shared__ double lds[Lane::kLds];
+    Lane L(G, order, H, other, ctl);
+    const int t = L.t, e = G.ns - 1;
     const size_t S = G.slots();
-    const size_t g0 = (size_t)(L.tile % G.ntx * kNt + L.a) + (size_t)G.nx * (L.tile / G.ntx * kNt + L.b);
-    const bool last_x = L.a == kNt - 1, last_y = L.b == kNt - 1;
+    const double2 *Bt = Bp + b_index(G, L.tile, 0, 0);
+    double *yt = yq + (size_t)L.tile * G.ns * 64;
+#pragma unroll
+    for (int c = 0; c < 3; c++) lds[3 * t + c] = 0.0;
     struct Slot {
         double f[38], y[3], d;
-        Hand<3> h;
-    } ring[kNatAhead];
-    auto fetch = [&](int s, Slot &Q) {
-        const int sc = max(s, 0);
-        const bool act = nat_active(G, L, sc);
-        const int tl = act ? t : 0;
-        const double2 *c = Bp + b_index(G, L.tile, sc, tl);
+        unsigned long long h[1];
+    } ring[AH];
+    const double *dpl = dp ? dp : yq;  // without dp a load that is not used
+    auto fetch = [&](int u, Slot &Q) {
+        const int uc = min(u, e), s = e - uc;
+        const int tl = L.active(G, uc) ? t : 0;
+        const double2 *c = Bt + (size_t)s * kBPairs * 64 + tl;
 #pragma unroll
         for (int p = 0; p < kBPairs; p++) {
             const double2 d = c[p * 64];
             Q.f[2 * p] = d.x;
             Q.f[2 * p + 1] = d.y;
         }
-        const size_t q = ((size_t)L.tile * G.ns + sc) * 64 + tl;
-        Q.y[0] = yq[q]; Q.y[1] = yq[S + q]; Q.y[2] = yq[2 * S + q];
-        Q.d = dp ? dp[act ? g0 + (size_t)(sc - L.a - L.b) * G.nx * G.ny : 0] : 0.0;
-        hand_look<3>(G, L, sc, Q.h);
+        const double *y = yt + (size_t)s * 64 + tl;
+        Q.y[0] = y[0]; Q.y[1] = y[S]; Q.y[2] = y[2 * S];
+        Q.d = dpl[dp ? L.cell(G, uc) : 0];
+        L.look(G, uc, Q.h);
     };
     double xp[3] = {0.0, 0.0, 0.0};
-    auto step = [&](int s, Slot &Q) {
-        double xx[3], xy[3];
+    auto step = [&](int u, Slot &Q) {
+        L.taken(G, u, Q.h, lds);
+        WAVE_FENCE();
+        double xx[3], xy[3], w[3], v[3] = {Q.y[0], Q.y[1], Q.y[2]};
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-            xx[c] = __shfl(xp[c], last_x ? t : t + 1, 64);
-            xy[c] = __shfl(xp[c], last_y ? t : t + kNt, 64);
+            xx[c] = lds[L.rx + c];
+            xy[c] = lds[L.ry + c];
         }
-        hand_take<3>(G, L, s, Q.h, spin, ctl);
+        mv3d(Q.f + 10, xx, w);
+        for (int c = 0; c < 3; c++) v[c] = v[c] - w[c];
+        mv3d(Q.f + 19, xy, w);
+        for (int c = 0; c < 3; c++) v[c] = v[c] - w[c];
+        mv3d(Q.f + 28, xp, w);
+        for (int c = 0; c < 3; c++) v[c] = v[c] - w[c];
+        mv3d(Q.f, v, w);
+        const bool act = L.active(G, u);
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-            xx[c] = last_x ? hand_val(Q.h.x[c]) : xx[c];
-            xy[c] = last_y ? hand_val(Q.h.y[c]) : xy[c];
+            xp[c] = act ? w[c] : 0.0;
+            lds[3 * t + c] = xp[c];
         }
-        if (nat_active(G, L, s)) {
-            double u[3], v[3] = {Q.y[0], Q.y[1], Q.y[2]};
-            mv3d(Q.f + 10, xx, u);
-            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
-            mv3d(Q.f + 19, xy, u);
-            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
-            mv3d(Q.f + 28, xp, u);
-            for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
-            mv3d(Q.f, v, xp);
-            hand_give<3>(L, s, xp);
-            double *o = out + 3 * (g0 + (size_t)(s - L.a - L.b) * G.nx * G.ny);
-            o[0] = dp ? Q.d + xp[0] : xp[0];
-            o[1] = xp[1];
-            o[2] = xp[2];
-        }
-        fetch(s - kNatAhead, Q);
+        WAVE_FENCE();
+        L.given(G, u, lds);
+        // an idle lane writes to its idle slot of yq, which nothing reads
+        const size_t gc = 3 * L.cell(G, u);
+        double *o0 = act ? out + gc : yt + (size_t)(e - u) * 64 + t;
+        double *o1 = act ? out + gc + 1 : o0 + S, *o2 = act ? out + gc + 2 : o0 + 2 * S;
+        *o0 = dp ? Q.d + xp[0] : xp[0];
+        *o1 = xp[1];
+        *o2 = xp[2];
+        fetch(u + AH, Q);
     };
-    const int e = G.ns - 1;
 #pragma unroll
-    for (int u = 0; u < kNatAhead; u++) fetch(e - u, ring[u]);
-    for (int s0 = e; s0 >= 0; s0 -= kNatAhead)
+    for (int u = 0; u < AH; u++) fetch(u, ring[u]);
+    for (int u0 = 0; u0 <= e; u0 += AH)
 #pragma unroll
-        for (int u = 0; u < kNatAhead; u++)
-            if (s0 - u >= 0) step(s0 - u, ring[u]);
+        for (int u = 0; u < AH; u++) {
+            if (u0 + u > e) return;
+            step(u0 + u, ring[u]);
+        }
 }
+
+constexpr int kNatFewTiles = 1024;  // one per SIMD
 
 NatGeom nat_geom(const Grid &g) {
     NatGeom G;
@@ -679,10 +704,14 @@ NatGeom nat_geom(const Grid &g) {
     return G;
 }
 
+// the handover memory: the factorisation's places (which the sweeps' two sets
+// share), then the ticket and the wait-expired mark
+size_t nat_hand_words(const NatGeom &G) { return (size_t)G.tiles() * (G.M + 1) * 64 * hand_words(9); }
+
 // factorisation of a plain grid from the operator's slot arrays
 bo_status nat_tile_launch(bo_cpr *pc, hipStream_t s) {
     const NatGeom G = nat_geom(pc->g);
-    const size_t S = G.slots(), nh = 2 * 9 * G.hand();
+    const size_t S = G.slots(), nh = nat_hand_words(G);
     BO_TRY(pc->nat_c.alloc(S * kCPairs));
     BO_TRY(pc->nat_b.alloc(S * kBPairs));
     BO_TRY(pc->nat_y.alloc(3 * S));
@@ -693,15 +722,20 @@ bo_status nat_tile_launch(bo_cpr *pc, hipStream_t s) {
     k_nat_order<<<grid_for(G.tiles()), kBlock, 0, s>>>(G.ntx, G.nty, pc->nat_perm.p);
     k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty);
     k_nat_tile_factor<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, H, ctl, pc->fflag.p);
+    k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
 
 bo_status nat_tile_apply(bo_cpr *pc, const double *r, const double *dp, double *out, hipStream_t s) {
     const NatGeom G = nat_geom(pc->g);
-    unsigned long long *H = pc->nat_hand.p, *ctl = H + 2 * 9 * G.hand();
-    k_nat_tile_forward<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, r, pc->nat_y.p, H, ctl);
-    k_nat_tile_backward<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_b.p, pc->nat_y.p, dp, out, H, ctl);
+    unsigned long long *H = pc->nat_hand.p, *ctl = H + nat_hand_words(G);
+    unsigned long long *Hb = H + nat_hand_words(G) / hand_words(9);  // one word per lane and row for each sweep
+    const bool few = G.tiles() <= kNatFewTiles;
+    (few ? k_nat_tile_forward<2> : k_nat_tile_forward<3>)<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, r,
+                                                                                   pc->nat_y.p, H, Hb, ctl);
+    (few ? k_nat_tile_backward<2> : k_nat_tile_backward<3>)<<<G.tiles(), 64, 0, s>>>(
+        G, pc->nat_perm.p, pc->nat_b.p, pc->nat_y.p, dp, out, Hb, H, ctl);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
