@@ -276,13 +276,14 @@ __device__ inline double block_sum(double v, double *sh) {
 // the stream before returning (so a buffer is idle whenever a call starts);
 // steady-state calls then do not allocate, and hipFree does not synchronise
 // the device.  One set per host thread; never freed.
-enum ScratchSlot { SC_SCAN = 0, SC_FLAG, SC_JAC_CNT, SC_SELL, SC_COUNT };
+enum ScratchSlot { SC_FLAG = 0, SC_JAC_CNT, SC_SELL, SC_COUNT };
 bo_status scratch_get(int slot, size_t bytes, void **ptr);
 
 // ---- small device-to-host reads ----------------------------------------------------
-// Each read goes through a pinned host buffer (one per host thread, 4 KB,
-// never freed), so the copy is a direct DMA; one stream synchronisation
-// serves all the reads of a call.
+// One kernel copies the words of a call's reads (at most four items of whole
+// words, 4 KB together) into a pinned host buffer (one per host thread, never
+// freed), behind everything enqueued on s before; the call returns when they
+// are there, so the work enqueued before has finished too.
 struct HostRead {
     const void *src;  // device
     size_t bytes;

@@ -12,6 +12,7 @@
 // partial sums in a fixed tree order, and a second one-workgroup kernel adds
 // the partials in a fixed order (no device-scope fences in the hot loop).
 #include <algorithm>
+#include <chrono>
 #include "bo_common.hpp"
 #include <cstring>
 #include "bo_linalg.hpp"
@@ -46,29 +47,99 @@ bo_status scratch_get(int slot, size_t bytes, void **ptr) {
     return BO_OK;
 }
 
-bo_status host_reads(const HostRead *r, int count, hipStream_t s) {
-    constexpr size_t kMail = 4096;
-    static thread_local char *mail = nullptr;
-    if (!mail) {
-        hipError_t e = hipHostMalloc((void **)&mail, kMail, hipHostMallocDefault);
-        if (e != hipSuccess) {
-            mail = nullptr;
-            return fail(BO_ERR_ALLOC, std::string("hipHostMalloc of the read buffer failed: ") + hipGetErrorString(e));
-        }
-    }
+// ---- small device-to-host reads ---------------------------------------------------
+// The words of a call's reads, copied by one kernel into pinned host memory,
+// then the call's number: the host waits for that word.  A read used to be a
+// copy command per item and a stream synchronisation (about 25 us where the
+// stream was idle); a setup makes some fifty of them.
+constexpr int kMailItems = 4;
+constexpr size_t kMail = 4096;     // bytes of the items; the number stands behind them
+struct MailItems {
+    const uint32_t *src[kMailItems];
+    uint32_t words[kMailItems], off[kMailItems];
+    int count;
+};
+struct Mail {
+    char *host = nullptr, *dev = nullptr;  // pinned, coherent; the same memory as the device addresses it
+    uint32_t seq = 0;
+    static constexpr size_t kFlag = kMail;
+};
+static thread_local Mail t_mail;
+
+// by the threads of one workgroup; the items' words first, then the number
+__device__ void mail_write(const MailItems &M, char *mail, uint32_t seq) {
+    for (int q = 0; q < M.count; q++)
+        for (uint32_t w = threadIdx.x; w < M.words[q]; w += blockDim.x)
+            __hip_atomic_store((uint32_t *)(mail + M.off[q]) + w,
+                               __hip_atomic_load(M.src[q] + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store((uint32_t *)(mail + kMail), seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ void k_mail(MailItems M, char *mail, uint32_t seq) { mail_write(M, mail, seq); }
+
+// the items of r as words in the mail buffer (sizes in whole words)
+static bo_status mail_items(const HostRead *r, int count, MailItems &M) {
+    if (count < 0 || count > kMailItems) return fail(BO_ERR_INVALID_ARG, "host_reads: at most four items");
     size_t off = 0;
+    M.count = count;
     for (int q = 0; q < count; q++) {
-        if (off + r[q].bytes > kMail) return fail(BO_ERR_INVALID_ARG, "host_reads: more than 4 KB");
-        BO_HIP(hipMemcpyAsync(mail + off, r[q].src, r[q].bytes, hipMemcpyDeviceToHost, s));
+        if (r[q].bytes % 4 != 0 || off + r[q].bytes > kMail)
+            return fail(BO_ERR_INVALID_ARG, "host_reads: whole words, at most 4 KB");
+        M.src[q] = (const uint32_t *)r[q].src;
+        M.words[q] = (uint32_t)(r[q].bytes / 4);
+        M.off[q] = (uint32_t)off;
         off += (r[q].bytes + 15) / 16 * 16;
     }
-    BO_HIP(hipStreamSynchronize(s));
-    off = 0;
-    for (int q = 0; q < count; q++) {
-        std::memcpy(r[q].dst, mail + off, r[q].bytes);
-        off += (r[q].bytes + 15) / 16 * 16;
+    if (!t_mail.host) {
+        char *host = nullptr, *dev = nullptr;
+        hipError_t e = hipHostMalloc((void **)&host, kMail + 64, hipHostMallocCoherent | hipHostMallocMapped);
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&dev, host, 0);
+        if (e != hipSuccess) {
+            if (host) (void)hipHostFree(host);
+            return fail(BO_ERR_ALLOC, std::string("the read buffer could not be allocated: ") + hipGetErrorString(e));
+        }
+        std::memset(host, 0, kMail + 64);
+        t_mail.host = host;
+        t_mail.dev = dev;
     }
+    t_mail.seq++;
     return BO_OK;
+}
+
+// waits for the mail of the last mail_items call (its kernel is enqueued on
+// s) and hands the items out.  The host polls for up to kPollMs; a longer wait,
+// and any error of the stream, goes through hipStreamSynchronize.
+static bo_status mail_take(const HostRead *r, int count, const MailItems &M, hipStream_t s) {
+    constexpr double kPollMs = 20.0;
+    const uint32_t *flag = (const uint32_t *)(t_mail.host + Mail::kFlag);
+    auto there = [&] { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == t_mail.seq; };
+    const auto t0 = std::chrono::steady_clock::now();
+    bool ok = false;
+    while (!(ok = there())) {
+        for (int k = 0; k < 64 && !ok; k++) {
+            __builtin_ia32_pause();
+            ok = there();
+        }
+        if (ok || std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count() > kPollMs)
+            break;
+    }
+    if (!ok) {
+        BO_HIP(hipStreamSynchronize(s));
+        if (!there()) return fail(BO_ERR_HIP, "host_reads: the read did not arrive");
+    }
+    for (int q = 0; q < count; q++) std::memcpy(r[q].dst, t_mail.host + M.off[q], r[q].bytes);
+    return BO_OK;
+}
+
+bo_status host_reads(const HostRead *r, int count, hipStream_t s) {
+    MailItems M;
+    BO_TRY(mail_items(r, count, M));
+    k_mail<<<1, kBlock, 0, s>>>(M, t_mail.dev, t_mail.seq);
+    BO_HIP(hipGetLastError());
+    return mail_take(r, count, M, s);
 }
 
 // ---- scan ------------------------------------------------------------------
@@ -143,6 +214,101 @@ bo_status scan_counts_async(const int32_t *counts, int32_t *out, int n, int32_t 
     return BO_OK;
 }
 
+// The same prefix sum in one pass (scan_counts): a workgroup takes a tile of
+// 4096 counts by ticket, publishes the tile's sum, looks back over the sums
+// and prefixes of the tiles before it (a wavefront reads 64 of them at a time)
+// and publishes its own prefix.  A word holds (call number, state, value), so
+// words of earlier calls read as not yet published and nothing is cleared
+// between calls; tickets count on from call to call.  A tile waits only for
+// tiles whose workgroups took their tickets before it, each of which
+// publishes its sum without waiting.  The workgroup that finishes last writes
+// the total and the caller's other words into the mail, so the words are free
+// for the next call, on whatever stream, once the mail is there.  Three
+// launches and a copy per word before.
+constexpr int kScanItems = 4, kScanTile = kScanBlock * kScanItems;
+enum : uint64_t { SCAN_SUM = 1, SCAN_PREFIX = 2 };
+__device__ __forceinline__ uint64_t scan_word(uint32_t call, uint64_t state, int32_t v) {
+    return ((uint64_t)(call & 0x3FFFFFFFu) << 34) | (state << 32) | (uint32_t)v;
+}
+// ctl: [0] tickets taken, [1] workgroups finished (both `first` at the call's start)
+__global__ void __launch_bounds__(kScanBlock) k_scan_mail(const int32_t *in, int32_t *out, int n, uint64_t *words,
+                                                          uint32_t *ctl, uint32_t first, uint32_t call, MailItems M,
+                                                          char *mail, uint32_t seq) {
+    __shared__ int32_t wsum[kScanBlock / 64];
+    __shared__ int32_t tile_s, prefix_s, last_s;
+    const int t = threadIdx.x, lane = t % 64, wave = t / 64;
+    if (t == 0) tile_s = (int)(atomicAdd(&ctl[0], 1u) - first);
+    __syncthreads();
+    const int tile = tile_s, ntiles = (n + kScanTile - 1) / kScanTile;
+    const int base = tile * kScanTile + t * kScanItems;
+    int32_t v[kScanItems], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kScanItems; q++) {
+        v[q] = base + q < n ? in[base + q] : 0;
+        sum += v[q];
+    }
+    int32_t inc = sum;  // inclusive over the wavefront, then over the workgroup
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t o = __shfl_up(inc, off, 64);
+        inc += lane >= off ? o : 0;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    int32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kScanBlock / 64; w++) {
+        before += w < wave ? wsum[w] : 0;
+        total += wsum[w];
+    }
+    if (wave == 0) {
+        int32_t prefix = 0;
+        if (tile > 0) {
+            if (lane == 0)
+                __hip_atomic_store(&words[tile], scan_word(call, SCAN_SUM, total), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            for (int end = tile; end > 0; end -= 64) {  // tiles end - 1 downwards, one per lane
+                const int j = end - 1 - lane;
+                uint64_t w = 0;
+                bool need = j >= 0;
+                do {
+                    if (need) w = __hip_atomic_load(&words[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    need = need && (uint32_t)(w >> 34) != (call & 0x3FFFFFFFu);
+                } while (__any(need));
+                const bool full = j >= 0 && ((w >> 32) & 3) == SCAN_PREFIX;
+                const uint64_t m = __ballot(full);
+                const int stop = m ? __ffsll((unsigned long long)m) - 1 : 64;  // the nearest published prefix
+                int32_t add = j >= 0 && lane <= stop ? (int32_t)(uint32_t)w : 0;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) add += __shfl_xor(add, off, 64);
+                prefix += add;
+                if (m) break;
+            }
+        }
+        if (lane == 0) {
+            __hip_atomic_store(&words[tile], scan_word(call, SCAN_PREFIX, prefix + total), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            prefix_s = prefix;
+        }
+    }
+    __syncthreads();
+    int32_t at = prefix_s + before + inc - sum;
+#pragma unroll
+    for (int q = 0; q < kScanItems; q++) {
+        if (base + q < n) out[base + q] = at;
+        at += v[q];
+    }
+    if (t == 0 && tile == ntiles - 1)
+        __hip_atomic_store(out + n, prefix_s + total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence();
+    __syncthreads();
+    if (t == 0) last_s = atomicAdd(&ctl[1], 1u) - first == (uint32_t)(ntiles - 1);
+    __syncthreads();
+    if (!last_s) return;
+    __threadfence();
+    mail_write(M, mail, seq);
+}
+
 bo_status scan_counts(const int32_t *counts, int32_t *out, int n, int32_t *total, hipStream_t s,
                       const HostRead *extra, int nextra) {
     if (nextra < 0 || nextra > 3) return fail(BO_ERR_INVALID_ARG, "scan_counts: at most three extra reads");
@@ -159,16 +325,43 @@ bo_status scan_counts(const int32_t *counts, int32_t *out, int n, int32_t *total
         if (total) *total = 0;
         return BO_OK;
     }
-    int nb = (n + kScanBlock - 1) / kScanBlock;
-    int32_t *sums = nullptr;
-    BO_TRY(scratch_get(SC_SCAN, sizeof(int32_t) * nb, (void **)&sums));
-    k_block_sums<<<nb, kScanBlock, 0, s>>>(counts, n, sums);
-    k_scan_sums<<<1, kScanBlock, 0, s>>>(sums, nb);
-    k_scan_apply<<<nb, kScanBlock, 0, s>>>(counts, n, sums, out);
-    BO_HIP(hipGetLastError());
+    const int nb = (n + kScanTile - 1) / kScanTile;
+    // the host thread's words and counters; new memory starts at zero
+    struct Work {
+        void *mem = nullptr;
+        size_t tiles = 0;
+        uint32_t call = 0, tickets = 0;
+    };
+    static thread_local Work W;
+    if ((size_t)nb > W.tiles || W.call >= 0x3FFFFFF0u) {
+        if (W.mem) (void)hipFree(W.mem);  // (waits for the device)
+        const size_t tiles = std::max<size_t>(nb, 1024);
+        W = Work{};
+        const hipError_t e = hipMalloc(&W.mem, 8 * (tiles + 1));
+        if (e != hipSuccess) {
+            W.mem = nullptr;
+            return fail(BO_ERR_ALLOC, std::string("scan_counts: hipMalloc failed: ") + hipGetErrorString(e));
+        }
+        BO_HIP(hipMemset(W.mem, 0, 8 * (tiles + 1)));
+        BO_HIP(hipDeviceSynchronize());
+        W.tiles = tiles;
+    }
     int32_t tot = 0;
     r[0] = HostRead{out + n, sizeof tot, &tot};
-    BO_TRY(host_reads(r, 1 + nextra, s));
+    MailItems M;
+    BO_TRY(mail_items(r, 1 + nextra, M));
+    const uint32_t first = W.tickets;
+    W.call++;
+    W.tickets += (uint32_t)nb;
+    k_scan_mail<<<nb, kScanBlock, 0, s>>>(counts, out, n, (uint64_t *)W.mem + 1, (uint32_t *)W.mem, first, W.call, M,
+                                          t_mail.dev, t_mail.seq);
+    const hipError_t le = hipGetLastError();
+    bo_status st = le != hipSuccess ? fail(BO_ERR_HIP, std::string("scan_counts: ") + hipGetErrorString(le))
+                                    : mail_take(r, 1 + nextra, M, s);
+    if (st != BO_OK) {
+        W.tiles = 0;  // the counters may not match the memory: start over with new memory
+        return st;
+    }
     if (total) *total = tot;
     return BO_OK;
 }
