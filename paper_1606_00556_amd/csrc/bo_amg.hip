@@ -39,41 +39,7 @@ __device__ __forceinline__ uint64_t prio(int i, int level) {
     return ((((uint64_t)h) << 32) | (uint32_t)i) + 1ull;
 }
 
-// ---- decoupling ---------------------------------------------------------------
-__global__ void k_qi_decouple(int nx, int ny, int nz, const double *__restrict__ A, int mode,
-                              double *__restrict__ cw, double *__restrict__ app,
-                              int32_t *__restrict__ bad) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int n = nx * ny * nz;
-    if (i >= n) return;
-    size_t N = (size_t)n;
-    const double *B = A + (size_t)S_D * 9 * N + i;
-    double a = B[4 * N], b = B[5 * N], c = B[7 * N], d = B[8 * N];
-    double p0 = B[1 * N], p1 = B[2 * N];
-    double w0, w1;
-    if (mode == BO_QI_DIAG) {
-        if (a == 0.0 || d == 0.0) { *bad = 1; w0 = w1 = 0.0; }
-        else { w0 = p0 / a; w1 = p1 / d; }
-    } else {
-        double det = a * d - b * c;
-        if (det == 0.0 || !isfinite(det)) { *bad = 1; w0 = w1 = 0.0; }
-        else {
-            w0 = (p0 * d - p1 * c) / det;
-            w1 = (p1 * a - p0 * b) / det;
-        }
-    }
-    double dpp = B[0] - w0 * B[3 * N] - w1 * B[6 * N];
-    double sg = dpp < 0.0 ? -1.0 : 1.0;
-    double c0 = sg, c1 = -sg * w0, c2 = -sg * w1;
-    cw[3 * (size_t)i] = c0;
-    cw[3 * (size_t)i + 1] = c1;
-    cw[3 * (size_t)i + 2] = c2;
-    for (int s = 0; s < NSLOT; s++) {
-        const double *As = A + (size_t)s * 9 * N + i;
-        app[(size_t)s * N + i] = c0 * As[0] + c1 * As[3 * N] + c2 * As[6 * N];
-    }
-}
-
+// ---- decoupling of the general form (a plain grid: grid_import) ----------------
 // General BSR form (no grid): the weights c_i of every block row from its
 // diagonal block (a fixed-rate well row has zero saturation couplings, so its
 // weights are (+-1, 0, 0), i.e. no decoupling)
@@ -147,13 +113,26 @@ __global__ void k_app_fill(int npr, const int32_t *__restrict__ rp, const int32_
     }
 }
 
+// entries of the 7-point stencil's rows before row g: seven a row less the
+// neighbours missing at the six faces
+__device__ __forceinline__ int stencil_offset(int g, int nx, int ny, int nz) {
+    const int nxy = nx * ny, k = g / nxy, rem = g % nxy;
+    return 7 * g - (g + nx - 1) / nx - g / nx - (k * nx + min(rem, nx)) - (k * nx + max(0, rem - (nxy - nx))) -
+           min(g, nxy) - max(0, g - nxy * (nz - 1));
+}
+inline long long stencil_entries(const Grid &g) {
+    return g.n() + 2 * ((long long)(g.nx - 1) * g.ny * g.nz + (long long)g.nx * (g.ny - 1) * g.nz +
+                        (long long)g.nx * g.ny * (g.nz - 1));
+}
+
 // level-0 CSR from the slot form (pattern = the 7-point stencil)
-__global__ void k_slots_to_csr(int nx, int ny, int nz, const double *__restrict__ app,
-                               const int32_t *__restrict__ rp, int32_t *__restrict__ ci, double *__restrict__ v) {
+__global__ void k_slots_to_csr(int nx, int ny, int nz, const double *__restrict__ app, int32_t *__restrict__ rp,
+                               int32_t *__restrict__ ci, double *__restrict__ v) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     int n = nx * ny * nz;
     if (i >= n) return;
-    int e = rp[i];
+    int e = stencil_offset(i, nx, ny, nz);
+    rp[i] = e;
     for (int s = 0; s < NSLOT; s++) {
         int j = nbr_of(i, s, nx, ny, nz);
         if (j < 0) continue;
@@ -161,15 +140,7 @@ __global__ void k_slots_to_csr(int nx, int ny, int nz, const double *__restrict_
         v[e] = app[(size_t)s * n + i];
         e++;
     }
-}
-
-__global__ void k_stencil_counts(int nx, int ny, int nz, int32_t *cnt) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int n = nx * ny * nz;
-    if (i >= n) return;
-    int c = 0;
-    for (int s = 0; s < NSLOT; s++) c += nbr_of(i, s, nx, ny, nz) >= 0;
-    cnt[i] = c;
+    if (i == n - 1) rp[n] = e;
 }
 
 // restriction of a 3N residual: rp_i = c_i . v_i
@@ -1732,44 +1703,31 @@ static bo_status to_f32(long long n, const double *a, float *b, hipStream_t s) {
     return BO_OK;
 }
 
-// ---- host: decoupling -------------------------------------------------------------
+// ---- host: decoupling of the general form --------------------------------------------
 bo_status qi_decouple(bo_cpr *pc, hipStream_t s) {
     long long n = pc->n;
-    if (pc->general) {
-        // weights of every row, then A_pp in CSR as level 0 of the hierarchy
-        BO_TRY(pc->cw.alloc(3 * n));
-        BO_HIP(hipMemsetAsync(pc->flag.p, 0, sizeof(int32_t), s));
-        k_qi_weights_bsr<<<grid_for(n), kBlock, 0, s>>>((int)n, pc->Arp.p, pc->Aci.p, pc->Aval.p, pc->o.qi_mode,
-                                                        pc->cw.p, pc->flag.p);
-        BO_HIP(hipGetLastError());
-        int32_t bad = 0;
-        BO_TRY(read_flag(pc->flag.p, s, &bad));
-        if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "quasi-IMPES: singular saturation block or missing diagonal");
-        Level &L0 = pc->lv[0];
-        int npr = pc->npr;
-        L0.n = npr;
-        BO_TRY(pc->sw.cnt.alloc(npr));
-        BO_TRY(L0.rp.alloc(npr + 1));
-        k_app_counts<<<grid_for(npr), kBlock, 0, s>>>(npr, pc->Arp.p, pc->Aci.p, pc->sw.cnt.p);
-        int32_t total = 0;
-        BO_TRY(scan_counts(pc->sw.cnt.p, L0.rp.p, npr, &total, s));
-        L0.nnz = total;
-        BO_TRY(L0.ci.alloc(total));
-        BO_TRY(L0.v.alloc(total));
-        k_app_fill<<<grid_for(npr), kBlock, 0, s>>>(npr, pc->Arp.p, pc->Aci.p, pc->Aval.p, pc->cw.p, L0.rp.p,
-                                                    L0.ci.p, L0.v.p);
-        BO_HIP(hipGetLastError());
-        return BO_OK;
-    }
     BO_TRY(pc->cw.alloc(3 * n));
-    BO_TRY(pc->app.alloc(7 * n));
     BO_HIP(hipMemsetAsync(pc->flag.p, 0, sizeof(int32_t), s));
-    k_qi_decouple<<<grid_for(n), kBlock, 0, s>>>(pc->g.nx, pc->g.ny, pc->g.nz, pc->A.p, pc->o.qi_mode,
-                                                 pc->cw.p, pc->app.p, pc->flag.p);
+    k_qi_weights_bsr<<<grid_for(n), kBlock, 0, s>>>((int)n, pc->Arp.p, pc->Aci.p, pc->Aval.p, pc->o.qi_mode,
+                                                    pc->cw.p, pc->flag.p);
     BO_HIP(hipGetLastError());
     int32_t bad = 0;
     BO_TRY(read_flag(pc->flag.p, s, &bad));
-    if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "quasi-IMPES: singular saturation block");
+    if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "quasi-IMPES: singular saturation block or missing diagonal");
+    Level &L0 = pc->lv[0];
+    int npr = pc->npr;
+    L0.n = npr;
+    BO_TRY(pc->sw.cnt.alloc(npr));
+    BO_TRY(L0.rp.alloc(npr + 1));
+    k_app_counts<<<grid_for(npr), kBlock, 0, s>>>(npr, pc->Arp.p, pc->Aci.p, pc->sw.cnt.p);
+    int32_t total = 0;
+    BO_TRY(scan_counts(pc->sw.cnt.p, L0.rp.p, npr, &total, s));
+    L0.nnz = total;
+    BO_TRY(L0.ci.alloc(total));
+    BO_TRY(L0.v.alloc(total));
+    k_app_fill<<<grid_for(npr), kBlock, 0, s>>>(npr, pc->Arp.p, pc->Aci.p, pc->Aval.p, pc->cw.p, L0.rp.p,
+                                                L0.ci.p, L0.v.p);
+    BO_HIP(hipGetLastError());
     return BO_OK;
 }
 
@@ -2018,13 +1976,9 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
     SetupWork &W = pc->sw;
     if (!pc->general) {
         L0.n = pc->n;
-        DBuf<int32_t> &cnt = W.cnt;
-        BO_TRY(cnt.alloc(L0.n));
         BO_TRY(L0.rp.alloc(L0.n + 1));
-        k_stencil_counts<<<grid_for(L0.n), kBlock, 0, s>>>(pc->g.nx, pc->g.ny, pc->g.nz, cnt.p);
-        int32_t total = 0;
-        BO_TRY(scan_counts(cnt.p, L0.rp.p, L0.n, &total, s));
-        L0.nnz = total;
+        const long long total = stencil_entries(pc->g);
+        L0.nnz = (int)total;
         BO_TRY(L0.ci.alloc(total));
         BO_TRY(L0.v.alloc(total));
         k_slots_to_csr<<<grid_for(L0.n), kBlock, 0, s>>>(pc->g.nx, pc->g.ny, pc->g.nz, pc->app.p, L0.rp.p,

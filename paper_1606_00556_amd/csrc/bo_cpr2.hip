@@ -98,29 +98,6 @@ __device__ __forceinline__ bool inv2_gj(const double *A, double *Ai) {
     return true;
 }
 
-__global__ void k_check_finite2(long long n, const double *__restrict__ v, int32_t *__restrict__ bad) {
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && !isfinite(v[i])) *bad = 1;
-}
-
-__global__ void k_bsr2_to_slots(int nx, int ny, int nz, const int32_t *__restrict__ rp,
-                                const int32_t *__restrict__ ci, const double *__restrict__ v,
-                                double *__restrict__ slots, int32_t *__restrict__ bad) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int n = nx * ny * nz;
-    if (i >= n) return;
-    size_t N = (size_t)n;
-    int e = rp[i], end = rp[i + 1];
-    for (int s = 0; s < NSLOT; s++) {
-        int nb = nbr_of(i, s, nx, ny, nz);
-        bool have = nb >= 0 && e < end && ci[e] == nb;
-        for (int z = 0; z < 4; z++) slots[((size_t)s * 4 + z) * N + i] = have ? v[4 * (size_t)e + z] : 0.0;
-        if (have) e++;
-        else if (nb >= 0) *bad = 1;  // a stencil neighbour is missing from the pattern
-    }
-    if (e != end) *bad = 1;          // entries outside the 7-point stencil
-}
-
 // y = alpha A x + beta y on the slot layout; blocks in ascending column order
 // (coefficients streamed past the caches, as in the black-oil SpMV)
 __global__ void __launch_bounds__(kBlock) k_slot2_spmv(int nx, int ny, int nz, const double *__restrict__ A,
@@ -182,29 +159,6 @@ __global__ void __launch_bounds__(kBlock) k_slot2_col0_residual(int nx, int ny, 
     }
     r[2 * (size_t)i] = v[2 * (size_t)i] - s0;
     r[2 * (size_t)i + 1] = v[2 * (size_t)i + 1] - s1;
-}
-
-// quasi-IMPES weights and the decoupled pressure block in slot form
-__global__ void k_qi2_decouple(int nx, int ny, int nz, const double *__restrict__ A, double *__restrict__ cw,
-                               double *__restrict__ app, int32_t *__restrict__ bad) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int n = nx * ny * nz;
-    if (i >= n) return;
-    size_t N = (size_t)n;
-    const double *D = A + (size_t)S_D * 4 * N + i;
-    double d11 = D[3 * N], d01 = D[1 * N];
-    double w = 0.0;
-    if (d11 == 0.0 || !isfinite(d11)) *bad = 1;
-    else w = d01 / d11;
-    double dpp = D[0] - w * D[2 * N];
-    double sg = dpp < 0.0 ? -1.0 : 1.0;
-    double c0 = sg, c1 = -sg * w;
-    cw[2 * (size_t)i] = c0;
-    cw[2 * (size_t)i + 1] = c1;
-    for (int s = 0; s < NSLOT; s++) {
-        const double *As = A + (size_t)s * 4 * N + i;
-        app[(size_t)s * N + i] = c0 * As[0] + c1 * As[2 * N];
-    }
 }
 
 __global__ void k_qi2_restrict(long long n, const double *__restrict__ cw, const double *__restrict__ v,
@@ -455,11 +409,6 @@ Tile2 tile_geom(const bo_cpr *pc) {
     return T;
 }
 
-bo_status read_flag(bo_cpr *pc, hipStream_t s, int32_t *out) {
-    HostRead rd{pc->flag.p, sizeof(int32_t), out};
-    return host_reads(&rd, 1, s);
-}
-
 }  // namespace
 
 bo_status slot2_spmv(bo_cpr *pc, double alpha, const double *x, double beta, double *y, hipStream_t s) {
@@ -562,39 +511,52 @@ static bo_status cpr2_setup_impl(const bo_bsr2 *A, const bo_grid *grid, const bo
     const long long n = pc->n;
     BO_TRY(pc->flag.alloc(1));
     BO_TRY(pc->A.alloc(28 * n));
-    BO_HIP(hipMemsetAsync(pc->flag.p, 0, sizeof(int32_t), s));
-    k_check_finite2<<<grid_for(4LL * A->nnzb), kBlock, 0, s>>>(4LL * A->nnzb, A->val, pc->flag.p);
-    BO_HIP(hipGetLastError());
-    int32_t bad = 0;
-    BO_TRY(read_flag(pc, s, &bad));
-    if (bad) return fail(BO_ERR_NONFINITE, "bo_cpr2_setup: the matrix holds NaN or Inf");
-    k_bsr2_to_slots<<<grid_for(n), kBlock, 0, s>>>(grid->nx, grid->ny, grid->nz, A->rowptr, A->colind, A->val,
-                                                   pc->A.p, pc->flag.p);
-    BO_HIP(hipGetLastError());
-    BO_TRY(read_flag(pc, s, &bad));
-    if (bad) return fail(BO_ERR_UNSUPPORTED, "bo_cpr2_setup: the pattern is not the grid's 7-point stencil");
     BO_TRY(pc->cw.alloc(2 * n));
     BO_TRY(pc->app.alloc(7 * n));
-    k_qi2_decouple<<<grid_for(n), kBlock, 0, s>>>(grid->nx, grid->ny, grid->nz, pc->A.p, pc->cw.p, pc->app.p,
-                                                  pc->flag.p);
-    BO_HIP(hipGetLastError());
-    BO_TRY(read_flag(pc, s, &bad));
-    if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "bo_cpr2_setup: a zero saturation diagonal entry (no decoupling)");
+    BO_TRY(grid_import<2>(pc->g, A->rowptr, A->colind, A->val, A->nnzb, 0, pc->A.p, pc->cw.p, pc->app.p, pc->flag.p,
+                          "bo_cpr2_setup", s));
+    // the F stage's factors depend on A alone: built on the handle's second
+    // stream beside the AMG setup, forked after level 0's aggregates (as for
+    // the 3x3-block handles), with a flag of their own
+    BO_TRY(pc->fflag.alloc(1));
+    if (!pc->side) BO_HIP(hipStreamCreateWithFlags(&pc->side, hipStreamNonBlocking));
+    for (hipEvent_t &e : pc->evs)
+        if (!e) BO_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    const Tile2 T = tile_geom(pc);
     if (pc->o.ftype == BO_F_BJ) {
         BO_TRY(pc->einv.alloc(4 * n));
-        k_bj2_setup<<<grid_for(n), kBlock, 0, s>>>(n, pc->A.p, pc->einv.p, pc->flag.p);
     } else {
-        const Tile2 T = tile_geom(pc);
         const size_t slots = (size_t)T.ntx * T.nty * T.ns * 64;
         BO_TRY(pc->ilu_f.alloc(slots * kPk2));
         BO_TRY(pc->ilu_b.alloc(slots * kPk2));
         BO_TRY(pc->ilu_w.alloc(2 * slots));
-        k_ilu2_factor<<<T.ntx * T.nty, 64, 0, s>>>(T, pc->A.p, pc->ilu_f.p, pc->ilu_b.p, pc->flag.p);
     }
-    BO_HIP(hipGetLastError());
-    BO_TRY(read_flag(pc, s, &bad));
+    bool forked = false;
+    auto fork = [&]() -> bo_status {
+        forked = true;
+        BO_HIP(hipEventRecord(pc->evs[0], s));
+        BO_HIP(hipStreamWaitEvent(pc->side, pc->evs[0], 0));
+        BO_HIP(hipMemsetAsync(pc->fflag.p, 0, sizeof(int32_t), pc->side));
+        if (pc->o.ftype == BO_F_BJ)
+            k_bj2_setup<<<grid_for(n), kBlock, 0, pc->side>>>(n, pc->A.p, pc->einv.p, pc->fflag.p);
+        else
+            k_ilu2_factor<<<T.ntx * T.nty, 64, 0, pc->side>>>(T, pc->A.p, pc->ilu_f.p, pc->ilu_b.p, pc->fflag.p);
+        BO_HIP(hipGetLastError());
+        return BO_OK;
+    };
+    bo_status ast = BO_OK, fst = BO_OK;
+    if (pc->o.use_amg) ast = amg_setup(pc, s, fork);
+    if (!forked) fst = fork();
+    // join on every path: nothing may still run on the second stream when this returns
+    BO_HIP(hipEventRecord(pc->evs[1], pc->side));
+    BO_HIP(hipStreamWaitEvent(s, pc->evs[1], 0));
+    int32_t bad = 0;
+    HostRead rd{pc->fflag.p, sizeof bad, &bad};
+    const bo_status rst = host_reads(&rd, 1, s);
+    if (fst != BO_OK) return fst;
+    if (rst != BO_OK) return rst;
     if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "bo_cpr2_setup: a singular 2x2 pivot block in the F stage");
-    if (pc->o.use_amg) BO_TRY(amg_setup(pc, s, nullptr));
+    if (ast != BO_OK) return ast;
     BO_TRY(pc->rp_.alloc(n));
     BO_TRY(pc->dp_.alloc(n));
     BO_TRY(pc->t3a.alloc(2 * n));

@@ -66,6 +66,9 @@ struct Mail {
 };
 static thread_local Mail t_mail;
 
+// waits until this wavefront's stores are acknowledged
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // by the threads of one workgroup; the items' words first, then the number
 __device__ void mail_write(const MailItems &M, char *mail, uint32_t seq) {
     for (int q = 0; q < M.count; q++)
@@ -73,10 +76,12 @@ __device__ void mail_write(const MailItems &M, char *mail, uint32_t seq) {
             __hip_atomic_store((uint32_t *)(mail + M.off[q]) + w,
                                __hip_atomic_load(M.src[q] + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __threadfence_system();
+    // the words are written through at system scope; once they are acknowledged
+    // the number may follow (a release fence would write back the whole L2)
+    stores_done();
     __syncthreads();
     if (threadIdx.x == 0)
-        __hip_atomic_store((uint32_t *)(mail + kMail), seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store((uint32_t *)(mail + kMail), seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __global__ void k_mail(MailItems M, char *mail, uint32_t seq) { mail_write(M, mail, seq); }
 
@@ -298,15 +303,15 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_mail(const int32_t *in, int
         if (base + q < n) out[base + q] = at;
         at += v[q];
     }
+    // out[n] is read by another workgroup below: written through, and there
+    // before this workgroup counts as finished
     if (t == 0 && tile == ntiles - 1)
         __hip_atomic_store(out + n, prefix_s + total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
+    stores_done();
     __syncthreads();
     if (t == 0) last_s = atomicAdd(&ctl[1], 1u) - first == (uint32_t)(ntiles - 1);
     __syncthreads();
-    if (!last_s) return;
-    __threadfence();
-    mail_write(M, mail, seq);
+    if (last_s) mail_write(M, mail, seq);
 }
 
 bo_status scan_counts(const int32_t *counts, int32_t *out, int n, int32_t *total, hipStream_t s,
@@ -367,29 +372,92 @@ bo_status scan_counts(const int32_t *counts, int32_t *out, int n, int32_t *total
 }
 
 // ---- BSR SpMV on the ABI layout ---------------------------------------------
-// Three threads per block row, thread r forming component r: per block it
-// reads block row r (three contiguous doubles), so the three threads of a
-// row read the block's 72 contiguous bytes together and a wavefront's loads
-// touch three times fewer cache lines than with one thread per row; each
-// component sums in block order and, within a block, in column order.
-__global__ void k_bsr_spmv(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                           const double *__restrict__ v, double alpha, const double *__restrict__ x,
-                           double beta, double *__restrict__ y) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 3LL * n) return;
-    const int i = (int)(t / 3), r = (int)(t - 3LL * i);
+// y = alpha A x + beta y for BS x BS blocks, BS threads per block row, thread r
+// forming component r; sums in block order and, within a block, in column
+// order.  A workgroup takes 64 consecutive rows: their blocks are one
+// contiguous piece of the value array, which goes through LDS in chunks of 448
+// blocks (the 7-point rows of a workgroup in one chunk) with 16-byte
+// non-temporal loads, each byte read once; the threads' column indices and x
+// entries are in flight beside it.  Bound by HBM.  Reading a block's row per
+// thread from global memory touched each line three times per component and was
+// bound by the L1: 324 us for the 1.23 GB of a 197x203x51 grid (3.8 TB/s), now
+// 229 us (5.4 TB/s; 248 us with temporal loads, 258 us with one contiguous
+// range of rows per XCD).
+// V16: the value array is 16-byte aligned.
+typedef double dvec2 __attribute__((ext_vector_type(2)));
+constexpr int kBsrRows = 64, kBsrChunk = 7 * kBsrRows;
+template <int BS, bool V16>
+__global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int n, const int32_t *__restrict__ rp,
+                                                           const int32_t *__restrict__ ci,
+                                                           const double *__restrict__ v, double alpha,
+                                                           const double *__restrict__ x, double beta,
+                                                           double *__restrict__ y) {
+    constexpr int B2 = BS * BS, NT = kBsrRows * BS, KB = 7;
+    constexpr int NLD = (kBsrChunk * B2 / 2 + 1 + NT - 1) / NT;  // pairs per thread
+    __shared__ __align__(16) double sv[kBsrChunk * B2 + 2];
+    const int t = threadIdx.x, r = t % BS;
+    const int r0 = blockIdx.x * kBsrRows, i = r0 + t / BS;
+    const bool row = i < n;
+    const int e0 = rp[min(i, n)], e1 = row ? rp[i + 1] : e0;
+    const int c_end = rp[min(r0 + kBsrRows, n)];
+    const double yi = row && beta != 0.0 ? beta * y[(size_t)i * BS + r] : 0.0;
     double s = 0.0;
-    const int e1 = rp[i + 1];
-    for (int e = rp[i]; e < e1; e++) {
-        const double *b3 = v + 9 * (size_t)e + 3 * r;
-        const double *xj = x + 3 * (size_t)ci[e];
-        s = s + b3[0] * xj[0];
-        s = s + b3[1] * xj[1];
-        s = s + b3[2] * xj[2];
+    for (int c0 = rp[r0], c1; c0 < c_end; c0 = c1) {
+        c1 = c_end - c0 > kBsrChunk ? c0 + kBsrChunk : c_end;
+        // this row's blocks in the chunk: the first KB columns and x entries
+        const int b0 = max(e0, c0), b1 = min(e1, c1);
+        int c[KB];
+        double xj[KB][BS];
+#pragma unroll
+        for (int k = 0; k < KB; k++) c[k] = ci[min(b0 + k, c1 - 1)];
+        // the chunk's values, from an even position on
+        const size_t d0 = (size_t)c0 * B2 & ~(size_t)1, d1 = (size_t)c1 * B2;
+        const int np = (int)((d1 - d0 + 1) / 2), skip = (int)((size_t)c0 * B2 - d0);
+        double2 ld[NLD];
+#pragma unroll
+        for (int u = 0; u < NLD; u++) {
+            const size_t d = d0 + 2 * (size_t)min(t + NT * u, np - 1);
+            if (V16 && d + 1 < d1) {
+                const dvec2 q = __builtin_nontemporal_load((const dvec2 *)(v + d));
+                ld[u] = make_double2(q.x, q.y);
+            } else ld[u] = make_double2(v[d], d + 1 < d1 ? v[d + 1] : 0.0);
+        }
+#pragma unroll
+        for (int k = 0; k < KB; k++)
+#pragma unroll
+            for (int z = 0; z < BS; z++) xj[k][z] = x[(size_t)c[k] * BS + z];
+#pragma unroll
+        for (int u = 0; u < NLD; u++)
+            if (t + NT * u < np) *(double2 *)(sv + 2 * (t + NT * u)) = ld[u];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KB; k++)
+            if (b0 + k < b1) {
+                const double *a = sv + skip + (b0 + k - c0) * B2 + BS * r;
+#pragma unroll
+                for (int z = 0; z < BS; z++) s = s + a[z] * xj[k][z];
+            }
+        for (int e = b0 + KB; e < b1; e++) {  // rows of more than KB blocks
+            const double *a = sv + skip + (e - c0) * B2 + BS * r, *xe = x + (size_t)ci[e] * BS;
+#pragma unroll
+            for (int z = 0; z < BS; z++) s = s + a[z] * xe[z];
+        }
+        __syncthreads();
     }
-    const double yi = beta == 0.0 ? 0.0 : beta * y[t];
-    y[t] = alpha * s + yi;
+    if (row) y[(size_t)i * BS + r] = alpha * s + yi;
 }
+
+template <int BS>
+bo_status bsr_spmv_launch(int n, const int32_t *rp, const int32_t *ci, const double *v, double alpha, const double *x,
+                          double beta, double *y, hipStream_t s) {
+    const unsigned nb = grid_for(n, kBsrRows);
+    if ((uintptr_t)v % 16 == 0) k_bsr_spmv<BS, true><<<nb, kBsrRows * BS, 0, s>>>(n, rp, ci, v, alpha, x, beta, y);
+    else k_bsr_spmv<BS, false><<<nb, kBsrRows * BS, 0, s>>>(n, rp, ci, v, alpha, x, beta, y);
+    BO_HIP(hipGetLastError());
+    return BO_OK;
+}
+template bo_status bsr_spmv_launch<2>(int, const int32_t *, const int32_t *, const double *, double, const double *,
+                                      double, double *, hipStream_t);
 
 // ---- sliced BSR (general operator of the solver) -------------------------------
 // the width of each slice: its longest row, or in a stencil slice 7 + the
@@ -572,23 +640,153 @@ __global__ void __launch_bounds__(kBlock) k_slot_col0_update(int nx, int ny, int
     ri[2] = ri[2] - s2;
 }
 
-// ---- BSR -> slot layout -------------------------------------------------------
-__global__ void k_bsr_to_slots(int nx, int ny, int nz, const int32_t *__restrict__ rp,
-                               const int32_t *__restrict__ ci, const double *__restrict__ v,
-                               double *__restrict__ slots, int32_t *__restrict__ bad) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int n = nx * ny * nz;
-    if (i >= n) return;
-    size_t N = (size_t)n;
-    int e = rp[i], end = rp[i + 1];
-    for (int s = 0; s < NSLOT; s++) {
-        int nb = nbr_of(i, s, nx, ny, nz);
-        bool have = nb >= 0 && e < end && ci[e] == nb;
-        for (int z = 0; z < 9; z++) slots[((size_t)s * 9 + z) * N + i] = have ? v[9 * (size_t)e + z] : 0.0;
-        if (have) e++;
-        else if (nb >= 0) *bad = 1;  // a stencil neighbour is missing from the pattern
+// quasi-IMPES weights of a cell from its diagonal block D (BS = 3: the 2x2
+// saturation block in full or its diagonal; BS = 2: the one saturation entry),
+// signed for a positive decoupled diagonal; false for a singular one
+template <int BS>
+__device__ __forceinline__ bool qi_weights(const double *D, int mode, double *c) {
+    bool ok = true;
+    double w0 = 0.0, w1 = 0.0, dpp;
+    if constexpr (BS == 3) {
+        const double a = D[4], b = D[5], cc = D[7], d = D[8], p0 = D[1], p1 = D[2];
+        if (mode == BO_QI_DIAG) {
+            ok = !(a == 0.0 || d == 0.0);
+            if (ok) { w0 = p0 / a; w1 = p1 / d; }
+        } else {
+            const double det = a * d - b * cc;
+            ok = !(det == 0.0 || !isfinite(det));
+            if (ok) {
+                w0 = (p0 * d - p1 * cc) / det;
+                w1 = (p1 * a - p0 * b) / det;
+            }
+        }
+        dpp = D[0] - w0 * D[3] - w1 * D[6];
+    } else {
+        const double d11 = D[3], d01 = D[1];
+        ok = !(d11 == 0.0 || !isfinite(d11));
+        if (ok) w0 = d01 / d11;
+        dpp = D[0] - w0 * D[2];
     }
-    if (e != end) *bad = 1;          // entries outside the 7-point stencil
+    const double sg = dpp < 0.0 ? -1.0 : 1.0;
+    c[0] = sg;
+    c[1] = -sg * w0;
+    if (BS == 3) c[2] = -sg * w1;
+    return ok;
+}
+
+// A grid's BSR matrix into the handle, in one pass over it: the slot layout,
+// the decoupling weights and the decoupled pressure block, with the checks.
+// flag: bit 1 a row that is not the 7-point stencil's, bit 2 a value that is
+// not finite, bit 4 a singular saturation block.  A workgroup stages the blocks
+// of 64 rows (one contiguous piece of at most 448 blocks) in LDS with 16-byte
+// loads and writes every slot plane 64 rows at a time.  Bound by HBM (BS = 3:
+// 504 B read and 588 B written per cell).  At 500k cells a finiteness pass, one
+// thread per row copying its blocks plane by plane and a decoupling pass over
+// the planes took 50 + 238 + 37 us, at 2M cells 200 + 924 + 150 us; now 101 and
+// 468 us (4.7 TB/s, the rate of a large copy).
+enum { IMP_PATTERN = 1, IMP_NONFINITE = 2, IMP_SINGULAR = 4 };
+template <int BS, bool V16>
+__global__ void __launch_bounds__(256) k_grid_import(int nx, int ny, int nz, const int32_t *__restrict__ rp,
+                                                     const int32_t *__restrict__ ci, const double *__restrict__ v,
+                                                     int mode, double *__restrict__ slots, double *__restrict__ cw,
+                                                     double *__restrict__ app, int32_t *__restrict__ flag) {
+    constexpr int B2 = BS * BS, NT = 256;
+    constexpr int NLD = (kBsrChunk * B2 / 2 + 1 + NT - 1) / NT;
+    __shared__ __align__(16) double sv[kBsrChunk * B2 + 2];
+    __shared__ int first[kBsrRows];  // a row's first block in the chunk
+    __shared__ unsigned have[kBsrRows];
+    const int n = nx * ny * nz, nxy = nx * ny;
+    const size_t N = (size_t)n;
+    const int t = threadIdx.x, lr = t % kBsrRows, grp = t / kBsrRows;
+    const int r0 = blockIdx.x * kBsrRows, r1 = min(r0 + kBsrRows, n), i = r0 + lr;
+    const int c0 = rp[r0], c1 = rp[r1];
+    if (c1 < c0 || c1 - c0 > kBsrChunk) {
+        if (t == 0) atomicOr(flag, IMP_PATTERN);
+        return;
+    }
+    int bad = 0;
+    // the chunk's values, from an even position on
+    const size_t d0 = (size_t)c0 * B2 & ~(size_t)1, d1 = (size_t)c1 * B2;
+    const int np = (int)((d1 - d0 + 1) / 2), skip = (int)((size_t)c0 * B2 - d0);
+    double2 ld[NLD];
+#pragma unroll
+    for (int u = 0; u < NLD; u++) {
+        const int q = t + NT * u;
+        const size_t d = d0 + 2 * (size_t)q;
+        ld[u] = make_double2(0.0, 0.0);
+        if (q < np) {
+            if (V16 && d + 1 < d1) {
+                const dvec2 w = __builtin_nontemporal_load((const dvec2 *)(v + d));
+                ld[u] = make_double2(w.x, w.y);
+            } else {
+                ld[u] = make_double2(v[d], d + 1 < d1 ? v[d + 1] : 0.0);
+            }
+        }
+    }
+    // the pattern, one row per thread of the first wavefront
+    if (grp == 0) {
+        unsigned m = 0;
+        int f = 0;
+        if (i < n) {
+            const int ix = i % nx, iy = (i / nx) % ny, iz = i / nxy;
+            m = (iz > 0 ? 1u << S_MZ : 0u) | (iy > 0 ? 1u << S_MY : 0u) | (ix > 0 ? 1u << S_MX : 0u) | (1u << S_D) |
+                (ix + 1 < nx ? 1u << S_PX : 0u) | (iy + 1 < ny ? 1u << S_PY : 0u) | (iz + 1 < nz ? 1u << S_PZ : 0u);
+            const int e0 = rp[i], e1 = rp[i + 1];
+            f = e0 - c0;
+            if (e1 - e0 != __popc(m) || f < 0 || f + __popc(m) > c1 - c0) {
+                bad |= IMP_PATTERN;
+                m = 0;
+            } else {
+                const int nb[NSLOT] = {i - nxy, i - nx, i - 1, i, i + 1, i + nx, i + nxy};
+#pragma unroll
+                for (int s = 0; s < NSLOT; s++)
+                    if ((m >> s) & 1u)
+                        if (ci[e0 + __popc(m & ((1u << s) - 1u))] != nb[s]) bad |= IMP_PATTERN;
+            }
+        }
+        first[lr] = f;
+        have[lr] = m;
+    }
+#pragma unroll
+    for (int u = 0; u < NLD; u++)
+        if (t + NT * u < np) {
+            if (!isfinite(ld[u].x) || !isfinite(ld[u].y)) bad |= IMP_NONFINITE;
+            *(double2 *)(sv + 2 * (t + NT * u)) = ld[u];
+        }
+    __syncthreads();
+    const unsigned m = have[lr];
+    const double *row = sv + skip + first[lr] * B2;
+    if (i < n) {
+        // (a wavefront writes one plane of its 64 rows at a time)
+        for (int p = grp; p < NSLOT * B2; p += NT / kBsrRows) {
+            const int s = p / B2, z = p % B2;
+            const bool h = (m >> s) & 1u;
+            slots[(size_t)p * N + i] = h ? row[__popc(m & ((1u << s) - 1u)) * B2 + z] : 0.0;
+        }
+        if (grp == NT / kBsrRows - 1) {
+            double D[B2], c[BS];
+#pragma unroll
+            for (int z = 0; z < B2; z++) D[z] = m ? row[__popc(m & ((1u << S_D) - 1u)) * B2 + z] : 0.0;
+            if (!qi_weights<BS>(D, mode, c)) bad |= IMP_SINGULAR;
+#pragma unroll
+            for (int z = 0; z < BS; z++) cw[(size_t)BS * i + z] = c[z];
+#pragma unroll
+            for (int s = 0; s < NSLOT; s++) {
+                const bool h = (m >> s) & 1u;
+                const double *a = row + (h ? __popc(m & ((1u << s) - 1u)) * B2 : 0);
+                double x = c[0] * (h ? a[0] : 0.0);
+#pragma unroll
+                for (int z = 1; z < BS; z++) x = x + c[z] * (h ? a[BS * z] : 0.0);
+                app[(size_t)s * N + i] = x;
+            }
+        }
+    }
+    if (bad) atomicOr(flag, bad);
+}
+
+__global__ void k_any_nonfinite(long long n, const double *__restrict__ v, int32_t *__restrict__ flag) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n && !isfinite(v[i])) atomicOr(flag, IMP_NONFINITE);
 }
 
 // y = alpha A x + beta y on the slot layout.  Each row sums its blocks in
@@ -1071,20 +1269,37 @@ bo_status slot_col0_update(const Grid &g, const double *A, const TD *dp, double 
 template bo_status slot_col0_update<double>(const Grid &, const double *, const double *, double *, hipStream_t);
 template bo_status slot_col0_update<float>(const Grid &, const double *, const float *, double *, hipStream_t);
 
-bo_status bsr_to_slots(const Grid &g, const int32_t *rp, const int32_t *ci, const double *v, double *slots,
-                       hipStream_t s) {
-    long long n = g.n();
-    int32_t *bad = nullptr;
-    BO_TRY(scratch_get(SC_FLAG, sizeof(int32_t), (void **)&bad));
-    BO_HIP(hipMemsetAsync(bad, 0, sizeof(int32_t), s));
-    k_bsr_to_slots<<<grid_for(n), kBlock, 0, s>>>(g.nx, g.ny, g.nz, rp, ci, v, slots, bad);
+template <int BS>
+bo_status grid_import(const Grid &g, const int32_t *rp, const int32_t *ci, const double *v, long long nnzb, int mode,
+                      double *slots, double *cw, double *app, int32_t *flag, const char *who, hipStream_t s) {
+    const unsigned nb = grid_for(g.n(), kBsrRows);
+    BO_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t), s));
+    if ((uintptr_t)v % 16 == 0)
+        k_grid_import<BS, true><<<nb, 256, 0, s>>>(g.nx, g.ny, g.nz, rp, ci, v, mode, slots, cw, app, flag);
+    else
+        k_grid_import<BS, false><<<nb, 256, 0, s>>>(g.nx, g.ny, g.nz, rp, ci, v, mode, slots, cw, app, flag);
     BO_HIP(hipGetLastError());
     int32_t h = 0;
-    HostRead r{bad, sizeof h, &h};
+    HostRead r{flag, sizeof h, &h};
     BO_TRY(host_reads(&r, 1, s));
-    if (h) return fail(BO_ERR_UNSUPPORTED, "matrix pattern is not the 7-point stencil of the grid");
+    if ((h & IMP_PATTERN) && !(h & IMP_NONFINITE)) {
+        // a wrong pattern leaves values unread: a value that is not finite comes first
+        const long long nv = (long long)BS * BS * nnzb;
+        k_any_nonfinite<<<grid_for(nv), kBlock, 0, s>>>(nv, v, flag);
+        BO_HIP(hipGetLastError());
+        BO_TRY(host_reads(&r, 1, s));
+    }
+    if (h & IMP_NONFINITE) return fail(BO_ERR_NONFINITE, std::string(who) + ": the matrix holds NaN or Inf");
+    if (h & IMP_PATTERN)
+        return fail(BO_ERR_UNSUPPORTED, std::string(who) + ": the pattern is not the grid's 7-point stencil");
+    if (h & IMP_SINGULAR)
+        return fail(BO_ERR_SINGULAR_BLOCK, std::string(who) + ": singular saturation block (no quasi-IMPES decoupling)");
     return BO_OK;
 }
+template bo_status grid_import<2>(const Grid &, const int32_t *, const int32_t *, const double *, long long, int,
+                                  double *, double *, double *, int32_t *, const char *, hipStream_t);
+template bo_status grid_import<3>(const Grid &, const int32_t *, const int32_t *, const double *, long long, int,
+                                  double *, double *, double *, int32_t *, const char *, hipStream_t);
 
 bo_status axpby(long long n, double a, const double *x, double b, double *y, hipStream_t s) {
     k_axpby<<<grid_for(n), kBlock, 0, s>>>(n, a, x, b, y);
@@ -1288,9 +1503,5 @@ extern "C" bo_status bo_bsr_spmv(const bo_bsr *A, double alpha, const double *x,
     if (!A || !x || !y || !A->rowptr || !A->colind || !A->val || A->nbrows < 0)
         return fail(BO_ERR_INVALID_ARG, "bo_bsr_spmv: NULL argument");
     if (A->nbrows == 0) return BO_OK;
-    hipStream_t s = (hipStream_t)stream;
-    k_bsr_spmv<<<grid_for(3LL * A->nbrows), kBlock, 0, s>>>(A->nbrows, A->rowptr, A->colind, A->val, alpha, x, beta,
-                                                            y);
-    BO_HIP(hipGetLastError());
-    return BO_OK;
+    return bsr_spmv_launch<3>(A->nbrows, A->rowptr, A->colind, A->val, alpha, x, beta, y, (hipStream_t)stream);
 }

@@ -3,6 +3,10 @@
 #include "bo_common.hpp"
 
 namespace bo {
+// y = alpha A x + beta y for a BSR matrix of BS x BS blocks (3 and 2)
+template <int BS>
+bo_status bsr_spmv_launch(int n, const int32_t *rp, const int32_t *ci, const double *v, double alpha, const double *x,
+                          double beta, double *y, hipStream_t s);
 
 bo_status slot_spmv(const Grid &g, const double *A, double alpha, const double *x, double beta, double *y,
                     hipStream_t s);
@@ -21,8 +25,13 @@ bo_status sell_build(int n, const int32_t *rp, const int32_t *ci, const double *
 bo_status sell_spmv(int n, const int32_t *soff, const int32_t *sci, const double *sv, const SellGrid &G,
                     double alpha, const double *x, double beta, double *y, hipStream_t s,
                     const double *yin = nullptr);
-bo_status bsr_to_slots(const Grid &g, const int32_t *rp, const int32_t *ci, const double *v, double *slots,
-                       hipStream_t s);
+// a grid's BSR matrix (BS x BS blocks, exactly the 7-point pattern) into slot
+// layout, decoupling weights cw (BS per row) and decoupled pressure block app
+// (7 planes), checked: BO_ERR_NONFINITE, BO_ERR_UNSUPPORTED (another pattern)
+// or BO_ERR_SINGULAR_BLOCK in who's name; reads one word back
+template <int BS>
+bo_status grid_import(const Grid &g, const int32_t *rp, const int32_t *ci, const double *v, long long nnzb, int mode,
+                      double *slots, double *cw, double *app, int32_t *flag, const char *who, hipStream_t s);
 // r -= A Pi_p dp in place (column 0 of each block; dp FP64 or FP32), on the
 // sliced layout (dp on the block columns below npr) and on the slot layout
 template <typename TD>

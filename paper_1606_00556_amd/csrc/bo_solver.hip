@@ -250,17 +250,16 @@ bo_status bo::cpr_setup_impl(const bo_bsr *A, const bo_grid *grid, const bo_cpr_
     pc->npr = (opts->npr > 0 && opts->npr < pc->n) ? opts->npr : pc->n;
     long long n = pc->n;
     BO_TRY(pc->flag.alloc(1));
-    if (!pc->general) BO_TRY(pc->A.alloc(63 * n));
-    // inputs must be finite
-    BO_HIP(hipMemsetAsync(pc->flag.p, 0, sizeof(int32_t), s));
-    k_check_finite<<<grid_for(9LL * A->nnzb), kBlock, 0, s>>>(9LL * A->nnzb, A->val, pc->flag.p);
-    BO_HIP(hipGetLastError());
-    int32_t bad = 0;
-    HostRead rd{pc->flag.p, sizeof bad, &bad};
-    BO_TRY(host_reads(&rd, 1, s));
-    if (bad) return fail(BO_ERR_NONFINITE, "bo_cpr_setup: the matrix holds NaN or Inf");
-    // the BSR copy: the general form's operator (and the pattern of its natural-order ILU)
     if (pc->general) {
+        // inputs must be finite
+        BO_HIP(hipMemsetAsync(pc->flag.p, 0, sizeof(int32_t), s));
+        k_check_finite<<<grid_for(9LL * A->nnzb), kBlock, 0, s>>>(9LL * A->nnzb, A->val, pc->flag.p);
+        BO_HIP(hipGetLastError());
+        int32_t bad = 0;
+        HostRead rd{pc->flag.p, sizeof bad, &bad};
+        BO_TRY(host_reads(&rd, 1, s));
+        if (bad) return fail(BO_ERR_NONFINITE, "bo_cpr_setup: the matrix holds NaN or Inf");
+        // the BSR copy: the general form's operator (and the pattern of its natural-order ILU)
         BO_TRY(pc->Arp.alloc(n + 1));
         BO_TRY(pc->Aci.alloc(A->nnzb));
         BO_TRY(pc->Aval.alloc(9 * (size_t)A->nnzb));
@@ -273,16 +272,18 @@ bo_status bo::cpr_setup_impl(const bo_bsr *A, const bo_grid *grid, const bo_cpr_
         if (A->val != pc->Aval.p)
             BO_HIP(hipMemcpyAsync(pc->Aval.p, A->val, sizeof(double) * 9 * (size_t)A->nnzb, hipMemcpyDeviceToDevice,
                                   s));
-    }
-    if (pc->general) {
         // a grid's cell rows (the first N rows) keep their stencil blocks at
         // implicit columns
         pc->Asg = grid && pc->g.n() <= n ? SellGrid{(int)pc->g.n(), pc->g.nx, pc->g.ny, pc->g.nz} : SellGrid{};
         BO_TRY(sell_build(n, pc->Arp.p, pc->Aci.p, pc->Aval.p, pc->Asg, pc->Asoff, pc->Asci, pc->Asv, s));
+        BO_TRY(qi_decouple(pc, s));
     } else {
-        BO_TRY(bsr_to_slots(pc->g, A->rowptr, A->colind, A->val, pc->A.p, s));
+        BO_TRY(pc->A.alloc(63 * n));
+        BO_TRY(pc->cw.alloc(3 * n));
+        BO_TRY(pc->app.alloc(7 * n));
+        BO_TRY(grid_import<3>(pc->g, A->rowptr, A->colind, A->val, A->nnzb, pc->o.qi_mode, pc->A.p, pc->cw.p,
+                              pc->app.p, pc->flag.p, "bo_cpr_setup", s));
     }
-    BO_TRY(qi_decouple(pc, s));
     // The F stage's factors depend on A alone: they are built on a second
     // stream, forked from s and joined back below, while the AMG setup (many
     // small launches and a few host reads) runs on s.  The fork waits for

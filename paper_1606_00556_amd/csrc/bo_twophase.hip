@@ -18,6 +18,7 @@
 // block row (same schedule as the black-oil kernel); one wavefront per well,
 // a lane per perforated layer, adds the well terms to the diagonal blocks.
 #include "bo_common.hpp"
+#include "bo_linalg.hpp"
 
 namespace bo {
 namespace {
@@ -243,32 +244,6 @@ __global__ void k_jac2_wells(Grid2 G, Fl2 f, const double *__restrict__ xn, int 
     }
 }
 
-// y = alpha A x + beta y, one thread per block row, blocks in stored order
-__global__ void __launch_bounds__(kBlock) k_bsr2_spmv(int n, const int32_t *__restrict__ rp,
-                                                       const int32_t *__restrict__ ci,
-                                                       const double *__restrict__ v, double alpha,
-                                                       const double *__restrict__ x, double beta,
-                                                       double *__restrict__ y) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double s0 = 0.0, s1 = 0.0;
-    for (int e = rp[i]; e < rp[i + 1]; e++) {
-        const double *a = v + 4 * (size_t)e;
-        const int j = ci[e];
-        const double x0 = x[2 * (size_t)j], x1 = x[2 * (size_t)j + 1];
-        s0 = s0 + a[0] * x0; s0 = s0 + a[1] * x1;
-        s1 = s1 + a[2] * x0; s1 = s1 + a[3] * x1;
-    }
-    double *yi = y + 2 * (size_t)i;
-    if (beta == 0.0) {
-        yi[0] = alpha * s0 + 0.0;
-        yi[1] = alpha * s1 + 0.0;
-    } else {
-        yi[0] = alpha * s0 + beta * yi[0];
-        yi[1] = alpha * s1 + beta * yi[1];
-    }
-}
-
 bo_status layout2(const bo_problem *p, long long &n, long long &nnz) {
     if (p->nx < 1 || p->ny < 1 || p->nz < 1) return fail(BO_ERR_INVALID_ARG, "grid dimensions must be >= 1");
     if (p->dual) return fail(BO_ERR_UNSUPPORTED, "bo_jacobian2_bsr: the two-phase path has no dual porosity");
@@ -362,8 +337,5 @@ extern "C" bo_status bo_bsr2_spmv(const bo_bsr2 *A, double alpha, const double *
         return fail(BO_ERR_INVALID_ARG, "bo_bsr2_spmv: NULL argument");
     if (A->nbrows < 0) return fail(BO_ERR_INVALID_ARG, "bo_bsr2_spmv: negative size");
     if (A->nbrows == 0) return BO_OK;
-    k_bsr2_spmv<<<grid_for(A->nbrows), kBlock, 0, (hipStream_t)stream>>>(A->nbrows, A->rowptr, A->colind, A->val,
-                                                                         alpha, x, beta, y);
-    BO_HIP(hipGetLastError());
-    return BO_OK;
+    return bsr_spmv_launch<2>(A->nbrows, A->rowptr, A->colind, A->val, alpha, x, beta, y, (hipStream_t)stream);
 }
