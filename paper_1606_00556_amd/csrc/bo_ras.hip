@@ -18,9 +18,7 @@
 //
 // Factors per slot (tile, step, lane): forward [l_-z, l_-y, l_-x, 0] with
 // l = a_ik / d_k, backward [d, a_+x, a_+y, a_+z], two double2 each (one
-// wavefront load of a double2 reads 1 KB); y in the same order.  The sweeps
-// keep the next step's loads in flight while the current step waits for the
-// neighbours' values (two shuffles).
+// wavefront load of a double2 reads 1 KB); y in the same order.
 //
 // The handle is a bo_cpr with block size 1: bo_cpr_apply applies RAS,
 // bo_cpr_spmv multiplies by the handle's copy of the coefficients, and
@@ -117,88 +115,106 @@ __global__ void __launch_bounds__(64) k_ras_factor(RasGeom T, const double *__re
     }
 }
 
+// The sweeps keep the loads of AH steps in flight in a ring of registers; every
+// load is issued on every path (idle slots load lane 0's data), so that the
+// waits for a step's loads leave the later ones in flight (vector memory
+// operations return in order).  Bound by the step chain (two shuffles, three
+// products, backward a division) and, from a few hundred tiles on, by HBM.
+// 125x125x47, both sweeps: 41.7 us with two steps in flight, 33.7 / 32.6 / 32.4
+// us with 4 / 6 / 8; 500x500x100: 1189, 1159 / 1164 / 1153 us (with unconditional
+// stores, idle lanes writing to idle slots, 1258 us).
+constexpr int kRasAhead = 6;
 struct RasStep {
     double2 f0, f1;
     double v;
 };
 
 // forward sweep: y (slot order) from r (cell order)
+template <int AH>
 __global__ void __launch_bounds__(64) k_ras_forward(RasGeom T, const double2 *__restrict__ Ff,
                                                     const double *__restrict__ r, double *__restrict__ Y) {
     const int t = threadIdx.x, tile = blockIdx.x;
     const Lane L = lane_of(T, tile, t);
-    double yp = 0.0;  // this lane's y of the previous step (the -z neighbour)
+    const int ab = L.active ? L.a + L.b : 1 << 30;
+    const size_t c0 = L.active ? (size_t)L.i + (size_t)T.nx * L.j : 0, nxy = (size_t)T.nx * T.ny;
+    const int lx = L.has_mx ? t - 1 : t, ly = L.has_my ? t - T.ex : t;
+    const double2 *Ft = Ff + ras_pk(T, tile, 0, 0, 0);
+    double *Yt = Y + ras_slot(T, tile, 0, t);
+    auto active = [&](int s) { return (unsigned)(s - ab) < (unsigned)T.nz; };
+    RasStep ring[AH];
     auto fetch = [&](int s, RasStep &F) {
         const int sc = min(s, T.ns - 1);
-        const int k = sc - L.a - L.b;
-        const bool act = L.active && k >= 0 && k < T.nz;
-        const int tl = act ? t : 0;
-        F.f0 = Ff[ras_pk(T, tile, sc, 0, tl)];
-        F.f1 = Ff[ras_pk(T, tile, sc, 1, tl)];
-        const size_t g = act ? (size_t)L.i + (size_t)T.nx * ((size_t)L.j + (size_t)T.ny * k) : 0;
-        F.v = r[g];
+        const bool act = active(sc);
+        const double2 *f = Ft + (size_t)sc * 128 + (act ? t : 0);
+        F.f0 = f[0];
+        F.f1 = f[64];
+        F.v = r[act ? c0 + (size_t)(sc - ab) * nxy : 0];
     };
-    auto step = [&](int s, const RasStep &F) {
-        const double yx = __shfl(yp, L.has_mx ? t - 1 : t, 64);
-        const double yy = __shfl(yp, L.has_my ? t - T.ex : t, 64);
-        const int k = s - L.a - L.b;
-        if (!(L.active && k >= 0 && k < T.nz)) return;
+    double yp = 0.0;  // this lane's y of the previous step (the -z neighbour)
+    auto step = [&](int s, RasStep &F) {
+        const double yx = __shfl(yp, lx, 64), yy = __shfl(yp, ly, 64);
         double y = F.v;
-        if (k > 0) y = y - F.f0.x * yp;
+        if (s - ab > 0) y = y - F.f0.x * yp;
         if (L.has_my) y = y - F.f0.y * yy;
         if (L.has_mx) y = y - F.f1.x * yx;
-        yp = y;
-        Y[ras_slot(T, tile, s, t)] = y;
+        const bool act = active(s);
+        yp = act ? y : 0.0;
+        if (act) Yt[(size_t)s * 64] = yp;
+        fetch(s + AH, F);
     };
-    RasStep R0, R1;
-    fetch(0, R0);
-    int s0 = 0;
-    for (; s0 + 2 <= T.ns; s0 += 2) {
-        fetch(s0 + 1, R1);
-        step(s0, R0);
-        fetch(s0 + 2, R0);
-        step(s0 + 1, R1);
-    }
-    if (s0 < T.ns) step(s0, R0);
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(u, ring[u]);
+    for (int s0 = 0; s0 < T.ns; s0 += AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {
+            if (s0 + u >= T.ns) return;
+            step(s0 + u, ring[u]);
+        }
 }
 
-// backward sweep: x (cell order, the tile's own cells) from y (slot order)
+// backward sweep: x (cell order, the tile's own cells) from y (slot order);
+// lanes without an own cell at a step store to their slot of Y, already read
+template <int AH>
 __global__ void __launch_bounds__(64) k_ras_backward(RasGeom T, const double2 *__restrict__ Fb,
                                                      const double *__restrict__ Y, double *__restrict__ x) {
     const int t = threadIdx.x, tile = blockIdx.x;
     const Lane L = lane_of(T, tile, t);
-    double xp = 0.0;  // this lane's x of the later step (the +z neighbour)
+    const int ab = L.active ? L.a + L.b : 1 << 30;
+    const size_t c0 = L.active ? (size_t)L.i + (size_t)T.nx * L.j : 0, nxy = (size_t)T.nx * T.ny;
+    const int lx = L.has_px ? t + 1 : t, ly = L.has_py ? t + T.ex : t;
+    const double2 *Ft = Fb + ras_pk(T, tile, 0, 0, 0);
+    const double *Yt = Y + ras_slot(T, tile, 0, 0);
+    auto active = [&](int s) { return (unsigned)(s - ab) < (unsigned)T.nz; };
+    RasStep ring[AH];
     auto fetch = [&](int s, RasStep &F) {
         const int sc = max(s, 0);
-        const int k = sc - L.a - L.b;
-        const bool act = L.active && k >= 0 && k < T.nz;
-        const int tl = act ? t : 0;
-        F.f0 = Fb[ras_pk(T, tile, sc, 0, tl)];
-        F.f1 = Fb[ras_pk(T, tile, sc, 1, tl)];
-        F.v = Y[ras_slot(T, tile, sc, tl)];
+        const int tl = active(sc) ? t : 0;
+        const double2 *f = Ft + (size_t)sc * 128 + tl;
+        F.f0 = f[0];
+        F.f1 = f[64];
+        F.v = Yt[(size_t)sc * 64 + tl];
     };
-    auto step = [&](int s, const RasStep &F) {
-        const double xx = __shfl(xp, L.has_px ? t + 1 : t, 64);
-        const double xy = __shfl(xp, L.has_py ? t + T.ex : t, 64);
-        const int k = s - L.a - L.b;
-        if (!(L.active && k >= 0 && k < T.nz)) return;
+    double xp = 0.0;  // this lane's x of the later step (the +z neighbour)
+    auto step = [&](int s, RasStep &F) {
+        const double xx = __shfl(xp, lx, 64), xy = __shfl(xp, ly, 64);
+        const bool act = active(s);
         double v = F.v;
         if (L.has_px) v = v - F.f0.y * xx;
         if (L.has_py) v = v - F.f1.x * xy;
-        if (k + 1 < T.nz) v = v - F.f1.y * xp;
-        xp = v / F.f0.x;
-        if (L.own) x[(size_t)L.i + (size_t)T.nx * ((size_t)L.j + (size_t)T.ny * k)] = xp;
+        if (s - ab + 1 < T.nz) v = v - F.f1.y * xp;
+        xp = act ? v / F.f0.x : 0.0;
+        if (act && L.own) x[c0 + (size_t)(s - ab) * nxy] = xp;
+        fetch(s - AH, F);
     };
-    RasStep R0, R1;
-    fetch(T.ns - 1, R0);
-    int s0 = T.ns - 1;
-    for (; s0 - 2 >= -1; s0 -= 2) {
-        fetch(s0 - 1, R1);
-        step(s0, R0);
-        fetch(s0 - 2, R0);
-        step(s0 - 1, R1);
-    }
-    if (s0 >= 0) step(s0, R0);
+    const int e = T.ns - 1;
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(e - u, ring[u]);
+    for (int s0 = e; s0 >= 0; s0 -= AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {
+            if (s0 - u < 0) return;
+            step(s0 - u, ring[u]);
+        }
 }
 
 __global__ void k_check_finite1(long long n, const double *__restrict__ v, int32_t *__restrict__ bad) {
@@ -230,9 +246,9 @@ bo_status scalar_spmv(const Grid &g, const double *A, double alpha, const double
 bo_status ras_apply(bo_cpr *pc, const double *r, double *z, hipStream_t s) {
     const RasGeom T = ras_geom(pc);
     const int tiles = T.ntx * T.nty;
-    k_ras_forward<<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, pc->ilu_w.p);
+    k_ras_forward<kRasAhead><<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, pc->ilu_w.p);
     BO_HIP(hipGetLastError());
-    k_ras_backward<<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, pc->ilu_w.p, z);
+    k_ras_backward<kRasAhead><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, pc->ilu_w.p, z);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
