@@ -563,7 +563,7 @@ static bo_status cpr2_setup_impl(const bo_bsr2 *A, const bo_grid *grid, const bo
     BO_TRY(pc->t3b.alloc(2 * n));
     BO_TRY(pc->t3c.alloc(2 * n));
     BO_TRY(pc->wf.alloc(2 * n));
-    BO_TRY(pc->red.init());
+    BO_TRY(pc->red.init(s));
     BO_HIP(hipStreamSynchronize(s));
     return BO_OK;
 }

@@ -886,18 +886,138 @@ __global__ void k_fill(long long n, double v, double *__restrict__ y) {
     if (i < n) y[i] = v;
 }
 
-// wavefront sum by butterfly shuffles (fixed order)
-__device__ __forceinline__ double wave_sum(double v) {
+// x of the lane whose number differs in bit MASK (8, 4, 2 or 1): row moves
+// within 16 lanes where the instruction has the pattern, LDS permutes for 4
+template <int MASK>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+    static_assert(MASK == 8 || MASK == 4 || MASK == 2 || MASK == 1, "within 16 lanes");
+    if constexpr (MASK == 4) return (uint32_t)__shfl_xor((int)x, 4, 64);
+    // row_ror:8, quad_perm [2,3,0,1], quad_perm [1,0,3,2]
+    constexpr int ctrl = MASK == 8 ? 0x128 : MASK == 2 ? 0x4E : 0xB1;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xF, 0xF, true);
+}
+// One step of a wavefront's butterfly sum over C values at once: lanes whose
+// bit MASK is clear go on with the even values, the others with the odd ones,
+// so a step halves the values and every value is added in the same order as a
+// butterfly of its own, x[lane] + x[lane ^ MASK].  An odd value stays in both.
+template <int MASK, int C>
+__device__ __forceinline__ void fold(const double (&v)[C], double (&o)[(C + 1) / 2]) {
+    auto lo = [](double x) { return (uint32_t)__double2loint(x); };
+    auto hi = [](double x) { return (uint32_t)__double2hiint(x); };
+    auto dbl = [](uint32_t l, uint32_t h) { return __hiloint2double((int)h, (int)l); };
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = v + __shfl_xor(v, off, 64);
-    return v;
+    for (int i = 0; i < (C + 1) / 2; i++) {
+        const double a = v[2 * i], b = v[2 * i + 1 < C ? 2 * i + 1 : 2 * i];
+        if constexpr (MASK >= 16) {
+            // the swap leaves [a, b] of the clear lanes in one register and
+            // [a, b] of the set lanes in the other
+            auto l = MASK == 32 ? __builtin_amdgcn_permlane32_swap(lo(a), lo(b), false, false)
+                                : __builtin_amdgcn_permlane16_swap(lo(a), lo(b), false, false);
+            auto h = MASK == 32 ? __builtin_amdgcn_permlane32_swap(hi(a), hi(b), false, false)
+                                : __builtin_amdgcn_permlane16_swap(hi(a), hi(b), false, false);
+            o[i] = dbl(l[0], h[0]) + dbl(l[1], h[1]);
+        } else {
+            const bool set = (threadIdx.x & MASK) != 0;
+            const double keep = set ? b : a, send = set ? a : b;
+            o[i] = keep + dbl(lane_xor<MASK>(lo(send)), lane_xor<MASK>(hi(send)));
+        }
+    }
+}
+// Wavefront sums of M values (M <= 64) in the order of a butterfly over lane
+// distances 32, 16, ... 1: lane sum_index<M>() ends with one of the sums.  For
+// M = 56 that is 56 exchanges of a double, where M butterflies take 336.
+template <int M>
+__device__ __forceinline__ double wave_sums(const double (&v)[M]) {
+    constexpr int c1 = (M + 1) / 2, c2 = (c1 + 1) / 2, c3 = (c2 + 1) / 2, c4 = (c3 + 1) / 2, c5 = (c4 + 1) / 2;
+    static_assert((c5 + 1) / 2 == 1, "at most 64 values");
+    double o1[c1], o2[c2], o3[c3], o4[c4], o5[c5], o6[1];
+    fold<32>(v, o1);
+    fold<16>(o1, o2);
+    fold<8>(o2, o3);
+    fold<4>(o3, o4);
+    fold<2>(o4, o5);
+    fold<1>(o5, o6);
+    return o6[0];
+}
+// which of the M sums this lane holds after wave_sums
+template <int M>
+__device__ __forceinline__ int sum_index() {
+    constexpr int c1 = (M + 1) / 2, c2 = (c1 + 1) / 2, c3 = (c2 + 1) / 2, c4 = (c3 + 1) / 2, c5 = (c4 + 1) / 2;
+    const int lane = threadIdx.x % 64;
+    int q = 0;
+    auto up = [&](int bit, int count) { q = min(2 * q + ((lane & bit) ? 1 : 0), count - 1); };
+    up(1, c5);
+    up(2, c4);
+    up(4, c3);
+    up(8, c2);
+    up(16, c1);
+    up(32, M);
+    return q;
+}
+// Sums of M values over the workgroup: thread q < M returns the q-th, its
+// wavefronts added in order.  sh may be used again after a barrier.
+template <int M>
+__device__ __forceinline__ double block_sums(const double (&v)[M], double (&sh)[M][kBlock / 64]) {
+    const double t = wave_sums(v);
+    sh[sum_index<M>()][threadIdx.x / 64] = t;
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x < M) {
+#pragma unroll
+        for (int u = 0; u < kBlock / 64; u++) s = s + sh[threadIdx.x][u];
+    }
+    return s;
+}
+
+// The workgroups' part of a reduction of M sums: partial[q * blocks + block].
+// With done set (a zeroed word) the workgroup that finishes last adds the
+// partial sums as k_partial_final does, in the same order, and writes out (and
+// mirror, pinned host memory): a launch less.  The partial sums are written
+// through and read past the caches, so no fence writes back a whole L2; the
+// word is zero again at the end.
+template <int M>
+__device__ __forceinline__ void finish_sums(const double (&acc)[M], double (&sh)[M][kBlock / 64], double *partial,
+                                            uint32_t *done, double *out, double *mirror) {
+    const double t = block_sums(acc, sh);
+    const uint32_t nb = gridDim.x;
+    if (!done) {
+        if (threadIdx.x < M) partial[(size_t)threadIdx.x * nb + blockIdx.x] = t;
+        return;
+    }
+    static_assert(M <= 64, "wavefront 0 holds the sums");
+    __shared__ uint32_t ticket;
+    if (threadIdx.x < 64) {
+        if (threadIdx.x < M)
+            __hip_atomic_store(&partial[(size_t)threadIdx.x * nb + blockIdx.x], t, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        stores_done();
+        if (threadIdx.x == 0)
+            ticket = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (ticket != nb - 1) return;
+    double s[M];
+#pragma unroll
+    for (int q = 0; q < M; q++) s[q] = 0.0;
+    for (uint32_t b = threadIdx.x; b < nb; b += kBlock) {
+#pragma unroll
+        for (int q = 0; q < M; q++)
+            s[q] = s[q] + __hip_atomic_load(&partial[(size_t)q * nb + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const double r = block_sums(s, sh);
+    if (threadIdx.x < M) {
+        out[threadIdx.x] = r;
+        if (mirror) mirror[threadIdx.x] = r;
+    }
+    if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Multi-dot, pass 1: each of the kRedBlocks workgroups writes the partial
 // sums of its grid-stride share, partial[q * nblocks + block] = sum x[e] V[q][e].
 template <int NV>
 __global__ void __launch_bounds__(kBlock) k_multidot_partial(long long n, const double *__restrict__ x, VecList V,
-                                                             double *__restrict__ partial) {
+                                                             double *__restrict__ partial, uint32_t *done,
+                                                             double *out) {
     __shared__ double sh[NV][kBlock / 64];
     double acc[NV];
 #pragma unroll
@@ -908,19 +1028,7 @@ __global__ void __launch_bounds__(kBlock) k_multidot_partial(long long n, const 
 #pragma unroll
         for (int q = 0; q < NV; q++) acc[q] = acc[q] + xe * V.p[q][e];
     }
-    int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-#pragma unroll
-    for (int q = 0; q < NV; q++) {
-        double w = wave_sum(acc[q]);
-        if (lane == 0) sh[q][wave] = w;
-    }
-    __syncthreads();
-    if (threadIdx.x < NV) {
-        double t = 0.0;
-#pragma unroll
-        for (int w = 0; w < kBlock / 64; w++) t = t + sh[threadIdx.x][w];
-        partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
-    }
+    finish_sums(acc, sh, partial, done, out, nullptr);
 }
 
 // Classical Gram-Schmidt pass over the basis V (nv <= NV vectors), one read of
@@ -963,20 +1071,8 @@ __global__ void __launch_bounds__(kBlock) k_cgs_pass(long long n, double *__rest
             acc[0] = acc[0] + we * we;
         }
     }
-    int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    int nout = (dots || !h) ? nv : 1;
-#pragma unroll
-    for (int q = 0; q < NV; q++) {
-        double t = wave_sum(acc[q]);
-        if (lane == 0) sh[q][wave] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < nout) {
-        double t = 0.0;
-#pragma unroll
-        for (int u = 0; u < kBlock / 64; u++) t = t + sh[threadIdx.x][u];
-        partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
-    }
+    const double t = block_sums(acc, sh);
+    if (threadIdx.x < ((dots || !h) ? nv : 1)) partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
 }
 
 // The same pass for exactly NV vectors below 4 GiB each, one kernel per mode
@@ -988,7 +1084,7 @@ __global__ void __launch_bounds__(kBlock) k_cgs_pass(long long n, double *__rest
 template <int NV, int MODE>
 __global__ void __launch_bounds__(kBlock) k_cgs_exact(uint32_t n, double *__restrict__ w, VecList V,
                                                       const double *__restrict__ h, int rev,
-                                                      double *__restrict__ partial) {
+                                                      double *__restrict__ partial, uint32_t *done, double *out) {
     constexpr bool upd = MODE != 0;
     constexpr int NA = MODE == 2 ? 1 : NV;  // accumulators
     __shared__ double hs[NV];
@@ -1022,19 +1118,7 @@ __global__ void __launch_bounds__(kBlock) k_cgs_exact(uint32_t n, double *__rest
             for (int q = 0; q < NV; q++) acc[q] = acc[q] + we * vq[q];
         }
     }
-    int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-#pragma unroll
-    for (int q = 0; q < NA; q++) {
-        double t = wave_sum(acc[q]);
-        if (lane == 0) sh[q][wave] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < NA) {
-        double t = 0.0;
-#pragma unroll
-        for (int u = 0; u < kBlock / 64; u++) t = t + sh[threadIdx.x][u];
-        partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
-    }
+    finish_sums(acc, sh, partial, done, out, nullptr);
 }
 
 // ---- Gram-Schmidt with the re-orthogonalisation delayed by one step ---------
@@ -1045,16 +1129,27 @@ __global__ void __launch_bounds__(kBlock) k_cgs_exact(uint32_t n, double *__rest
 //
 // Dots: against u and w, for every vector of [V[0..j), u] (NV = j + 1):
 // partial sums of <V[q], u> into rows q, of <V[q], w> into rows NV + q.
+//
+// Bound by the read of the NV + 1 vectors.  The compiler is told that two
+// wavefronts per SIMD are enough: left to itself it keeps registers for eight
+// and issues the loads of an element a few at a time; with all NV + 1 in
+// flight, eight wavefronts per compute unit cover the latency.  The 2 NV sums
+// of a wavefront are folded together (wave_sums): as butterflies of their own
+// they took as long as the loads at 150 k elements.  Time with its final sums,
+// before and now: 150 k elements, 8 vectors 13.7 and 6.4 us, 28 vectors 36.2
+// and 8.8 us; 734 k, 20 vectors 48.1 and 23.1 us; 6 M, 12 vectors 162 and
+// 104 us, 28 vectors 370 and 226 us (6.1 TB/s).
 template <int NV>
-__global__ void __launch_bounds__(kBlock) k_dcgs_dots(uint32_t n, VecList V, const double *__restrict__ w,
-                                                      double *__restrict__ partial) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 2))) k_dcgs_dots(uint32_t n, VecList V, const double *__restrict__ w,
+                                                      double *__restrict__ partial, uint32_t *done, double *out,
+                                                      double *mirror) {
     __shared__ double sh[2 * NV][kBlock / 64];
     auto at = [](const double *p, uint32_t boff) -> const double * {
         return (const double *)((const char *)p + boff);
     };
-    double a1[NV], a2[NV];
+    double acc[2 * NV];
 #pragma unroll
-    for (int q = 0; q < NV; q++) a1[q] = a2[q] = 0.0;
+    for (int q = 0; q < 2 * NV; q++) acc[q] = 0.0;
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
         const uint32_t boff = e * (uint32_t)sizeof(double);
@@ -1065,23 +1160,11 @@ __global__ void __launch_bounds__(kBlock) k_dcgs_dots(uint32_t n, VecList V, con
         const double u = vq[NV - 1];
 #pragma unroll
         for (int q = 0; q < NV; q++) {
-            a1[q] = a1[q] + vq[q] * u;
-            a2[q] = a2[q] + vq[q] * we;
+            acc[q] = acc[q] + vq[q] * u;
+            acc[NV + q] = acc[NV + q] + vq[q] * we;
         }
     }
-    int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-#pragma unroll
-    for (int q = 0; q < NV; q++) {
-        double t1 = wave_sum(a1[q]), t2 = wave_sum(a2[q]);
-        if (lane == 0) { sh[q][wave] = t1; sh[NV + q][wave] = t2; }
-    }
-    __syncthreads();
-    if (threadIdx.x < 2 * NV) {
-        double t = 0.0;
-#pragma unroll
-        for (int u = 0; u < kBlock / 64; u++) t = t + sh[threadIdx.x][u];
-        partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
-    }
+    finish_sums(acc, sh, partial, done, out, mirror);
 }
 
 // Update for step J, from the dots red = [<V[i],u> (s_i), <u,u>, <V[i],w> (p_i),
@@ -1091,12 +1174,17 @@ __global__ void __launch_bounds__(kBlock) k_dcgs_dots(uint32_t n, VecList V, con
 // its squared norm.  beta and r go to sc[0], sc[1] (workgroup 0); every
 // workgroup forms the same coefficients.  A pending vector inside the span of
 // the basis (beta^2 <= 0) leaves beta = 0 in sc[0] and zero vectors.
+//
+// Registers for two wavefronts per SIMD as in the dots: 6 M elements, step 11
+// 169 and now 139 us, step 27 372 and 285 us (5.2 TB/s); steps 15 to 19 lose
+// 4 % of it.
 template <int J>
-__global__ void __launch_bounds__(kBlock) k_dcgs_update(uint32_t n, VecList V, const double *__restrict__ red,
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 2))) k_dcgs_update(uint32_t n, VecList V, const double *__restrict__ red,
                                                         double *__restrict__ sc, int rev,
-                                                        double *__restrict__ partial, double *sc_mirror) {
+                                                        double *__restrict__ partial, double *sc_mirror, uint32_t *done,
+                                                        double *norm2, double *norm2_mirror) {
     __shared__ double cs[J > 0 ? J : 1], cp[J > 0 ? J : 1], cb[2];
-    __shared__ double sh[kBlock / 64];
+    __shared__ double sh[1][kBlock / 64];
     if (threadIdx.x == 0) {
         double ss = 0.0, sp = 0.0;
         for (int i = 0; i < J; i++) {
@@ -1125,7 +1213,7 @@ __global__ void __launch_bounds__(kBlock) k_dcgs_update(uint32_t n, VecList V, c
     auto at = [](const double *p, uint32_t boff) -> double * {
         return (double *)((const char *)p + boff);
     };
-    double acc = 0.0;
+    double acc[1] = {0.0};
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
         const uint32_t boff = (rev ? n - 1 - e : e) * (uint32_t)sizeof(double);
@@ -1143,18 +1231,9 @@ __global__ void __launch_bounds__(kBlock) k_dcgs_update(uint32_t n, VecList V, c
         double wn = we - s2 - r * v;
         *at(V.p[J], boff) = v;
         *at(V.p[J + 1], boff) = wn;
-        acc = acc + wn * wn;
+        acc[0] = acc[0] + wn * wn;
     }
-    int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    double t = wave_sum(acc);
-    if (lane == 0) sh[wave] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double u = 0.0;
-#pragma unroll
-        for (int k = 0; k < kBlock / 64; k++) u = u + sh[k];
-        partial[blockIdx.x] = u;
-    }
+    finish_sums(acc, sh, partial, done, norm2, norm2_mirror);
 }
 
 // pass 2 (one workgroup per result): out[q] = sum over the partials in a
@@ -1164,17 +1243,12 @@ __global__ void __launch_bounds__(kBlock) k_dcgs_update(uint32_t n, VecList V, c
 // the host reads after the stream's next event, instead of a copy)
 __global__ void __launch_bounds__(kBlock) k_partial_final(int nblocks, const double *__restrict__ partial,
                                                           double *__restrict__ out, double *mirror = nullptr) {
-    __shared__ double sh[kBlock / 64];
-    int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    int q = blockIdx.x;
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) s = s + partial[(size_t)q * nblocks + b];
-    s = wave_sum(s);
-    if (lane == 0) sh[wave] = s;
-    __syncthreads();
+    __shared__ double sh[1][kBlock / 64];
+    const int q = blockIdx.x;
+    double s[1] = {0.0};
+    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) s[0] = s[0] + partial[(size_t)q * nblocks + b];
+    const double t = block_sums(s, sh);
     if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < kBlock / 64; w++) t = t + sh[w];
         out[q] = t;
         if (mirror) mirror[q] = t;
     }
@@ -1336,8 +1410,15 @@ bo_status scale_copy(long long n, const double *inv, const double *x, double *y,
     return BO_OK;
 }
 
-bo_status Reducer::init() {
+__global__ void k_clear_word(uint32_t *w) { *w = 0; }
+
+bo_status Reducer::init(hipStream_t s) {
     BO_TRY(partial.alloc((size_t)kRedBlocks * kMaxVecList));
+    if (!done.p) {
+        BO_TRY(done.alloc(1));
+        k_clear_word<<<1, 1, 0, s>>>(done.p);
+        BO_HIP(hipGetLastError());
+    }
     return BO_OK;
 }
 
@@ -1365,6 +1446,19 @@ static int resident_blocks(const void *kernel, int slot) {
     return c;
 }
 
+// Workgroups that a pass over n elements needs: one without an element would
+// add a zero to the partial sums, in the order of the rest.
+static int used_blocks(int nb, long long n) {
+    return (int)std::max<long long>(1, std::min<long long>(nb, (n + kBlock - 1) / kBlock));
+}
+
+// Whether the workgroup that ends last adds up the partial sums itself instead
+// of a second kernel: with few workgroups (up to 32 k elements).  Their counts
+// go to one word one after the other, about 9 ns each.  Dots of 4 vectors with
+// their final sums: in place 3.8 us at 6 k elements (24 workgroups) and 11.2
+// at 150 k (586), where those by a second kernel take 6.1 us.
+static bool finish_in_place(int nb) { return nb <= 128; }
+
 bo_status Reducer::cgs_pass(long long n, double *w, const double *const *Vhost, int nv, const double *h, bool dots,
                             double *out, hipStream_t s, bool reverse) {
     if (nv < 1 || nv > kMaxVecList) return fail(BO_ERR_INVALID_ARG, "cgs_pass: 1..64 vectors");
@@ -1373,14 +1467,17 @@ bo_status Reducer::cgs_pass(long long n, double *w, const double *const *Vhost, 
     // a fixed grid per vector count (the partial sums' order does not depend
     // on the device), small enough to be resident at once
     int nb = kRedBlocks;
+    const int nout = (dots || !h) ? nv : 1;
+    bool fin = false;
     if (nv <= kCgsExactMax && n < (1ll << 29)) {
         const uint32_t n32 = (uint32_t)n;
         const int mode = !h ? 0 : dots ? 1 : 2, rev = reverse ? 1 : 0;
         switch (nv * 4 + mode) {
 #define BO_CGS1(K, M)                                                                  \
     case K * 4 + M:                                                                    \
-        nb = resident_blocks((const void *)k_cgs_exact<K, M>, K * 4 + M);              \
-        k_cgs_exact<K, M><<<nb, kBlock, 0, s>>>(n32, w, L, h, rev, partial.p);              \
+        nb = used_blocks(resident_blocks((const void *)k_cgs_exact<K, M>, K * 4 + M), n); \
+        fin = finish_in_place(nb);                                               \
+        k_cgs_exact<K, M><<<nb, kBlock, 0, s>>>(n32, w, L, h, rev, partial.p, fin ? done.p : nullptr, out); \
         break;
 #define BO_CGS(K) BO_CGS1(K, 0) BO_CGS1(K, 1) BO_CGS1(K, 2)
             BO_CGS(1) BO_CGS(2) BO_CGS(3) BO_CGS(4) BO_CGS(5) BO_CGS(6) BO_CGS(7) BO_CGS(8)
@@ -1400,20 +1497,25 @@ bo_status Reducer::cgs_pass(long long n, double *w, const double *const *Vhost, 
     } else {
         k_cgs_pass<64><<<nb, kBlock, 0, s>>>(n, w, L, nv, h, dots ? 1 : 0, partial.p);
     }
-    int nout = (dots || !h) ? nv : 1;
-    k_partial_final<<<nout, kBlock, 0, s>>>(nb, partial.p, out);
+    if (!fin) k_partial_final<<<nout, kBlock, 0, s>>>(nb, partial.p, out);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
 
-static void launch_partial(int nv, long long n, const double *x, const VecList &L, double *partial, hipStream_t s) {
+bo_status Reducer::multidot_16(long long n, const double *x, const VecList &L, int nv, double *out, hipStream_t s) {
+    const int nb = used_blocks(kRedBlocks, n);
+    const bool fin = finish_in_place(nb);
+    uint32_t *d = fin ? done.p : nullptr;
     switch (nv) {
-#define BO_MD(K) case K: k_multidot_partial<K><<<kRedBlocks, kBlock, 0, s>>>(n, x, L, partial); break;
+#define BO_MD(K) case K: k_multidot_partial<K><<<nb, kBlock, 0, s>>>(n, x, L, partial.p, d, out); break;
         BO_MD(1) BO_MD(2) BO_MD(3) BO_MD(4) BO_MD(5) BO_MD(6) BO_MD(7) BO_MD(8)
         BO_MD(9) BO_MD(10) BO_MD(11) BO_MD(12) BO_MD(13) BO_MD(14) BO_MD(15) BO_MD(16)
 #undef BO_MD
     default: break;
     }
+    if (!fin) k_partial_final<<<nv, kBlock, 0, s>>>(nb, partial.p, out);
+    BO_HIP(hipGetLastError());
+    return BO_OK;
 }
 
 bo_status Reducer::multidot(long long n, const double *x, const double *const *Vhost, int nv, double *out,
@@ -1422,10 +1524,8 @@ bo_status Reducer::multidot(long long n, const double *x, const double *const *V
         int c = std::min(16, nv - q0);
         VecList L{};
         for (int q = 0; q < c; q++) L.p[q] = Vhost[q0 + q];
-        launch_partial(c, n, x, L, partial.p, s);
-        k_partial_final<<<c, kBlock, 0, s>>>(kRedBlocks, partial.p, out + q0);
+        BO_TRY(multidot_16(n, x, L, c, out + q0, s));
     }
-    BO_HIP(hipGetLastError());
     return BO_OK;
 }
 
@@ -1437,11 +1537,13 @@ bo_status Reducer::dcgs_dots(long long n, const double *const *Vhost, int nv, co
     for (int q = 0; q < nv; q++) L.p[q] = Vhost[q];
     const uint32_t n32 = (uint32_t)n;
     int nb = kRedBlocks;
+    bool fin = false;
     switch (nv) {
 #define BO_D(K)                                                                   \
     case K:                                                                       \
-        nb = resident_blocks((const void *)k_dcgs_dots<K>, 4 * K + 3);            \
-        k_dcgs_dots<K><<<nb, kBlock, 0, s>>>(n32, L, w, partial.p);               \
+        nb = used_blocks(resident_blocks((const void *)k_dcgs_dots<K>, 4 * K + 3), n); \
+        fin = finish_in_place(nb);                                         \
+        k_dcgs_dots<K><<<nb, kBlock, 0, s>>>(n32, L, w, partial.p, fin ? done.p : nullptr, out, mirror); \
         break;
         BO_D(1) BO_D(2) BO_D(3) BO_D(4) BO_D(5) BO_D(6) BO_D(7) BO_D(8)
         BO_D(9) BO_D(10) BO_D(11) BO_D(12) BO_D(13) BO_D(14) BO_D(15) BO_D(16)
@@ -1450,7 +1552,7 @@ bo_status Reducer::dcgs_dots(long long n, const double *const *Vhost, int nv, co
 #undef BO_D
     default: break;
     }
-    k_partial_final<<<2 * nv, kBlock, 0, s>>>(nb, partial.p, out, mirror);
+    if (!fin) k_partial_final<<<2 * nv, kBlock, 0, s>>>(nb, partial.p, out, mirror);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
@@ -1464,11 +1566,14 @@ bo_status Reducer::dcgs_update(long long n, const double *const *Vhost, int j, c
     const uint32_t n32 = (uint32_t)n;
     const int rev = reverse ? 1 : 0;
     int nb = kRedBlocks;
+    bool fin = false;
     switch (j) {
 #define BO_U(K)                                                                     \
     case K:                                                                         \
-        nb = resident_blocks((const void *)k_dcgs_update<K>, 4 * (kCgsExactMax + 1) + K);          \
-        k_dcgs_update<K><<<nb, kBlock, 0, s>>>(n32, L, red, sc, rev, partial.p, sc_mirror); \
+        nb = used_blocks(resident_blocks((const void *)k_dcgs_update<K>, 4 * (kCgsExactMax + 1) + K), n); \
+        fin = finish_in_place(nb);                                                  \
+        k_dcgs_update<K><<<nb, kBlock, 0, s>>>(n32, L, red, sc, rev, partial.p, sc_mirror, fin ? done.p : nullptr, \
+                                               norm2, norm2_mirror);                \
         break;
         BO_U(0) BO_U(1) BO_U(2) BO_U(3) BO_U(4) BO_U(5) BO_U(6) BO_U(7)
         BO_U(8) BO_U(9) BO_U(10) BO_U(11) BO_U(12) BO_U(13) BO_U(14) BO_U(15)
@@ -1477,7 +1582,7 @@ bo_status Reducer::dcgs_update(long long n, const double *const *Vhost, int j, c
 #undef BO_U
     default: break;
     }
-    k_partial_final<<<1, kBlock, 0, s>>>(nb, partial.p, norm2, norm2_mirror);
+    if (!fin) k_partial_final<<<1, kBlock, 0, s>>>(nb, partial.p, norm2, norm2_mirror);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
@@ -1485,10 +1590,7 @@ bo_status Reducer::dcgs_update(long long n, const double *const *Vhost, int j, c
 bo_status Reducer::dot(long long n, const double *x, const double *y, double *out, hipStream_t s) {
     VecList L{};
     L.p[0] = y;
-    launch_partial(1, n, x, L, partial.p, s);
-    k_partial_final<<<1, kBlock, 0, s>>>(kRedBlocks, partial.p, out);
-    BO_HIP(hipGetLastError());
-    return BO_OK;
+    return multidot_16(n, x, L, 1, out, s);
 }
 
 }  // namespace bo

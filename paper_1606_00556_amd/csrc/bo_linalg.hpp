@@ -59,7 +59,8 @@ constexpr int kRedBlocks = 1024;  // fixed reduction grid (determinism)
 // Deterministic dot products; results land in device memory.
 struct Reducer {
     DBuf<double> partial;
-    bo_status init();
+    DBuf<uint32_t> done;  // workgroups finished in the running pass; zero between passes
+    bo_status init(hipStream_t s);
     // out[q] = <x, V[q]>, q < nv; Vhost is a host array of device pointers
     bo_status multidot(long long n, const double *x, const double *const *Vhost, int nv, double *out,
                        hipStream_t s);
@@ -80,6 +81,9 @@ struct Reducer {
     bo_status dcgs_update(long long n, const double *const *Vhost, int j, const double *red, double *sc,
                           double *norm2, hipStream_t s, bool reverse, double *sc_mirror = nullptr,
                           double *norm2_mirror = nullptr);
+
+  private:
+    bo_status multidot_16(long long n, const double *x, const VecList &L, int nv, double *out, hipStream_t s);
 };
 
 }  // namespace bo

@@ -103,11 +103,15 @@ extern "C" bo_status bo_newton_create(const bo_problem *p, const bo_grid *grid, 
         (st = h->b.alloc(3 * (size_t)n)) || (st = h->dx.alloc(3 * (size_t)n)) ||
         (st = h->rprev.alloc(3 * (size_t)n)) || (st = h->tmp.alloc(3 * (size_t)n)) ||
         (st = h->xold.alloc(3 * (size_t)n)) || (st = h->dsmax.alloc(1)) || (st = h->nrm.alloc(1)) ||
-        (st = h->red.init())) {
+        (st = h->red.init((hipStream_t)stream))) {
         delete h;
         return st;
     }
-    (void)stream;
+    // steps may run on another stream
+    if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) {
+        delete h;
+        return fail(BO_ERR_HIP, "bo_newton_create: stream error");
+    }
     *out = h;
     return BO_OK;
 }

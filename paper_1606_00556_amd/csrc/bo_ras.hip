@@ -289,7 +289,7 @@ static bo_status ras_setup_impl(const bo_grid *grid, const double *coef, const b
     BO_TRY(host_reads(&rd, 1, s));
     if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "bo_ras_setup: a zero or non-finite ILU(0) pivot");
     BO_TRY(pc->t3a.alloc(n));
-    BO_TRY(pc->red.init());
+    BO_TRY(pc->red.init(s));
     BO_HIP(hipStreamSynchronize(s));
     return BO_OK;
 }

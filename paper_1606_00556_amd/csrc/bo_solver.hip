@@ -325,7 +325,7 @@ bo_status bo::cpr_setup_impl(const bo_bsr *A, const bo_grid *grid, const bo_cpr_
     BO_TRY(pc->t3b.alloc(3 * n));
     BO_TRY(pc->t3c.alloc(3 * n));
     BO_TRY(pc->wf.alloc(3 * n));
-    BO_TRY(pc->red.init());
+    BO_TRY(pc->red.init(s));
     BO_HIP(hipStreamSynchronize(s));
     return BO_OK;
 }

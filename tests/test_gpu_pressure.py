@@ -95,6 +95,28 @@ def test_gmres_steps_match_oracle(B, k):
     assert gi["rel_residual"] == pytest.approx(rel, rel=1e-8)
 
 
+@pytest.mark.parametrize("orth", [1, 2])
+@pytest.mark.parametrize("grid,k", [((5, 3, 1), 3), ((16, 4, 4), 12), ((32, 32, 32), 30), ((43, 27, 29), 29)])
+def test_gmres_sums_over_few_and_many_workgroups(B, grid, k, orth):
+    """The Gram-Schmidt sums: part of a wavefront, one whole workgroup, the
+    most workgroups whose sums the last one adds up itself (32,768 elements)
+    and more, up to the longest basis; iterate and residual as above."""
+    import torch
+    c = cg.pressure_case(*grid, seed=16)
+    coef = to_dev(c.coef.reshape(-1))
+    pc = B.bo_ras_setup(grid_of(c), coef)
+    xo, oi = PR.solve(c, tile=(6, 6), overlap=1, m=30, maxit=k)
+    x = torch.zeros(c.n, dtype=torch.float64, device="cuda")
+    opts = B.bo_fgmres_default_opts(flexible=0, maxit=k, rtol=1e-300, orth=orth)
+    for _ in range(2):  # the second solve finds the counters as the first left them
+        x.zero_()
+        gi = B.bo_scalar_solve(pc, coef, to_dev(c.b), x, opts)
+        assert gi["iterations"] == oi["iterations"] == k
+        assert rel_err(to_host(x), xo) <= 1e-8
+        rel = np.linalg.norm(c.b - PR.spmv(c.nx, c.ny, c.nz, c.coef, to_host(x))) / np.linalg.norm(c.b)
+        assert rel == pytest.approx(oi["rel_residual"], rel=1e-6, abs=1e-14)
+
+
 def test_flexible_and_standard_agree(B):
     """With a fixed linear preconditioner flexible GMRES and the standard
     form build the same iterate: RAS on the scalar system, and the black-oil
