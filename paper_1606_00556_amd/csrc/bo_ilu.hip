@@ -100,49 +100,79 @@ __device__ __forceinline__ void shfl_arr(const double *src, double *dst, int lan
     for (int z = 0; z < K; z++) dst[z] = __shfl(src[z], lane, 64);
 }
 
-// Factorisation in two passes, in FP64 for every storage format.  Pack: one
-// thread per slot (tile, step, lane), all slots at once, gathers its cell's
-// blocks into the FP64 packed layout (forward slot: [A_ii | Az Ay Ax] with
-// the lower blocks -z, -y, -x; backward slot: [- | Uz Ux Uy] with the upper
-// blocks +z, +x, +y; zero where the neighbour lies outside the tile or grid)
-// and records the slot of each cell.  Chain: one wavefront per tile walks the
-// steps; lane t = a + tile_x*b at step s handles layer k = s - a - b and forms
-// E_i = A_ii - sum over -z, -y, -x of (A_ik E_k^{-1}) U_ki from the values its
-// neighbours held one step earlier (shuffled), reading each step's blocks
-// from the packed layout (1 KB per load instruction), and E_i^{-1} by
-// Gauss-Jordan with partial pivoting.
+// Factorisation in two passes, in FP64 for every storage format.  Pack: the
+// blocks of every slot (tile, step, lane) into the FP64 packed layout (forward
+// slot: [A_ii | Az Ay Ax] with the lower blocks -z, -y, -x; backward slot:
+// [- | Uz Ux Uy] with the upper blocks +z, +x, +y; zero where the neighbour
+// lies outside the tile or grid), and the slot of each cell.  Chain: one
+// wavefront per tile walks the steps; lane t = a + tile_x*b at step s handles
+// layer k = s - a - b and forms E_i = A_ii - sum over -z, -y, -x of
+// (A_ik E_k^{-1}) U_ki from the values its neighbours held one step earlier
+// (shuffled), reading each step's blocks from the packed layout (1 KB per load
+// instruction), and E_i^{-1} by Gauss-Jordan with partial pivoting.
+//
+// The pack is bound by the memory it reads and writes.  The lanes of a step
+// lie in as many layers as the tile is wide, so a thread gathering its own
+// slot reads 64 separate sectors per load, and the cells beside them come in
+// later steps: eight times the matrix through the L2.  A workgroup takes
+// kPackSteps steps of a tile instead and reads runs of a tile's row at one
+// layer, 18 planes at a time (two blocks), into LDS at their slots; it touches
+// a sector (kPackSteps + tile_x - 1) / kPackSteps times.  2 M cells: 1062 and now
+// 650 us alone (2.1 GB); chunks of 4 steps 684 us, workgroups dealt to the
+// XCDs in turn instead of in ranges 702 us.
+constexpr int kPackSteps = 8;
 __global__ void __launch_bounds__(kBlock) k_ilu_pack(TileGeom T, const double *__restrict__ A,
                                                      double2 *__restrict__ Ff, double2 *__restrict__ Fb,
                                                      int32_t *__restrict__ slot_of) {
-    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= T.slots()) return;
-    const int t = (int)(q % 64);
-    const long long ts = q / 64;
-    const int s = (int)(ts % T.ns), tile = (int)(ts / T.ns);
-    const int a = t % T.tx, b = t / T.tx;
+    __shared__ double buf[18][kPackSteps * 64];
+    const int chunks = (T.ns + kPackSteps - 1) / kPackSteps;
+    const int wg = xcd_block(blockIdx.x, gridDim.x);
+    const int tile = wg / chunks, s0 = (wg % chunks) * kPackSteps;
     const int ti = tile % T.ntx, tj = tile / T.ntx;
-    const int i = ti * T.tx + a, j = tj * T.ty + b, k = s - a - b;
-    if (!(t < T.tx * T.ty && i < T.nx && j < T.ny && k >= 0 && k < T.nz)) return;  // idle slot
+    const int wave = threadIdx.x / 64, t = threadIdx.x % 64;
+    const int a = t % T.tx, b = t / T.tx;
+    const int i = ti * T.tx + a, j = tj * T.ty + b;
+    const bool column = t < T.tx * T.ty && i < T.nx && j < T.ny;
     const bool has_mx = a > 0, has_my = b > 0;
     const bool has_px = a + 1 < T.tx && i + 1 < T.nx, has_py = b + 1 < T.ty && j + 1 < T.ny;
     const size_t N = (size_t)T.nx * T.ny * T.nz;
-    const int g = i + T.nx * (j + T.ny * k);
-    double fw[36], bw[36];
+    // blocks 2h and 2h + 1 of [A_ii Az Ay Ax - Uz Ux Uy]
+#pragma unroll 1
+    for (int h = 0; h < 4; h++) {
+        const int sl0 = h == 0 ? S_D : h == 1 ? S_MY : h == 2 ? -1 : S_PX;
+        const int sl1 = h == 0 ? S_MZ : h == 1 ? S_MX : h == 2 ? S_PZ : S_PY;
+        // pass `it`: layer k = s - a - b of the lanes whose step s = s0 + u is in the chunk
+        for (int it = wave; it < kPackSteps + T.tx - 1; it += kBlock / 64) {
+            const int u = it - (T.tx - 1) + a, k = s0 + u - a - b;
+            if (!(column && u >= 0 && u < kPackSteps && k >= 0 && k < T.nz)) continue;
+            const bool h0 = h == 0 ? true : h == 1 ? has_my : h == 2 ? false : has_px;
+            const bool h1 = h == 0 ? k > 0 : h == 1 ? has_mx : h == 2 ? k + 1 < T.nz : has_py;
+            const int g = i + T.nx * (j + T.ny * k);
+            double x[18];
+            if (h0) load_blk(A, sl0, N, g, x);
+            else
+                for (int z = 0; z < 9; z++) x[z] = 0.0;
+            if (h1) load_blk(A, sl1, N, g, x + 9);
+            else
+                for (int z = 9; z < 18; z++) x[z] = 0.0;
 #pragma unroll
-    for (int z = 0; z < 36; z++) fw[z] = bw[z] = 0.0;
-    load_blk(A, S_D, N, g, fw);
-    if (k > 0) load_blk(A, S_MZ, N, g, fw + 9);
-    if (has_my) load_blk(A, S_MY, N, g, fw + 18);
-    if (has_mx) load_blk(A, S_MX, N, g, fw + 27);
-    if (k + 1 < T.nz) load_blk(A, S_PZ, N, g, bw + 9);
-    if (has_px) load_blk(A, S_PX, N, g, bw + 18);
-    if (has_py) load_blk(A, S_PY, N, g, bw + 27);
+            for (int z = 0; z < 18; z++) buf[z][u * 64 + t] = x[z];
+        }
+        __syncthreads();
+        for (int u = wave; u < kPackSteps; u += kBlock / 64) {
+            const int s = s0 + u, k = s - a - b;
+            if (!(column && s < T.ns && k >= 0 && k < T.nz)) continue;  // idle slot
+            double2 *const F = h < 2 ? Ff : Fb;
 #pragma unroll
-    for (int p2 = 0; p2 < kPairs; p2++) {
-        Ff[pk_index(tile, T.ns, s, p2, t)] = make_double2(fw[2 * p2], fw[2 * p2 + 1]);
-        if (p2 >= 4) Fb[pk_index(tile, T.ns, s, p2, t)] = make_double2(bw[2 * p2], bw[2 * p2 + 1]);
+            for (int p = 0; p < 9; p++) {
+                if (h == 2 && p < 4) continue;  // values 0..7 of the backward slot: the chain's
+                F[pk_index(tile, T.ns, s, (h & 1) * 9 + p, t)] =
+                    make_double2(buf[2 * p][u * 64 + t], buf[2 * p + 1][u * 64 + t]);
+            }
+            if (h == 0) slot_of[i + T.nx * (j + T.ny * k)] = (int32_t)(((long long)tile * T.ns + s) * 64 + t);
+        }
+        __syncthreads();
     }
-    slot_of[g] = (int32_t)q;
 }
 
 // The same pack straight from a BSR matrix whose first N block rows are the
@@ -939,7 +969,8 @@ bo_status fstage_launch(bo_cpr *pc, hipStream_t s) {
             k_ilu_pack_bsr<<<grid_for(T.slots()), kBlock, 0, s>>>(T, pc->Arp.p, pc->Aci.p, pc->Aval.p, Pf, Pb,
                                                                   pc->ilu_slot.p, ff);
         else
-            k_ilu_pack<<<grid_for(T.slots()), kBlock, 0, s>>>(T, pc->A.p, Pf, Pb, pc->ilu_slot.p);
+            k_ilu_pack<<<nb * ((T.ns + kPackSteps - 1) / kPackSteps), kBlock, 0, s>>>(T, pc->A.p, Pf, Pb,
+                                                                                     pc->ilu_slot.p);
         if (f64)
             k_ilu_chain<ST_F64><<<nb, 64, 0, s>>>(T, Pf, Pb, ff, ext ? pc->x_einv_f.p : nullptr, nullptr, nullptr);
         else if (st == ST_F32)
