@@ -1022,10 +1022,22 @@ __global__ void __launch_bounds__(kBlock) k_sort_rows(int n, const int32_t *__re
 // G lanes own one output row and an LDS hash of H slots (keys and values).
 // The row of A is walked in ascending order; for one entry a_ik the lanes
 // take the entries of row k of B in parallel.  Those have distinct columns,
-// so no two lanes touch one slot at the same time, and each output value is
+// so no two lanes add to one slot at the same time, and each output value is
 // accumulated in ascending k exactly as in a row-by-row Gustavson product.
-// The distinct columns are then compacted, ranked (sorted) and written.
-
+// The counting pass counts the slots it fills; the numeric pass compacts the
+// distinct columns, ranks (sorts) and writes them.
+//
+// Bound by latency: of the loads of B's rows, then of the LDS.  The loads of kP
+// entries of A are issued together, on every path (see below), their products
+// look up their slots together and are then added by LDS atomics in the order
+// of those entries (a wavefront's LDS operations run in order), so a round trip
+// to memory and two to the LDS are paid per kP entries and not per entry.
+// kP: 4 in the numeric pass (8 take more registers than five wavefronts per
+// SIMD leave: 518 and 418 us at 210 k rows of a level 1), 8 in the counting
+// pass (371 us; 4 take 396), 5 with 8 lanes a row (237 us at 2 M rows of a level
+// 0; 4 take 260, 8 take 278).  2 M cells, R (A P) of level 0 (264 k rows), the
+// counting pass 641 and now 362 us, the numeric pass 537 and now 347 us; A P of
+// level 1: 175 and 136 us, 286 and 213 us.
 // products of each row (sum of the B row lengths it touches) and seven
 // reductions over the rows, kRedSlots words each (one atomic per workgroup):
 // [0] the largest product count, [1] rows above kLongProducts, [2] rows above
@@ -1162,116 +1174,145 @@ __global__ void __launch_bounds__(256) k_spgemm(int n, const int32_t *__restrict
     constexpr int HV = NUM ? H : 1;  // the counting pass keeps no values
     __shared__ int key[R][H];
     __shared__ double val[R][HV];
-    __shared__ int nl[R];
     int grp = threadIdx.x / G, sub = threadIdx.x % G;
     int idx = blockIdx.x * R + grp;
     for (int t = sub; t < H; t += G) key[grp][t] = -1;
     if (NUM)
         for (int t = sub; t < HV; t += G) val[grp][t] = 0.0;
-    if (sub == 0) nl[grp] = 0;
     __syncthreads();
     if (idx >= n) return;
     const int i = rows ? rows[idx] : idx;
     if (prod && prod[i] > plimit) return;  // left to the launch over the listed rows
     constexpr bool numeric = NUM;
-    // one product: the column's slot (linear probing), then its sum
-    auto insert = [&](int c, double prod) {
-        unsigned h = ((unsigned)c * 2654435761u) & (H - 1);
-        int slot = -1;
-        for (int probe = 0; probe < H; probe++) {
-            int old = atomicCAS(&key[grp][h], -1, c);
-            if (old == -1 || old == c) { slot = (int)h; break; }
+    // a column's slot (linear probing from its hash), with what the first look
+    // there returned; -1 if the table is full
+    int fresh = 0;  // slots this lane filled
+    auto look = [&](int c, unsigned h) { return atomicCAS(&key[grp][h], -1, c); };
+    auto hash = [](int c) { return ((unsigned)c * 2654435761u) & (H - 1); };
+    auto settle = [&](int c, unsigned h, int old) -> int {
+#pragma unroll 1
+        for (int probe = 1; old != -1 && old != c; probe++) {
+            if (probe >= H) { *bad = 1; return -1; }
             h = (h + 1) & (H - 1);
+            old = look(c, h);
         }
-        if (slot < 0) { *bad = 1; return; }
-        if (numeric) val[grp][slot % HV] = val[grp][slot % HV] + prod;
+        fresh += old == -1;
+        return (int)h;
+    };
+    auto add = [&](int slot, double prod) {
+        __hip_atomic_fetch_add(&val[grp][slot % HV], prod, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     // The row of A goes in chunks of G entries: lane u of the group holds
     // entry u of the chunk with the bounds of its row of B.  The first G
     // entries of the next kP rows of B are loaded together before they are
-    // hashed, so the loads' latency is paid once per kP entries of A.
-    constexpr int kP = 8;
+    // hashed.
+    constexpr int kP = NUM ? 4 : G == 8 ? 5 : 8;
     const int a0 = arp[i], a1 = arp[i + 1];
     for (int c0 = a0; c0 < a1; c0 += G) {
         const int m = min(G, a1 - c0);
-        int lk_s = 0, lk_e = 0;
-        double lk_a = 0.0;
-        if (sub < m) {
-            int k = aci[c0 + sub];
-            lk_s = brp[k];
-            lk_e = brp[k + 1];
-            lk_a = numeric ? av[c0 + sub] : 0.0;
-        }
+        // (lanes and entries past the end read a valid one instead: a load that
+        // only some paths issue makes every later use wait for all in flight)
+        const int lk = c0 + min(sub, m - 1), lk_k = aci[lk];
+        const int lk_s = brp[lk_k], lk_e = brp[lk_k + 1];
+        const double lk_a = numeric ? av[lk] : 0.0;
         for (int u0 = 0; u0 < m; u0 += kP) {
             int cc[kP], fs[kP], fe[kP];
             double bb[kP], aq[kP];
 #pragma unroll
             for (int q = 0; q < kP; q++) {
-                cc[q] = -1; bb[q] = 0.0; aq[q] = 0.0; fs[q] = 0; fe[q] = 0;
-                if (u0 + q < m) {
-                    fs[q] = __shfl(lk_s, u0 + q, G);
-                    fe[q] = __shfl(lk_e, u0 + q, G);
-                    aq[q] = __shfl(lk_a, u0 + q, G);
-                    int f = fs[q] + sub;
-                    if (f < fe[q]) {
-                        cc[q] = bci[f];
-                        if (numeric) bb[q] = bv[f];
-                    }
-                }
+                const int u = min(u0 + q, m - 1);
+                fs[q] = __shfl(lk_s, u, G);
+                fe[q] = __shfl(lk_e, u, G);
+                if (numeric) aq[q] = __shfl(lk_a, u, G);
             }
 #pragma unroll
             for (int q = 0; q < kP; q++) {
+                const int f = fs[q] + sub;
+                const bool take = u0 + q < m && f < fe[q];
+                const int c = bci[take ? f : 0];
+                if (numeric) bb[q] = bv[take ? f : 0];
+                cc[q] = take ? c : -1;
+            }
+            unsigned hh[kP];
+            int old[kP], slot[kP];
+#pragma unroll
+            for (int q = 0; q < kP; q++) {
+                hh[q] = hash(cc[q]);
+                old[q] = -1;
+                if (cc[q] >= 0) old[q] = look(cc[q], hh[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < kP; q++) slot[q] = cc[q] >= 0 ? settle(cc[q], hh[q], old[q]) : -1;
+#pragma unroll
+            for (int q = 0; q < kP; q++) {
+                if (numeric && slot[q] >= 0) add(slot[q], aq[q] * bb[q]);
                 if (u0 + q < m) {
-                    if (cc[q] >= 0) insert(cc[q], aq[q] * bb[q]);
-                    for (int f = fs[q] + sub + G; f < fe[q]; f += G) insert(bci[f], numeric ? aq[q] * bv[f] : 0.0);
+                    for (int f = fs[q] + sub + G; f < fe[q]; f += G) {
+                        const int c = bci[f];
+                        const double x = numeric ? aq[q] * bv[f] : 0.0;
+                        const unsigned h = hash(c);
+                        const int sl = settle(c, h, look(c, h));
+                        if (numeric && sl >= 0) add(sl, x);
+                    }
                 }
-                // the next entry of A may add to the same columns
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                // the adds of the next entry of A come after these
                 __builtin_amdgcn_wave_barrier();
             }
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    // compact the occupied slots into a dense list at the front of key/val:
-    // every lane first takes its slots into registers
-    constexpr int PER = H / G;
-    int kk[PER];
-    double vv[PER];
-#pragma unroll
-    for (int u = 0; u < PER; u++) {
-        kk[u] = key[grp][sub + u * G];
-        vv[u] = numeric ? val[grp][(sub + u * G) % HV] : 0.0;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int u = 0; u < PER; u++)
-        if (kk[u] >= 0) {
-            int p = atomicAdd(&nl[grp], 1);
-            key[grp][p] = kk[u];
-            if (numeric) val[grp][p % HV] = vv[u];
-        }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    int L = nl[grp];
     if constexpr (!numeric) {
+        int L = fresh;
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) L += __shfl_xor(L, off, G);
         if (sub == 0) {
             cnt[i] = L;
             if (L > H / 2) *bad = 1;
             // rows rarely raise the maximum: read it before the atomic
             if (L > __hip_atomic_load(maxl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxl, L);
         }
-    } else {
-        // each distinct column goes to its rank among the row's columns
-        int base = crp[i];
-        for (int t = sub; t < L; t += G) {
-            int c = key[grp][t];
-            int rank = 0;
-            for (int u = 0; u < L; u++) rank += key[grp][u] < c;
-            cci[base + rank] = c;
-            cv[base + rank] = val[grp][t];
+        return;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    // compact the occupied slots into a dense list at the front of key/val:
+    // every lane first takes its slots into registers; its list starts at the
+    // number of slots the lanes below it hold
+    constexpr int PER = H / G;
+    int kk[PER], mine = 0;
+    double vv[PER];
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        kk[u] = key[grp][sub + u * G];
+        vv[u] = val[grp][(sub + u * G) % HV];
+        mine += kk[u] >= 0;
+    }
+    int upto = mine;
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+        const int below = __shfl_up(upto, off, G);
+        if (sub >= off) upto += below;
+    }
+    const int L = __shfl(upto, G - 1, G);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    int p = upto - mine;
+#pragma unroll
+    for (int u = 0; u < PER; u++)
+        if (kk[u] >= 0) {
+            key[grp][p] = kk[u];
+            val[grp][p % HV] = vv[u];
+            p++;
         }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    // each distinct column goes to its rank among the row's columns
+    const int base = crp[i];
+    for (int t = sub; t < L; t += G) {
+        const int c = key[grp][t];
+        int rank = 0;
+        for (int u = 0; u < L; u++) rank += key[grp][u] < c;
+        cci[base + rank] = c;
+        cv[base + rank] = val[grp][t];
     }
 }
 
