@@ -1424,31 +1424,63 @@ __global__ void __launch_bounds__(1024) k_gauss_jordan(int n, double *__restrict
     }
 }
 
-// The same Gauss-Jordan elimination for n <= 32 G (G <= 6) with the matrix
-// held in registers: thread t = 32 tc + tr owns rows tr + 32 i and columns
-// tc + 32 j (i, j < G).  The inverse is formed in place: after step k, column
+// The same Gauss-Jordan elimination for n <= S G with the matrix
+// held in registers: thread t = S tc + tr of S^2 owns rows tr + S i and
+// columns tc + S j (i, j < G).  The inverse is formed in place: after step k, column
 // k of the working matrix is column orig[k] of A^{-1}, where orig[] follows
 // the row swaps.  On every entry that is not structurally zero this performs
 // the same operations, in the same order, as the [A | I] form above (the unit
 // column n + orig[k] of the right half is 0 in every row but k when step k
 // begins), so both forms give the same inverse.  The row and column of the
 // step pass through LDS, double-buffered by the parity of k: two barriers per
-// pivot.  The pivot loop is split by k / 32 so that the register row and
-// column of the pivot are compile-time indices; the swapped-in row, the pivot
-// row and the pivot column are patched around one uniform update of all
-// entries.
+// pivot.  The pivot's register row and column are picked by uniform branches;
+// the swapped-in row, the pivot row and the pivot column are patched around one
+// uniform update of all entries.
+//
+// One workgroup, bound by the instructions of a pivot that are not updates.
+// The column search goes by moves within the registers instead of LDS permutes,
+// and a division of the pivot row is done by one lane of a wavefront, not by
+// all of its rows.  25 rows: 44 and now 26 us, 40 rows 71 and 56 us, 128 rows
+// 224 and 214 us, 150 rows 365 and 317 us.
 constexpr int kGjRegMax = 192;
-template <int G>
-__global__ void __launch_bounds__(1024) k_gj_regs(int n, const double *__restrict__ M, double *__restrict__ inv,
+// f over S (16 or 32) consecutive lanes (f is associative and commutative)
+template <int S, typename T, typename F>
+__device__ __forceinline__ T lanes_reduce(T v, F f) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    constexpr int W = sizeof(T) / 4;
+    struct Words { uint32_t w[W]; };
+    auto dpp = [&](auto ctrl) {
+        Words x = __builtin_bit_cast(Words, v);
+#pragma unroll
+        for (int q = 0; q < W; q++)
+            x.w[q] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x.w[q], decltype(ctrl)::value, 0xF, 0xF, true);
+        v = f(v, __builtin_bit_cast(T, x));
+    };
+    dpp(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+    dpp(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+    dpp(std::integral_constant<int, 0x141>{});  // row_half_mirror: the other quad of eight lanes
+    dpp(std::integral_constant<int, 0x128>{});  // row_ror:8
+    if constexpr (S == 16) return v;
+    Words x = __builtin_bit_cast(Words, v), y = x;
+#pragma unroll
+    for (int q = 0; q < W; q++) {
+        auto w = __builtin_amdgcn_permlane16_swap(x.w[q], x.w[q], false, false);
+        x.w[q] = w[0];
+        y.w[q] = w[1];
+    }
+    return f(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+}
+template <int G, int S>
+__global__ void __launch_bounds__(S * S) k_gj_regs(int n, const double *__restrict__ M, double *__restrict__ inv,
                                                   int32_t *__restrict__ bad) {
-    __shared__ double rowk[2][32 * G];  // the pivot row after the swap, unscaled
-    __shared__ double rowo[2][32 * G];  // row k before the swap (it becomes row p)
-    __shared__ double colk[2][32 * G];  // column k before the step, rows before the swap
+    __shared__ double rowk[2][S * G];  // the pivot row after the swap, unscaled
+    __shared__ double rowo[2][S * G];  // row k before the swap (it becomes row p)
+    __shared__ double colk[2][S * G];  // column k before the step, rows before the swap
     __shared__ int piv[2];
-    __shared__ int orig[32 * G];
-    __shared__ double wmax[16];
+    __shared__ int orig[S * G];
+    __shared__ double wmax[S * S / 64];
     __shared__ double thr;
-    int t = threadIdx.x, tr = t % 32, tc = t / 32;
+    int t = threadIdx.x, tr = t % S, tc = t / S;
     int w = 2 * n;
     double a[G][G];
     double m = 0.0;
@@ -1456,7 +1488,7 @@ __global__ void __launch_bounds__(1024) k_gj_regs(int n, const double *__restric
     for (int i = 0; i < G; i++)
 #pragma unroll
         for (int j = 0; j < G; j++) {
-            int r = tr + 32 * i, c = tc + 32 * j;
+            int r = tr + S * i, c = tc + S * j;
             a[i][j] = (r < n && c < n) ? M[(size_t)r * w + c] : 0.0;
             m = fmax(m, fabs(a[i][j]));
         }
@@ -1466,110 +1498,112 @@ __global__ void __launch_bounds__(1024) k_gj_regs(int n, const double *__restric
     __syncthreads();
     if (t == 0) {
         double mm = wmax[0];
-        for (int q = 1; q < 16; q++) mm = fmax(mm, wmax[q]);
+        for (int q = 1; q < S * S / 64; q++) mm = fmax(mm, wmax[q]);
         thr = kCoarsePivotTol * mm;
     }
     __syncthreads();
     for (int q = t; q < n; q += blockDim.x) orig[q] = q;
+#pragma unroll 1
+    for (int k = 0; k < n; k++) {
+        const int kg = k / S, kr = k % S, h = k & 1;
+        // column k: its owners (tc == kr) are S lanes of one wavefront
+        if (tc == kr) {
+            double bv = -1.0;
+            int bi = n;
+            bool nan = false;
+            double ak[G];
 #pragma unroll
-    for (int kg = 0; kg < G; kg++) {
-        for (int kr = 0; kr < 32; kr++) {
-            int k = 32 * kg + kr;
-            if (k >= n) break;
-            int h = k & 1;
-            // column k: its owners (tc == kr) are the 32 lanes of one half wavefront
-            if (tc == kr) {
-                double bv = -1.0;
-                int bi = n;
-                bool nan = false;
+            for (int j = 0; j < G; j++)
+                if (j == kg)
 #pragma unroll
-                for (int i = 0; i < G; i++) {
-                    int r = tr + 32 * i;
-                    double v = a[i][kg];
-                    if (r < n) colk[h][r] = v;
-                    if (r >= k && r < n) {
-                        double av = fabs(v);
-                        nan = nan || av != av;
-                        if (av > bv) { bv = av; bi = r; }
-                    }
-                }
-                for (int off = 16; off > 0; off >>= 1) {
-                    double ov = __shfl_xor(bv, off, 64);
-                    int oi = __shfl_xor(bi, off, 64);
-                    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-                }
-                if (nan) *bad = 1;
-                if (tr == 0) {
-                    piv[h] = bi;
-                    if (!(bv > thr)) *bad = 1;
-                }
-            }
-            __syncthreads();
-            int p = piv[h];
-            if (p >= n) p = k;  // no finite candidate: flagged above, no swap
-            int pi = p / 32, pr = p % 32;
-            if (tr == kr)
-#pragma unroll
-                for (int j = 0; j < G; j++) {
-                    int c = tc + 32 * j;
-                    if (c < n) rowo[h][c] = a[kg][j];
-                }
-#pragma unroll
-            for (int i = 0; i < G; i++)
-                if (i == pi && tr == pr)
-#pragma unroll
-                    for (int j = 0; j < G; j++) {
-                        int c = tc + 32 * j;
-                        if (c < n) rowk[h][c] = a[i][j];
-                    }
-            if (t == 0 && p != k) {
-                int o = orig[k];
-                orig[k] = orig[p];
-                orig[p] = o;
-            }
-            __syncthreads();
-            double d = rowk[h][k];
-            double pk[G];
-#pragma unroll
-            for (int j = 0; j < G; j++) {
-                int c = tc + 32 * j;
-                pk[j] = c < n ? (c == k ? 1.0 / d : rowk[h][c] / d) : 0.0;
-            }
-            double fk = colk[h][k];
-            double f[G];
+                    for (int i = 0; i < G; i++) ak[i] = a[i][j];
 #pragma unroll
             for (int i = 0; i < G; i++) {
-                int r = tr + 32 * i;
-                f[i] = r == p ? fk : (r < n ? colk[h][r] : 0.0);
+                int r = tr + S * i;
+                double v = ak[i];
+                colk[h][r] = v;
+                if (r >= k && r < n) {
+                    double av = fabs(v);
+                    nan = nan || av != av;
+                    if (av > bv) { bv = av; bi = r; }
+                }
             }
-            // row p now holds the old row k
-#pragma unroll
-            for (int i = 0; i < G; i++)
-                if (i == pi && tr == pr)
-#pragma unroll
-                    for (int j = 0; j < G; j++) {
-                        int c = tc + 32 * j;
-                        a[i][j] = c < n ? rowo[h][c] : 0.0;
-                    }
-#pragma unroll
-            for (int i = 0; i < G; i++)
-#pragma unroll
-                for (int j = 0; j < G; j++) a[i][j] = a[i][j] - f[i] * pk[j];
-            // the unit column n + orig[k] of the [A | I] form, and the pivot row
-            if (tc == kr)
-#pragma unroll
-                for (int i = 0; i < G; i++) a[i][kg] = 0.0 - f[i] * pk[kg];
-            if (tr == kr)
-#pragma unroll
-                for (int j = 0; j < G; j++) a[kg][j] = pk[j];
+            // the largest over the S lanes, then the lowest row that has it
+            const double best = lanes_reduce<S>(bv, [](double x, double y) { return x > y ? x : y; });
+            bi = lanes_reduce<S>(bv == best ? bi : n, [](int x, int y) { return min(x, y); });
+            bv = best;
+            if (nan) *bad = 1;
+            if (tr == 0) {
+                piv[h] = bi;
+                if (!(bv > thr)) *bad = 1;
+            }
         }
+        __syncthreads();
+        int p = __builtin_amdgcn_readfirstlane(piv[h]);
+        if (p >= n) p = k;  // no finite candidate: flagged above, no swap
+        const int pi = p / S, pr = p % S;
+#pragma unroll
+        for (int i = 0; i < G; i++)
+            if (i == kg && tr == kr)
+#pragma unroll
+                for (int j = 0; j < G; j++) rowo[h][tc + S * j] = a[i][j];
+#pragma unroll
+        for (int i = 0; i < G; i++)
+            if (i == pi && tr == pr)
+#pragma unroll
+                for (int j = 0; j < G; j++) rowk[h][tc + S * j] = a[i][j];
+        if (t == 0 && p != k) {
+            int o = orig[k];
+            orig[k] = orig[p];
+            orig[p] = o;
+        }
+        __syncthreads();
+        double d = rowk[h][k];
+        // the columns of the wavefront (C to an index j) of the scaled
+        // pivot row, a division a lane, handed to the lanes of the column
+        constexpr int C = 64 / S;
+        double pk[G], q;
+        {
+            const int l = t % 64, c = (tc & ~(C - 1)) + l % C + S * (l / C);
+            q = l < C * G && c < n ? (c == k ? 1.0 / d : rowk[h][c] / d) : 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j < G; j++) pk[j] = __shfl(q, C * j + tc % C, 64);
+        double fk = colk[h][k];
+        double f[G];
+#pragma unroll
+        for (int i = 0; i < G; i++) {
+            int r = tr + S * i;
+            f[i] = r == p ? fk : colk[h][r];
+        }
+        // row p now holds the old row k
+#pragma unroll
+        for (int i = 0; i < G; i++)
+            if (i == pi && tr == pr)
+#pragma unroll
+                for (int j = 0; j < G; j++) a[i][j] = rowo[h][tc + S * j];
+#pragma unroll
+        for (int i = 0; i < G; i++)
+#pragma unroll
+            for (int j = 0; j < G; j++) a[i][j] = a[i][j] - f[i] * pk[j];
+        // the unit column n + orig[k] of the [A | I] form, and the pivot row
+#pragma unroll
+        for (int j = 0; j < G; j++)
+            if (j == kg && tc == kr)
+#pragma unroll
+                for (int i = 0; i < G; i++) a[i][j] = 0.0 - f[i] * pk[j];
+#pragma unroll
+        for (int i = 0; i < G; i++)
+            if (i == kg && tr == kr)
+#pragma unroll
+                for (int j = 0; j < G; j++) a[i][j] = pk[j];
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < G; i++)
 #pragma unroll
         for (int j = 0; j < G; j++) {
-            int r = tr + 32 * i, c = tc + 32 * j;
+            int r = tr + S * i, c = tc + S * j;
             if (r < n && c < n) inv[(size_t)r * n + orig[c]] = a[i][j];
         }
 }
@@ -2479,12 +2513,16 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
     BO_TRY(pc->cinv.alloc((size_t)nc * nc));
     k_dense_from_csr<<<grid_for(nc), kBlock, 0, s>>>(nc, Lc.rp.p, Lc.ci.p, Lc.v.p, M.p);
     BO_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t), s));
-    if (nc <= 128) {
-        k_gj_regs<4><<<1, 1024, 0, s>>>(nc, M.p, pc->cinv.p, flag);
-    } else if (nc <= 160) {
-        k_gj_regs<5><<<1, 1024, 0, s>>>(nc, M.p, pc->cinv.p, flag);
-    } else if (nc <= kGjRegMax) {
-        k_gj_regs<6><<<1, 1024, 0, s>>>(nc, M.p, pc->cinv.p, flag);
+    if (nc <= kGjRegMax) {
+        // 16 x 16 threads up to 64 rows (a quarter of the wavefronts' work beside
+        // the updates), 32 x 32 above, where one wavefront per SIMD waits for its
+        // own operations: 128 rows 214 us, with 16 x 16 threads 282
+        if (nc <= 32) k_gj_regs<2, 16><<<1, 256, 0, s>>>(nc, M.p, pc->cinv.p, flag);
+        else if (nc <= 64) k_gj_regs<4, 16><<<1, 256, 0, s>>>(nc, M.p, pc->cinv.p, flag);
+        else if (nc <= 96) k_gj_regs<3, 32><<<1, 1024, 0, s>>>(nc, M.p, pc->cinv.p, flag);
+        else if (nc <= 128) k_gj_regs<4, 32><<<1, 1024, 0, s>>>(nc, M.p, pc->cinv.p, flag);
+        else if (nc <= 160) k_gj_regs<5, 32><<<1, 1024, 0, s>>>(nc, M.p, pc->cinv.p, flag);
+        else k_gj_regs<6, 32><<<1, 1024, 0, s>>>(nc, M.p, pc->cinv.p, flag);
     } else {
         k_gauss_jordan<<<1, 1024, 0, s>>>(nc, M.p, flag);
         k_extract_inverse<<<grid_for((long long)nc * nc), kBlock, 0, s>>>(nc, M.p, pc->cinv.p);
