@@ -351,72 +351,66 @@ __global__ void k_is_root(int n, const uint8_t *__restrict__ state, int32_t *__r
     root[i] = state[i] == IN;
 }
 
-// phase 1: a root and its strong neighbours form an aggregate
-__global__ void k_agg1(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                       const uint8_t *__restrict__ sf, const uint8_t *__restrict__ state,
-                       const int32_t *__restrict__ id, int32_t *__restrict__ a1) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int a = -1;
-    if (state[i] == IN) {
-        a = id[i];
-    } else {
-        // entry order (the last strong root neighbour wins), kB entries'
-        // loads at a time
-        constexpr int kB = 8;
-        const int b = rp[i], e1 = rp[i + 1];
-        for (int e0 = b; e0 < e1; e0 += kB) {
-            int cc[kB], ss[kB], st[kB], idv[kB];
-#pragma unroll
-            for (int k = 0; k < kB; k++) {
-                const int e = min(e0 + k, e1 - 1);
-                cc[k] = ci[e];
-                ss[k] = sf[e];
-            }
-#pragma unroll
-            for (int k = 0; k < kB; k++) { st[k] = state[cc[k]]; idv[k] = id[cc[k]]; }
-#pragma unroll
-            for (int k = 0; k < kB; k++)
-                if (e0 + k < e1 && ss[k] && st[k] == IN) a = idv[k];
-        }
+// phase 1: a root and its strong neighbours form an aggregate.  G lanes per
+// row; the last strong root neighbour wins.  A thread per row took as many round
+// trips to memory as a row has batches.  264 k rows of 36 entries: this phase 32
+// and now 21 us, the second 28 and 27 us; 700 rows: 9.8 and 3.7, 11.1 and 4.6 us.
+template <int G>
+__global__ void __launch_bounds__(kBlock) k_agg1(int n, const int32_t *__restrict__ rp,
+                                                 const int32_t *__restrict__ ci, const uint8_t *__restrict__ sf,
+                                                 const uint8_t *__restrict__ state, const int32_t *__restrict__ id,
+                                                 int32_t *__restrict__ a1) {
+    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (int)(gid / G), sub = (int)(gid % G);
+    if (i >= n) return;  // whole groups leave together
+    const int b = rp[i], e1 = rp[i + 1], own = id[i];
+    const bool root = state[i] == IN;
+    int from = -1, to = -1;  // the last entry found and its column
+#pragma unroll 2
+    for (int e0 = b; e0 < e1; e0 += G) {
+        const int e = min(e0 + sub, e1 - 1), c = ci[e];
+        const bool hit = sf[e] && state[c] == IN;
+        if (hit) { from = e; to = c; }
     }
-    a1[i] = a;
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) {
+        const int f2 = __shfl_xor(from, off, G), t2 = __shfl_xor(to, off, G);
+        if (f2 > from) { from = f2; to = t2; }
+    }
+    if (sub == 0) a1[i] = root ? own : to >= 0 ? id[to] : -1;
 }
 
 // phase 2: join the strongest assigned strong neighbour (ties: smaller id)
-__global__ void k_agg2(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                       const double *__restrict__ v, const uint8_t *__restrict__ sf,
-                       const uint8_t *__restrict__ state, const int32_t *__restrict__ a1,
-                       int32_t *__restrict__ agg, int32_t *__restrict__ bad) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+template <int G>
+__global__ void __launch_bounds__(kBlock) k_agg2(int n, const int32_t *__restrict__ rp,
+                                                 const int32_t *__restrict__ ci, const double *__restrict__ v,
+                                                 const uint8_t *__restrict__ sf, const uint8_t *__restrict__ state,
+                                                 const int32_t *__restrict__ a1, int32_t *__restrict__ agg,
+                                                 int32_t *__restrict__ bad) {
+    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (int)(gid / G), sub = (int)(gid % G);
     if (i >= n) return;
     int a = a1[i];
     if (a < 0 && state[i] != ISO) {
         int best = -1;
         double bv = -1.0;
-        constexpr int kB = 8;
         const int b = rp[i], e1 = rp[i + 1];
-        for (int e0 = b; e0 < e1; e0 += kB) {
-            int ss[kB], aj[kB];
-            double vv[kB];
+#pragma unroll 2
+        for (int e0 = b; e0 < e1; e0 += G) {
+            const int e = min(e0 + sub, e1 - 1), aj = a1[ci[e]];
+            const double x = fabs(v[e]);
+            if (sf[e] && aj >= 0 && (x > bv || (x == bv && aj < best))) { bv = x; best = aj; }
+        }
 #pragma unroll
-            for (int k = 0; k < kB; k++) {
-                const int e = min(e0 + k, e1 - 1);
-                ss[k] = sf[e];
-                aj[k] = a1[ci[e]];
-                vv[k] = v[e];
-            }
-#pragma unroll
-            for (int k = 0; k < kB; k++) {
-                if (e0 + k >= e1 || !ss[k] || aj[k] < 0) continue;
-                double x = fabs(vv[k]);
-                if (x > bv || (x == bv && aj[k] < best)) { bv = x; best = aj[k]; }
-            }
+        for (int off = G / 2; off > 0; off >>= 1) {
+            const double x = __shfl_xor(bv, off, G);
+            const int aj = __shfl_xor(best, off, G);
+            if (x > bv || (x == bv && aj < best)) { bv = x; best = aj; }
         }
         a = best;
         if (a < 0) *bad = 1;
     }
-    agg[i] = a;
+    if (sub == 0) agg[i] = a;
 }
 
 // filtered diagonal and the Gershgorin ratio of D_F^{-1} A_F (max via the
@@ -439,55 +433,137 @@ __device__ __forceinline__ void block_max_to_slots(uint64_t v, unsigned long lon
     }
 }
 
+// A workgroup's rows are staged through LDS, kFilterChunk entries at a time in
+// runs of consecutive words, and summed there by a thread a row in entry order.
+// A thread reading its own row from memory waited for every batch of eight
+// entries, twice over.  264 k rows of 36 entries: 121 and now 44 us.
+constexpr int kFilterChunk = 2048;
+constexpr int kFilterFew = 1 << 14;  // rows up to which k_filter_rows is taken
+template <int R>
 __global__ void __launch_bounds__(kBlock) k_filter(int n, const int32_t *__restrict__ rp,
                                                    const int32_t *__restrict__ ci, const double *__restrict__ v,
                                                    const int32_t *__restrict__ dpos, const uint8_t *__restrict__ sf,
                                                    double *__restrict__ aF, unsigned long long *__restrict__ rho_bits) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    static_assert(R <= kBlock, "a thread a row");
+    constexpr int kB = 16;  // entries whose LDS reads are in flight together
+    __shared__ double sv[kFilterChunk];
+    __shared__ int32_t sc[kFilterChunk];
+    __shared__ uint8_t ss[kFilterChunk];
+    const int i0 = blockIdx.x * R, i = i0 + threadIdx.x, i1 = min(i0 + R, n);
+    const bool mine = (int)threadIdx.x < R && i < n;
+    const int E0 = rp[i0], E1 = rp[i1];
+    const int b = mine ? rp[i] : 0, e1 = mine ? rp[i + 1] : 0;
+    auto stage = [&](int c0) {
+        __syncthreads();  // the sums over the chunk before
+        const int len = min(kFilterChunk, E1 - c0);
+        constexpr int kL = kFilterChunk / kBlock;
+        double x[kL];
+        int32_t c[kL];
+        uint8_t f[kL];
+#pragma unroll
+        for (int u = 0; u < kL; u++) {  // all loads of the chunk in flight
+            const int e = c0 + min((int)threadIdx.x + u * kBlock, len - 1);
+            x[u] = v[e]; c[u] = ci[e]; f[u] = sf[e];
+        }
+#pragma unroll
+        for (int u = 0; u < kL; u++) {
+            const int e = threadIdx.x + u * kBlock;
+            sv[e] = x[u]; sc[e] = c[u]; ss[e] = f[u];
+        }
+        __syncthreads();
+    };
+    const double aii = mine ? v[dpos[i]] : 1.0;
+    double d = aii;
+    for (int c0 = E0; c0 < E1; c0 += kFilterChunk) {
+        stage(c0);
+        const int hi = min(e1, c0 + min(kFilterChunk, E1 - c0));
+        for (int e = max(b, c0); e < hi; e += kB) {
+            double x[kB];
+            bool weak[kB];
+#pragma unroll
+            for (int k = 0; k < kB; k++) {
+                const int q = min(e + k, hi - 1) - c0;
+                x[k] = sv[q];
+                weak[k] = (e + k < hi) & (sc[q] != i) & !ss[q];
+            }
+#pragma unroll
+            for (int k = 0; k < kB; k++) d = weak[k] ? d + x[k] : d;
+        }
+    }
+    if (d == 0.0) d = aii;
+    double rs = 0.0;
+    for (int c0 = E0; c0 < E1; c0 += kFilterChunk) {
+        if (E1 - E0 > kFilterChunk) stage(c0);  // one chunk is there still
+        const int hi = min(e1, c0 + min(kFilterChunk, E1 - c0));
+        for (int e = max(b, c0); e < hi; e += kB) {
+            double x[kB];
+            bool take[kB];
+#pragma unroll
+            for (int k = 0; k < kB; k++) {
+                const int q = min(e + k, hi - 1) - c0;
+                const bool own = sc[q] == i;
+                x[k] = fabs(own ? d : sv[q]);
+                take[k] = (e + k < hi) & (own | (ss[q] != 0));
+            }
+#pragma unroll
+            for (int k = 0; k < kB; k++) rs = take[k] ? rs + x[k] : rs;
+        }
+    }
     uint64_t bits = 0;
-    if (i < n) {
-        // the row in batches of kB entries: every load of a batch is issued
-        // before the sums, which still run in entry order; the row's values
-        // stay in registers for the second sum only as one batch, so it
-        // reloads them (cache hits)
-        constexpr int kB = 8;
-        const int b = rp[i], e1 = rp[i + 1];
-        double aii = v[dpos[i]];
-        double d = aii;
-        for (int e0 = b; e0 < e1; e0 += kB) {
-            int cc[kB], ss[kB];
-            double vv[kB];
-#pragma unroll
-            for (int k = 0; k < kB; k++) {
-                const int e = min(e0 + k, e1 - 1);  // rows are never empty (diagonal)
-                cc[k] = ci[e]; ss[k] = sf[e]; vv[k] = v[e];
-            }
-#pragma unroll
-            for (int k = 0; k < kB; k++)
-                if (e0 + k < e1 && cc[k] != i && !ss[k]) d = d + vv[k];
-        }
-        if (d == 0.0) d = aii;
+    if (mine) {
         aF[i] = d;
-        double rs = 0.0;
-        for (int e0 = b; e0 < e1; e0 += kB) {
-            int cc[kB], ss[kB];
-            double vv[kB];
-#pragma unroll
-            for (int k = 0; k < kB; k++) {
-                const int e = min(e0 + k, e1 - 1);
-                cc[k] = ci[e]; ss[k] = sf[e]; vv[k] = v[e];
-            }
-#pragma unroll
-            for (int k = 0; k < kB; k++) {
-                if (e0 + k >= e1) continue;
-                if (cc[k] == i) rs = rs + fabs(d);
-                else if (ss[k]) rs = rs + fabs(vv[k]);
-            }
-        }
-        double ratio = rs / fabs(d);
-        bits = (uint64_t)__double_as_longlong(ratio);
+        bits = (uint64_t)__double_as_longlong(rs / fabs(d));
     }
     // the ratios are >= 0, so their bit patterns order as the values
+    block_max_to_slots(bits, rho_bits);
+}
+
+// The same with a wavefront per row, whose entries are added one after the other
+// from the lanes' registers: the form for few rows, where the longest row's
+// thread is what takes the time.  900 rows, the longest a few hundred entries:
+// 29 us by a thread from memory, 30 from LDS, now 7 us; 5.5 k rows 19, 19 and
+// 7 us.  52 k rows take 36 us here and 24 us from LDS, 210 k rows 131 and 44 us.
+__global__ void __launch_bounds__(kBlock) k_filter_rows(int n, const int32_t *__restrict__ rp,
+                                                        const int32_t *__restrict__ ci, const double *__restrict__ v,
+                                                        const int32_t *__restrict__ dpos,
+                                                        const uint8_t *__restrict__ sf, double *__restrict__ aF,
+                                                        unsigned long long *__restrict__ rho_bits) {
+    const int lane = threadIdx.x % 64, row = (int)(((long long)blockIdx.x * kBlock + threadIdx.x) / 64);
+    uint64_t bits = 0;
+    if (row < n) {  // a whole wavefront
+        const int i = __builtin_amdgcn_readfirstlane(row), b = rp[i], e1 = rp[i + 1];
+        const double aii = v[dpos[i]];
+        auto add = [](double s, double x, uint64_t m) {
+            for (; m; m &= m - 1) {
+                const int w = __ffsll((unsigned long long)m) - 1;
+                s = s + __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), w),
+                                         __builtin_amdgcn_readlane(__double2loint(x), w));
+            }
+            return s;
+        };
+        double x = 0.0;
+        int c = 0;
+        bool strong = false;
+        auto load = [&](int e0) {
+            const int e = min(e0 + lane, e1 - 1);  // rows are never empty (diagonal)
+            x = v[e]; c = ci[e]; strong = sf[e];
+        };
+        double d = aii;
+        for (int e0 = b; e0 < e1; e0 += 64) {
+            load(e0);
+            d = add(d, x, __ballot(e0 + lane < e1 && c != i && !strong));
+        }
+        if (d == 0.0) d = aii;
+        double rs = 0.0;
+        for (int e0 = b; e0 < e1; e0 += 64) {
+            if (e1 - b > 64) load(e0);
+            rs = add(rs, fabs(c == i ? d : x), __ballot(e0 + lane < e1 && (c == i || strong)));
+        }
+        if (lane == 0) {
+            aF[i] = d;
+            bits = (uint64_t)__double_as_longlong(rs / fabs(d));
+        }
+    }
     block_max_to_slots(bits, rho_bits);
 }
 
@@ -841,79 +917,120 @@ __global__ void __launch_bounds__(kBlock) k_slot_p_fill(SlotGraph G, const doubl
     }
 }
 
-// Long rows of the prolongator (more than KP entries): one wavefront per row.
-// The row's (aggregate, filtered value) pairs are staged in LDS; an entry is
-// the first appearance of its aggregate if no earlier entry has it; the
-// entry's lane then sums the aggregate's values in ascending order and writes
-// the result at the aggregate's rank among the row's distinct aggregates.
+// Long rows of the prolongator (more than KP entries, up to KW): one wavefront
+// per row, its (aggregate, filtered value) pairs in registers, 64 to a register.
+// The aggregates are taken one after the other in order of first appearance;
+// their values are added in entry order, and the first appearance's lane writes
+// the result at the aggregate's rank among the row's distinct ones.  A search
+// for first appearances through LDS, quadratic in the row, took 153 us to count
+// 264 k rows of 36 entries and 301 us to fill them, now 72 us on average; 8.6 k
+// rows of more entries 35 and now 7 us.
 constexpr int KW = 512;
 constexpr int kPWaves = 4;
 
-__global__ void __launch_bounds__(64 * kPWaves) k_p_long(int n, const int32_t *__restrict__ rp,
+__global__ void __launch_bounds__(64 * kPWaves) k_p_long(const int32_t *__restrict__ rp,
                                                           const int32_t *__restrict__ ci, const double *__restrict__ v,
                                                           const uint8_t *__restrict__ sf,
                                                           const int32_t *__restrict__ agg,
                                                           const double *__restrict__ aF, const double *__restrict__ omega,
                                                           const int32_t *__restrict__ prp, int32_t *__restrict__ pci,
                                                           double *__restrict__ pv, int32_t *__restrict__ cnt,
-                                                          int32_t *__restrict__ bad,
                                                           const int32_t *__restrict__ plong) {
-    __shared__ int J[kPWaves][KW];
-    __shared__ double A[kPWaves][KW];
-    __shared__ uint8_t first[kPWaves][KW];
-    int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     // the rows k_p_count listed, a wavefront each, over a fixed grid
-    const int nl = plong[0];
-    for (int idx = blockIdx.x * kPWaves + wave; idx < nl; idx += gridDim.x * kPWaves) {
-    const int i = plong[1 + idx];
-    int b = rp[i], len = rp[i + 1] - b;
-    if (len > KW) continue;  // handled by k_p_vlong
-    // the previous row's LDS reads are done before this row's writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    for (int q = lane; q < len; q += 64) {
-        int e = b + q;
-        bool take = p_takes(e, i, ci, sf, agg);
-        J[wave][q] = take ? agg[ci[e]] : -1;
-        A[wave][q] = take ? (ci[e] == i ? aF[i] : v[e]) : 0.0;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    int mycount = 0;
-    for (int q = lane; q < len; q += 64) {
-        int Jq = J[wave][q];
-        bool f = Jq >= 0;
-        for (int u = 0; u < q && f; u++) f = J[wave][u] != Jq;
-        first[wave][q] = f;
-        mycount += f;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    if (cnt) {
+    const int nl = plong[0], step = gridDim.x * kPWaves;
+    int idx = blockIdx.x * kPWaves + wave;
+    if (idx >= nl) return;
+    auto lane_of = [](double x, int w) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), w),
+                                __builtin_amdgcn_readlane(__double2loint(x), w));
+    };
+    auto lowest = [](uint64_t m) { return __ffsll((unsigned long long)m) - 1; };
+    // one row of at most 64 NR entries
+    auto row = [&](auto nr_, int i, int b, int len) {
+        constexpr int NR = decltype(nr_)::value;
+        const double xi = aF[i];
+        const int ai = agg[i];
+        int c[NR], J[NR];
+        bool strong[NR];
+        double A[NR], sum[NR];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mycount += __shfl_xor(mycount, off, 64);
-        if (lane == 0) cnt[i] = mycount;
-        continue;
-    }
-    double d = omega[0] / aF[i];
-    int ai = agg[i];
-    for (int q = lane; q < len; q += 64) {
-        if (!first[wave][q]) continue;
-        int Jq = J[wave][q];
-        double sum = 0.0;
-        int rank = 0;
-        for (int u = 0; u < len; u++) {
-            int Ju = J[wave][u];
-            if (u >= q && Ju == Jq) sum = sum + A[wave][u];
-            rank += first[wave][u] && Ju < Jq;
+        for (int r = 0; r < NR; r++) {
+            const int e = b + min(64 * r + lane, len - 1);
+            c[r] = ci[e];
+            strong[r] = sf[e];
+            A[r] = v[e];
         }
-        pci[prp[i] + rank] = Jq;
-        pv[prp[i] + rank] = (ai == Jq ? 1.0 : 0.0) - d * sum;
-    }
+#pragma unroll
+        for (int r = 0; r < NR; r++) J[r] = agg[c[r]];
+        uint64_t rem[NR], leaders[NR];
+#pragma unroll
+        for (int r = 0; r < NR; r++) {
+            const bool take = 64 * r + lane < len && (c[r] == i || strong[r]) && J[r] >= 0;
+            if (c[r] == i) A[r] = xi;
+            rem[r] = __ballot(take);
+            leaders[r] = 0;
+            sum[r] = 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            while (rem[r]) {
+                const int u = lowest(rem[r]), Ju = __builtin_amdgcn_readlane(J[r], u);
+                leaders[r] |= 1ull << u;
+                double t = 0.0;
+#pragma unroll
+                for (int q = r; q < NR; q++) {
+                    const uint64_t same = __ballot(J[q] == Ju) & rem[q];
+                    rem[q] &= ~same;
+                    if (!cnt)
+                        for (uint64_t m = same; m; m &= m - 1) t = t + lane_of(A[q], lowest(m));
+                }
+                if (lane == u) sum[r] = t;
+            }
+        if (cnt) {
+            int distinct = 0;
+#pragma unroll
+            for (int r = 0; r < NR; r++) distinct += __popcll(leaders[r]);
+            if (lane == 0) cnt[i] = distinct;
+            return;
+        }
+        const int base = prp[i];
+        const double d = omega[0] / xi;
+        int rank[NR];
+#pragma unroll
+        for (int r = 0; r < NR; r++) rank[r] = 0;
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            for (uint64_t m = leaders[r]; m; m &= m - 1) {
+                const int Ju = __builtin_amdgcn_readlane(J[r], lowest(m));
+#pragma unroll
+                for (int q = 0; q < NR; q++) rank[q] += Ju < J[q];
+            }
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            if ((leaders[r] >> lane) & 1) {
+                pci[base + rank[r]] = J[r];
+                pv[base + rank[r]] = (ai == J[r] ? 1.0 : 0.0) - d * sum[r];
+            }
+    };
+    // the next row's number and bounds are loaded while a row is worked on
+    int i1 = plong[1 + idx], b1 = rp[i1], e1 = rp[i1 + 1], i2 = plong[1 + min(idx + step, nl - 1)];
+    for (; idx < nl; idx += step) {
+        const int i = __builtin_amdgcn_readfirstlane(i1), b = __builtin_amdgcn_readfirstlane(b1);
+        const int len = __builtin_amdgcn_readfirstlane(e1) - b;
+        i1 = i2;
+        b1 = rp[i1];
+        e1 = rp[i1 + 1];
+        i2 = plong[1 + (int)min((long long)idx + 2LL * step, (long long)nl - 1)];
+        if (len <= 64) row(std::integral_constant<int, 1>{}, i, b, len);
+        else if (len <= 128) row(std::integral_constant<int, 2>{}, i, b, len);
+        else if (len <= 256) row(std::integral_constant<int, 4>{}, i, b, len);
+        else if (len <= KW) row(std::integral_constant<int, 8>{}, i, b, len);
+        // longer ones are k_p_vlong's
     }
 }
 
-// The same for the rare rows longer than the LDS staging (a well row and its
+// The same for the rare rows longer than the registers (a well row and its
 // aggregates on coarse levels): one wavefront per row, the row's aggregate
 // ids and values re-read from global memory, quadratic in the row length.
 __global__ void __launch_bounds__(64 * kPWaves) k_p_vlong(int n, const int32_t *__restrict__ rp,
@@ -2409,9 +2526,19 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
             k_slot_agg1<<<grid_for(n), kBlock, 0, s>>>(SG, state.p, id.p, a1.p);
             k_slot_agg2<<<grid_for(n), kBlock, 0, s>>>(SG, pc->app.p, state.p, a1.p, L.agg.p, W.dfl.p + 1);
         } else {
-            k_agg1<<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, state.p, id.p, a1.p);
-            k_agg2<<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, state.p, a1.p, L.agg.p,
-                                                  W.dfl.p + 1);
+            // lanes per row: about two to four entries per lane
+#define BO_AGG(G)                                                                                             \
+    do {                                                                                                      \
+        const unsigned gb = grid_for((long long)n * G);                                                      \
+        k_agg1<G><<<gb, kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, state.p, id.p, a1.p);                     \
+        k_agg2<G><<<gb, kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, state.p, a1.p, L.agg.p,            \
+                                        W.dfl.p + 1);                                                        \
+    } while (0)
+            const double avg = (double)L.nnz / n;
+            if (avg <= 20.0) BO_AGG(4);
+            else if (avg <= 40.0) BO_AGG(8);
+            else BO_AGG(16);
+#undef BO_AGG
         }
         BO_HIP(hipGetLastError());
         L.nc = nc;
@@ -2422,7 +2549,14 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         BO_TRY(aF.alloc(n)); BO_TRY(rho.alloc(kRedSlots));
         BO_HIP(hipMemsetAsync(rho.p, 0, sizeof(unsigned long long) * kRedSlots, s));
         if (slots) k_slot_filter<<<grid_for(n), kBlock, 0, s>>>(SG, pc->g.ny, pc->g.nz, pc->app.p, aF.p, rho.p);
-        else k_filter<<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.diagpos.p, L.sf.p, aF.p, rho.p);
+        else if (L.nnz <= 8LL * n)
+            k_filter<256><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.diagpos.p, L.sf.p, aF.p, rho.p);
+        else if (n <= kFilterFew)
+            k_filter_rows<<<grid_for(64LL * n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.diagpos.p, L.sf.p, aF.p,
+                                                                rho.p);
+        else
+            k_filter<64><<<(n + 63) / 64, kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.diagpos.p, L.sf.p, aF.p,
+                                                          rho.p);
         const double *omega = W.omg.p + l;
         BO_TRY(W.plong.alloc(n + 1));
         k_omega<<<1, 1, 0, s>>>(rho.p, W.omg.p + l, W.dfl.p + 2, W.plong.p);
@@ -2434,8 +2568,8 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         } else {
             if (kp8) k_p_count<8><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, L.agg.p, cnt.p, W.plong.p);
             else k_p_count<16><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, L.agg.p, cnt.p, W.plong.p);
-            k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, nullptr,
-                                                    nullptr, nullptr, cnt.p, flag, W.plong.p);
+            k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, nullptr,
+                                                    nullptr, nullptr, cnt.p, W.plong.p);
             k_p_vlong<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, nullptr,
                                                      nullptr, nullptr, cnt.p, W.plong.p);
         }
@@ -2454,8 +2588,8 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
             else
                 k_p_fill<16><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega,
                                                             L.prp.p, L.pci.p, L.pv.p);
-            k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
-                                                    L.pci.p, L.pv.p, nullptr, flag, W.plong.p);
+            k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
+                                                    L.pci.p, L.pv.p, nullptr, W.plong.p);
             k_p_vlong<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
                                                      L.pci.p, L.pv.p, nullptr, W.plong.p);
         }
