@@ -231,12 +231,14 @@ __global__ void k_strength(int n, const int32_t *__restrict__ rp, const int32_t 
 
 enum { UND = 0, IN = 1, OUT = 2, ISO = 3 };
 
-// (also clears the change words of the level's MIS rounds, kMisWords of them)
+// (also clears the change words of the level's MIS rounds, kMisWords of them, and
+// as many reduction words of the filter)
 constexpr int kMisWords = 64;
 __global__ void k_mis_init(int n, const int32_t *__restrict__ rp, const uint8_t *__restrict__ sf,
-                           uint8_t *__restrict__ state, int32_t *__restrict__ words) {
+                           uint8_t *__restrict__ state, int32_t *__restrict__ words,
+                           unsigned long long *__restrict__ rho) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kMisWords) words[i] = 0;
+    if (i < kMisWords) { words[i] = 0; rho[i] = 0; }
     if (i >= n) return;
     int deg = 0;
     constexpr int kB = 8;
@@ -574,11 +576,11 @@ __device__ __forceinline__ bool p_takes(int e, int i, const int32_t *ci, const u
 
 // Row data of the prolongator: the aggregate J of each entry that takes part
 // ({i} and the strong neighbours, aggregated) or -1, and its filtered value.
-// Register fast path for rows of up to KP entries (8 on levels of at most 8
-// entries a row on average, else 16: the fully unrolled first-appearance
-// and rank loops grow with the cube of KP); longer rows go to k_p_long,
-// which forms the same sums in the same order.
-template <int KP>
+// Register path for rows of up to KP entries (the fully unrolled first-appearance
+// and rank loops grow with the cube of KP: with 16 on coarse levels the filling
+// alone took 23 us at 5.5 k rows, now 4, and the counting 12 and 4.5); longer rows go to
+// k_p_long, which forms the same sums in the same order.
+constexpr int KP = 8;
 __global__ void k_p_count(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                           const uint8_t *__restrict__ sf, const int32_t *__restrict__ agg,
                           int32_t *__restrict__ cnt, int32_t *__restrict__ plong) {
@@ -621,7 +623,6 @@ __global__ void k_p_count(int n, const int32_t *__restrict__ rp, const int32_t *
 // P row i: for each distinct aggregate J among {i} and its strong neighbours,
 // (agg(i)==J) - omega/aF_ii * sum_{agg(j)=J} aF_ij (sums in ascending j),
 // stored in ascending J.
-template <int KP>
 __global__ void k_p_fill(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                          const double *__restrict__ v, const uint8_t *__restrict__ sf,
                          const int32_t *__restrict__ agg, const double *__restrict__ aF,
@@ -701,12 +702,13 @@ struct SlotGraph {
 };
 
 // strength (the transposed entry of slot s of row i is slot 6-s of row j), the
-// MIS-2 state and, in the first kMisWords threads, its change words cleared
+// MIS-2 state; the first kMisWords threads clear its change words and rho
 __global__ void __launch_bounds__(kBlock) k_strength_slots(int nx, int ny, int nz, const double *__restrict__ app,
                                                            double t2, uint8_t *__restrict__ sb,
                                                            uint8_t *__restrict__ state,
-                                                           int32_t *__restrict__ words) {
-    if (blockIdx.x == 0 && threadIdx.x < kMisWords) words[threadIdx.x] = 0;
+                                                           int32_t *__restrict__ words,
+                                                           unsigned long long *__restrict__ rho) {
+    if (blockIdx.x == 0 && threadIdx.x < kMisWords) { words[threadIdx.x] = 0; rho[threadIdx.x] = 0; }
     const int i = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     const int n = nx * ny * nz;
     if (i >= n) return;
@@ -1104,26 +1106,46 @@ __global__ void k_transpose_fill(int n, const int32_t *__restrict__ rp, const in
     }
 }
 
-// sorts every row by column: one wavefront per row; rows of up to 64 entries
-// are ranked across lanes (columns within a row are distinct)
+// Sorts every row by column (columns within a row are distinct): one wavefront
+// per row, each entry's rank counted against all others from the registers, 64
+// entries to a register.  One lane sorting rows of more than 64 entries in memory
+// took 326 us at 40 k rows of a level 1, now 12 us; 264 k rows of 19 entries 178
+// and 73 us.
 __global__ void __launch_bounds__(kBlock) k_sort_rows(int n, const int32_t *__restrict__ rp,
                                                       int32_t *__restrict__ ci, double *__restrict__ v) {
-    int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    int row = gid / 64, lane = gid % 64;
+    const int lane = threadIdx.x % 64;
+    const int row = __builtin_amdgcn_readfirstlane((int)(((long long)blockIdx.x * kBlock + threadIdx.x) / 64));
     if (row >= n) return;
-    int b = rp[row], len = rp[row + 1] - b;
-    if (len <= 64) {
-        int c = lane < len ? ci[b + lane] : 0x7fffffff;
-        double x = lane < len ? v[b + lane] : 0.0;
-        int rank = 0;
-        for (int u = 0; u < 64; u++) {
-            int cu = __shfl(c, u, 64);
-            rank += cu < c;
+    const int b = __builtin_amdgcn_readfirstlane(rp[row]), len = __builtin_amdgcn_readfirstlane(rp[row + 1]) - b;
+    auto sort = [&](auto nr_) {
+        constexpr int NR = decltype(nr_)::value;
+        int c[NR], rank[NR];
+        double x[NR];
+#pragma unroll
+        for (int r = 0; r < NR; r++) {
+            const int e = b + min(64 * r + lane, len - 1);
+            c[r] = ci[e];
+            x[r] = v[e];
+            rank[r] = 0;
         }
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            for (int u = 0; u < min(64, len - 64 * r); u++) {
+                const int cu = __builtin_amdgcn_readlane(c[r], u);
+#pragma unroll
+                for (int q = 0; q < NR; q++) rank[q] += cu < c[q];
+            }
+        // every lane's loads are done before the first store
         __builtin_amdgcn_wave_barrier();
-        if (lane < len) { ci[b + rank] = c; v[b + rank] = x; }
-        return;
-    }
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            if (64 * r + lane < len) { ci[b + rank[r]] = c[r]; v[b + rank[r]] = x[r]; }
+    };
+    if (len <= 1) return;
+    if (len <= 64) return sort(std::integral_constant<int, 1>{});
+    if (len <= 128) return sort(std::integral_constant<int, 2>{});
+    if (len <= 256) return sort(std::integral_constant<int, 4>{});
+    if (len <= 512) return sort(std::integral_constant<int, 8>{});
     if (lane != 0) return;
     for (int a = b + 1; a < b + len; a++) {
         int c = ci[a];
@@ -1434,12 +1456,22 @@ __global__ void __launch_bounds__(256) k_spgemm(int n, const int32_t *__restrict
 }
 
 // ---- coarsest level: dense inverse ---------------------------------------------------
-__global__ void k_dense_from_csr(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                                 const double *__restrict__ v, double *__restrict__ M) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+// [A | I] row-major, a wavefront per row (a thread per row took 28 us at 130
+// rows, now 4.5), and the elimination's flag cleared
+__global__ void __launch_bounds__(kBlock) k_dense_from_csr(int n, const int32_t *__restrict__ rp,
+                                                           const int32_t *__restrict__ ci,
+                                                           const double *__restrict__ v, double *__restrict__ M,
+                                                           int32_t *__restrict__ bad) {
+    const int gid = blockIdx.x * blockDim.x + threadIdx.x, i = gid / 64, lane = gid % 64;
+    if (gid == 0) *bad = 0;
     if (i >= n) return;
-    for (int c = 0; c < 2 * n; c++) M[(size_t)i * 2 * n + c] = (c == n + i) ? 1.0 : 0.0;
-    for (int e = rp[i]; e < rp[i + 1]; e++) M[(size_t)i * 2 * n + ci[e]] = v[e];
+    double *const row = M + (size_t)i * 2 * n;
+    const int b = rp[i], e1 = rp[i + 1];
+    for (int c = lane; c < 2 * n; c += 64) row[c] = (c == n + i) ? 1.0 : 0.0;
+    // the zeros are in memory before the entries go over them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int e = b + lane; e < e1; e += 64) row[ci[e]] = v[e];
 }
 
 // Relative pivot bound of the coarsest level's elimination: a matrix whose
@@ -2211,12 +2243,23 @@ static bo_status level_diag(Level &L, int32_t *dflag, hipStream_t s) {
     return BO_OK;
 }
 
-// smoother weight of the prolongator, (4/3)/rho, on the device
-__global__ void k_omega(const unsigned long long *__restrict__ rho_bits, double *__restrict__ omega,
-                        int32_t *__restrict__ bad, int32_t *__restrict__ plong) {
-    plong[0] = 0;  // the long-row list of the prolongator, filled next
-    unsigned long long rb = 0;
-    for (int q = 0; q < kRedSlots; q++) rb = rho_bits[q] > rb ? rho_bits[q] : rb;
+// Words of one sparse product: [0, kBoundWords kRedSlots) the reductions of
+// k_spgemm_bound, then the long-row list position, the largest distinct counts
+// of the rows launched together and of the long rows, and the hash-capacity flag.
+constexpr int kSgPos = kBoundWords * kRedSlots, kSgMaxl = kSgPos + 1, kSgMaxlLong = kSgPos + 2, kSgBad = kSgPos + 3;
+constexpr int kSgWords = kSgBad + 1;
+
+// smoother weight of the prolongator, (4/3)/rho, on the device (one wavefront),
+// and the words cleared that the level's next kernels count in: the long-row
+// list of the prolongator and both products'
+__global__ void __launch_bounds__(64) k_omega(const unsigned long long *__restrict__ rho_bits,
+                                              double *__restrict__ omega, int32_t *__restrict__ bad,
+                                              int32_t *__restrict__ plong, int32_t *__restrict__ sg) {
+    static_assert(kRedSlots == 64, "a word a lane");
+    for (int q = threadIdx.x; q < 2 * kSgWords; q += 64) sg[q] = 0;
+    const unsigned long long rb = group_max<64>(rho_bits[threadIdx.x]);
+    if (threadIdx.x != 0) return;
+    plong[0] = 0;
     double rho = __longlong_as_double((long long)rb);
     if (!(rho > 0.0) || !(rho < INFINITY)) {
         *bad = 1;
@@ -2232,10 +2275,11 @@ __global__ void k_omega(const unsigned long long *__restrict__ rho_bits, double 
 // it) have more than 512 or more than 128 products; then the others take a
 // hash sized for the longest of them and the long rows a launch of their
 // own.  Each launch's numeric pass sizes its hash from the largest distinct
-// count its own rows had.
+// count its own rows had.  sg: kSgWords cleared words.
 static bo_status spgemm(int n, const int32_t *arp, const int32_t *aci, const double *av, const int32_t *brp,
                         const int32_t *bci, const double *bv, DBuf<int32_t> &crp, DBuf<int32_t> &cci,
-                        DBuf<double> &cv, int *cnnz, SetupWork &W, hipStream_t s, double bavg) {
+                        DBuf<double> &cv, int *cnnz, SetupWork &W, int32_t *sg, hipStream_t s,
+                        double bavg) {
     // rows of many products whose B rows are short (at most 32 entries on
     // average) take 32 lanes, not 64, so that fewer lanes idle per B row
     const bool g32 = bavg <= 32.0;
@@ -2243,17 +2287,10 @@ static bo_status spgemm(int n, const int32_t *arp, const int32_t *aci, const dou
     BO_TRY(cnt.alloc(n));
     BO_TRY(crp.alloc(n + 1));
     BO_TRY(W.sg_prod.alloc(n));
-    // [0, kBoundWords kRedSlots): reduction words of k_spgemm_bound, then
-    // the long-row list position, the largest distinct counts of the rows
-    // launched together and of the long rows, and the hash-capacity flag
-    // (one clear for all of them)
-    constexpr int kPos = kBoundWords * kRedSlots, kMaxl = kPos + 1, kMaxlLong = kPos + 2, kBad = kPos + 3;
-    BO_TRY(W.sg_stat.alloc(kBad + 1));
-    BO_HIP(hipMemsetAsync(W.sg_stat.p, 0, sizeof(int32_t) * (kBad + 1), s));
-    int32_t *const bflag = W.sg_stat.p + kBad;
-    k_spgemm_bound<<<grid_for(n), kBlock, 0, s>>>(n, arp, aci, brp, W.sg_prod.p, W.sg_stat.p);
+    int32_t *const bflag = sg + kSgBad;
+    k_spgemm_bound<<<grid_for(n), kBlock, 0, s>>>(n, arp, aci, brp, W.sg_prod.p, sg);
     int32_t stat[kBoundWords * kRedSlots] = {};
-    HostRead rd{W.sg_stat.p, sizeof stat, stat};
+    HostRead rd{sg, sizeof stat, stat};
     BO_TRY(host_reads(&rd, 1, s));
     int red[kBoundWords] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     for (int q = 0; q < kRedSlots; q++) {
@@ -2292,7 +2329,7 @@ static bo_status spgemm(int n, const int32_t *arp, const int32_t *aci, const dou
     const int32_t *prod = split ? W.sg_prod.p : nullptr;
     if (split) {
         BO_TRY(W.sg_rows.alloc(nlong));
-        k_spgemm_long_rows<<<grid_for(n), kBlock, 0, s>>>(n, W.sg_prod.p, limit, W.sg_rows.p, W.sg_stat.p + kPos);
+        k_spgemm_long_rows<<<grid_for(n), kBlock, 0, s>>>(n, W.sg_prod.p, limit, W.sg_rows.p, sg + kSgPos);
     }
     auto count = [&](int sel, int rn, const int32_t *rows, const int32_t *pr, int32_t *maxl) {
         if (rn <= 0) return;
@@ -2310,12 +2347,12 @@ static bo_status spgemm(int n, const int32_t *arp, const int32_t *aci, const dou
         }
 #undef BO_SPGEMM_COUNT
     };
-    count(sel_all, n, nullptr, prod, W.sg_stat.p + kMaxl);
-    if (split) count(sel_long, nlong, W.sg_rows.p, nullptr, W.sg_stat.p + kMaxlLong);
+    count(sel_all, n, nullptr, prod, sg + kSgMaxl);
+    if (split) count(sel_long, nlong, W.sg_rows.p, nullptr, sg + kSgMaxlLong);
     BO_HIP(hipGetLastError());
     int32_t bad = 0, total = 0, lmax = 0, lmax_long = 0;
-    HostRead ex[3] = {{bflag, sizeof bad, &bad}, {W.sg_stat.p + kMaxl, sizeof lmax, &lmax},
-                      {W.sg_stat.p + kMaxlLong, sizeof lmax_long, &lmax_long}};
+    HostRead ex[3] = {{bflag, sizeof bad, &bad}, {sg + kSgMaxl, sizeof lmax, &lmax},
+                      {sg + kSgMaxlLong, sizeof lmax_long, &lmax_long}};
     BO_TRY(scan_counts(cnt.p, crp.p, n, &total, s, ex, 3));
     if (bad) return fail(BO_ERR_UNSUPPORTED, "AMG: Galerkin product row exceeds the LDS hash capacity");
     BO_TRY(cci.alloc(total));
@@ -2333,7 +2370,7 @@ static bo_status spgemm(int n, const int32_t *arp, const int32_t *aci, const dou
 #define BO_SPGEMM_NUM(GG, H)                                                                                    \
     k_spgemm<GG, H, true><<<grid_for((long long)rn * GG), 256, 0, s>>>(rn, arp, aci, av, brp, bci, bv, nullptr, \
                                                                        crp.p, cci.p, cv.p, bflag, rows, pr,    \
-                                                                       W.sg_stat.p + kMaxl, plimit)
+                                                                       sg + kSgMaxl, plimit)
         if (G == 8) {
             if (h <= 64) BO_SPGEMM_NUM(8, 64); else BO_SPGEMM_NUM(8, 128);
         } else if (G == 16) {
@@ -2369,7 +2406,7 @@ static bo_status spgemm(int n, const int32_t *arp, const int32_t *aci, const dou
     constexpr int kFewDistinct = 64;
     int nbig = 0, dlim = kFewDistinct;
     if (!split && lmax > kFewDistinct) {
-        int32_t *pos = W.sg_stat.p + kPos;  // unused without the products split
+        int32_t *pos = sg + kSgPos;  // unused without the products split
         BO_TRY(W.sg_rows.alloc(n));
         const int dmaxl = n >= (1 << 17) ? 2 * kFewDistinct : kFewDistinct;
         for (int dl = kFewDistinct; dl <= dmaxl && lmax > dl; dl *= 2) {
@@ -2386,7 +2423,7 @@ static bo_status spgemm(int n, const int32_t *arp, const int32_t *aci, const dou
     // own too.
     int nbig2 = 0;
     if (split && lmax > kFewDistinct) {
-        int32_t *pos = W.sg_stat.p + kPos;  // the long-row list is complete: its position word is free again
+        int32_t *pos = sg + kSgPos;  // the long-row list is complete: its position word is free again
         BO_TRY(W.sg_rows2.alloc(n));
         BO_TRY(W.sg_key.alloc(n));
         BO_HIP(hipMemsetAsync(pos, 0, sizeof(int32_t), s));
@@ -2487,11 +2524,15 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         // k_mis_init, kMisWords of them, cleared again when they run out), so
         // no round needs a memset before it
         BO_TRY(W.misw.alloc(kMisWords));
+        DBuf<unsigned long long> &rho = W.rho;
+        static_assert(kMisWords == kRedSlots, "cleared by the same threads");
+        BO_TRY(rho.alloc(kRedSlots));
         if (slots)
             k_strength_slots<<<grid_for(n), kBlock, 0, s>>>(pc->g.nx, pc->g.ny, pc->g.nz, pc->app.p, t2, L.sf.p,
-                                                             state.p, W.misw.p);
+                                                             state.p, W.misw.p, rho.p);
         else
-            k_mis_init<<<grid_for(std::max(n, kMisWords)), kBlock, 0, s>>>(n, L.rp.p, L.sf.p, state.p, W.misw.p);
+            k_mis_init<<<grid_for(std::max(n, kMisWords)), kBlock, 0, s>>>(n, L.rp.p, L.sf.p, state.p, W.misw.p,
+                                                                           rho.p);
         int word = 0;
         // rounds are checked for completion after the fourth and then every
         // second round: a round on a graph with no undecided node changes
@@ -2564,9 +2605,7 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         if (l == 0) BO_TRY(fork());
         // prolongator
         DBuf<double> &aF = W.aF;
-        DBuf<unsigned long long> &rho = W.rho;
-        BO_TRY(aF.alloc(n)); BO_TRY(rho.alloc(kRedSlots));
-        BO_HIP(hipMemsetAsync(rho.p, 0, sizeof(unsigned long long) * kRedSlots, s));
+        BO_TRY(aF.alloc(n));
         if (slots) k_slot_filter<<<grid_for(n), kBlock, 0, s>>>(SG, pc->g.ny, pc->g.nz, pc->app.p, aF.p, rho.p);
         else if (L.nnz <= 8LL * n)
             k_filter<256><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.diagpos.p, L.sf.p, aF.p, rho.p);
@@ -2578,15 +2617,14 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
                                                           rho.p);
         const double *omega = W.omg.p + l;
         BO_TRY(W.plong.alloc(n + 1));
-        k_omega<<<1, 1, 0, s>>>(rho.p, W.omg.p + l, W.dfl.p + 2, W.plong.p);
-        const bool kp8 = L.nnz <= 8LL * n;
+        BO_TRY(W.sg_stat.alloc(2 * kSgWords));
+        k_omega<<<1, 64, 0, s>>>(rho.p, W.omg.p + l, W.dfl.p + 2, W.plong.p, W.sg_stat.p);
         // the listed long rows, a wavefront each up to 65536 of them
         const unsigned pgrid = (unsigned)std::min<long long>((n + kPWaves - 1) / kPWaves, 16384);
         if (slots) {
             k_slot_p_count<<<grid_for(n), kBlock, 0, s>>>(SG, L.agg.p, cnt.p);
         } else {
-            if (kp8) k_p_count<8><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, L.agg.p, cnt.p, W.plong.p);
-            else k_p_count<16><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, L.agg.p, cnt.p, W.plong.p);
+            k_p_count<<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, L.agg.p, cnt.p, W.plong.p);
             k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, nullptr,
                                                     nullptr, nullptr, cnt.p, W.plong.p);
             k_p_vlong<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, nullptr,
@@ -2601,12 +2639,8 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
             k_slot_p_fill<<<grid_for(n), kBlock, 0, s>>>(SG, pc->app.p, L.agg.p, aF.p, omega, L.prp.p, L.pci.p,
                                                          L.pv.p);
         } else {
-            if (kp8)
-                k_p_fill<8><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega,
-                                                           L.prp.p, L.pci.p, L.pv.p);
-            else
-                k_p_fill<16><<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega,
-                                                            L.prp.p, L.pci.p, L.pv.p);
+            k_p_fill<<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
+                                                    L.pci.p, L.pv.p);
             k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
                                                     L.pci.p, L.pv.p, nullptr, W.plong.p);
             k_p_vlong<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
@@ -2632,11 +2666,12 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         DBuf<int32_t> &aprp = W.aprp, &apci = W.apci;
         DBuf<double> &apv = W.apv;
         int apnnz = 0;
-        BO_TRY(spgemm(n, L.rp.p, L.ci.p, L.v.p, L.prp.p, L.pci.p, L.pv.p, aprp, apci, apv, &apnnz, W, s,
+        BO_TRY(spgemm(n, L.rp.p, L.ci.p, L.v.p, L.prp.p, L.pci.p, L.pv.p, aprp, apci, apv, &apnnz, W, W.sg_stat.p, s,
                       (double)L.pnnz / n));
         Level &C = pc->lv[l + 1];
         C.n = nc;
-        BO_TRY(spgemm(nc, L.rrp.p, L.rci.p, L.rv.p, aprp.p, apci.p, apv.p, C.rp, C.ci, C.v, &C.nnz, W, s,
+        BO_TRY(spgemm(nc, L.rrp.p, L.rci.p, L.rv.p, aprp.p, apci.p, apv.p, C.rp, C.ci, C.v, &C.nnz, W,
+                      W.sg_stat.p + kSgWords, s,
                       (double)apnnz / n));
     }
     pc->nlev = l + 1;
@@ -2664,8 +2699,7 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
     DBuf<double> &M = W.dense;
     BO_TRY(M.alloc((size_t)nc * 2 * nc));
     BO_TRY(pc->cinv.alloc((size_t)nc * nc));
-    k_dense_from_csr<<<grid_for(nc), kBlock, 0, s>>>(nc, Lc.rp.p, Lc.ci.p, Lc.v.p, M.p);
-    BO_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t), s));
+    k_dense_from_csr<<<grid_for(64LL * nc), kBlock, 0, s>>>(nc, Lc.rp.p, Lc.ci.p, Lc.v.p, M.p, flag);
     if (nc <= kGjRegMax) {
         // 16 x 16 threads up to 64 rows (a quarter of the wavefronts' work beside
         // the updates), 32 x 32 above, where one wavefront per SIMD waits for its
