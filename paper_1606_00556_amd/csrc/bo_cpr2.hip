@@ -273,18 +273,35 @@ __global__ void __launch_bounds__(64) k_ilu2_factor(Tile2 T, const double *__res
     }
 }
 
-// The sweeps walk the steps with the next step's loads in flight: its
-// factors (1 KB per load instruction), and its r (forward) or u and dp
-// (backward), are fetched into the second of two register buffers before the
-// current step's arithmetic, which waits only for the shuffled neighbour
-// values of the previous step.  Lanes idle at a step load slot 0 of the tile
-// and cell 0 (all in bounds) so that no load is skipped on some paths.
+// The sweeps walk the steps with the loads of the next AH - 1 steps in flight in a
+// ring of register buffers: a step's factors (1 KB per load instruction) and its
+// r (forward) or u and dp (backward); its arithmetic waits only for the shuffled
+// neighbour values of the previous step.  Lanes idle at a step load slot 0 of the
+// tile and cell 0 (all in bounds) so that no load is skipped on some paths.  Bound
+// by the memory it streams (390 and 410 MB at 2 M cells): forward and backward
+// sweep with 2 buffers 82 and 99 us, with 4 81 and 95 us, with 4 and the factors
+// read past the cache 77 and 85 us (2 buffers: 78 and 88 us).
+constexpr int kIlu2Ahead = 4;
+// Factors of more than the 256 MB last-level cache are read past it (NT), as the
+// 3x3 form's are.
+constexpr size_t kCacheBytes = 256u << 20;
+template <bool NT>
+__device__ __forceinline__ double2 load_factor(const double2 *p) {
+    typedef double V __attribute__((ext_vector_type(2)));
+    if constexpr (NT) {
+        const V v = __builtin_nontemporal_load((const V *)p);
+        return make_double2(v.x, v.y);
+    } else {
+        return *p;
+    }
+}
 struct Step2 {
     double f[16];
     double v0, v1, d;
 };
 
 // forward sweep: u (slot order) from r (cell order)
+template <int AH, bool NT>
 __global__ void __launch_bounds__(64) k_ilu2_forward(Tile2 T, const double2 *__restrict__ Ff,
                                                      const double *__restrict__ r, double2 *__restrict__ U) {
     const int t = threadIdx.x;
@@ -302,7 +319,7 @@ __global__ void __launch_bounds__(64) k_ilu2_forward(Tile2 T, const double2 *__r
         const int tl = act ? t : 0;
 #pragma unroll
         for (int p2 = 0; p2 < kPk2; p2++) {
-            const double2 d = Ff[pk2(T, tile, sc, p2, tl)];
+            const double2 d = load_factor<NT>(&Ff[pk2(T, tile, sc, p2, tl)]);
             F.f[2 * p2] = d.x;
             F.f[2 * p2 + 1] = d.y;
         }
@@ -325,19 +342,19 @@ __global__ void __launch_bounds__(64) k_ilu2_forward(Tile2 T, const double2 *__r
         mv2(f, yv, up);
         U[slot2(T, tile, s, t)] = make_double2(up[0], up[1]);
     };
-    Step2 R0, R1;
-    fetch(0, R0);
-    int s0 = 0;
-    for (; s0 + 2 <= T.ns; s0 += 2) {
-        fetch(s0 + 1, R1);
-        step(s0, R0);
-        fetch(s0 + 2, R0);
-        step(s0 + 1, R1);
-    }
-    if (s0 < T.ns) step(s0, R0);
+    Step2 R[AH];
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(u, R[u]);
+    for (int s0 = 0; s0 < T.ns; s0 += AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {  // past the last step every lane is idle
+            step(s0 + u, R[u]);
+            fetch(s0 + u + AH, R[u]);
+        }
 }
 
 // backward sweep: x (cell order) from u (slot order), + Pi_p dp when given
+template <int AH, bool NT, bool DP>
 __global__ void __launch_bounds__(64) k_ilu2_backward(Tile2 T, const double2 *__restrict__ Fb,
                                                       const double2 *__restrict__ U,
                                                       const double *__restrict__ dp, double *__restrict__ x) {
@@ -356,7 +373,7 @@ __global__ void __launch_bounds__(64) k_ilu2_backward(Tile2 T, const double2 *__
         const int tl = act ? t : 0;
 #pragma unroll
         for (int p2 = 0; p2 < kPk2; p2++) {
-            const double2 d = Fb[pk2(T, tile, sc, p2, tl)];
+            const double2 d = load_factor<NT>(&Fb[pk2(T, tile, sc, p2, tl)]);
             F.f[2 * p2] = d.x;
             F.f[2 * p2 + 1] = d.y;
         }
@@ -364,7 +381,7 @@ __global__ void __launch_bounds__(64) k_ilu2_backward(Tile2 T, const double2 *__
         F.v0 = u.x;
         F.v1 = u.y;
         const size_t g = act ? (size_t)i + (size_t)T.nx * ((size_t)j + (size_t)T.ny * k) : 0;
-        F.d = dp ? dp[g] : 0.0;
+        if constexpr (DP) F.d = dp[g];
     };
     auto step = [&](int s, const Step2 &F) {
         double xx[2], xy[2];
@@ -384,19 +401,19 @@ __global__ void __launch_bounds__(64) k_ilu2_backward(Tile2 T, const double2 *__
         xp[0] = F.v0 - c[0];
         xp[1] = F.v1 - c[1];
         const size_t g = (size_t)i + (size_t)T.nx * ((size_t)j + (size_t)T.ny * k);
-        x[2 * g] = dp ? xp[0] + F.d : xp[0];
+        if constexpr (DP) x[2 * g] = xp[0] + F.d;
+        else x[2 * g] = xp[0];
         x[2 * g + 1] = xp[1];
     };
-    Step2 R0, R1;
-    fetch(T.ns - 1, R0);
-    int s0 = T.ns - 1;
-    for (; s0 - 2 >= -1; s0 -= 2) {
-        fetch(s0 - 1, R1);
-        step(s0, R0);
-        fetch(s0 - 2, R0);
-        step(s0 - 1, R1);
-    }
-    if (s0 >= 0) step(s0, R0);
+    Step2 R[AH];
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(T.ns - 1 - u, R[u]);
+    for (int s0 = T.ns - 1; s0 >= 0; s0 -= AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {  // before the first step every lane is idle
+            step(s0 - u, R[u]);
+            fetch(s0 - u - AH, R[u]);
+        }
 }
 
 Tile2 tile_geom(const bo_cpr *pc) {
@@ -432,9 +449,16 @@ bo_status fstage2_apply(bo_cpr *pc, const double *r, const double *dp, double *o
     }
     const Tile2 T = tile_geom(pc);
     const int tiles = T.ntx * T.nty;
-    k_ilu2_forward<<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, (double2 *)pc->ilu_w.p);
-    BO_HIP(hipGetLastError());
-    k_ilu2_backward<<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, (const double2 *)pc->ilu_w.p, dp, out);
+    const bool nt = (size_t)tiles * T.ns * 64 * kPk2 * sizeof(double2) > kCacheBytes;
+    double2 *const u = (double2 *)pc->ilu_w.p;
+    auto sweeps = [&](auto nt_) {
+        constexpr bool NT = decltype(nt_)::value;
+        k_ilu2_forward<kIlu2Ahead, NT><<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, u);
+        if (dp) k_ilu2_backward<kIlu2Ahead, NT, true><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, u, dp, out);
+        else k_ilu2_backward<kIlu2Ahead, NT, false><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, u, dp, out);
+    };
+    if (nt) sweeps(std::true_type{});
+    else sweeps(std::false_type{});
     BO_HIP(hipGetLastError());
     return BO_OK;
 }

@@ -396,9 +396,17 @@ struct Factors {
     static constexpr int kCount = St == ST_F64 ? kPairs - kFirst : kQuads;
     static constexpr int kStride = St == ST_F64 ? kPairs : kQuads;
     Raw raw[kCount];
+    static constexpr size_t kBytes = kCount * sizeof(Raw);  // read per slot
+    template <bool NT>
     __device__ __forceinline__ void load(const Raw *__restrict__ p) {
+        typedef uint32_t V __attribute__((ext_vector_type(sizeof(Raw) / 4)));
 #pragma unroll
-        for (int i = 0; i < kCount; i++) raw[i] = p[(kFirst + i) * 64];
+        for (int i = 0; i < kCount; i++) {
+            if constexpr (NT)
+                raw[i] = __builtin_bit_cast(Raw, __builtin_nontemporal_load((const V *)(p + (kFirst + i) * 64)));
+            else
+                raw[i] = p[(kFirst + i) * 64];
+        }
     }
     // values 9 q .. 9 q + 8 of the slot's 36 (q = 1..3 in the FP64 forward form)
     template <typename T>
@@ -459,7 +467,7 @@ struct SweepLane {
 // factors L_ik = A_ik E_k^{-1}; FP32 / BF16: w = E^{-1}(r - sum_lower A w_lower)
 // (w = E^{-1} y).  r (FP64) in natural order, read at the slot's cell and
 // rounded to T; the result in (tile, step, lane) order
-template <int St, typename T, int AH>
+template <int St, typename T, int AH, bool NT>
 __global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__restrict__ F,
                                                     const double *__restrict__ r, T *__restrict__ wq) {
     typedef Factors<St, true> Fac;
@@ -476,7 +484,7 @@ __global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__re
     } ring[AH];
     auto fetch = [&](int s, Slot &Q) {
         const int sc = min(s, ns - 1);
-        Q.f.load(Ft + (size_t)sc * Fac::kStride * 64 + (L.active(G, sc) ? t : 0));
+        Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + (L.active(G, sc) ? t : 0));
         const double *rg = r + 3 * L.cell(G, sc);
         Q.r[0] = rg[0]; Q.r[1] = rg[1]; Q.r[2] = rg[2];
     };
@@ -534,7 +542,7 @@ __global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__re
 // the first finished layer write the last layer's places, in the ZIN form with
 // the values they hold).  Without staging (STAGE false, where D layers do not fit) every lane
 // writes its 24 bytes at its cell, and the partial lines cost HBM writes of more than twice the output's size.
-template <int St, typename T, typename TD, int AH, bool ZIN, bool STAGE>
+template <int St, typename T, typename TD, int AH, bool NT, bool ZIN, bool STAGE>
 __global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__restrict__ F, T *__restrict__ wq,
                                                      const TD *__restrict__ dp, double *out, int D,
                                                      const double *zin) {
@@ -573,7 +581,7 @@ __global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__r
         const int sc = max(s, 0);
         const bool act = L.active(G, sc);
         const int tl = act ? t : 0;
-        Q.f.load(Ft + (size_t)sc * Fac::kStride * 64 + tl);
+        Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + tl);
         const T *w = wt + (size_t)sc * 64 + tl;
         Q.w[0] = w[0]; Q.w[1] = w[S]; Q.w[2] = w[2 * S];
         const size_t g = L.cell(G, sc);
@@ -879,27 +887,46 @@ inline int stage_layers(const TileGeom &G) {
 // steps, 58.4 us with 2 and 2, 64.0 us with 6 and 4), beyond that more
 // tiles per SIMD do (400x400x100: 2.16 ms either way, HBM bound).
 constexpr int kFewTiles = 1024, kAheadF = 4, kAheadB = 3;
+// Factors of more than the 256 MB last-level cache are read past it: they are
+// gone before the next sweep reads them, and leave it to what the products and
+// the V-cycle read again (400x400x100 in FP64, both sweeps: 2156 and now 2119 us).
+// Factors that stay in part must not be: 100x100x50
+// in FP64, 155 MB, forward sweep 41 us cached and 70 us past the cache.
+constexpr size_t kCacheBytes = 256u << 20;
+template <int St, bool FWD> bool past_cache(const TileGeom &G) {
+    return (size_t)G.slots() * Factors<St, FWD>::kBytes > kCacheBytes;
+}
 template <int St, typename T>
 void launch_forward(const TileGeom &G, const void *F, const double *r, T *wq, hipStream_t s) {
     const int nb = G.ntx * G.nty;
-    if (nb <= kFewTiles) k_ilu_forward<St, T, kAheadF><<<nb, 64, 0, s>>>(G, F, r, wq);
-    else k_ilu_forward<St, T, 2><<<nb, 64, 0, s>>>(G, F, r, wq);
+    const bool few = nb <= kFewTiles, nt = past_cache<St, true>(G);
+    if (few && nt) k_ilu_forward<St, T, kAheadF, true><<<nb, 64, 0, s>>>(G, F, r, wq);
+    else if (few) k_ilu_forward<St, T, kAheadF, false><<<nb, 64, 0, s>>>(G, F, r, wq);
+    else if (nt) k_ilu_forward<St, T, 2, true><<<nb, 64, 0, s>>>(G, F, r, wq);
+    else k_ilu_forward<St, T, 2, false><<<nb, 64, 0, s>>>(G, F, r, wq);
 }
-template <int St, typename T, typename TD, int AH, bool ZIN>
+template <int St, typename T, typename TD, int AH, bool NT, bool ZIN>
 void launch_backward_ah(const TileGeom &G, const void *F, T *wq, const TD *dp, double *out, const double *zin,
                         hipStream_t s) {
     const int nb = G.ntx * G.nty, D = stage_layers(G);
-    if (D > 0) k_ilu_backward<St, T, TD, AH, ZIN, true><<<nb, 64, D * kStageBytes, s>>>(G, F, wq, dp, out, D, zin);
-    else k_ilu_backward<St, T, TD, AH, ZIN, false><<<nb, 64, 0, s>>>(G, F, wq, dp, out, D, zin);
+    if (D > 0)
+        k_ilu_backward<St, T, TD, AH, NT, ZIN, true><<<nb, 64, D * kStageBytes, s>>>(G, F, wq, dp, out, D, zin);
+    else k_ilu_backward<St, T, TD, AH, NT, ZIN, false><<<nb, 64, 0, s>>>(G, F, wq, dp, out, D, zin);
+}
+template <int St, typename T, typename TD, bool ZIN>
+void launch_backward_zin(const TileGeom &G, const void *F, T *wq, const TD *dp, double *out, const double *zin,
+                         hipStream_t s) {
+    const bool few = G.ntx * G.nty <= kFewTiles, nt = past_cache<St, false>(G);
+    if (few && nt) launch_backward_ah<St, T, TD, kAheadB, true, ZIN>(G, F, wq, dp, out, zin, s);
+    else if (few) launch_backward_ah<St, T, TD, kAheadB, false, ZIN>(G, F, wq, dp, out, zin, s);
+    else if (nt) launch_backward_ah<St, T, TD, 2, true, ZIN>(G, F, wq, dp, out, zin, s);
+    else launch_backward_ah<St, T, TD, 2, false, ZIN>(G, F, wq, dp, out, zin, s);
 }
 template <int St, typename T, typename TD>
 void launch_backward(const TileGeom &G, const void *F, T *wq, const TD *dp, double *out, const double *zin,
                      hipStream_t s) {
-    const bool few = G.ntx * G.nty <= kFewTiles;
-    if (zin && few) launch_backward_ah<St, T, TD, kAheadB, true>(G, F, wq, dp, out, zin, s);
-    else if (zin) launch_backward_ah<St, T, TD, 2, true>(G, F, wq, dp, out, zin, s);
-    else if (few) launch_backward_ah<St, T, TD, kAheadB, false>(G, F, wq, dp, out, zin, s);
-    else launch_backward_ah<St, T, TD, 2, false>(G, F, wq, dp, out, zin, s);
+    if (zin) launch_backward_zin<St, T, TD, true>(G, F, wq, dp, out, zin, s);
+    else launch_backward_zin<St, T, TD, false>(G, F, wq, dp, out, zin, s);
 }
 
 TileGeom geom(const bo_cpr *pc) {
