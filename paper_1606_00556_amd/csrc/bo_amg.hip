@@ -436,6 +436,12 @@ __global__ void k_is_root(int n, const uint8_t *__restrict__ state, int32_t *__r
     root[i] = state[i] == IN;
 }
 
+// zero[0..2 nc) cleared by a launch of at least nc threads
+__device__ __forceinline__ void clear_pairs(int32_t *zero, int nc) {
+    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q < nc) zero[q] = zero[nc + q] = 0;
+}
+
 // phase 1: a root and its strong neighbours form an aggregate.  G lanes per
 // row; the last strong root neighbour wins.  A thread per row took as many round
 // trips to memory as a row has batches.  264 k rows of 36 entries: this phase 32
@@ -444,7 +450,8 @@ template <int G>
 __global__ void __launch_bounds__(kBlock) k_agg1(int n, const int32_t *__restrict__ rp,
                                                  const int32_t *__restrict__ ci, const uint8_t *__restrict__ sf,
                                                  const uint8_t *__restrict__ state, const int32_t *__restrict__ id,
-                                                 int32_t *__restrict__ a1) {
+                                                 int32_t *__restrict__ a1, int32_t *__restrict__ zero, int nc) {
+    clear_pairs(zero, nc);
     const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const int i = (int)(gid / G), sub = (int)(gid % G);
     if (i >= n) return;  // whole groups leave together
@@ -669,8 +676,8 @@ __global__ void k_p_count(int n, const int32_t *__restrict__ rp, const int32_t *
                           int32_t *__restrict__ cnt, int32_t *__restrict__ plong) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     int len = i < n ? rp[i + 1] - rp[i] : 0;
-    // rows longer than KP go to plong[1..] (count in plong[0]) for k_p_long /
-    // k_p_vlong: one atomic per wavefront, each lane at its rank among them
+    // rows longer than KP go to plong[1..] (count in plong[0]) for k_p_long:
+    // one atomic per wavefront, each lane at its rank among them
     const bool lng = len > KP;
     const uint64_t m = __ballot(lng);
     if (m) {
@@ -710,7 +717,8 @@ __global__ void k_p_fill(int n, const int32_t *__restrict__ rp, const int32_t *_
                          const double *__restrict__ v, const uint8_t *__restrict__ sf,
                          const int32_t *__restrict__ agg, const double *__restrict__ aF,
                          const double *__restrict__ omega, const int32_t *__restrict__ prp,
-                         int32_t *__restrict__ pci, double *__restrict__ pv) {
+                         int32_t *__restrict__ pci, double *__restrict__ pv,
+                         int32_t *__restrict__ ccnt) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double d = omega[0] / aF[i];
@@ -749,6 +757,7 @@ __global__ void k_p_fill(int n, const int32_t *__restrict__ rp, const int32_t *_
                 for (int w = 0; w < u; w++) fu = fu && J[w] != J[u];
                 rank += fu;
             }
+            atomicAdd(&ccnt[J[q]], 1);
             pci[prp[i] + rank] = J[q];
             pv[prp[i] + rank] = (ai == J[q] ? 1.0 : 0.0) - d * sum;
         }
@@ -874,7 +883,9 @@ __global__ void __launch_bounds__(kBlock) k_slot_mis_update(SlotGraph G, const u
 
 // the two phases of the aggregation (k_agg1, k_agg2)
 __global__ void __launch_bounds__(kBlock) k_slot_agg1(SlotGraph G, const uint8_t *__restrict__ state,
-                                                      const int32_t *__restrict__ id, int32_t *__restrict__ a1) {
+                                                      const int32_t *__restrict__ id, int32_t *__restrict__ a1,
+                                                      int32_t *__restrict__ zero, int nc) {
+    clear_pairs(zero, nc);
     const int i = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     if (i >= G.n) return;
     const int bits = G.sb[i];
@@ -970,7 +981,7 @@ __global__ void __launch_bounds__(kBlock) k_slot_p_fill(SlotGraph G, const doubl
                                                         const double *__restrict__ aF,
                                                         const double *__restrict__ omega,
                                                         const int32_t *__restrict__ prp, int32_t *__restrict__ pci,
-                                                        double *__restrict__ pv) {
+                                                        double *__restrict__ pv, int32_t *__restrict__ ccnt) {
     const int i = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     if (i >= G.n) return;
     int J[NSLOT];
@@ -997,13 +1008,14 @@ __global__ void __launch_bounds__(kBlock) k_slot_p_fill(SlotGraph G, const doubl
             if (u >= q && J[u] == J[q]) sum = sum + a[u];
             rank += first[u] && J[u] < J[q];
         }
+        atomicAdd(&ccnt[J[q]], 1);
         pci[base + rank] = J[q];
         pv[base + rank] = (ai == J[q] ? 1.0 : 0.0) - d * sum;
     }
 }
 
-// Long rows of the prolongator (more than KP entries, up to KW): one wavefront
-// per row, its (aggregate, filtered value) pairs in registers, 64 to a register.
+// Long rows of the prolongator (more than KP entries): one wavefront per row, up
+// to KW entries with its (aggregate, filtered value) pairs in registers, 64 to a register.
 // The aggregates are taken one after the other in order of first appearance;
 // their values are added in entry order, and the first appearance's lane writes
 // the result at the aggregate's rank among the row's distinct ones.  A search
@@ -1020,6 +1032,7 @@ __global__ void __launch_bounds__(64 * kPWaves) k_p_long(const int32_t *__restri
                                                           const double *__restrict__ aF, const double *__restrict__ omega,
                                                           const int32_t *__restrict__ prp, int32_t *__restrict__ pci,
                                                           double *__restrict__ pv, int32_t *__restrict__ cnt,
+                                                          int32_t *__restrict__ ccnt,
                                                           const int32_t *__restrict__ plong) {
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     // the rows k_p_count listed, a wavefront each, over a fixed grid
@@ -1094,9 +1107,50 @@ __global__ void __launch_bounds__(64 * kPWaves) k_p_long(const int32_t *__restri
 #pragma unroll
         for (int r = 0; r < NR; r++)
             if ((leaders[r] >> lane) & 1) {
+                atomicAdd(&ccnt[J[r]], 1);
                 pci[base + rank[r]] = J[r];
                 pv[base + rank[r]] = (ai == J[r] ? 1.0 : 0.0) - d * sum[r];
             }
+    };
+    // the rare rows longer than the registers (a well row and its aggregates on
+    // coarse levels): the row's aggregate ids and values re-read from memory,
+    // quadratic in the row length
+    auto long_row = [&](int i, int b, int len) {
+        auto jof = [&](int q) -> int { int e = b + q; return p_takes(e, i, ci, sf, agg) ? agg[ci[e]] : -1; };
+        auto aof = [&](int q) -> double {
+            int e = b + q;
+            return p_takes(e, i, ci, sf, agg) ? (ci[e] == i ? aF[i] : v[e]) : 0.0;
+        };
+        auto is_first = [&](int q, int Jq) -> bool {
+            if (Jq < 0) return false;
+            for (int u = 0; u < q; u++)
+                if (jof(u) == Jq) return false;
+            return true;
+        };
+        if (cnt) {
+            int mycount = 0;
+            for (int q = lane; q < len; q += 64) mycount += is_first(q, jof(q));
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) mycount += __shfl_xor(mycount, off, 64);
+            if (lane == 0) cnt[i] = mycount;
+            return;
+        }
+        double d = omega[0] / aF[i];
+        int ai = agg[i];
+        for (int q = lane; q < len; q += 64) {
+            int Jq = jof(q);
+            if (!is_first(q, Jq)) continue;
+            double sum = 0.0;
+            int rank = 0;
+            for (int u = 0; u < len; u++) {
+                int Ju = jof(u);
+                if (u >= q && Ju == Jq) sum = sum + aof(u);
+                rank += Ju >= 0 && Ju < Jq && is_first(u, Ju);
+            }
+            atomicAdd(&ccnt[Jq], 1);
+            pci[prp[i] + rank] = Jq;
+            pv[prp[i] + rank] = (ai == Jq ? 1.0 : 0.0) - d * sum;
+        }
     };
     // the next row's number and bounds are loaded while a row is worked on
     int i1 = plong[1 + idx], b1 = rp[i1], e1 = rp[i1 + 1], i2 = plong[1 + min(idx + step, nl - 1)];
@@ -1111,71 +1165,11 @@ __global__ void __launch_bounds__(64 * kPWaves) k_p_long(const int32_t *__restri
         else if (len <= 128) row(std::integral_constant<int, 2>{}, i, b, len);
         else if (len <= 256) row(std::integral_constant<int, 4>{}, i, b, len);
         else if (len <= KW) row(std::integral_constant<int, 8>{}, i, b, len);
-        // longer ones are k_p_vlong's
-    }
-}
-
-// The same for the rare rows longer than the registers (a well row and its
-// aggregates on coarse levels): one wavefront per row, the row's aggregate
-// ids and values re-read from global memory, quadratic in the row length.
-__global__ void __launch_bounds__(64 * kPWaves) k_p_vlong(int n, const int32_t *__restrict__ rp,
-                                                           const int32_t *__restrict__ ci,
-                                                           const double *__restrict__ v,
-                                                           const uint8_t *__restrict__ sf,
-                                                           const int32_t *__restrict__ agg,
-                                                           const double *__restrict__ aF, const double *__restrict__ omega,
-                                                           const int32_t *__restrict__ prp, int32_t *__restrict__ pci,
-                                                           double *__restrict__ pv, int32_t *__restrict__ cnt,
-                                                           const int32_t *__restrict__ plong) {
-    int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int nl = plong[0];
-    for (int idx = blockIdx.x * kPWaves + wave; idx < nl; idx += gridDim.x * kPWaves) {
-    const int i = plong[1 + idx];
-    int b = rp[i], len = rp[i + 1] - b;
-    if (len <= KW) continue;
-    auto jof = [&](int q) -> int { int e = b + q; return p_takes(e, i, ci, sf, agg) ? agg[ci[e]] : -1; };
-    auto aof = [&](int q) -> double {
-        int e = b + q;
-        return p_takes(e, i, ci, sf, agg) ? (ci[e] == i ? aF[i] : v[e]) : 0.0;
-    };
-    auto is_first = [&](int q, int Jq) -> bool {
-        if (Jq < 0) return false;
-        for (int u = 0; u < q; u++)
-            if (jof(u) == Jq) return false;
-        return true;
-    };
-    if (cnt) {
-        int mycount = 0;
-        for (int q = lane; q < len; q += 64) mycount += is_first(q, jof(q));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mycount += __shfl_xor(mycount, off, 64);
-        if (lane == 0) cnt[i] = mycount;
-        continue;
-    }
-    double d = omega[0] / aF[i];
-    int ai = agg[i];
-    for (int q = lane; q < len; q += 64) {
-        int Jq = jof(q);
-        if (!is_first(q, Jq)) continue;
-        double sum = 0.0;
-        int rank = 0;
-        for (int u = 0; u < len; u++) {
-            int Ju = jof(u);
-            if (u >= q && Ju == Jq) sum = sum + aof(u);
-            rank += Ju >= 0 && Ju < Jq && is_first(u, Ju);
-        }
-        pci[prp[i] + rank] = Jq;
-        pv[prp[i] + rank] = (ai == Jq ? 1.0 : 0.0) - d * sum;
-    }
+        else long_row(i, b, len);
     }
 }
 
 // transpose helpers
-__global__ void k_col_counts(int nnz, const int32_t *__restrict__ ci, int32_t *__restrict__ cnt) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < nnz) atomicAdd(&cnt[ci[e]], 1);
-}
-
 __global__ void k_transpose_fill(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                                  const double *__restrict__ v, const int32_t *__restrict__ trp,
                                  int32_t *__restrict__ fillpos, int32_t *__restrict__ tci, double *__restrict__ tv) {
@@ -2689,15 +2683,20 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         int32_t nc = 0;
         BO_TRY(scan_counts(cnt.p, id.p, n, &nc, s));
         if (nc == 0 || (double)nc > 0.8 * (double)n) break;
+        // P's column counts (the kernels that fill P count them) and R's fill
+        // positions in one buffer, cleared by the first of these
+        DBuf<int32_t> &rc = W.rc;
+        BO_TRY(rc.alloc(2 * (size_t)nc));
+        int32_t *const rcnt = rc.p, *const fp = rc.p + nc;
         if (slots) {
-            k_slot_agg1<<<grid_for(n), kBlock, 0, s>>>(SG, state.p, id.p, a1.p);
+            k_slot_agg1<<<grid_for(n), kBlock, 0, s>>>(SG, state.p, id.p, a1.p, rc.p, nc);
             k_slot_agg2<<<grid_for(n), kBlock, 0, s>>>(SG, pc->app.p, state.p, a1.p, L.agg.p, W.dfl.p + 1);
         } else {
             // lanes per row: about two to four entries per lane
 #define BO_AGG(G)                                                                                             \
     do {                                                                                                      \
         const unsigned gb = grid_for((long long)n * G);                                                      \
-        k_agg1<G><<<gb, kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, state.p, id.p, a1.p);                     \
+        k_agg1<G><<<gb, kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, state.p, id.p, a1.p, rc.p, nc);           \
         k_agg2<G><<<gb, kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, state.p, a1.p, L.agg.p,            \
                                         W.dfl.p + 1);                                                        \
     } while (0)
@@ -2733,9 +2732,7 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         } else {
             k_p_count<<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.sf.p, L.agg.p, cnt.p, W.plong.p);
             k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, nullptr,
-                                                    nullptr, nullptr, cnt.p, W.plong.p);
-            k_p_vlong<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, nullptr,
-                                                     nullptr, nullptr, cnt.p, W.plong.p);
+                                                    nullptr, nullptr, cnt.p, nullptr, W.plong.p);
         }
         BO_TRY(L.prp.alloc(n + 1));
         int32_t pnnz = 0;
@@ -2744,24 +2741,16 @@ bo_status amg_setup(bo_cpr *pc, hipStream_t s, const std::function<bo_status()> 
         BO_TRY(L.pci.alloc(pnnz)); BO_TRY(L.pv.alloc(pnnz));
         if (slots) {
             k_slot_p_fill<<<grid_for(n), kBlock, 0, s>>>(SG, pc->app.p, L.agg.p, aF.p, omega, L.prp.p, L.pci.p,
-                                                         L.pv.p);
+                                                         L.pv.p, rcnt);
         } else {
             k_p_fill<<<grid_for(n), kBlock, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
-                                                    L.pci.p, L.pv.p);
+                                                    L.pci.p, L.pv.p, rcnt);
             k_p_long<<<pgrid, 64 * kPWaves, 0, s>>>(L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
-                                                    L.pci.p, L.pv.p, nullptr, W.plong.p);
-            k_p_vlong<<<pgrid, 64 * kPWaves, 0, s>>>(n, L.rp.p, L.ci.p, L.v.p, L.sf.p, L.agg.p, aF.p, omega, L.prp.p,
-                                                     L.pci.p, L.pv.p, nullptr, W.plong.p);
+                                                    L.pci.p, L.pv.p, nullptr, rcnt, W.plong.p);
         }
         BO_HIP(hipGetLastError());
         // R = P^T
-        // column counts and fill positions in one buffer (one clear); R has
-        // P's nnz, so its row pointers need no read back
-        DBuf<int32_t> &rc = W.rc;
-        BO_TRY(rc.alloc(2 * (size_t)nc));
-        int32_t *const rcnt = rc.p, *const fp = rc.p + nc;
-        BO_HIP(hipMemsetAsync(rc.p, 0, sizeof(int32_t) * 2 * nc, s));
-        k_col_counts<<<grid_for(pnnz), kBlock, 0, s>>>(pnnz, L.pci.p, rcnt);
+        // (R has P's nnz, so its row pointers need no read back)
         BO_TRY(L.rrp.alloc(nc + 1));
         BO_TRY(W.scan_sums.alloc(scan_sum_words(nc)));
         BO_TRY(scan_counts_async(rcnt, L.rrp.p, nc, W.scan_sums.p, s));

@@ -69,3 +69,22 @@ def test_scans_from_two_threads(B):
     for t in th:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (31, 33, 1), (32, 32, 1), (25, 41, 1), (64, 2, 127), (32, 32, 16),
+                                   (5, 29, 113)])
+def test_row_pointers_without_a_read(B, shape):
+    """The sums whose total is not read back (bo_jacobian_bsr_noalloc): one
+    workgroup up to 16384 counts, three launches above."""
+    import torch
+    nx, ny, nz = shape
+    case = cg.tiny_case(nx, ny, nz, seed=8, step=0.01, wells=[])
+    p = B.problem_from_case(case)
+    n, nnzb = B.bo_jacobian_bsr_size(p)
+    J = B.DeviceBsr(torch.full((n + 1,), -7, dtype=torch.int32, device="cuda"),
+                    torch.full((nnzb,), 123456, dtype=torch.int32, device="cuda"),
+                    torch.zeros(9 * nnzb, dtype=torch.float64, device="cuda"))
+    b = torch.zeros(3 * n, dtype=torch.float64, device="cuda")
+    x = torch.from_numpy(case.x_old).cuda()
+    B.bo_jacobian_bsr_noalloc(p, x, x, case.dt, J, b)
+    assert np.array_equal(to_host(J.rowptr), stencil_rowptr(nx, ny, nz))
