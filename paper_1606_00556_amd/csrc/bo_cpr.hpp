@@ -143,10 +143,10 @@ struct bo_cpr {
     bo::DBuf<float> ilu_w32;           // mixed form
     bo::DBuf<int32_t> ilu_slot;
     // natural-order block ILU(0) (BO_F_ILU_NATURAL).  Plain grid: packed
-    // factors of the forward and backward sweeps by tile and step, the
-    // handed-over tile edges with the tile ticket and the wait-expired mark
-    // behind them, the tiles in dependence order (nat_perm), the forward
-    // sweep's result by slot (nat_y).  Grid with well rows: the factors over the
+    // factors of the forward (with the forward sweep's result) and backward
+    // sweeps by tile and row, the handed-over tile edges with the tile ticket
+    // and the wait-expired mark behind them, the tiles in dependence order
+    // (nat_perm).  Grid with well rows: the factors over the
     // pattern of Arp / Aci (unit-lower blocks L_ik at the lower entries, the
     // updated blocks at the others), the pivots' inverses (9 per row), the
     // grid's cells by hyperplane with the hyperplanes' offsets (host and

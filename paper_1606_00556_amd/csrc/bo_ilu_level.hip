@@ -217,34 +217,51 @@ __global__ void k_nat_add_p(int npr, const double *__restrict__ dp, double *out)
 
 // ---- plain grid: tiles of 8x8 columns with handed-over edges ----------------------
 constexpr int kNt = 8;                    // columns of a tile in x and in y
-constexpr int kCPairs = 32, kFPairs = 14, kBPairs = 19;
+constexpr int kCPairs = 16, kFPairs = 14, kBPairs = 19;
 struct NatGeom {
-    int nx, ny, nz, ntx, nty, ns, M;
+    int nx, ny, nz, ntx, nty, ns;
     __host__ __device__ int tiles() const { return ntx * nty; }
-    __host__ __device__ size_t slots() const { return (size_t)ntx * nty * ns * 64; }
+    __host__ __device__ size_t cells() const { return (size_t)nx * ny * nz; }
 };
-// Packed blocks, as double2 pairs in (tile, step, pair, lane) order (1 KB per
-// wavefront load).  C, 32 pairs a slot: [A_ii | A_i,-z | A_i,-y | A_i,-x |
-// A_-z,i | A_-y,i | A_-x,i], the factorisation's input; it leaves the unit-lower
-// factors [L_-z | L_-y | L_-x] in the first 14 pairs.  Bp, 19 pairs:
-// [E^-1, pad | A_i,+x | A_i,+y | A_i,+z], blocks outside the grid zero.
-__device__ __forceinline__ size_t c_index(const NatGeom &G, int tile, int s, int lane) {
-    return ((size_t)tile * G.ns + s) * kCPairs * 64 + lane;
-}
-__device__ __forceinline__ size_t b_index(const NatGeom &G, int tile, int s, int lane) {
-    return ((size_t)tile * G.ns + s) * kBPairs * 64 + lane;
+// Packed blocks, as double2 pairs in (tile, row, pair, column) order, the columns
+// of a tile being those inside the grid (W of them, 64 but at the grid's edge).
+// Layer k of column (a, b) belongs to step s = k + a + b and stands in row
+// s mod nz: the steps of a column fall on nz different rows, so the lanes of a
+// step read one row (1 KB per wavefront load) and every cell has exactly one
+// slot: 816 B a cell with the sweeps' vector, on one layer as on a hundred.
+// (A row a step would hold nz + 14 rows of 64 columns: 12.6 KB a cell on one
+// layer.)
+// C, twice 16 pairs a slot: [A_ii | A_i,-z | A_i,-y | A_i,-x | A_-z,i | A_-y,i |
+// A_-x,i], the factorisation's input.  The first 16 pairs of all slots stand
+// together: the factorisation leaves the unit-lower factors [L_-z | L_-y | L_-x]
+// in 14 of them, and the forward sweep's result y goes into the other two (y0, y1
+// as a pair; y2 as one run of doubles), so that the sweeps read the part without
+// gaps.  Bp, 19 pairs: [E^-1, pad | A_i,+x | A_i,+y | A_i,+z], blocks outside the
+// grid zero.
+struct NatTile {
+    int i0, j0, wx, wy;  // its first column, its columns in x and y
+    size_t base;         // cells of the tiles before it
+    __device__ NatTile(const NatGeom &G, int I, int J)
+        : i0(I * kNt), j0(J * kNt), wx(min(kNt, G.nx - i0)), wy(min(kNt, G.ny - j0)),
+          base(((size_t)j0 * G.nx + (size_t)i0 * wy) * G.nz) {}
+};
+// where lanes without a cell at a step store (never read), behind Bp's slots
+constexpr int kSinks = 64;
+__device__ __forceinline__ double2 *nat_sink(const NatGeom &G, double2 *Bp, int lane) {
+    return Bp + G.cells() * kBPairs + (blockIdx.x % kSinks) * 64 + lane;
 }
 
 __global__ void __launch_bounds__(kBlock) k_nat_pack(NatGeom G, const double *__restrict__ A, double2 *__restrict__ C,
                                                      double2 *__restrict__ Bp) {
-    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= G.slots()) return;
-    const int t = (int)(q % 64);
-    const int s = (int)((q / 64) % G.ns), tile = (int)(q / 64 / G.ns);
-    const int a = t % kNt, b = t / kNt;
-    const int i = tile % G.ntx * kNt + a, j = tile / G.ntx * kNt + b, k = s - a - b;
-    if (i >= G.nx || j >= G.ny || k < 0 || k >= G.nz) return;  // idle slot, never read
-    const size_t N = (size_t)G.nx * G.ny * G.nz;
+    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x, N = G.cells();
+    if (q >= N) return;
+    // the tile, row and column of slot q
+    const size_t strip = (size_t)G.nx * kNt * G.nz;  // cells of a full row of tiles
+    const int J = (int)(q / strip), wy = min(kNt, G.ny - J * kNt);
+    const NatTile T(G, (int)(q % strip / ((size_t)kNt * wy * G.nz)), J);
+    const int W = T.wx * T.wy, row = (int)((q - T.base) / W), col = (int)((q - T.base) % W);
+    const int a = col % T.wx, b = col / T.wx;
+    const int i = T.i0 + a, j = T.j0 + b, k0 = (row - a - b) % G.nz, k = k0 < 0 ? k0 + G.nz : k0;
     const int nxy = G.nx * G.ny, g = i + G.nx * j + nxy * k;
     double v[64], u[38];
     auto blk = [&](bool have, int slot, int row, double *o) {
@@ -264,11 +281,14 @@ __global__ void __launch_bounds__(kBlock) k_nat_pack(NatGeom G, const double *__
     blk(j + 1 < G.ny, S_PY, g, u + 19);
     blk(k + 1 < G.nz, S_PZ, g, u + 28);
     u[37] = 0.0;
-    double2 *c = C + c_index(G, tile, s, t), *d = Bp + b_index(G, tile, s, t);
+    double2 *c = C + (T.base + (size_t)row * W) * kCPairs + col, *d = Bp + (T.base + (size_t)row * W) * kBPairs + col;
 #pragma unroll
-    for (int p = 0; p < kCPairs; p++) c[p * 64] = make_double2(v[2 * p], v[2 * p + 1]);
+    for (int p = 0; p < kCPairs; p++) {
+        c[p * W] = make_double2(v[2 * p], v[2 * p + 1]);
+        c[N * kCPairs + p * W] = make_double2(v[32 + 2 * p], v[33 + 2 * p]);
+    }
 #pragma unroll
-    for (int p = 5; p < kBPairs; p++) d[p * 64] = make_double2(u[2 * p], u[2 * p + 1]);
+    for (int p = 5; p < kBPairs; p++) d[p * W] = make_double2(u[2 * p], u[2 * p + 1]);
 }
 
 // order[q]: the tiles by ascending I + J, then I (each tile after the ones its
@@ -293,18 +313,19 @@ __global__ void k_nat_hand_init(size_t n, unsigned long long *__restrict__ H, un
 // mirrored lane coordinates: p = a, q = b, u = s forward, p = 7 - a, q = 7 - b,
 // u = ns - 1 - s backward, so that a tile always takes from the sides p = 0 and
 // q = 0 and gives from p = 7 and q = 7.  What a tile takes at step u stands in
-// row u of its own places: K values of each of the 8 edge cells of the x side,
-// then of the y side, then padding up to NW * 64 words, so that a wavefront
-// looks at the whole row with NW loads.  A place is written by one lane of the
-// neighbour and read by one lane.  It is empty while it holds kEmpty (a
+// row u mod nz of its own places (an edge column's nz steps fall on nz different
+// rows): K values of each of the 8 edge cells of the x side, then of the y side,
+// then padding up to NW * 64 words, so that a wavefront looks at the whole row
+// with NW loads.  A place is written by one lane of the neighbour and read by
+// one lane, once a sweep.  It is empty while it holds kEmpty (a
 // signalling NaN with a payload no arithmetic produces); the reader polls until
 // it holds something else.  The forward and the backward sweep have their own
 // places, and each empties the other's behind its own steps (the factorisation
 // has the backward sweep's ones emptied by a launch of its own).  Accesses are
 // relaxed 64-bit atomics at agent scope (the XCDs' L2s are not coherent with
 // each other otherwise); a value is its own flag, so no ordering between
-// accesses is needed.  Row M takes the writes of lanes that have nothing to
-// give or to empty.
+// accesses is needed.  Row nz takes the writes of lanes that have nothing to
+// give.
 // Tiles are taken from a ticket in dependence order, so a tile only ever
 // waits for tiles that workgroups already running hold.  Waiting is bounded:
 // a wavefront polls at most kSpin times in all, then goes on with what it has
@@ -331,13 +352,15 @@ template <int K, bool FWD>
 struct NatLane {
     static constexpr int NW = hand_words(K);
     static constexpr int kLds = 64 * K + NW * 64;  // doubles
-    int t, a, b, ab, tile;          // ab: first step (in u) of the lane's column, out of reach without one
+    int t, ab, W, c;                // ab: first step (in u) of the lane's column, out of reach without one;
+                                    // the tile's columns, the lane's number among them (0 without one)
+    size_t base;                    // the tile's first slot
     size_t g0;                      // the column's cell in layer 0
     int rx, ry;                     // LDS places of the -/+x and y neighbours' values
     int take[NW], give[NW], gsrc[NW];  // first steps of taking and giving a word (out of reach: never), its LDS source
     unsigned long long *row, *clr;  // this lane's word in row 0 of the own and of the other sweep's places
     unsigned long long *dst[NW];    // this lane's words in the taking tile's row 0
-    unsigned long long *ctl, *sink; // sink: this lane's word of the own row M
+    unsigned long long *ctl, *sink; // sink: this lane's word of the own row nz
     int spin;
     static constexpr int kNever = 1 << 30;
     __device__ NatLane(const NatGeom &G, const int32_t *__restrict__ order, unsigned long long *H,
@@ -346,15 +369,18 @@ struct NatLane {
         unsigned qt = 0;
         if (t == 0) qt = (unsigned)(atomicAdd(ctl, 1ull) % (unsigned long long)G.tiles());
         qt = __builtin_amdgcn_readfirstlane(qt);
-        tile = order[FWD ? qt : G.tiles() - 1 - qt];
-        a = t % kNt;
-        b = t / kNt;
+        const int tile = __builtin_amdgcn_readfirstlane(order[FWD ? qt : G.tiles() - 1 - qt]);
+        const int a = t % kNt, b = t / kNt;
         const int I = tile % G.ntx, J = tile / G.ntx;
+        const NatTile T(G, I, J);
+        W = T.wx * T.wy;
+        base = T.base;
         const int p = FWD ? a : kNt - 1 - a, q = FWD ? b : kNt - 1 - b;
         auto col = [&](int pp, int qq) {  // a column of the grid, by mirrored coordinates
             return I * kNt + (FWD ? pp : kNt - 1 - pp) < G.nx && J * kNt + (FWD ? qq : kNt - 1 - qq) < G.ny;
         };
         ab = col(p, q) ? p + q : kNever;
+        c = col(p, q) ? a + T.wx * b : 0;
         g0 = (size_t)(I * kNt + a) + (size_t)G.nx * (J * kNt + b);
         rx = p > 0 ? (FWD ? t - 1 : t + 1) * K : 64 * K + q * K;
         ry = q > 0 ? (FWD ? t - kNt : t + kNt) * K : 64 * K + (8 + p) * K;
@@ -362,10 +388,10 @@ struct NatLane {
         const bool has_gx = FWD ? I + 1 < G.ntx : I > 0, has_gy = FWD ? J + 1 < G.nty : J > 0;
         const int nx_tile = FWD ? tile + 1 : tile - 1, ny_tile = FWD ? tile + G.ntx : tile - G.ntx;
         const size_t pitch = NW * 64;
-        auto place = [&](unsigned long long *set, int tl) { return set + (size_t)tl * (G.M + 1) * pitch + t; };
+        auto place = [&](unsigned long long *set, int tl) { return set + (size_t)tl * (G.nz + 1) * pitch + t; };
         row = place(H, tile);
         clr = place(other, tile);
-        sink = row + (size_t)G.M * pitch;
+        sink = row + (size_t)G.nz * pitch;
 #pragma unroll
         for (int w = 0; w < NW; w++) {
             const int l = t + 64 * w, e = l / (8 * K), o = l / K % 8, z = l % K;  // side, cell, value
@@ -385,15 +411,18 @@ struct NatLane {
         const int k = FWD ? u - ab : G.nz - 1 - (u - ab);
         return active(G, u) ? g0 + (size_t)k * ((size_t)G.nx * G.ny) : 0;
     }
-    // first look at the row of step u
-    __device__ __forceinline__ void look(const NatGeom &G, int u, unsigned long long *h) const {
-        const unsigned long long *r = row + (size_t)min(u, G.M) * (NW * 64);
+    // the lane's column in the slots of step u (column 0 for an idle lane)
+    __device__ __forceinline__ int slot(const NatGeom &G, int u) const { return active(G, u) ? c : 0; }
+    // first look at a row of places
+    __device__ __forceinline__ void look(int r, unsigned long long *h) const {
+        const unsigned long long *p = row + (size_t)r * (NW * 64);
 #pragma unroll
-        for (int w = 0; w < NW; w++) h[w] = hand_get(r + 64 * w);
+        for (int w = 0; w < NW; w++) h[w] = hand_get(p + 64 * w);
     }
-    // wait for the row of step u, put it behind the lanes' values in LDS (0
-    // where nothing is taken) and empty the other sweep's row u
-    __device__ __forceinline__ void taken(const NatGeom &G, int u, unsigned long long *h, double *lds) {
+    // wait for the values of step u in row r (u mod nz), put them behind the
+    // lanes' values in LDS (0 where nothing is taken) and empty the other
+    // sweep's row
+    __device__ __forceinline__ void taken(const NatGeom &G, int u, int r, unsigned long long *h, double *lds) {
         bool need[NW], miss = false;
 #pragma unroll
         for (int w = 0; w < NW; w++) {
@@ -407,35 +436,43 @@ struct NatLane {
                     break;
                 }
                 spin--;
-                look(G, u, h);
+                look(r, h);
                 miss = false;
 #pragma unroll
                 for (int w = 0; w < NW; w++) miss = miss || (need[w] && h[w] == kEmpty);
             } while (__any(miss));
         }
-        const size_t o = (size_t)min(u, G.M) * (NW * 64);
+        const size_t o = (size_t)r * (NW * 64);
 #pragma unroll
         for (int w = 0; w < NW; w++) {
             lds[64 * K + t + 64 * w] = need[w] ? __longlong_as_double((long long)h[w]) : 0.0;
             if (K == 3) hand_put(clr + o + 64 * w, kEmpty);
         }
     }
-    // after the lanes' values of step u are in LDS: hand the edges over
-    __device__ __forceinline__ void given(const NatGeom &G, int u, const double *lds) const {
+    // after the lanes' values of step u are in LDS: hand the edges over, into
+    // row r = (u - 7) mod nz of the tiles that take them
+    __device__ __forceinline__ void given(const NatGeom &G, int u, int r, const double *lds) const {
 #pragma unroll
         for (int w = 0; w < NW; w++) {
             const bool g = (unsigned)(u - give[w]) < (unsigned)G.nz;
-            unsigned long long *d = g ? dst[w] + (size_t)(u - (kNt - 1)) * (NW * 64) : sink + 64 * w;
+            unsigned long long *d = g ? dst[w] + (size_t)r * (NW * 64) : sink + 64 * w;
             hand_put(d, hand_bits(lds[gsrc[w]]));
         }
     }
+};
+// A row number (a step mod nz) that moves with the steps
+struct NatRow {
+    int r;
+    __device__ NatRow(const NatGeom &G, int step) : r(step % G.nz) { r += r < 0 ? G.nz : 0; }
+    __device__ __forceinline__ void up(const NatGeom &G) { r = r + 1 == G.nz ? 0 : r + 1; }
+    __device__ __forceinline__ void down(const NatGeom &G) { r = r == 0 ? G.nz - 1 : r - 1; }
 };
 #define WAVE_FENCE() __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront")
 
 // Factorisation: E_i = A_ii - sum over -z, -y, -x of (A_ik E_k^-1) A_ki, one
 // wavefront per tile.  Bound by the arithmetic of a step (six 3x3 products and
-// an inverse, FP64 without contraction) times the hyperplanes; a launch per
-// hyperplane took 38 us each (8.8 ms on 99x101x31).
+// an inverse, FP64 without contraction) times the hyperplanes: 99x101x31 0.77 ms
+// (8.8 ms with a launch per hyperplane).
 __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int32_t *__restrict__ order,
                                                            double2 *__restrict__ C, double2 *__restrict__ Bp,
                                                            unsigned long long *__restrict__ H,
@@ -444,7 +481,10 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int3
     typedef NatLane<9, true> Lane;
     __shared__ double lds[Lane::kLds];
     Lane L(G, order, H, H, ctl);
-    const int t = L.t;
+    const int t = L.t, W = L.W;
+    const size_t second = G.cells() * kCPairs;
+    double2 *const Ct = C + L.base * kCPairs, *const Bt = Bp + L.base * kBPairs, *const sink = nat_sink(G, Bp, t);
+    NatRow now(G, 0), ahead(G, 0), gives(G, 1 - kNt);
 #pragma unroll
     for (int z = 0; z < 9; z++) lds[9 * t + z] = 0.0;
     struct Slot {
@@ -455,18 +495,20 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int3
 #pragma unroll
     for (int z = 0; z < 9; z++) Ep[z] = 0.0;
     auto fetch = [&](int s, Slot &S) {
-        const int sc = min(s, G.ns - 1);
-        const double2 *c = C + c_index(G, L.tile, sc, L.active(G, sc) ? t : 0);
+        const double2 *c = Ct + (size_t)ahead.r * W * kCPairs + L.slot(G, s);
 #pragma unroll
         for (int p = 0; p < kCPairs; p++) {
-            const double2 d = c[p * 64];
+            const double2 d = c[p * W], e = c[second + p * W];
             S.v[2 * p] = d.x;
             S.v[2 * p + 1] = d.y;
+            S.v[32 + 2 * p] = e.x;
+            S.v[33 + 2 * p] = e.y;
         }
-        L.look(G, sc, S.h);
+        L.look(ahead.r, S.h);
+        ahead.up(G);
     };
     auto step = [&](int s, Slot &S) {
-        L.taken(G, s, S.h, lds);
+        L.taken(G, s, now.r, S.h, lds);
         WAVE_FENCE();
         double Ex[9], Ey[9];
 #pragma unroll
@@ -506,13 +548,16 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int3
             lds[9 * t + z] = Ep[z];
         }
         WAVE_FENCE();
-        L.given(G, s, lds);
-        // (an idle lane's results go to its idle slot)
-        double2 *c = C + c_index(G, L.tile, s, t), *d = Bp + b_index(G, L.tile, s, t);
+        L.given(G, s, gives.r, lds);
+        const int w = act ? W : 0;  // an idle lane's results go to its sink
+        double2 *c = act ? Ct + (size_t)now.r * W * kCPairs + L.c : sink;
+        double2 *d = act ? Bt + (size_t)now.r * W * kBPairs + L.c : sink;
 #pragma unroll
-        for (int p = 0; p < kFPairs; p++) c[p * 64] = make_double2(lw[2 * p], lw[2 * p + 1]);
+        for (int p = 0; p < kFPairs; p++) c[p * w] = make_double2(lw[2 * p], lw[2 * p + 1]);
 #pragma unroll
-        for (int p = 0; p < 5; p++) d[p * 64] = make_double2(Ei[2 * p], Ei[2 * p + 1]);
+        for (int p = 0; p < 5; p++) d[p * w] = make_double2(Ei[2 * p], Ei[2 * p + 1]);
+        now.up(G);
+        gives.up(G);
         fetch(s + 2, S);
     };
     fetch(0, R0);
@@ -530,29 +575,31 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int3
 // that came too early (vector memory operations return in order and are
 // counted statically: a store some paths skip, or the poll as a loop around
 // the first look, makes each step wait for the loads of the steps ahead too).
-// Sums in the row's column order.  Bound by the latency of a step (0.62 us)
-// times the nx+ny+nz-2 hyperplanes and the handovers between tiles (3.3 us
-// each): 104x104x31, both sweeps, 464 us (4.3 ms with a launch per hyperplane).
-// A look AH steps ahead needs the neighbour that much further ahead, so a short
-// ring wins while every tile has a SIMD of its own (464 / 499 / 565 us with 2 /
-// 3 / 4 steps); with more tiles the HBM bandwidth does (400x400x100: 4.43 / 4.09
-// / 4.35 ms).
+// Sums in the row's column order.  Bound by the latency of a step times the
+// nx+ny+nz-2 hyperplanes and by the handovers between tiles: 104x104x31, both
+// sweeps, 378 us (3.4 ms with a launch per hyperplane, 456 us with a row of slots
+// per step).  A look AH steps ahead needs the neighbour that much further ahead,
+// so a short ring wins while every tile has a SIMD of its own (378 / 410 / 490 us
+// with 2 / 3 / 4 steps); with more tiles than SIMDs the forward sweep takes 4
+// (forward / backward steps 2/2, 3/3, 4/3, 4/2: 4.23, 4.54, 4.21, 4.17 ms on
+// 400x400x100, 3/3, 4/3, 4/2: 2.94, 2.71, 2.76 ms on 300x300x100; runs differ by 4 %).
 
-// forward: y_i = r_i - sum_{-z,-y,-x} L y, into yq[3][slot]
+// forward: y_i = r_i - sum_{-z,-y,-x} L y, into Y, the pairs of C behind the factors
 template <int AH>
 __global__ void __launch_bounds__(64, 1) k_nat_tile_forward(NatGeom G, const int32_t *__restrict__ order,
                                                             const double2 *__restrict__ C,
-                                                            const double *__restrict__ r, double *__restrict__ yq,
+                                                            double2 *__restrict__ Y, double2 *__restrict__ Bp,
+                                                            const double *__restrict__ r,
                                                             unsigned long long *__restrict__ H,
                                                             unsigned long long *__restrict__ other,
                                                             unsigned long long *__restrict__ ctl) {
     typedef NatLane<3, true> Lane;
     __shared__ double lds[Lane::kLds];
     Lane L(G, order, H, other, ctl);
-    const int t = L.t;
-    const size_t S = G.slots();
-    const double2 *Ct = C + c_index(G, L.tile, 0, 0);
-    double *yt = yq + (size_t)L.tile * G.ns * 64 + t;
+    const int t = L.t, W = L.W;
+    const double2 *Ct = C + L.base * kCPairs;
+    double2 *const Yt = Y + L.base * kCPairs + (size_t)kFPairs * W, *const sink = nat_sink(G, Bp, t);
+    NatRow now(G, 0), ahead(G, 0), gives(G, 1 - kNt);
 #pragma unroll
     for (int c = 0; c < 3; c++) lds[3 * t + c] = 0.0;
     struct Slot {
@@ -560,21 +607,21 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_forward(NatGeom G, const int
         unsigned long long h[1];
     } ring[AH];
     auto fetch = [&](int s, Slot &Q) {
-        const int sc = min(s, G.ns - 1);
-        const double2 *c = Ct + (size_t)sc * kCPairs * 64 + (L.active(G, sc) ? t : 0);
+        const double2 *c = Ct + (size_t)ahead.r * W * kCPairs + L.slot(G, s);
 #pragma unroll
         for (int p = 0; p < kFPairs; p++) {
-            const double2 d = c[p * 64];
+            const double2 d = c[p * W];
             Q.f[2 * p] = d.x;
             Q.f[2 * p + 1] = d.y;
         }
-        const double *rg = r + 3 * L.cell(G, sc);
+        const double *rg = r + 3 * L.cell(G, s);
         Q.r[0] = rg[0]; Q.r[1] = rg[1]; Q.r[2] = rg[2];
-        L.look(G, sc, Q.h);
+        L.look(ahead.r, Q.h);
+        ahead.up(G);
     };
     double yp[3] = {0.0, 0.0, 0.0};
     auto step = [&](int s, Slot &Q) {
-        L.taken(G, s, Q.h, lds);
+        L.taken(G, s, now.r, Q.h, lds);
         WAVE_FENCE();
         double yx[3], yy[3], u[3], v[3] = {Q.r[0], Q.r[1], Q.r[2]};
 #pragma unroll
@@ -589,15 +636,18 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_forward(NatGeom G, const int
         mv3d(Q.f + 18, yx, u);
         for (int c = 0; c < 3; c++) v[c] = v[c] - u[c];
         const bool act = L.active(G, s);
-        double *y = yt + (size_t)s * 64;  // (an idle lane's value goes to its idle slot)
 #pragma unroll
         for (int c = 0; c < 3; c++) {
             yp[c] = act ? v[c] : 0.0;
             lds[3 * t + c] = yp[c];
-            y[c * S] = yp[c];
         }
+        double2 *y = Yt + (size_t)now.r * W * kCPairs;
+        *(act ? y + L.c : sink) = make_double2(yp[0], yp[1]);
+        *(act ? (double *)(y + W) + L.c : (double *)sink) = yp[2];
         WAVE_FENCE();
-        L.given(G, s, lds);
+        L.given(G, s, gives.r, lds);
+        now.up(G);
+        gives.up(G);
         fetch(s + AH, Q);
     };
 #pragma unroll
@@ -614,7 +664,7 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_forward(NatGeom G, const int
 // natural order (dp may be NULL)
 template <int AH>
 __global__ void __launch_bounds__(64, 1) k_nat_tile_backward(NatGeom G, const int32_t *__restrict__ order,
-                                                             const double2 *__restrict__ Bp, double *__restrict__ yq,
+                                                             const double2 *__restrict__ C, double2 *__restrict__ Bp,
                                                              const double *__restrict__ dp, double *__restrict__ out,
                                                              unsigned long long *__restrict__ H,
                                                              unsigned long long *__restrict__ other,
@@ -622,35 +672,37 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_backward(NatGeom G, const in
     typedef NatLane<3, false> Lane;
     __shared__ double lds[Lane::kLds];
     Lane L(G, order, H, other, ctl);
-    const int t = L.t, e = G.ns - 1;
-    const size_t S = G.slots();
-    const double2 *Bt = Bp + b_index(G, L.tile, 0, 0);
-    double *yt = yq + (size_t)L.tile * G.ns * 64;
+    const int t = L.t, W = L.W, e = G.ns - 1;
+    const double2 *Bt = Bp + L.base * kBPairs, *Yt = C + L.base * kCPairs + (size_t)kFPairs * W;
+    double2 *const sink = nat_sink(G, Bp, t);
+    // rows of the places (by steps u) and of the slots (by steps s = ns - 1 - u)
+    NatRow now(G, 0), ahead(G, 0), gives(G, 1 - kNt), from(G, e);
 #pragma unroll
     for (int c = 0; c < 3; c++) lds[3 * t + c] = 0.0;
     struct Slot {
         double f[38], y[3], d;
         unsigned long long h[1];
     } ring[AH];
-    const double *dpl = dp ? dp : yq;  // without dp a load that is not used
+    const double *dpl = dp ? dp : (const double *)C;  // without dp a load that is not used
     auto fetch = [&](int u, Slot &Q) {
-        const int uc = min(u, e), s = e - uc;
-        const int tl = L.active(G, uc) ? t : 0;
-        const double2 *c = Bt + (size_t)s * kBPairs * 64 + tl;
+        const int cl = L.slot(G, u);
+        const double2 *c = Bt + (size_t)from.r * W * kBPairs + cl;
 #pragma unroll
         for (int p = 0; p < kBPairs; p++) {
-            const double2 d = c[p * 64];
+            const double2 d = c[p * W];
             Q.f[2 * p] = d.x;
             Q.f[2 * p + 1] = d.y;
         }
-        const double *y = yt + (size_t)s * 64 + tl;
-        Q.y[0] = y[0]; Q.y[1] = y[S]; Q.y[2] = y[2 * S];
-        Q.d = dpl[dp ? L.cell(G, uc) : 0];
-        L.look(G, uc, Q.h);
+        const double2 *y = Yt + (size_t)from.r * W * kCPairs, y01 = y[cl];
+        Q.y[0] = y01.x; Q.y[1] = y01.y; Q.y[2] = ((const double *)(y + W))[cl];
+        Q.d = dpl[dp ? L.cell(G, u) : 0];
+        L.look(ahead.r, Q.h);
+        ahead.up(G);
+        from.down(G);
     };
     double xp[3] = {0.0, 0.0, 0.0};
     auto step = [&](int u, Slot &Q) {
-        L.taken(G, u, Q.h, lds);
+        L.taken(G, u, now.r, Q.h, lds);
         WAVE_FENCE();
         double xx[3], xy[3], w[3], v[3] = {Q.y[0], Q.y[1], Q.y[2]};
 #pragma unroll
@@ -672,14 +724,13 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_backward(NatGeom G, const in
             lds[3 * t + c] = xp[c];
         }
         WAVE_FENCE();
-        L.given(G, u, lds);
-        // an idle lane writes to its idle slot of yq, which nothing reads
-        const size_t gc = 3 * L.cell(G, u);
-        double *o0 = act ? out + gc : yt + (size_t)(e - u) * 64 + t;
-        double *o1 = act ? out + gc + 1 : o0 + S, *o2 = act ? out + gc + 2 : o0 + 2 * S;
-        *o0 = dp ? Q.d + xp[0] : xp[0];
-        *o1 = xp[1];
-        *o2 = xp[2];
+        L.given(G, u, gives.r, lds);
+        now.up(G);
+        gives.up(G);
+        double *o = act ? out + 3 * L.cell(G, u) : (double *)sink;
+        o[0] = dp ? Q.d + xp[0] : xp[0];
+        o[1] = xp[1];
+        o[act ? 2 : 0] = xp[2];
         fetch(u + AH, Q);
     };
 #pragma unroll
@@ -700,25 +751,23 @@ NatGeom nat_geom(const Grid &g) {
     G.ntx = (g.nx + kNt - 1) / kNt;
     G.nty = (g.ny + kNt - 1) / kNt;
     G.ns = g.nz + 2 * (kNt - 1);
-    G.M = g.nz + kNt - 1;
     return G;
 }
 
 // the handover memory: the factorisation's places (which the sweeps' two sets
 // share), then the ticket and the wait-expired mark
-size_t nat_hand_words(const NatGeom &G) { return (size_t)G.tiles() * (G.M + 1) * 64 * hand_words(9); }
+size_t nat_hand_words(const NatGeom &G) { return (size_t)G.tiles() * (G.nz + 1) * 64 * hand_words(9); }
 
 // factorisation of a plain grid from the operator's slot arrays
 bo_status nat_tile_launch(bo_cpr *pc, hipStream_t s) {
     const NatGeom G = nat_geom(pc->g);
-    const size_t S = G.slots(), nh = nat_hand_words(G);
-    BO_TRY(pc->nat_c.alloc(S * kCPairs));
-    BO_TRY(pc->nat_b.alloc(S * kBPairs));
-    BO_TRY(pc->nat_y.alloc(3 * S));
+    const size_t N = G.cells(), nh = nat_hand_words(G);
+    BO_TRY(pc->nat_c.alloc(2 * N * kCPairs));
+    BO_TRY(pc->nat_b.alloc(N * kBPairs + kSinks * 64));
     BO_TRY(pc->nat_hand.alloc(nh + 2));
     BO_TRY(pc->nat_perm.alloc(G.tiles()));
     unsigned long long *H = pc->nat_hand.p, *ctl = H + nh;
-    k_nat_pack<<<grid_for((long long)S), kBlock, 0, s>>>(G, pc->A.p, pc->nat_c.p, pc->nat_b.p);
+    k_nat_pack<<<grid_for((long long)N), kBlock, 0, s>>>(G, pc->A.p, pc->nat_c.p, pc->nat_b.p);
     k_nat_order<<<grid_for(G.tiles()), kBlock, 0, s>>>(G.ntx, G.nty, pc->nat_perm.p);
     k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty);
     k_nat_tile_factor<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, H, ctl, pc->fflag.p);
@@ -732,10 +781,10 @@ bo_status nat_tile_apply(bo_cpr *pc, const double *r, const double *dp, double *
     unsigned long long *H = pc->nat_hand.p, *ctl = H + nat_hand_words(G);
     unsigned long long *Hb = H + nat_hand_words(G) / hand_words(9);  // one word per lane and row for each sweep
     const bool few = G.tiles() <= kNatFewTiles;
-    (few ? k_nat_tile_forward<2> : k_nat_tile_forward<3>)<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, r,
-                                                                                   pc->nat_y.p, H, Hb, ctl);
-    (few ? k_nat_tile_backward<2> : k_nat_tile_backward<3>)<<<G.tiles(), 64, 0, s>>>(
-        G, pc->nat_perm.p, pc->nat_b.p, pc->nat_y.p, dp, out, Hb, H, ctl);
+    (few ? k_nat_tile_forward<2> : k_nat_tile_forward<4>)<<<G.tiles(), 64, 0, s>>>(
+        G, pc->nat_perm.p, pc->nat_c.p, pc->nat_c.p, pc->nat_b.p, r, H, Hb, ctl);
+    k_nat_tile_backward<2><<<G.tiles(), 64, 0, s>>>(
+        G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, dp, out, Hb, H, ctl);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }

@@ -232,3 +232,51 @@ def test_natural_tiles_hand_over_every_edge(B, O, shape):
     fresh = B.bo_cpr_setup(mats[1][4], (nx, ny, nz), opts)
     assert np.array_equal(run_stage(B, gpc, B.bo_cpr_fstage, v, 3 * case.n),
                           run_stage(B, fresh, B.bo_cpr_fstage, v, 3 * case.n))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (70, 1, 1), (1, 37, 2), (65, 66, 1), (9, 1, 40), (24, 16, 2)])
+def test_natural_thin_grids(B, O, shape):
+    """Grids of one layer, one column or one cell: fewer rows than the steps in
+    flight, tiles of one column and of one row of columns."""
+    nx, ny, nz = shape
+    case = cg.tiny_case(nx, ny, nz, seed=43, step=0.01, wells=[cg.Well(0, 0, 0, nz - 1, "inj", "bhp", 3500.0)])
+    P = O.Problem(case)
+    rp, ci, val, R = O.jacobian(P)
+    opc = O.Cpr(P, rp, ci, val, ftype=O.F_ILU_NATURAL, use_amg=0)
+    gpc = B.bo_cpr_setup(device_bsr(B, rp, ci, val), shape,
+                         B.bo_cpr_default_opts(ftype=B.BO_F_ILU_NATURAL, use_amg=0))
+    v = np.random.default_rng(9).standard_normal(3 * case.n)
+    for _ in range(2):
+        got = run_stage(B, gpc, B.bo_cpr_fstage, v, 3 * case.n)
+        assert rel_err_parts(got, opc.fstage(v)) <= 1e-10
+
+
+@pytest.mark.parametrize("shape", [(256, 256, 1), (2048, 8, 2), (64, 64, 16)])
+def test_natural_storage_per_cell(B, O, shape):
+    """The factors take one slot a cell (51 pairs of doubles), whatever the
+    number of layers, and the edge places a row a layer: measured through a
+    caller's allocator against the block-Jacobi handle (9 doubles a cell)."""
+    import torch
+    nx, ny, nz = shape
+    case = cg.tiny_case(nx, ny, nz, seed=44, step=0.01, wells=[cg.Well(0, 0, 0, nz - 1, "inj", "bhp", 3500.0)])
+    rp, ci, val, R = O.jacobian(O.Problem(case))
+    A = device_bsr(B, rp, ci, val)
+
+    def bytes_of(ftype):
+        live = {}
+
+        def alloc(nbytes, stream):
+            t = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
+            live[t.data_ptr()] = t
+            return t.data_ptr()
+
+        pc = B.bo_cpr_setup(A, shape, B.bo_cpr_default_opts(ftype=ftype, use_amg=0),
+                            allocator=(alloc, lambda ptr, stream: live.pop(ptr)))
+        total = sum(t.numel() for t in live.values())
+        pc.close()
+        return total
+
+    tiles = -(-nx // 8) * -(-ny // 8)
+    places = tiles * (nz + 1) * 3 * 64 * 8
+    extra = bytes_of(B.BO_F_ILU_NATURAL) - bytes_of(B.BO_F_BJ) + 72 * case.n
+    assert extra <= 51 * 16 * case.n + places + (1 << 17), extra / case.n
