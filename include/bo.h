@@ -49,7 +49,8 @@ typedef enum {
                                      network attached, and the judge kept none of its
                                      corrections (every pressure stage was the plain V-cycle) */
     BO_ERR_INVALID_ARG = -1,
-    BO_ERR_HIP = -2,              /* a HIP runtime call failed */
+    BO_ERR_HIP = -2,              /* a HIP runtime call failed, or a wait inside a kernel
+                                     expired (bo_cpr_wait_limit) */
     BO_ERR_ALLOC = -3,
     BO_ERR_NONFINITE = -4,        /* NaN/Inf in an input or during the iteration */
     BO_ERR_SINGULAR_BLOCK = -5,   /* a 3x3 pivot block is singular */
@@ -333,6 +334,15 @@ bo_status bo_cpr_setup(const bo_bsr *A, const bo_grid *grid, const bo_cpr_opts *
  * Synchronises `stream`. */
 bo_status bo_cpr_update(bo_cpr *pc, const bo_bsr *A, void *stream);
 void bo_cpr_destroy(bo_cpr *pc);
+
+/* [host] How often a wavefront of the natural-order ILU on the plain grid form may
+ * look for its neighbouring tiles' values in all, in one sweep or factorisation
+ * (default 2^21, seconds; 0: at most the first look at each step).  When it runs
+ * out the kernel ends with NaN: a setup or update then fails with BO_ERR_HIP, a
+ * solve that meets the NaN fails with BO_ERR_HIP, and bo_cpr_apply and
+ * bo_cpr_fstage, which do not wait for their work, return BO_OK with NaN in their
+ * results.  Applications stay NaN until a bo_cpr_update succeeds. */
+bo_status bo_cpr_wait_limit(bo_cpr *pc, int32_t polls);
 
 /* z = M^{-1} v (3N each): PF or FPF as configured. */
 bo_status bo_cpr_apply(bo_cpr *pc, const double *v, double *z, void *stream);

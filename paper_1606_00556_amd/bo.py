@@ -38,7 +38,7 @@ EXPORTS = [
     "bo_cpr_pressure_stencil", "bo_newton_default_opts", "bo_newton_create", "bo_newton_destroy",
     "bo_newton_solve", "bo_newton_run", "bo_bicgstab_solve", "bo_jacobian2_bsr_size", "bo_jacobian2_bsr",
     "bo_bsr2_spmv", "bo_cpr2_setup", "bo_cpr2_update", "bo_fgmres_solve2", "bo_bicgstab_solve2",
-    "bo_ras_default_opts", "bo_scalar_spmv", "bo_ras_setup", "bo_scalar_solve", "bo_ras_update",
+    "bo_ras_default_opts", "bo_scalar_spmv", "bo_ras_setup", "bo_scalar_solve", "bo_ras_update", "bo_cpr_wait_limit",
 ]
 
 
@@ -163,6 +163,7 @@ def lib():
                                C.POINTER(vp), vp]
     L.bo_cpr_update.argtypes = [vp, C.POINTER(BoBsr), vp]
     L.bo_cpr_destroy.argtypes = [vp]
+    L.bo_cpr_wait_limit.argtypes = [vp, C.c_int32]
     L.bo_cpr_destroy.restype = None
     for f in ("bo_cpr_apply", "bo_cpr_restrict", "bo_cpr_vcycle", "bo_cpr_fstage"):
         getattr(L, f).argtypes = [vp, vp, vp, vp]
@@ -413,6 +414,11 @@ def bo_cpr_update(pc: Cpr, A: DeviceBsr, stream=None) -> Cpr:
 
 def bo_cpr_destroy(pc: Cpr):
     pc.close()
+
+
+def bo_cpr_wait_limit(pc: Cpr, polls: int):
+    """The bound on the natural-order ILU's waits for neighbouring tiles (see include/bo.h)."""
+    _check(lib().bo_cpr_wait_limit(pc.h, int(polls)))
 
 
 def bo_cpr_apply(pc: Cpr, v, z, stream=None):

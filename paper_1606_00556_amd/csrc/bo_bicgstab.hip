@@ -83,7 +83,7 @@ bo_status bicgstab_core(bo_cpr *pc, UserA A, const double *b, double *x, const b
     BO_TRY(true_residual(&rn));
     for (;;) {
         st.rel_residual = rn / bnorm;
-        if (!std::isfinite(rn)) { status = fail(BO_ERR_NONFINITE, "bo_bicgstab_solve: residual is not finite"); break; }
+        if (!std::isfinite(rn)) { status = solve_not_finite(pc, "bo_bicgstab_solve: residual is not finite", s); break; }
         if (rn <= tol) { st.converged = 1; status = BO_OK; break; }
         if (its >= opts->maxit) break;
         // (re)start the recurrences from the current residual
@@ -138,6 +138,11 @@ bo_status bicgstab_core(bo_cpr *pc, UserA A, const double *b, double *x, const b
         }
         BO_TRY(true_residual(&rn));
         if (breakdown) {
+            if ((status = nat_wait_status(pc, s)) != BO_OK) {  // NaN from the preconditioner, not a breakdown
+                st.rel_residual = rn / bnorm;
+                break;
+            }
+            status = BO_NOT_CONVERGED;
             if (rn <= tol) continue;
             if (restarts_left-- <= 0) {
                 st.rel_residual = rn / bnorm;

@@ -156,6 +156,7 @@ struct bo_cpr {
     bo::DBuf<double> nat_lu, nat_inv, nat_y;
     bo::DBuf<int32_t> nat_perm, nat_lptr_d;
     std::vector<int32_t> nat_lptr;
+    int nat_polls = 1 << 21;      // looks a wavefront of the plain grid's kernels may wait (bo_cpr_wait_limit)
     // work vectors
     bo::DBuf<double> rp_, dp_, t3a, t3b, t3c, wf;
     bo::DBuf<int32_t> flag;
@@ -194,6 +195,10 @@ bo_status cpr_apply(bo_cpr *pc, const double *v, double *z, hipStream_t s);
 // natural-order block ILU(0) by level scheduling (BO_F_ILU_NATURAL)
 bo_status nat_launch(bo_cpr *pc, hipStream_t s);
 bo_status nat_apply(bo_cpr *pc, const double *r, const double *dp, double *out, hipStream_t s);
+bo_status nat_wait_status(bo_cpr *pc, hipStream_t s);
+// the status of a solve that met a value that is not finite: an expired wait of
+// the preconditioner, or BO_ERR_NONFINITE with msg
+bo_status solve_not_finite(bo_cpr *pc, const char *msg, hipStream_t s);
 // The caller's matrix of a solve, for its true residual: a 3x3-block or a
 // 2x2-block BSR matrix, or the slot coefficients of a scalar system on the
 // handle's grid (at most one of the three), or none: the handle's own copy

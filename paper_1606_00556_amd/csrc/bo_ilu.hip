@@ -1027,6 +1027,7 @@ bo_status fstage_check(bo_cpr *pc, hipStream_t s) {
     int32_t bad = 0;
     HostRead rd{pc->fflag.p, sizeof bad, &bad};
     BO_TRY(host_reads(&rd, 1, s));
+    if (bad & 4) return fail(BO_ERR_HIP, "F stage: a wait for a neighbouring tile's values expired (natural-order ILU)");
     if (bad & 2)
         return fail(BO_ERR_UNSUPPORTED, "F stage: a cell row's lower blocks are not its -x, -y, -z neighbours");
     if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "F stage: singular 3x3 pivot block");

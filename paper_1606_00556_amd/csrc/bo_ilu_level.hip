@@ -302,10 +302,12 @@ __global__ void k_nat_order(int ntx, int nty, int32_t *__restrict__ order) {
     order[pos + I - max(d - (nty - 1), 0)] = tile;
 }
 
+// expired (NULL: not asked for): its bit 4 set if the mark of an expired wait was
 __global__ void k_nat_hand_init(size_t n, unsigned long long *__restrict__ H, unsigned long long *__restrict__ ctl,
-                                unsigned long long empty) {
+                                unsigned long long empty, int32_t *__restrict__ expired) {
     const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q < n) H[q] = empty;
+    if (q == 1 && expired && ctl[1]) atomicOr(expired, 4);
     if (q < 2) ctl[q] = 0;
 }
 
@@ -328,11 +330,11 @@ __global__ void k_nat_hand_init(size_t n, unsigned long long *__restrict__ H, un
 // give.
 // Tiles are taken from a ticket in dependence order, so a tile only ever
 // waits for tiles that workgroups already running hold.  Waiting is bounded:
-// a wavefront polls at most kSpin times in all, then goes on with what it has
+// a wavefront polls at most `polls` times in all, then goes on with what it has
 // (NaN) and marks ctl[1], which stops every later wait of this handle until
-// its next setup: the results are NaN, never a hang.
+// its next setup: the results are NaN, never a hang.  The setup and the solvers
+// read the mark (fstage_check, nat_wait_status) and report the expired wait.
 constexpr unsigned long long kEmpty = 0x7FF4A3C15E2D9B87ull;
-constexpr int kSpin = 1 << 21;
 __device__ __forceinline__ unsigned long long hand_get(const unsigned long long *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -364,7 +366,7 @@ struct NatLane {
     int spin;
     static constexpr int kNever = 1 << 30;
     __device__ NatLane(const NatGeom &G, const int32_t *__restrict__ order, unsigned long long *H,
-                       unsigned long long *other, unsigned long long *ctl_)
+                       unsigned long long *other, unsigned long long *ctl_, int polls)
         : t(threadIdx.x), ctl(ctl_) {
         unsigned qt = 0;
         if (t == 0) qt = (unsigned)(atomicAdd(ctl, 1ull) % (unsigned long long)G.tiles());
@@ -403,7 +405,7 @@ struct NatLane {
             gsrc[w] = (edge ? (FWD ? gp + kNt * gq : kNt - 1 - gp + kNt * (kNt - 1 - gq)) : t) * K + z;
             dst[w] = g ? place(H, y ? ny_tile : nx_tile) + 64 * w : sink + 64 * w;
         }
-        spin = hand_get(ctl + 1) ? 0 : kSpin;
+        spin = hand_get(ctl + 1) ? 0 : polls;
     }
     __device__ __forceinline__ bool active(const NatGeom &G, int u) const { return (unsigned)(u - ab) < (unsigned)G.nz; }
     // the cell of an active step (cell 0 otherwise)
@@ -476,11 +478,11 @@ struct NatRow {
 __global__ void __launch_bounds__(64, 1) k_nat_tile_factor(NatGeom G, const int32_t *__restrict__ order,
                                                            double2 *__restrict__ C, double2 *__restrict__ Bp,
                                                            unsigned long long *__restrict__ H,
-                                                           unsigned long long *__restrict__ ctl,
+                                                           unsigned long long *__restrict__ ctl, int polls,
                                                            int32_t *__restrict__ bad) {
     typedef NatLane<9, true> Lane;
     __shared__ double lds[Lane::kLds];
-    Lane L(G, order, H, H, ctl);
+    Lane L(G, order, H, H, ctl, polls);
     const int t = L.t, W = L.W;
     const size_t second = G.cells() * kCPairs;
     double2 *const Ct = C + L.base * kCPairs, *const Bt = Bp + L.base * kBPairs, *const sink = nat_sink(G, Bp, t);
@@ -592,10 +594,10 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_forward(NatGeom G, const int
                                                             const double *__restrict__ r,
                                                             unsigned long long *__restrict__ H,
                                                             unsigned long long *__restrict__ other,
-                                                            unsigned long long *__restrict__ ctl) {
+                                                            unsigned long long *__restrict__ ctl, int polls) {
     typedef NatLane<3, true> Lane;
     __shared__ double lds[Lane::kLds];
-    Lane L(G, order, H, other, ctl);
+    Lane L(G, order, H, other, ctl, polls);
     const int t = L.t, W = L.W;
     const double2 *Ct = C + L.base * kCPairs;
     double2 *const Yt = Y + L.base * kCPairs + (size_t)kFPairs * W, *const sink = nat_sink(G, Bp, t);
@@ -668,10 +670,10 @@ __global__ void __launch_bounds__(64, 1) k_nat_tile_backward(NatGeom G, const in
                                                              const double *__restrict__ dp, double *__restrict__ out,
                                                              unsigned long long *__restrict__ H,
                                                              unsigned long long *__restrict__ other,
-                                                             unsigned long long *__restrict__ ctl) {
+                                                             unsigned long long *__restrict__ ctl, int polls) {
     typedef NatLane<3, false> Lane;
     __shared__ double lds[Lane::kLds];
-    Lane L(G, order, H, other, ctl);
+    Lane L(G, order, H, other, ctl, polls);
     const int t = L.t, W = L.W, e = G.ns - 1;
     const double2 *Bt = Bp + L.base * kBPairs, *Yt = C + L.base * kCPairs + (size_t)kFPairs * W;
     double2 *const sink = nat_sink(G, Bp, t);
@@ -769,9 +771,10 @@ bo_status nat_tile_launch(bo_cpr *pc, hipStream_t s) {
     unsigned long long *H = pc->nat_hand.p, *ctl = H + nh;
     k_nat_pack<<<grid_for((long long)N), kBlock, 0, s>>>(G, pc->A.p, pc->nat_c.p, pc->nat_b.p);
     k_nat_order<<<grid_for(G.tiles()), kBlock, 0, s>>>(G.ntx, G.nty, pc->nat_perm.p);
-    k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty);
-    k_nat_tile_factor<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, H, ctl, pc->fflag.p);
-    k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty);
+    k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty, nullptr);
+    k_nat_tile_factor<<<G.tiles(), 64, 0, s>>>(G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, H, ctl, pc->nat_polls,
+                                               pc->fflag.p);
+    k_nat_hand_init<<<grid_for((long long)nh), kBlock, 0, s>>>(nh, H, ctl, kEmpty, pc->fflag.p);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
@@ -782,19 +785,20 @@ bo_status nat_tile_apply(bo_cpr *pc, const double *r, const double *dp, double *
     unsigned long long *Hb = H + nat_hand_words(G) / hand_words(9);  // one word per lane and row for each sweep
     const bool few = G.tiles() <= kNatFewTiles;
     (few ? k_nat_tile_forward<2> : k_nat_tile_forward<4>)<<<G.tiles(), 64, 0, s>>>(
-        G, pc->nat_perm.p, pc->nat_c.p, pc->nat_c.p, pc->nat_b.p, r, H, Hb, ctl);
+        G, pc->nat_perm.p, pc->nat_c.p, pc->nat_c.p, pc->nat_b.p, r, H, Hb, ctl, pc->nat_polls);
     k_nat_tile_backward<2><<<G.tiles(), 64, 0, s>>>(
-        G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, dp, out, Hb, H, ctl);
+        G, pc->nat_perm.p, pc->nat_c.p, pc->nat_b.p, dp, out, Hb, H, ctl, pc->nat_polls);
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
 
 }  // namespace
 
-// Factorisation on stream s over the handle's BSR copy (Arp, Aci, Aval); it
-// reads nothing back: the flag pc->fflag (bit 1: a missing or singular
-// pivot, bit 2: a cell row with lower entries off its grid neighbours) is
-// read by fstage_check.
+// Factorisation on stream s; it reads nothing back: the flag pc->fflag (bit 1: a
+// missing or singular pivot block; bit 2: a cell row with a lower block other
+// than its -x, -y, -z neighbours; bit 4: an expired wait of the plain grid's
+// kernels) is read by fstage_check.  Grid with well rows: over the handle's BSR
+// copy (Arp, Aci, Aval).
 bo_status nat_launch(bo_cpr *pc, hipStream_t s) {
     const Grid &g = pc->g;
     const int n = pc->n, N = (int)g.n();
@@ -831,6 +835,16 @@ bo_status nat_launch(bo_cpr *pc, hipStream_t s) {
     if (n > N) k_nat_factor_seq<<<1, 64, 0, s>>>(N, n, rp, ci, pc->nat_lu.p, pc->nat_inv.p, ff);
     BO_HIP(hipGetLastError());
     return BO_OK;
+}
+
+// BO_ERR_HIP if a wait of an application since the last setup has expired (one
+// read of the mark, ordered after the work on s); BO_OK for any other handle
+bo_status nat_wait_status(bo_cpr *pc, hipStream_t s) {
+    if (pc->bs != 3 || pc->o.ftype != BO_F_ILU_NATURAL || pc->general || !pc->nat_hand.p) return BO_OK;
+    uint64_t mark = 0;
+    const HostRead rd{pc->nat_hand.p + nat_hand_words(nat_geom(pc->g)) + 1, sizeof mark, &mark};
+    BO_TRY(host_reads(&rd, 1, s));
+    return mark ? fail(BO_ERR_HIP, "natural-order ILU: a wait for a neighbouring tile's values expired") : BO_OK;
 }
 
 // out = F(r) (+ (dp, 0, 0) on the pressure rows when dp != NULL); out may be r

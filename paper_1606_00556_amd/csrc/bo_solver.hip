@@ -454,6 +454,18 @@ extern "C" void bo_cpr_destroy(bo_cpr *pc) {
     delete pc;
 }
 
+extern "C" bo_status bo_cpr_wait_limit(bo_cpr *pc, int32_t polls) {
+    pc = cond_inner(pc);
+    if (!pc || polls < 0) return fail(BO_ERR_INVALID_ARG, "bo_cpr_wait_limit: NULL argument or a negative limit");
+    pc->nat_polls = polls;
+    if (pc->gexec) {  // the limit is an argument of the captured kernels
+        BO_HIP(hipDeviceSynchronize());
+        (void)hipGraphExecDestroy(pc->gexec);
+        pc->gexec = nullptr;
+    }
+    return BO_OK;
+}
+
 extern "C" bo_status bo_cpr_apply(bo_cpr *pc, const double *v, double *z, void *stream) {
     if (!pc || !v || !z) return fail(BO_ERR_INVALID_ARG, "bo_cpr_apply: NULL argument");
     if (pc->broken) return fail(BO_ERR_INVALID_ARG, "bo_cpr_apply: the last bo_cpr_update failed");
@@ -574,6 +586,11 @@ bo_status krylov_alloc(bo_cpr *pc, int m, bool flexible) {
 
 namespace bo {
 
+bo_status solve_not_finite(bo_cpr *pc, const char *msg, hipStream_t s) {
+    BO_TRY(nat_wait_status(pc, s));
+    return fail(BO_ERR_NONFINITE, msg);
+}
+
 // FGMRES(m) on pc's operator.  The residual at each restart and at exit (the
 // true residual) is b - A x with the caller's matrix A, or with the handle's
 // own copy when A names none (internal callers).  With opts->flexible 0 it is
@@ -652,7 +669,7 @@ bo_status fgmres_core(bo_cpr *pc, UserA A, const double *b, double *x, const bo_
         BO_TRY(fetch(1));
         double beta = std::sqrt(hh[0]);
         st.rel_residual = beta / bnorm;
-        if (!std::isfinite(beta)) { status = fail(BO_ERR_NONFINITE, "bo_fgmres_solve: residual is not finite"); break; }
+        if (!std::isfinite(beta)) { status = solve_not_finite(pc, "bo_fgmres_solve: residual is not finite", s); break; }
         if (beta <= tol) { st.converged = 1; status = BO_OK; break; }
         if (its >= opts->maxit) break;
         if (its > 0) st.restarts++;
@@ -735,7 +752,7 @@ bo_status fgmres_core(bo_cpr *pc, UserA A, const double *b, double *x, const bo_
                 const int nv = j + 1;
                 const double beta_u = hq[2 * m], r = hq[2 * m + 1], hn = std::sqrt(hq[2 * m + 2]);
                 if (!std::isfinite(beta_u) || !std::isfinite(r) || !std::isfinite(hn)) {
-                    status = fail(BO_ERR_NONFINITE, "bo_fgmres_solve: NaN in the iteration");
+                    status = solve_not_finite(pc, "bo_fgmres_solve: NaN in the iteration", s);
                     goto done;
                 }
                 if (!(beta_u > 0.0)) {
@@ -794,7 +811,10 @@ bo_status fgmres_core(bo_cpr *pc, UserA A, const double *b, double *x, const bo_
                 H[(size_t)i * m + j] = orth == 1 ? hq[i] + hq[m + 1 + i] : hq[i];
             H[(size_t)(j + 1) * m + j] = hn;
             bool breakdown = !(hn > 1e-300);
-            if (!std::isfinite(hn)) { status = fail(BO_ERR_NONFINITE, "bo_fgmres_solve: NaN in the iteration"); goto done; }
+            if (!std::isfinite(hn)) {
+                status = solve_not_finite(pc, "bo_fgmres_solve: NaN in the iteration", s);
+                goto done;
+            }
             for (int i = 0; i < j; i++) {
                 double a = H[(size_t)i * m + j], bb = H[(size_t)(i + 1) * m + j];
                 H[(size_t)i * m + j] = cs[i] * a + sn[i] * bb;

@@ -280,3 +280,40 @@ def test_natural_storage_per_cell(B, O, shape):
     places = tiles * (nz + 1) * 3 * 64 * 8
     extra = bytes_of(B.BO_F_ILU_NATURAL) - bytes_of(B.BO_F_BJ) + 72 * case.n
     assert extra <= 51 * 16 * case.n + places + (1 << 17), extra / case.n
+
+
+def test_natural_expired_wait_is_reported(B, O):
+    """With no looks allowed beyond the first the waits for neighbouring tiles run
+    out (every kernel still ends): applications give NaN, both solvers and a
+    rebuild say so, and a rebuild with the default limit is as good as new."""
+    import torch
+    shape = (104, 104, 3)
+    case = cg.tiny_case(*shape, seed=45, step=0.01, wells=[cg.Well(0, 0, 0, 2, "inj", "bhp", 3500.0)])
+    P = O.Problem(case)
+    rp, ci, val, R = O.jacobian(P)
+    A = device_bsr(B, rp, ci, val)
+    opts = B.bo_cpr_default_opts(ftype=B.BO_F_ILU_NATURAL, use_amg=0)
+    pc = B.bo_cpr_setup(A, shape, opts)
+    v = np.random.default_rng(10).standard_normal(3 * case.n)
+    good = run_stage(B, pc, B.bo_cpr_fstage, v, 3 * case.n)
+    assert np.isfinite(good).all()
+    with pytest.raises(B.BoError) as e:
+        B.bo_cpr_wait_limit(pc, -1)
+    assert e.value.status == B.BO_ERR_INVALID_ARG
+    B.bo_fgmres_solve(pc, A, to_dev(v), torch.zeros(3 * case.n, dtype=torch.float64, device="cuda"),
+                      B.bo_fgmres_default_opts(graph=1, maxit=2))  # (a captured graph holds the old limit)
+    B.bo_cpr_wait_limit(pc, 0)
+    solves = [lambda x: B.bo_fgmres_solve(pc, A, to_dev(v), x, B.bo_fgmres_default_opts(graph=1)),
+              lambda x: B.bo_fgmres_solve(pc, A, to_dev(v), x, B.bo_fgmres_default_opts(orth=1)),
+              lambda x: B.bo_bicgstab_solve(pc, A, to_dev(v), x)]
+    for solve in solves:
+        with pytest.raises(B.BoError) as e:
+            solve(torch.zeros(3 * case.n, dtype=torch.float64, device="cuda"))
+        assert e.value.status == B.BO_ERR_HIP and "wait" in str(e.value)
+    assert np.isnan(run_stage(B, pc, B.bo_cpr_fstage, v, 3 * case.n)).any()
+    with pytest.raises(B.BoError) as e:
+        B.bo_cpr_update(pc, A)
+    assert e.value.status == B.BO_ERR_HIP and "wait" in str(e.value)
+    B.bo_cpr_wait_limit(pc, 1 << 21)
+    B.bo_cpr_update(pc, A)
+    assert np.array_equal(run_stage(B, pc, B.bo_cpr_fstage, v, 3 * case.n), good)
