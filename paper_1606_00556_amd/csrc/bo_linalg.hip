@@ -425,7 +425,7 @@ bo_status scan_counts(const int32_t *counts, int32_t *out, int n, int32_t *total
 typedef double dvec2 __attribute__((ext_vector_type(2)));
 constexpr int kBsrRows = 64, kBsrChunk = 7 * kBsrRows;
 template <int BS, bool V16>
-__global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int n, const int32_t *__restrict__ rp,
+__global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int first, int n, const int32_t *__restrict__ rp,
                                                            const int32_t *__restrict__ ci,
                                                            const double *__restrict__ v, double alpha,
                                                            const double *__restrict__ x, double beta,
@@ -433,21 +433,23 @@ __global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int n, const int32_t 
     constexpr int B2 = BS * BS, NT = kBsrRows * BS, KB = 7;
     constexpr int NLD = (kBsrChunk * B2 / 2 + 1 + NT - 1) / NT;  // pairs per thread
     __shared__ __align__(16) double sv[kBsrChunk * B2 + 2];
+    // (rows and blocks are counted from r0 and c0: n and the block count may be 2^31 - 1)
     const int t = threadIdx.x, r = t % BS;
-    const int r0 = blockIdx.x * kBsrRows, i = r0 + t / BS;
-    const bool row = i < n;
-    const int e0 = rp[min(i, n)], e1 = row ? rp[i + 1] : e0;
-    const int c_end = rp[min(r0 + kBsrRows, n)];
+    const int r0 = first + blockIdx.x * kBsrRows, r1 = n - r0 > kBsrRows ? r0 + kBsrRows : n;
+    const bool row = t / BS < r1 - r0;
+    const int i = row ? r0 + t / BS : r1;
+    const int e0 = rp[i], e1 = row ? rp[i + 1] : e0;
+    const int c_end = rp[r1];
     const double yi = row && beta != 0.0 ? beta * y[(size_t)i * BS + r] : 0.0;
     double s = 0.0;
     for (int c0 = rp[r0], c1; c0 < c_end; c0 = c1) {
         c1 = c_end - c0 > kBsrChunk ? c0 + kBsrChunk : c_end;
         // this row's blocks in the chunk: the first KB columns and x entries
-        const int b0 = max(e0, c0), b1 = min(e1, c1);
+        const int b0 = min(max(e0, c0), c1) - c0, b1 = min(e1, c1) - c0;
         int c[KB];
         double xj[KB][BS];
 #pragma unroll
-        for (int k = 0; k < KB; k++) c[k] = ci[min(b0 + k, c1 - 1)];
+        for (int k = 0; k < KB; k++) c[k] = ci[c0 + min(b0 + k, c1 - c0 - 1)];
         // the chunk's values, from an even position on
         const size_t d0 = (size_t)c0 * B2 & ~(size_t)1, d1 = (size_t)c1 * B2;
         const int np = (int)((d1 - d0 + 1) / 2), skip = (int)((size_t)c0 * B2 - d0);
@@ -471,12 +473,12 @@ __global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int n, const int32_t 
 #pragma unroll
         for (int k = 0; k < KB; k++)
             if (b0 + k < b1) {
-                const double *a = sv + skip + (b0 + k - c0) * B2 + BS * r;
+                const double *a = sv + skip + (b0 + k) * B2 + BS * r;
 #pragma unroll
                 for (int z = 0; z < BS; z++) s = s + a[z] * xj[k][z];
             }
         for (int e = b0 + KB; e < b1; e++) {  // rows of more than KB blocks
-            const double *a = sv + skip + (e - c0) * B2 + BS * r, *xe = x + (size_t)ci[e] * BS;
+            const double *a = sv + skip + e * B2 + BS * r, *xe = x + (size_t)ci[c0 + e] * BS;
 #pragma unroll
             for (int z = 0; z < BS; z++) s = s + a[z] * xe[z];
         }
@@ -488,10 +490,17 @@ __global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int n, const int32_t 
 template <int BS>
 bo_status bsr_spmv_launch(int n, const int32_t *rp, const int32_t *ci, const double *v, double alpha, const double *x,
                           double beta, double *y, hipStream_t s) {
-    const unsigned nb = grid_for(n, kBsrRows);
-    if ((uintptr_t)v % 16 == 0) k_bsr_spmv<BS, true><<<nb, kBsrRows * BS, 0, s>>>(n, rp, ci, v, alpha, x, beta, y);
-    else k_bsr_spmv<BS, false><<<nb, kBsrRows * BS, 0, s>>>(n, rp, ci, v, alpha, x, beta, y);
-    BO_HIP(hipGetLastError());
+    // a launch holds fewer than 2^32 threads
+    constexpr long long kRows = (long long)kBsrRows << 24;
+    for (long long r = 0; r < n; r += kRows) {
+        const int end = (int)std::min<long long>(n, r + kRows);
+        const unsigned nb = grid_for(end - r, kBsrRows);
+        if ((uintptr_t)v % 16 == 0)
+            k_bsr_spmv<BS, true><<<nb, kBsrRows * BS, 0, s>>>((int)r, end, rp, ci, v, alpha, x, beta, y);
+        else
+            k_bsr_spmv<BS, false><<<nb, kBsrRows * BS, 0, s>>>((int)r, end, rp, ci, v, alpha, x, beta, y);
+        BO_HIP(hipGetLastError());
+    }
     return BO_OK;
 }
 template bo_status bsr_spmv_launch<2>(int, const int32_t *, const int32_t *, const double *, double, const double *,

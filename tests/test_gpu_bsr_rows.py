@@ -50,3 +50,22 @@ def test_bsr_spmv_rows_of_every_length(B, bs, rows, shift):
             else:
                 # a sum of m terms: at most m eps of the terms' magnitudes
                 assert np.all(np.abs(got - ref) <= 4500 * 2.3e-16 * (2.0 * am + np.abs(y0)))
+
+
+def test_bsr2_spmv_of_as_many_rows_and_blocks_as_an_index_holds(B):
+    """2^31 - 1 rows of one block each: row and block numbers up to the largest
+    32-bit index (119 GB of operands)."""
+    import torch
+    n = 2**31 - 1
+    dev = "cuda"
+    A = B.DeviceBsr2(torch.arange(n + 1, dtype=torch.int32, device=dev),
+                     torch.zeros(n, dtype=torch.int32, device=dev),
+                     torch.ones(4 * n, dtype=torch.float64, device=dev))
+    x = torch.tensor([1.0, 2.0], dtype=torch.float64, device=dev)
+    y = torch.full((2 * n,), float("nan"), dtype=torch.float64, device=dev)
+    B.bo_bsr2_spmv(A, 2.0, x, 0.0, y)
+    try:
+        assert all(bool((c == 6.0).all()) for c in y.split(1 << 28))
+    finally:
+        del A, y
+        torch.cuda.empty_cache()
