@@ -120,10 +120,6 @@ __device__ __forceinline__ int stencil_offset(int g, int nx, int ny, int nz) {
     return 7 * g - (g + nx - 1) / nx - g / nx - (k * nx + min(rem, nx)) - (k * nx + max(0, rem - (nxy - nx))) -
            min(g, nxy) - max(0, g - nxy * (nz - 1));
 }
-inline long long stencil_entries(const Grid &g) {
-    return g.n() + 2 * ((long long)(g.nx - 1) * g.ny * g.nz + (long long)g.nx * (g.ny - 1) * g.nz +
-                        (long long)g.nx * g.ny * (g.nz - 1));
-}
 
 // Level-0 CSR from the slot form (pattern = the 7-point stencil), and the
 // check of its diagonal.  A workgroup's rows are gathered in LDS and written as

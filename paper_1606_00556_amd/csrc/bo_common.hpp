@@ -134,6 +134,11 @@ struct Grid {
     int nx, ny, nz;
     long long n() const { return (long long)nx * ny * nz; }
 };
+// entries of its 7-point stencil's rows
+inline long long stencil_entries(const Grid &g) {
+    return g.n() + 2 * ((long long)(g.nx - 1) * g.ny * g.nz + (long long)g.nx * (g.ny - 1) * g.nz +
+                        (long long)g.nx * g.ny * (g.nz - 1));
+}
 
 // neighbour of cell g through slot s, or -1 outside the grid
 __device__ __forceinline__ int nbr_of(int g, int s, int nx, int ny, int nz) {

@@ -1403,8 +1403,9 @@ bo_status grid_import(const Grid &g, const int32_t *rp, const int32_t *ci, const
     int32_t h = 0;
     HostRead r{flag, sizeof h, &h};
     BO_TRY(host_reads(&r, 1, s));
-    if ((h & IMP_PATTERN) && !(h & IMP_NONFINITE)) {
-        // a wrong pattern leaves values unread: a value that is not finite comes first
+    if (((h & IMP_PATTERN) || nnzb != stencil_entries(g)) && !(h & IMP_NONFINITE)) {
+        // a wrong pattern, or blocks behind the last row, leave values unread: a
+        // value that is not finite comes first
         const long long nv = (long long)BS * BS * nnzb;
         k_any_nonfinite<<<grid_for(nv), kBlock, 0, s>>>(nv, v, flag);
         BO_HIP(hipGetLastError());
