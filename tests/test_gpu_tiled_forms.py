@@ -1,0 +1,87 @@
+"""The tiled ILU's sweeps against the oracle at every line of their dispatch: up to
+1024 tiles and beyond, factors that the 256 MB last-level cache holds and larger
+ones, finished layers staged through LDS and (tile_x + tile_y - 1 > 21) not.
+
+Tolerances as for the stages elsewhere: 1e-10 per unknown in FP64, 1e-5 (FP32) and
+2^-7 (BF16) of the oracle's emulation of the same form."""
+import numpy as np
+import pytest
+
+import bo_casegen as cg
+from tests import test_gpu_twophase as T2
+from tests.gpu_util import rel_err_parts, run_stage, setup_both
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-10, "fp32": 1e-5, "bf16": 2.0**-7}
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_1606_00556_amd import bo
+    bo.lib()
+    return bo
+
+
+@pytest.fixture(scope="module")
+def O():
+    from oracle import oracle
+    oracle.lib()
+    return oracle
+
+
+def case_of(shape, seed):
+    nx, ny, nz = shape
+    return cg.tiny_case(nx, ny, nz, seed=seed, step=0.01,
+                        wells=[cg.Well(0, 0, 0, nz - 1, "inj", "bhp", 3500.0),
+                               cg.Well(nx - 1, ny - 1, 0, nz - 1, "prod", "bhp", 2500.0)])
+
+
+# (grid, tile, precision): tiles and megabytes of a sweep's factors (forward, backward)
+FORMS = [
+    ((132, 132, 1), (4, 4), "fp64"),     # 1089 tiles, 104 and 134 MB
+    ((265, 265, 3), (8, 8), "fp64"),     # 1156 tiles, 269 and 346 MB
+    ((265, 265, 3), (8, 8), "fp32"),     # 1156 tiles, 173 MB
+    ((265, 265, 3), (8, 8), "bf16"),     # 1156 tiles, 86 MB
+    ((530, 530, 1), (8, 8), "fp32"),     # 4489 tiles, 592 MB
+    ((530, 530, 1), (8, 8), "bf16"),     # 4489 tiles, 296 MB
+    ((250, 250, 6), (8, 8), "fp64"),     # 1024 tiles, 280 and 360 MB
+    ((1024, 64, 1), (64, 1), "fp64"),    # 1024 tiles, 896 and 1152 MB, not staged
+    ((1024, 64, 1), (64, 1), "fp32"),    # 1024 tiles, 576 MB, not staged
+    ((1024, 64, 1), (64, 1), "bf16"),    # 1024 tiles, 288 MB, not staged
+    ((600, 30, 2), (1, 24), "fp64"),     # 1200 tiles, 410 and 527 MB, not staged
+    ((600, 30, 2), (1, 24), "bf16"),     # 1200 tiles, 132 MB, not staged
+]
+
+
+@pytest.mark.parametrize("shape,tile,prec", FORMS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_sweeps_at_every_line_of_the_dispatch(B, O, shape, tile, prec):
+    case = case_of(shape, 71)
+    v = np.random.default_rng(72).standard_normal(3 * case.n)
+    for fpf in (0, 1):  # 1: the last F stage is added to z
+        _, _, _, _, _, opc, gpc = setup_both(B, O, case, tile=tile, precision=prec, use_amg=0, fpf=fpf)
+        got = run_stage(B, gpc, B.bo_cpr_apply, v, 3 * case.n)
+        assert rel_err_parts(got, opc.apply(v)) <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("tile", [(32, 2), (1, 64), (21, 1), (22, 1)])
+def test_sweeps_around_the_staging_limit(B, O, tile, prec):
+    """Tiles of 21 layers in flight (the last that are staged) and more, with the
+    pressure correction added (PF) and all of it added to z (FPF)."""
+    case = case_of((70, 66, 5), 73)
+    v = np.random.default_rng(74).standard_normal(3 * case.n)
+    for fpf in (0, 1):
+        _, _, _, _, _, opc, gpc = setup_both(B, O, case, tile=tile, precision=prec, coarse_max=40, fpf=fpf)
+        got = run_stage(B, gpc, B.bo_cpr_apply, v, 3 * case.n)
+        assert rel_err_parts(got, opc.apply(v)) <= TOL[prec]
+
+
+def test_two_phase_sweeps_past_the_cache(B, O):
+    """2209 tiles of 8x8 columns on one layer: 259 MB of factors a sweep."""
+    case = cg.two_phase(case_of((375, 375, 1), 75))
+    v = np.random.default_rng(76).standard_normal(2 * case.n)
+    for kw in (dict(use_amg=0), dict(use_amg=0, fpf=1), dict(coarse_max=40)):
+        _, _, _, _, _, opc, gpc = T2.setup_both2(B, O, case, **kw)
+        got = T2.run(B, gpc, B.bo_cpr_apply, v, 2 * case.n)
+        assert rel_err_parts(got, opc.apply(v), parts=2) <= 1e-10
