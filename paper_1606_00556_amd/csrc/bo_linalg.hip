@@ -1185,11 +1185,12 @@ __global__ void __launch_bounds__(kBlock) k_cgs_exact(uint32_t n, double *__rest
 // they took as long as the loads at 150 k elements.  Time with its final sums,
 // before and now: 150 k elements, 8 vectors 13.7 and 6.4 us, 28 vectors 36.2
 // and 8.8 us; 734 k, 20 vectors 48.1 and 23.1 us; 6 M, 12 vectors 162 and
-// 104 us, 28 vectors 370 and 226 us (6.1 TB/s).
+// 104 us, 28 vectors 370 and 226 us (6.1 TB/s).  Up to three vectors are too few
+// loads for eight wavefronts (48 M, one vector: 136 us, and 208 with two per SIMD).
 template <int NV>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 2))) k_dcgs_dots(uint32_t n, VecList V, const double *__restrict__ w,
-                                                      double *__restrict__ partial, uint32_t *done, double *out,
-                                                      double *mirror) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, NV < 4 ? 8 : 2)))
+k_dcgs_dots(uint32_t n, VecList V, const double *__restrict__ w, double *__restrict__ partial, uint32_t *done,
+            double *out, double *mirror) {
     __shared__ double sh[2 * NV][kBlock / 64];
     auto at = [](const double *p, uint32_t boff) -> const double * {
         return (const double *)((const char *)p + boff);
@@ -1222,14 +1223,14 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 
 // workgroup forms the same coefficients.  A pending vector inside the span of
 // the basis (beta^2 <= 0) leaves beta = 0 in sc[0] and zero vectors.
 //
-// Registers for two wavefronts per SIMD as in the dots: 6 M elements, step 11
-// 169 and now 139 us, step 27 372 and 285 us (5.2 TB/s); steps 15 to 19 lose
-// 4 % of it.
+// Registers for two wavefronts per SIMD as in the dots, but not where they do not
+// pay.  6 M elements with the compiler's choice and with two: step 11 149 and
+// 125 us, step 27 353 and 275 us (5.4 TB/s), but step 15 160 and 173 us, step 19
+// 197 and 211 us; 48 M: step 0 262 and 326 us, step 4 586 and 565 us.
 template <int J>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 2))) k_dcgs_update(uint32_t n, VecList V, const double *__restrict__ red,
-                                                        double *__restrict__ sc, int rev,
-                                                        double *__restrict__ partial, double *sc_mirror, uint32_t *done,
-                                                        double *norm2, double *norm2_mirror) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, J < 2 || (J > 11 && J < 20) ? 8 : 2)))
+k_dcgs_update(uint32_t n, VecList V, const double *__restrict__ red, double *__restrict__ sc, int rev,
+              double *__restrict__ partial, double *sc_mirror, uint32_t *done, double *norm2, double *norm2_mirror) {
     __shared__ double cs[J > 0 ? J : 1], cp[J > 0 ? J : 1], cb[2];
     __shared__ double sh[1][kBlock / 64];
     if (threadIdx.x == 0) {
