@@ -768,7 +768,8 @@ __global__ void k_p_fill(int n, const int32_t *__restrict__ rp, const int32_t *_
 // values read the seven slot arrays.  Slots are in column order: the same sums
 // in the same order as over the CSR rows.  2 M cells, CSR and slots: a MIS-2
 // round 125 and 37 us, aggregation 67 and 34 us, the
-// filtered diagonal 58 and 28 us, the prolongator's rows 233 and 51 us.
+// filtered diagonal 58 and 28 us, the prolongator's rows with the counts of its
+// columns 386 and 167 us (of which 157 fill them, bound by the counts' atomics).
 struct SlotGraph {
     int n, nx, nxy;
     const uint8_t *sb;
@@ -1231,26 +1232,7 @@ __global__ void __launch_bounds__(kBlock) k_sort_rows(int n, const int32_t *__re
 }
 
 // ---- row-wise sparse product C = A B ----------------------------------------------
-// G lanes own one output row and an LDS hash of H slots (keys and values).
-// The row of A is walked in ascending order; for one entry a_ik the lanes
-// take the entries of row k of B in parallel.  Those have distinct columns,
-// so no two lanes add to one slot at the same time, and each output value is
-// accumulated in ascending k exactly as in a row-by-row Gustavson product.
-// The counting pass counts the slots it fills; the numeric pass compacts the
-// distinct columns, ranks (sorts) and writes them.
-//
-// Bound by latency: of the loads of B's rows, then of the LDS.  The loads of kP
-// entries of A are issued together, on every path (see below), their products
-// look up their slots together and are then added by LDS atomics in the order
-// of those entries (a wavefront's LDS operations run in order), so a round trip
-// to memory and two to the LDS are paid per kP entries and not per entry.
-// kP: 4 in the numeric pass (8 take more registers than five wavefronts per
-// SIMD leave: 518 and 418 us at 210 k rows of a level 1), 8 in the counting
-// pass (371 us; 4 take 396), 5 with 8 lanes a row (237 us at 2 M rows of a level
-// 0; 4 take 260, 8 take 278).  2 M cells, R (A P) of level 0 (264 k rows), the
-// counting pass 641 and now 362 us, the numeric pass 537 and now 347 us; A P of
-// level 1: 175 and 136 us, 286 and 213 us.
-// products of each row (sum of the B row lengths it touches) and seven
+// products of each row (sum of the B row lengths it touches) and nine
 // reductions over the rows, kRedSlots words each (one atomic per workgroup):
 // [0] the largest product count, [1] rows above kLongProducts, [2] rows above
 // kVeryLongProducts, [3] the largest count at or below kLongProducts, [4] the
@@ -1365,6 +1347,26 @@ __global__ void k_spgemm_classify(int n, const int32_t *__restrict__ prod, int p
     if (many) rows[base + __popcll(m & ((1ull << lane) - 1))] = i;
 }
 
+// G lanes own one output row and an LDS hash of H slots (keys and values).
+// The row of A is walked in ascending order; for one entry a_ik the lanes
+// take the entries of row k of B in parallel.  Those have distinct columns,
+// so no two lanes add to one slot at the same time, and each output value is
+// accumulated in ascending k exactly as in a row-by-row Gustavson product.
+// The counting pass counts the slots it fills; the numeric pass compacts the
+// distinct columns, ranks (sorts) and writes them.
+//
+// Bound by latency: of the loads of B's rows, then of the LDS.  The loads of kP
+// entries of A are issued together, on every path (see below), their products
+// look up their slots together and are then added by LDS atomics in the order
+// of those entries (a wavefront's LDS operations run in order), so a round trip
+// to memory and two to the LDS are paid per kP entries and not per entry.
+// kP: 4 in the numeric pass (8 take more registers than five wavefronts per
+// SIMD leave: 518 and 418 us at 210 k rows of a level 1), 8 in the counting
+// pass (371 us; 4 take 396), 5 with 8 lanes a row (237 us at 2 M rows of a level
+// 0; 4 take 260, 8 take 278).  2 M cells, R (A P) of level 0 (264 k rows), the
+// counting pass 680 and now 361 us, the numeric pass 616 and now 408 us; A P of
+// level 1: 166 and 127 us, 271 and 214 us.
+//
 // Rows: with rows != NULL the kernel takes rows[0..n) (listed rows); with
 // prod != NULL it takes rows 0..n-1 except those with prod[i] > plimit (the
 // long rows by products, or in the numeric pass the rows of many distinct

@@ -83,7 +83,10 @@ bo_status bicgstab_core(bo_cpr *pc, UserA A, const double *b, double *x, const b
     BO_TRY(true_residual(&rn));
     for (;;) {
         st.rel_residual = rn / bnorm;
-        if (!std::isfinite(rn)) { status = solve_not_finite(pc, "bo_bicgstab_solve: residual is not finite", s); break; }
+        if (!std::isfinite(rn)) {
+            status = solve_not_finite(pc, "bo_bicgstab_solve: residual is not finite", s);
+            break;
+        }
         if (rn <= tol) { st.converged = 1; status = BO_OK; break; }
         if (its >= opts->maxit) break;
         // (re)start the recurrences from the current residual

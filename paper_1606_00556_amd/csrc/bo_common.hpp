@@ -107,6 +107,9 @@ struct DBuf {
 };
 
 // ---- launch geometry --------------------------------------------------------
+// bytes of the last-level cache; data of more is read past it where each pass
+// reads all of it
+constexpr size_t kCacheBytes = 256u << 20;
 constexpr int kBlock = 256;
 inline unsigned grid_for(long long n, int block = kBlock) {
     long long g = (n + block - 1) / block;
@@ -277,11 +280,12 @@ __device__ inline double block_sum(double v, double *sh) {
 }
 
 // ---- process-lifetime scratch ------------------------------------------------------
-// Grow-only device buffers for temporaries of host wrappers that synchronise
-// the stream before returning (so a buffer is idle whenever a call starts);
-// steady-state calls then do not allocate, and hipFree does not synchronise
-// the device.  One set per host thread; never freed.
-enum ScratchSlot { SC_FLAG = 0, SC_JAC_CNT, SC_SELL, SC_COUNT };
+// Grow-only device buffers for temporaries of host wrappers that read a result
+// back after the buffer's last reader (scan_counts), so that a buffer is idle
+// whenever a call starts, on whatever stream; steady-state calls then do not
+// allocate, and hipFree does not synchronise the device.  One set per host
+// thread; never freed.
+enum ScratchSlot { SC_JAC_CNT = 0, SC_SELL, SC_COUNT };
 bo_status scratch_get(int slot, size_t bytes, void **ptr);
 
 // ---- small device-to-host reads ----------------------------------------------------
@@ -298,9 +302,10 @@ bo_status host_reads(const HostRead *r, int count, hipStream_t s);
 
 // ---- host-side scan / reductions (declared in bo_linalg.hip) -------------------
 // Exclusive prefix sum of n int32 counts into out (n+1 entries, out[n] = total);
-// returns the total on the host (synchronises the stream).  The nextra reads
-// in extra (device words the caller wants) are served in the same
-// synchronisation (at most three).
+// returns the total on the host.  The nextra reads in extra (device words the
+// caller wants, at most three) come with it.  When the call returns the counts
+// have been read and everything enqueued on s before has finished, but the
+// kernel may still be ending: out is there for later work on s only.
 bo_status scan_counts(const int32_t *counts, int32_t *out, int n, int32_t *total, hipStream_t s,
                       const HostRead *extra = nullptr, int nextra = 0);
 // The same prefix sum enqueued without reading anything back (no

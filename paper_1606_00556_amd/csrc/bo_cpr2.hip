@@ -282,9 +282,8 @@ __global__ void __launch_bounds__(64) k_ilu2_factor(Tile2 T, const double *__res
 // sweep with 2 buffers 82 and 99 us, with 4 81 and 95 us, with 4 and the factors
 // read past the cache 77 and 85 us (2 buffers: 78 and 88 us).
 constexpr int kIlu2Ahead = 4;
-// Factors of more than the 256 MB last-level cache are read past it (NT), as the
-// 3x3 form's are.
-constexpr size_t kCacheBytes = 256u << 20;
+// Factors larger than the last-level cache are read past it (NT), as the 3x3
+// form's are.
 template <bool NT>
 __device__ __forceinline__ double2 load_factor(const double2 *p) {
     typedef double V __attribute__((ext_vector_type(2)));

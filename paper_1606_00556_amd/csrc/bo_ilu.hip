@@ -678,7 +678,7 @@ __global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__r
             step(s0 - u, ring[u], true);
         }
     if constexpr (STAGE) {
-        // layer 0; its zin values were loaded by the fetch for step -1
+        // layer 0, complete with the last step
         double o[3], z[3] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int u = 0; u < 3; u++) {
@@ -887,12 +887,11 @@ inline int stage_layers(const TileGeom &G) {
 // steps, 58.4 us with 2 and 2, 64.0 us with 6 and 4), beyond that more
 // tiles per SIMD do (400x400x100: 2.16 ms either way, HBM bound).
 constexpr int kFewTiles = 1024, kAheadF = 4, kAheadB = 3;
-// Factors of more than the 256 MB last-level cache are read past it: they are
-// gone before the next sweep reads them, and leave it to what the products and
-// the V-cycle read again (400x400x100 in FP64, both sweeps: 2156 and now 2119 us).
-// Factors that stay in part must not be: 100x100x50
-// in FP64, 155 MB, forward sweep 41 us cached and 70 us past the cache.
-constexpr size_t kCacheBytes = 256u << 20;
+// Factors larger than the last-level cache are read past it: they are gone
+// before the next sweep reads them, and leave it to what the products and the
+// V-cycle read again (400x400x100 in FP64, both sweeps: 2156 and now 2119 us).
+// Factors that stay in part must not be: 100x100x50 in FP64, 155 MB, forward
+// sweep 41 us cached and 70 us past the cache.
 template <int St, bool FWD> bool past_cache(const TileGeom &G) {
     return (size_t)G.slots() * Factors<St, FWD>::kBytes > kCacheBytes;
 }
@@ -1027,7 +1026,8 @@ bo_status fstage_check(bo_cpr *pc, hipStream_t s) {
     int32_t bad = 0;
     HostRead rd{pc->fflag.p, sizeof bad, &bad};
     BO_TRY(host_reads(&rd, 1, s));
-    if (bad & 4) return fail(BO_ERR_HIP, "F stage: a wait for a neighbouring tile's values expired (natural-order ILU)");
+    if (bad & 4)
+        return fail(BO_ERR_HIP, "F stage: a wait for a neighbouring tile's values expired (natural-order ILU)");
     if (bad & 2)
         return fail(BO_ERR_UNSUPPORTED, "F stage: a cell row's lower blocks are not its -x, -y, -z neighbours");
     if (bad) return fail(BO_ERR_SINGULAR_BLOCK, "F stage: singular 3x3 pivot block");

@@ -407,7 +407,9 @@ struct NatLane {
         }
         spin = hand_get(ctl + 1) ? 0 : polls;
     }
-    __device__ __forceinline__ bool active(const NatGeom &G, int u) const { return (unsigned)(u - ab) < (unsigned)G.nz; }
+    __device__ __forceinline__ bool active(const NatGeom &G, int u) const {
+        return (unsigned)(u - ab) < (unsigned)G.nz;
+    }
     // the cell of an active step (cell 0 otherwise)
     __device__ __forceinline__ size_t cell(const NatGeom &G, int u) const {
         const int k = FWD ? u - ab : G.nz - 1 - (u - ab);

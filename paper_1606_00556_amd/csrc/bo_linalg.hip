@@ -257,7 +257,8 @@ bo_status scan_counts_async(const int32_t *counts, int32_t *out, int n, int32_t 
     return BO_OK;
 }
 
-// The same prefix sum in one pass (scan_counts): a workgroup takes a tile of
+// The same prefix sum in one pass (scan_counts), the single-pass scan with
+// decoupled look-back of Merrill and Garland (2016): a workgroup takes a tile of
 // 4096 counts by ticket, publishes the tile's sum, looks back over the sums
 // and prefixes of the tiles before it (a wavefront reads 64 of them at a time)
 // and publishes its own prefix.  A word holds (call number, state, value), so
@@ -1416,7 +1417,8 @@ bo_status grid_import(const Grid &g, const int32_t *rp, const int32_t *ci, const
     if (h & IMP_PATTERN)
         return fail(BO_ERR_UNSUPPORTED, std::string(who) + ": the pattern is not the grid's 7-point stencil");
     if (h & IMP_SINGULAR)
-        return fail(BO_ERR_SINGULAR_BLOCK, std::string(who) + ": singular saturation block (no quasi-IMPES decoupling)");
+        return fail(BO_ERR_SINGULAR_BLOCK,
+                    std::string(who) + ": singular saturation block (no quasi-IMPES decoupling)");
     return BO_OK;
 }
 template bo_status grid_import<2>(const Grid &, const int32_t *, const int32_t *, const double *, long long, int,

@@ -346,8 +346,9 @@ __global__ void __launch_bounds__(384) k_nn_wgrad(Vol V, int ntiles, const uint1
                 const uint16_t *p = xb + ((rz + dzi) * HY + ry + dy) * PX;
                 const uint4 w = *(const uint4 *)p;
                 const uint32_t w4 = *(const uint32_t *)(p + 8);
-                const uint4 m = make_uint4(__builtin_amdgcn_alignbit(w.y, w.x, 16), __builtin_amdgcn_alignbit(w.z, w.y, 16),
-                                           __builtin_amdgcn_alignbit(w.w, w.z, 16), __builtin_amdgcn_alignbit(w4, w.w, 16));
+                const uint4 m =
+                    make_uint4(__builtin_amdgcn_alignbit(w.y, w.x, 16), __builtin_amdgcn_alignbit(w.z, w.y, 16),
+                               __builtin_amdgcn_alignbit(w.w, w.z, 16), __builtin_amdgcn_alignbit(w4, w.w, 16));
                 acc[3 * dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf8(w), acc[3 * dy], 0, 0, 0);
                 acc[3 * dy + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf8(m), acc[3 * dy + 1], 0, 0, 0);
                 acc[3 * dy + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf8(make_uint4(w.y, w.z, w.w, w4)),

@@ -172,8 +172,8 @@ __global__ void __launch_bounds__(64) k_ras_forward(RasGeom T, const double2 *__
         }
 }
 
-// backward sweep: x (cell order, the tile's own cells) from y (slot order);
-// lanes without an own cell at a step store to their slot of Y, already read
+// backward sweep: x (cell order) from y (slot order); only lanes with one of the
+// tile's own cells at a step store
 template <int AH>
 __global__ void __launch_bounds__(64) k_ras_backward(RasGeom T, const double2 *__restrict__ Fb,
                                                      const double *__restrict__ Y, double *__restrict__ x) {

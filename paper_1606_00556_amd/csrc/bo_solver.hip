@@ -669,7 +669,10 @@ bo_status fgmres_core(bo_cpr *pc, UserA A, const double *b, double *x, const bo_
         BO_TRY(fetch(1));
         double beta = std::sqrt(hh[0]);
         st.rel_residual = beta / bnorm;
-        if (!std::isfinite(beta)) { status = solve_not_finite(pc, "bo_fgmres_solve: residual is not finite", s); break; }
+        if (!std::isfinite(beta)) {
+            status = solve_not_finite(pc, "bo_fgmres_solve: residual is not finite", s);
+            break;
+        }
         if (beta <= tol) { st.converged = 1; status = BO_OK; break; }
         if (its >= opts->maxit) break;
         if (its > 0) st.restarts++;
