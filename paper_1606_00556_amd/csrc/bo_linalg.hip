@@ -414,24 +414,27 @@ bo_status scan_counts(const int32_t *counts, int32_t *out, int n, int32_t *total
 // y = alpha A x + beta y for BS x BS blocks, BS threads per block row, thread r
 // forming component r; sums in block order and, within a block, in column
 // order.  A workgroup takes 64 consecutive rows: their blocks are one
-// contiguous piece of the value array, which goes through LDS in chunks of 448
-// blocks (the 7-point rows of a workgroup in one chunk) with 16-byte
-// non-temporal loads, each byte read once; the threads' column indices and x
-// entries are in flight beside it.  Bound by HBM.  Reading a block's row per
-// thread from global memory touched each line three times per component and was
-// bound by the L1: 324 us for the 1.23 GB of a 197x203x51 grid (3.8 TB/s), now
-// 229 us (5.4 TB/s; 248 us with temporal loads, 258 us with one contiguous
-// range of rows per XCD).
-// V16: the value array is 16-byte aligned.
+// contiguous piece of the value array, which goes through LDS in chunks of 64 CH
+// blocks (one chunk for rows of up to CH blocks) with 16-byte non-temporal loads,
+// each byte read once; the threads' column indices and x entries are in flight
+// beside it.  Bound by HBM.  Reading a block's row per thread from global memory
+// (k_bsr_spmv_rows) touches each line three times per component and is bound by
+// the L1: 312 us for the 1.23 GB of a 197x203x51 grid (3.9 TB/s), here 204 us (6.0
+// TB/s; with temporal loads 8 % more, with one contiguous range of rows per XCD
+// 13 % more).
+// V16: the value array is 16-byte aligned.  CH 7: 7-point rows; 8: shorter rows on
+// average among which some are longer, as in a dual-porosity matrix (fracture
+// cells 8, matrix cells 2), whose second chunk of 64 blocks cost as much as the
+// first: 16 M rows 379 us, 450 with 7; a 7-point grid's 204 us are 206 with 8.
 typedef double dvec2 __attribute__((ext_vector_type(2)));
-constexpr int kBsrRows = 64, kBsrChunk = 7 * kBsrRows;
-template <int BS, bool V16>
+constexpr int kBsrRows = 64;
+template <int BS, bool V16, int CH>
 __global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int first, int n, const int32_t *__restrict__ rp,
                                                            const int32_t *__restrict__ ci,
                                                            const double *__restrict__ v, double alpha,
                                                            const double *__restrict__ x, double beta,
                                                            double *__restrict__ y) {
-    constexpr int B2 = BS * BS, NT = kBsrRows * BS, KB = 7;
+    constexpr int B2 = BS * BS, NT = kBsrRows * BS, KB = 7, kBsrChunk = CH * kBsrRows;
     constexpr int NLD = (kBsrChunk * B2 / 2 + 1 + NT - 1) / NT;  // pairs per thread
     __shared__ __align__(16) double sv[kBsrChunk * B2 + 2];
     // (rows and blocks are counted from r0 and c0: n and the block count may be 2^31 - 1)
@@ -457,6 +460,7 @@ __global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int first, int n, con
         double2 ld[NLD];
 #pragma unroll
         for (int u = 0; u < NLD; u++) {
+            if (u == NLD - 1 && t + NT * u >= np) continue;  // (a chunk is rarely that full)
             const size_t d = d0 + 2 * (size_t)min(t + NT * u, np - 1);
             if (V16 && d + 1 < d1) {
                 const dvec2 q = __builtin_nontemporal_load((const dvec2 *)(v + d));
@@ -488,23 +492,56 @@ __global__ void __launch_bounds__(kBsrRows *BS) k_bsr_spmv(int first, int n, con
     if (row) y[(size_t)i * BS + r] = alpha * s + yi;
 }
 
+// The same with BS threads a block row reading their blocks from memory: for few
+// rows, where a launch takes what its longest chain of loads takes (2 k rows 3.8 us,
+// staged 4.1; 20 k rows 4.0 and 5.1; 32 k rows 6.0 and 5.4; with about 5 blocks a row
+// 50 k rows 6.4 and 7.4, 128 k 13.2 and 13.6, 200 k 23.5 and 20.4), and for rows
+// that fill a chunk badly or many times over (1 M rows of 2 blocks 32 and 60 us,
+// 50 k of 27 30 and 40 us, 20 k of 60 34 and 125 us).
 template <int BS>
-bo_status bsr_spmv_launch(int n, const int32_t *rp, const int32_t *ci, const double *v, double alpha, const double *x,
-                          double beta, double *y, hipStream_t s) {
+__global__ void __launch_bounds__(kBlock) k_bsr_spmv_rows(int first, int n, const int32_t *__restrict__ rp,
+                                                          const int32_t *__restrict__ ci,
+                                                          const double *__restrict__ v, double alpha,
+                                                          const double *__restrict__ x, double beta,
+                                                          double *__restrict__ y) {
+    const unsigned t = blockIdx.x * kBlock + threadIdx.x, lr = t / BS;
+    if (lr >= (unsigned)(n - first)) return;
+    const int i = first + (int)lr, r = (int)(t % BS);
+    double s = 0.0;
+    const int e1 = rp[i + 1];
+    for (int e = rp[i]; e < e1; e++) {
+        const double *a = v + (size_t)(BS * BS) * e + BS * r, *xe = x + (size_t)BS * ci[e];
+#pragma unroll
+        for (int z = 0; z < BS; z++) s = s + a[z] * xe[z];
+    }
+    double *const yi = y + (size_t)BS * i + r;
+    *yi = alpha * s + (beta == 0.0 ? 0.0 : beta * *yi);
+}
+
+template <int BS>
+bo_status bsr_spmv_launch(int n, int nnzb, const int32_t *rp, const int32_t *ci, const double *v, double alpha,
+                          const double *x, double beta, double *y, hipStream_t s) {
+    const long long b = nnzb, full = 6LL * n;
+    const bool staged = b >= 4LL * n && b < 8LL * n && n > (b > full ? 3 << 13 : 1 << 17);
+    const bool v16 = (uintptr_t)v % 16 == 0;
     // a launch holds fewer than 2^32 threads
     constexpr long long kRows = (long long)kBsrRows << 24;
     for (long long r = 0; r < n; r += kRows) {
-        const int end = (int)std::min<long long>(n, r + kRows);
+        const int r0 = (int)r, end = (int)std::min<long long>(n, r + kRows);
         const unsigned nb = grid_for(end - r, kBsrRows);
-        if ((uintptr_t)v % 16 == 0)
-            k_bsr_spmv<BS, true><<<nb, kBsrRows * BS, 0, s>>>((int)r, end, rp, ci, v, alpha, x, beta, y);
-        else
-            k_bsr_spmv<BS, false><<<nb, kBsrRows * BS, 0, s>>>((int)r, end, rp, ci, v, alpha, x, beta, y);
+        constexpr unsigned NT = kBsrRows * BS;
+        if (!staged)
+            k_bsr_spmv_rows<BS><<<grid_for((long long)BS * (end - r0)), kBlock, 0, s>>>(r0, end, rp, ci, v, alpha, x,
+                                                                                       beta, y);
+        else if (b > full && v16) k_bsr_spmv<BS, true, 7><<<nb, NT, 0, s>>>(r0, end, rp, ci, v, alpha, x, beta, y);
+        else if (b > full) k_bsr_spmv<BS, false, 7><<<nb, NT, 0, s>>>(r0, end, rp, ci, v, alpha, x, beta, y);
+        else if (v16) k_bsr_spmv<BS, true, 8><<<nb, NT, 0, s>>>(r0, end, rp, ci, v, alpha, x, beta, y);
+        else k_bsr_spmv<BS, false, 8><<<nb, NT, 0, s>>>(r0, end, rp, ci, v, alpha, x, beta, y);
         BO_HIP(hipGetLastError());
     }
     return BO_OK;
 }
-template bo_status bsr_spmv_launch<2>(int, const int32_t *, const int32_t *, const double *, double, const double *,
+template bo_status bsr_spmv_launch<2>(int, int, const int32_t *, const int32_t *, const double *, double, const double *,
                                       double, double *, hipStream_t);
 
 // ---- sliced BSR (general operator of the solver) -------------------------------
@@ -732,6 +769,7 @@ __device__ __forceinline__ bool qi_weights(const double *D, int mode, double *c)
 // thread per row copying its blocks plane by plane and a decoupling pass over
 // the planes took 50 + 238 + 37 us, at 2M cells 200 + 924 + 150 us; now 101 and
 // 468 us (4.7 TB/s, the rate of a large copy).
+constexpr int kStencilChunk = 7 * kBsrRows;
 enum { IMP_PATTERN = 1, IMP_NONFINITE = 2, IMP_SINGULAR = 4 };
 template <int BS, bool V16>
 __global__ void __launch_bounds__(256) k_grid_import(int nx, int ny, int nz, const int32_t *__restrict__ rp,
@@ -739,8 +777,8 @@ __global__ void __launch_bounds__(256) k_grid_import(int nx, int ny, int nz, con
                                                      int mode, double *__restrict__ slots, double *__restrict__ cw,
                                                      double *__restrict__ app, int32_t *__restrict__ flag) {
     constexpr int B2 = BS * BS, NT = 256;
-    constexpr int NLD = (kBsrChunk * B2 / 2 + 1 + NT - 1) / NT;
-    __shared__ __align__(16) double sv[kBsrChunk * B2 + 2];
+    constexpr int NLD = (kStencilChunk * B2 / 2 + 1 + NT - 1) / NT;
+    __shared__ __align__(16) double sv[kStencilChunk * B2 + 2];
     __shared__ int first[kBsrRows];  // a row's first block in the chunk
     __shared__ unsigned have[kBsrRows];
     const int n = nx * ny * nz, nxy = nx * ny;
@@ -748,7 +786,7 @@ __global__ void __launch_bounds__(256) k_grid_import(int nx, int ny, int nz, con
     const int t = threadIdx.x, lr = t % kBsrRows, grp = t / kBsrRows;
     const int r0 = blockIdx.x * kBsrRows, r1 = min(r0 + kBsrRows, n), i = r0 + lr;
     const int c0 = rp[r0], c1 = rp[r1];
-    if (c1 < c0 || c1 - c0 > kBsrChunk) {
+    if (c1 < c0 || c1 - c0 > kStencilChunk) {
         if (t == 0) atomicOr(flag, IMP_PATTERN);
         return;
     }
@@ -1656,5 +1694,6 @@ extern "C" bo_status bo_bsr_spmv(const bo_bsr *A, double alpha, const double *x,
     if (!A || !x || !y || !A->rowptr || !A->colind || !A->val || A->nbrows < 0)
         return fail(BO_ERR_INVALID_ARG, "bo_bsr_spmv: NULL argument");
     if (A->nbrows == 0) return BO_OK;
-    return bsr_spmv_launch<3>(A->nbrows, A->rowptr, A->colind, A->val, alpha, x, beta, y, (hipStream_t)stream);
+    return bsr_spmv_launch<3>(A->nbrows, A->nnzb, A->rowptr, A->colind, A->val, alpha, x, beta, y,
+                              (hipStream_t)stream);
 }

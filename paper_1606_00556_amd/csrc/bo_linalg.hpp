@@ -5,8 +5,8 @@
 namespace bo {
 // y = alpha A x + beta y for a BSR matrix of BS x BS blocks (3 and 2)
 template <int BS>
-bo_status bsr_spmv_launch(int n, const int32_t *rp, const int32_t *ci, const double *v, double alpha, const double *x,
-                          double beta, double *y, hipStream_t s);
+bo_status bsr_spmv_launch(int n, int nnzb, const int32_t *rp, const int32_t *ci, const double *v, double alpha,
+                          const double *x, double beta, double *y, hipStream_t s);
 
 bo_status slot_spmv(const Grid &g, const double *A, double alpha, const double *x, double beta, double *y,
                     hipStream_t s);

@@ -337,5 +337,6 @@ extern "C" bo_status bo_bsr2_spmv(const bo_bsr2 *A, double alpha, const double *
         return fail(BO_ERR_INVALID_ARG, "bo_bsr2_spmv: NULL argument");
     if (A->nbrows < 0) return fail(BO_ERR_INVALID_ARG, "bo_bsr2_spmv: negative size");
     if (A->nbrows == 0) return BO_OK;
-    return bsr_spmv_launch<2>(A->nbrows, A->rowptr, A->colind, A->val, alpha, x, beta, y, (hipStream_t)stream);
+    return bsr_spmv_launch<2>(A->nbrows, A->nnzb, A->rowptr, A->colind, A->val, alpha, x, beta, y,
+                              (hipStream_t)stream);
 }

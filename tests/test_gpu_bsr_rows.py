@@ -69,3 +69,34 @@ def test_bsr2_spmv_of_as_many_rows_and_blocks_as_an_index_holds(B):
     finally:
         del A, y
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("bs", [2, 3])
+@pytest.mark.parametrize("rows,lengths", [(24576, (6, 8)), (24577, (6, 8)), (131073, (2, 8))])
+def test_bsr_spmv_staged_rows(B, bs, rows, lengths, shift):
+    """The products whose blocks are staged: the first size that is staged of 7-point
+    and of shorter rows (long ones first, so that some workgroups fill their chunk),
+    with rows of 600 blocks, empty rows and a ragged last workgroup."""
+    import torch
+    rng = np.random.default_rng(7 * bs + rows + shift)
+    lo, hi = lengths
+    ln = rng.integers(lo, hi, rows)
+    if lo == 2:
+        ln[:rows // 2], ln[rows // 2:] = 8, 2
+    ln[1000:1100] = 0
+    ln[[70, 71, rows - 1]] = 600
+    rp = np.concatenate([[0], np.cumsum(ln)]).astype(np.int32)
+    assert 4 * rows <= rp[-1] < 8 * rows and (rp[-1] > 6 * rows) == (lo == 6)
+    ci = rng.integers(0, rows, rp[-1]).astype(np.int32)
+    val = rng.integers(-8, 9, (int(rp[-1]), bs, bs)).astype(np.float64)
+    x, y0 = rng.integers(-8, 9, (rows, bs)).astype(np.float64), rng.integers(-8, 9, (rows, bs)).astype(np.float64)
+    buf = torch.zeros(val.size + 1, dtype=torch.float64, device="cuda")
+    buf[shift:shift + val.size] = to_dev(val.reshape(-1))
+    A = (B.DeviceBsr2 if bs == 2 else B.DeviceBsr)(to_dev(rp), to_dev(ci), buf[shift:shift + val.size])
+    ax = np.zeros((rows, bs))
+    np.add.at(ax, np.repeat(np.arange(rows), ln), np.einsum("eij,ej->ei", val, x[ci]))
+    for alpha, beta in ((-1.0, 1.0), (2.0, 0.0)):
+        y = to_dev(y0.reshape(-1).copy())
+        (B.bo_bsr2_spmv if bs == 2 else B.bo_bsr_spmv)(A, alpha, to_dev(x.reshape(-1)), beta, y)
+        assert np.array_equal(to_host(y).reshape(rows, bs), alpha * ax + beta * y0)
