@@ -188,6 +188,23 @@ struct bo_cpr {
 };
 
 namespace bo {
+// Bytes of the 128-byte cache lines that a sweep over the tiles of a grid reads of
+// factors stored by step for 64 lanes, `count` values of `size` bytes a slot: a
+// line is read at the steps at which one of its lanes (column t of the tile, layer
+// s - a - b) has a cell.  Few layers or small tiles leave most of the storage unread.
+inline size_t tile_bytes_read(int tiles, int tx, int ty, int nz, int count, int size) {
+    const int per = 128 / size;
+    size_t lines = 0;
+    for (int t0 = 0; t0 < tx * ty; t0 += per) {
+        int lo = tx + ty, hi = 0;
+        for (int t = t0; t < std::min(t0 + per, tx * ty); t++) {
+            lo = std::min(lo, t % tx + t / tx);
+            hi = std::max(hi, t % tx + t / tx);
+        }
+        lines += (size_t)(nz + hi - lo);
+    }
+    return (size_t)tiles * count * lines * 128;
+}
 // setup of a handle (plain grid, extended grid or general form), see bo_cpr_setup
 bo_status cpr_setup_impl(const bo_bsr *A, const bo_grid *grid, const bo_cpr_opts *opts, bo_cpr *pc, hipStream_t s);
 bo_status cpr_check(int32_t nbrows, const bo_grid *grid, const bo_cpr_opts *opts);

@@ -448,7 +448,7 @@ bo_status fstage2_apply(bo_cpr *pc, const double *r, const double *dp, double *o
     }
     const Tile2 T = tile_geom(pc);
     const int tiles = T.ntx * T.nty;
-    const bool nt = (size_t)tiles * T.ns * 64 * kPk2 * sizeof(double2) > kCacheBytes;
+    const bool nt = tile_bytes_read(tiles, T.tx, T.ty, T.nz, kPk2, sizeof(double2)) > kCacheBytes;
     double2 *const u = (double2 *)pc->ilu_w.p;
     auto sweeps = [&](auto nt_) {
         constexpr bool NT = decltype(nt_)::value;

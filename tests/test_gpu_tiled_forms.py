@@ -37,20 +37,22 @@ def case_of(shape, seed):
                                cg.Well(nx - 1, ny - 1, 0, nz - 1, "prod", "bhp", 2500.0)])
 
 
-# (grid, tile, precision): tiles and megabytes of a sweep's factors (forward, backward)
+# (grid, tile, precision): tiles and megabytes that the sweeps read of their factors
+# (forward, backward)
 FORMS = [
-    ((132, 132, 1), (4, 4), "fp64"),     # 1089 tiles, 104 and 134 MB
-    ((265, 265, 3), (8, 8), "fp64"),     # 1156 tiles, 269 and 346 MB
-    ((265, 265, 3), (8, 8), "fp32"),     # 1156 tiles, 173 MB
-    ((265, 265, 3), (8, 8), "bf16"),     # 1156 tiles, 86 MB
-    ((530, 530, 1), (8, 8), "fp32"),     # 4489 tiles, 592 MB
-    ((530, 530, 1), (8, 8), "bf16"),     # 4489 tiles, 296 MB
-    ((250, 250, 6), (8, 8), "fp64"),     # 1024 tiles, 280 and 360 MB
-    ((1024, 64, 1), (64, 1), "fp64"),    # 1024 tiles, 896 and 1152 MB, not staged
-    ((1024, 64, 1), (64, 1), "fp32"),    # 1024 tiles, 576 MB, not staged
-    ((1024, 64, 1), (64, 1), "bf16"),    # 1024 tiles, 288 MB, not staged
-    ((600, 30, 2), (1, 24), "fp64"),     # 1200 tiles, 410 and 527 MB, not staged
-    ((600, 30, 2), (1, 24), "bf16"),     # 1200 tiles, 132 MB, not staged
+    ((132, 132, 1), (4, 4), "fp64"),     # 1089 tiles, 19 and 24 MB
+    ((100, 100, 50), (4, 4), "fp64"),    # 625 tiles, 115 and 148 MB (of 480 and 617 stored)
+    ((530, 530, 1), (8, 8), "fp64"),     # 4489 tiles, 491 and 631 MB
+    ((530, 530, 1), (8, 8), "fp32"),     # 4489 tiles, 316 MB
+    ((700, 700, 1), (8, 8), "bf16"),     # 7744 tiles, 306 MB
+    ((265, 265, 3), (8, 8), "fp32"),     # 1156 tiles, 102 MB
+    ((265, 265, 3), (8, 8), "bf16"),     # 1156 tiles, 56 MB
+    ((256, 256, 12), (8, 8), "fp64"),    # 1024 tiles, 266 and 342 MB
+    ((256, 256, 22), (8, 8), "fp32"),    # 1024 tiles, 261 MB
+    ((1600, 100, 1), (64, 1), "fp64"),   # 2500 tiles, 273 and 352 MB, not staged
+    ((2560, 100, 1), (64, 1), "fp32"),   # 4000 tiles, 281 MB, not staged
+    ((600, 30, 2), (1, 24), "fp64"),     # 1200 tiles, 55 and 71 MB, not staged
+    ((600, 30, 2), (1, 24), "bf16"),     # 1200 tiles, 34 MB, not staged
 ]
 
 
@@ -77,11 +79,13 @@ def test_sweeps_around_the_staging_limit(B, O, tile, prec):
         assert rel_err_parts(got, opc.apply(v)) <= TOL[prec]
 
 
-def test_two_phase_sweeps_past_the_cache(B, O):
-    """2209 tiles of 8x8 columns on one layer: 259 MB of factors a sweep."""
-    case = cg.two_phase(case_of((375, 375, 1), 75))
+@pytest.mark.parametrize("shape,tile", [((530, 530, 1), (8, 8)), ((375, 375, 2), (3, 2))])
+def test_two_phase_sweeps_of_many_tiles(B, O, shape, tile):
+    """4489 tiles that read 281 MB of factors a sweep, and 23500 of five steps that
+    read 115 MB."""
+    case = cg.two_phase(case_of(shape, 75))
     v = np.random.default_rng(76).standard_normal(2 * case.n)
     for kw in (dict(use_amg=0), dict(use_amg=0, fpf=1), dict(coarse_max=40)):
-        _, _, _, _, _, opc, gpc = T2.setup_both2(B, O, case, **kw)
+        _, _, _, _, _, opc, gpc = T2.setup_both2(B, O, case, tile=tile, **kw)
         got = T2.run(B, gpc, B.bo_cpr_apply, v, 2 * case.n)
         assert rel_err_parts(got, opc.apply(v), parts=2) <= 1e-10
