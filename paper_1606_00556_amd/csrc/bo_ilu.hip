@@ -115,24 +115,31 @@ __device__ __forceinline__ void shfl_arr(const double *src, double *dst, int lan
 // lie in as many layers as the tile is wide, so a thread gathering its own
 // slot reads 64 separate sectors per load, and the cells beside them come in
 // later steps: eight times the matrix through the L2.  A workgroup takes
-// kPackSteps steps of a tile instead and reads runs of a tile's row at one
-// layer, 18 planes at a time (two blocks), into LDS at their slots; it touches
-// a sector (kPackSteps + tile_x - 1) / kPackSteps times.  2 M cells: 1062 and now
-// 650 us alone (2.1 GB); chunks of 4 steps 684 us, workgroups dealt to the
-// XCDs in turn instead of in ranges 702 us.
+// kPackSteps steps of a tile instead (as many more as a wavefront holds tiles) and
+// reads runs of that many cells of a tile's rows at one layer, 18 planes at a time
+// (two blocks), into LDS at their slots: in pass f lane (a, b) takes step (f + a)
+// mod steps, so that all lanes work in every pass whatever the tile's width.
+// 2 M cells, a thread per slot and now: tiles of 8x8 978 and 647 us (2.1 GB), of
+// 16x4 1223 and 608, of 4x4 1241 and 607, of 3x2 1330 and 702, of 64x1 758 and 562
+// us; with passes by layer, where lanes without a step in the chunk idle, 8x8 628,
+// 3x2 1705, 64x1 976 us.  Chunks of 4 steps 684 us, workgroups dealt to the
+// XCDs in turn instead of in ranges 702 us (8x8).
 constexpr int kPackSteps = 8;
+__host__ __device__ inline int pack_steps(const TileGeom &T) { return kPackSteps * (64 / (T.tx * T.ty)); }
 __global__ void __launch_bounds__(kBlock) k_ilu_pack(TileGeom T, const double *__restrict__ A,
                                                      double2 *__restrict__ Ff, double2 *__restrict__ Fb,
                                                      int32_t *__restrict__ slot_of) {
     __shared__ double buf[18][kPackSteps * 64];
-    const int chunks = (T.ns + kPackSteps - 1) / kPackSteps;
+    const int cols = T.tx * T.ty, sets = 64 / cols, steps = pack_steps(T);
+    const int chunks = (T.ns + steps - 1) / steps;
     const int wg = xcd_block(blockIdx.x, gridDim.x);
-    const int tile = wg / chunks, s0 = (wg % chunks) * kPackSteps;
+    const int tile = wg / chunks, s0 = (wg % chunks) * steps;
     const int ti = tile % T.ntx, tj = tile / T.ntx;
-    const int wave = threadIdx.x / 64, t = threadIdx.x % 64;
+    // a wavefront takes as many layers (or steps) at a time as it holds a tile's columns
+    const int t = threadIdx.x % 64 % cols, set = threadIdx.x % 64 / cols, first = threadIdx.x / 64 * sets + set;
     const int a = t % T.tx, b = t / T.tx;
     const int i = ti * T.tx + a, j = tj * T.ty + b;
-    const bool column = t < T.tx * T.ty && i < T.nx && j < T.ny;
+    const bool column = set < sets && i < T.nx && j < T.ny;
     const bool has_mx = a > 0, has_my = b > 0;
     const bool has_px = a + 1 < T.tx && i + 1 < T.nx, has_py = b + 1 < T.ty && j + 1 < T.ny;
     const size_t N = (size_t)T.nx * T.ny * T.nz;
@@ -141,10 +148,11 @@ __global__ void __launch_bounds__(kBlock) k_ilu_pack(TileGeom T, const double *_
     for (int h = 0; h < 4; h++) {
         const int sl0 = h == 0 ? S_D : h == 1 ? S_MY : h == 2 ? -1 : S_PX;
         const int sl1 = h == 0 ? S_MZ : h == 1 ? S_MX : h == 2 ? S_PZ : S_PY;
-        // pass `it`: layer k = s - a - b of the lanes whose step s = s0 + u is in the chunk
-        for (int it = wave; it < kPackSteps + T.tx - 1; it += kBlock / 64) {
-            const int u = it - (T.tx - 1) + a, k = s0 + u - a - b;
-            if (!(column && u >= 0 && u < kPackSteps && k >= 0 && k < T.nz)) continue;
+        // pass f: step s0 + u of each lane, u = (f + a) mod steps, so that runs of
+        // `steps` lanes of a row read one layer
+        for (int f = first; f < steps; f += kBlock / 64 * sets) {
+            const int u = (f + a) % steps, k = s0 + u - a - b;
+            if (!(column && k >= 0 && k < T.nz)) continue;
             const bool h0 = h == 0 ? true : h == 1 ? has_my : h == 2 ? false : has_px;
             const bool h1 = h == 0 ? k > 0 : h == 1 ? has_mx : h == 2 ? k + 1 < T.nz : has_py;
             const int g = i + T.nx * (j + T.ny * k);
@@ -156,10 +164,10 @@ __global__ void __launch_bounds__(kBlock) k_ilu_pack(TileGeom T, const double *_
             else
                 for (int z = 9; z < 18; z++) x[z] = 0.0;
 #pragma unroll
-            for (int z = 0; z < 18; z++) buf[z][u * 64 + t] = x[z];
+            for (int z = 0; z < 18; z++) buf[z][u * cols + t] = x[z];
         }
         __syncthreads();
-        for (int u = wave; u < kPackSteps; u += kBlock / 64) {
+        for (int u = first; u < steps; u += kBlock / 64 * sets) {
             const int s = s0 + u, k = s - a - b;
             if (!(column && s < T.ns && k >= 0 && k < T.nz)) continue;  // idle slot
             double2 *const F = h < 2 ? Ff : Fb;
@@ -167,7 +175,7 @@ __global__ void __launch_bounds__(kBlock) k_ilu_pack(TileGeom T, const double *_
             for (int p = 0; p < 9; p++) {
                 if (h == 2 && p < 4) continue;  // values 0..7 of the backward slot: the chain's
                 F[pk_index(tile, T.ns, s, (h & 1) * 9 + p, t)] =
-                    make_double2(buf[2 * p][u * 64 + t], buf[2 * p + 1][u * 64 + t]);
+                    make_double2(buf[2 * p][u * cols + t], buf[2 * p + 1][u * cols + t]);
             }
             if (h == 0) slot_of[i + T.nx * (j + T.ny * k)] = (int32_t)(((long long)tile * T.ns + s) * 64 + t);
         }
@@ -997,7 +1005,7 @@ bo_status fstage_launch(bo_cpr *pc, hipStream_t s) {
             k_ilu_pack_bsr<<<grid_for(T.slots()), kBlock, 0, s>>>(T, pc->Arp.p, pc->Aci.p, pc->Aval.p, Pf, Pb,
                                                                   pc->ilu_slot.p, ff);
         else
-            k_ilu_pack<<<nb * ((T.ns + kPackSteps - 1) / kPackSteps), kBlock, 0, s>>>(T, pc->A.p, Pf, Pb,
+            k_ilu_pack<<<nb * ((T.ns + pack_steps(T) - 1) / pack_steps(T)), kBlock, 0, s>>>(T, pc->A.p, Pf, Pb,
                                                                                      pc->ilu_slot.p);
         if (f64)
             k_ilu_chain<ST_F64><<<nb, 64, 0, s>>>(T, Pf, Pb, ff, ext ? pc->x_einv_f.p : nullptr, nullptr, nullptr);
