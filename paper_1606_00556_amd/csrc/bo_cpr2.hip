@@ -280,8 +280,10 @@ __global__ void __launch_bounds__(64) k_ilu2_factor(Tile2 T, const double *__res
 // tile and cell 0 (all in bounds) so that no load is skipped on some paths.  Bound
 // by the memory it streams (390 and 410 MB at 2 M cells): forward and backward
 // sweep with 2 buffers 82 and 99 us, with 4 81 and 95 us, with 4 and the factors
-// read past the cache 77 and 85 us (2 buffers: 78 and 88 us).
-constexpr int kIlu2Ahead = 4;
+// read past the cache 73 and 75 us (2 buffers: 77 and 77 us).  With more tiles than
+// SIMDs three buffers leave room for more of them (375x375x2 42 and 43 us, with
+// four 44 and 46; in tiles of 64x1 86 and 88, 94 and 95 us).
+constexpr int kIlu2Few = 1024;
 // Factors larger than the last-level cache are read past it (NT), as the 3x3
 // form's are.
 template <bool NT>
@@ -298,6 +300,29 @@ struct Step2 {
     double f[16];
     double v0, v1, d;
 };
+// Steps 0 .. n - 1 over a ring of AH buffers, each filled once: the whole rounds
+// without a test inside (one that may leave the loop makes every step of the
+// unrolled round wait for all loads: 10 % of a sweep), the last two rounds with.
+template <int AH, typename Step, typename Fetch>
+__device__ __forceinline__ void ring_steps(int n, Step2 (&R)[AH], Step step, Fetch fetch) {
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(u, R[u]);
+    int q = 0;
+    for (; q + 2 * AH <= n; q += AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {
+            step(q + u, R[u]);
+            fetch(q + u + AH, R[u]);
+        }
+#pragma unroll
+    for (int u = 0; u < AH; u++) {
+        if (q + u < n) step(q + u, R[u]);
+        if (q + u + AH < n) fetch(q + u + AH, R[u]);
+    }
+#pragma unroll
+    for (int u = 0; u + 1 < AH; u++)
+        if (q + AH + u < n) step(q + AH + u, R[u]);
+}
 
 // forward sweep: u (slot order) from r (cell order)
 template <int AH, bool NT>
@@ -342,14 +367,7 @@ __global__ void __launch_bounds__(64) k_ilu2_forward(Tile2 T, const double2 *__r
         U[slot2(T, tile, s, t)] = make_double2(up[0], up[1]);
     };
     Step2 R[AH];
-#pragma unroll
-    for (int u = 0; u < AH; u++) fetch(u, R[u]);
-    for (int s0 = 0; s0 < T.ns; s0 += AH)
-#pragma unroll
-        for (int u = 0; u < AH; u++) {  // past the last step every lane is idle
-            step(s0 + u, R[u]);
-            fetch(s0 + u + AH, R[u]);
-        }
+    ring_steps<AH>(T.ns, R, step, fetch);
 }
 
 // backward sweep: x (cell order) from u (slot order), + Pi_p dp when given
@@ -405,14 +423,9 @@ __global__ void __launch_bounds__(64) k_ilu2_backward(Tile2 T, const double2 *__
         x[2 * g + 1] = xp[1];
     };
     Step2 R[AH];
-#pragma unroll
-    for (int u = 0; u < AH; u++) fetch(T.ns - 1 - u, R[u]);
-    for (int s0 = T.ns - 1; s0 >= 0; s0 -= AH)
-#pragma unroll
-        for (int u = 0; u < AH; u++) {  // before the first step every lane is idle
-            step(s0 - u, R[u]);
-            fetch(s0 - u - AH, R[u]);
-        }
+    ring_steps<AH>(
+        T.ns, R, [&](int q, const Step2 &F) { step(T.ns - 1 - q, F); },
+        [&](int q, Step2 &F) { fetch(T.ns - 1 - q, F); });
 }
 
 Tile2 tile_geom(const bo_cpr *pc) {
@@ -450,14 +463,19 @@ bo_status fstage2_apply(bo_cpr *pc, const double *r, const double *dp, double *o
     const int tiles = T.ntx * T.nty;
     const bool nt = tile_bytes_read(tiles, T.tx, T.ty, T.nz, kPk2, sizeof(double2)) > kCacheBytes;
     double2 *const u = (double2 *)pc->ilu_w.p;
-    auto sweeps = [&](auto nt_) {
+    auto sweeps = [&](auto ah_, auto nt_) {
+        constexpr int AH = decltype(ah_)::value;
         constexpr bool NT = decltype(nt_)::value;
-        k_ilu2_forward<kIlu2Ahead, NT><<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, u);
-        if (dp) k_ilu2_backward<kIlu2Ahead, NT, true><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, u, dp, out);
-        else k_ilu2_backward<kIlu2Ahead, NT, false><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, u, dp, out);
+        k_ilu2_forward<AH, NT><<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, u);
+        if (dp) k_ilu2_backward<AH, NT, true><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, u, dp, out);
+        else k_ilu2_backward<AH, NT, false><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, u, dp, out);
     };
-    if (nt) sweeps(std::true_type{});
-    else sweeps(std::false_type{});
+    typedef std::integral_constant<int, 4> Few;
+    typedef std::integral_constant<int, 3> Many;
+    if (tiles <= kIlu2Few && nt) sweeps(Few{}, std::true_type{});
+    else if (tiles <= kIlu2Few) sweeps(Few{}, std::false_type{});
+    else if (nt) sweeps(Many{}, std::true_type{});
+    else sweeps(Many{}, std::false_type{});
     BO_HIP(hipGetLastError());
     return BO_OK;
 }
