@@ -441,8 +441,8 @@ struct Factors {
 // AH steps are in flight: a ring of register buffers, the step loop unrolled by
 // its length, so a buffer is refilled in place once its step is done and no
 // register with a load in flight is ever copied (a copy would wait for it).
-// Every load and store is issued on every path (idle slots read lane 0's data
-// of the step, stores that have nothing to do repeat a value): the hardware
+// Every load and store is issued on every path (idle slots read another lane's
+// data of the step, stores that have nothing to do repeat a value): the hardware
 // returns vector memory operations in order and the compiler counts them
 // statically, so one that some paths skip makes later waits take in the next
 // steps' loads too.  (With conditional output stores and two wavefronts
@@ -450,6 +450,12 @@ struct Factors {
 // length: 1.17 us backward and 0.57 us forward on one tile, 0.46 us now; both
 // sweeps of a 104x104x31 grid 77.8 -> 54.4 us, of a 100x100x50 grid 115 -> 94
 // us, where 169 tiles on 256 CUs reach 3.4 TB/s.)
+// Idle slots read the data of a lane that has a cell, which is loaded anyway: lane
+// 0's lines, where lane 0 is idle too, are a fifth of a one-layer grid's traffic
+// (both sweeps of 1000x1000x1 in FP64 1045 and now 950 us, in BF16 384 and 346 us;
+// 200x200x50 in FP64 273 and 266 us).  Finding that lane costs the mixed forms with
+// few tiles more than the lines do (100x100x50 in BF16 61 us, 63 so).
+template <int St, int AH> constexpr bool kShare = St == ST_F64 || AH == 2;
 struct SweepLane {
     int t, a, b, ab;  // ab: first step of the column, out of reach for a lane without one
     size_t c0;        // the column's cell in layer 0
@@ -463,6 +469,16 @@ struct SweepLane {
     }
     __device__ __forceinline__ bool active(const TileGeom &G, int s) const {
         return (unsigned)(s - ab) < (unsigned)G.nz;
+    }
+    // the lane whose slot of step s this lane loads: its own, an idle one the
+    // first lane's that has a cell (SHARE) or lane 0's
+    template <bool SHARE>
+    __device__ __forceinline__ int load_lane(const TileGeom &G, int s) const {
+        const bool act = active(G, s);
+        if constexpr (!SHARE) return act ? t : 0;
+        const uint64_t m = __ballot(act);
+        const int first = m ? __ffsll((unsigned long long)m) - 1 : 0;
+        return act ? t : first;
     }
     // the grid cell of a slot (cell 0 for an idle one)
     __device__ __forceinline__ size_t cell(const TileGeom &G, int s) const {
@@ -491,7 +507,7 @@ __global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__re
     } ring[AH];
     auto fetch = [&](int s, Slot &Q) {
         const int sc = min(s, ns - 1);
-        Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + (L.active(G, sc) ? t : 0));
+        Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + L.template load_lane<kShare<St, AH>>(G, sc));
         const double *rg = r + 3 * L.cell(G, sc);
         Q.r[0] = rg[0]; Q.r[1] = rg[1]; Q.r[2] = rg[2];
     };
@@ -585,9 +601,7 @@ __global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__r
     } ring[AH];
     const TD *dpl = dp ? dp : (const TD *)wq;  // without dp a load that is not used
     auto fetch = [&](int s, Slot &Q) {
-        const int sc = max(s, 0);
-        const bool act = L.active(G, sc);
-        const int tl = act ? t : 0;
+        const int sc = max(s, 0), tl = L.template load_lane<kShare<St, AH>>(G, sc);
         Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + tl);
         const T *w = wt + (size_t)sc * 64 + tl;
         Q.w[0] = w[0]; Q.w[1] = w[S]; Q.w[2] = w[2 * S];
