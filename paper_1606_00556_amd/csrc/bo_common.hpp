@@ -279,6 +279,32 @@ __device__ inline double block_sum(double v, double *sh) {
     return r;
 }
 
+// ---- sweeps ------------------------------------------------------------------------
+// Steps 0 .. n - 1 over a ring of AH buffers, each filled once, AH steps ahead: the
+// whole rounds without a test inside (one that may leave the loop makes every step of
+// the unrolled round wait for all loads: 10 % of a two-phase sweep), the last two rounds
+// with.
+template <int AH, typename Buf, typename Step, typename Fetch>
+__device__ __forceinline__ void ring_steps(int n, Buf (&R)[AH], Step step, Fetch fetch) {
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(u, R[u]);
+    int q = 0;
+    for (; q + 2 * AH <= n; q += AH)
+#pragma unroll
+        for (int u = 0; u < AH; u++) {
+            step(q + u, R[u]);
+            fetch(q + u + AH, R[u]);
+        }
+#pragma unroll
+    for (int u = 0; u < AH; u++) {
+        if (q + u < n) step(q + u, R[u]);
+        if (q + u + AH < n) fetch(q + u + AH, R[u]);
+    }
+#pragma unroll
+    for (int u = 0; u + 1 < AH; u++)
+        if (q + AH + u < n) step(q + AH + u, R[u]);
+}
+
 // ---- process-lifetime scratch ------------------------------------------------------
 // Grow-only device buffers for temporaries of host wrappers that read a result
 // back after the buffer's last reader (scan_counts), so that a buffer is idle

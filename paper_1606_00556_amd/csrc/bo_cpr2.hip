@@ -300,30 +300,6 @@ struct Step2 {
     double f[16];
     double v0, v1, d;
 };
-// Steps 0 .. n - 1 over a ring of AH buffers, each filled once: the whole rounds
-// without a test inside (one that may leave the loop makes every step of the
-// unrolled round wait for all loads: 10 % of a sweep), the last two rounds with.
-template <int AH, typename Step, typename Fetch>
-__device__ __forceinline__ void ring_steps(int n, Step2 (&R)[AH], Step step, Fetch fetch) {
-#pragma unroll
-    for (int u = 0; u < AH; u++) fetch(u, R[u]);
-    int q = 0;
-    for (; q + 2 * AH <= n; q += AH)
-#pragma unroll
-        for (int u = 0; u < AH; u++) {
-            step(q + u, R[u]);
-            fetch(q + u + AH, R[u]);
-        }
-#pragma unroll
-    for (int u = 0; u < AH; u++) {
-        if (q + u < n) step(q + u, R[u]);
-        if (q + u + AH < n) fetch(q + u + AH, R[u]);
-    }
-#pragma unroll
-    for (int u = 0; u + 1 < AH; u++)
-        if (q + AH + u < n) step(q + AH + u, R[u]);
-}
-
 // forward sweep: u (slot order) from r (cell order)
 template <int AH, bool NT>
 __global__ void __launch_bounds__(64) k_ilu2_forward(Tile2 T, const double2 *__restrict__ Ff,

@@ -24,6 +24,7 @@
 // bo_cpr_spmv multiplies by the handle's copy of the coefficients, and
 // bo_scalar_solve runs GMRES(m) (or FGMRES) with it.
 #include <cmath>
+#include <type_traits>
 #include "bo_cpr.hpp"
 
 namespace bo {
@@ -120,9 +121,11 @@ __global__ void __launch_bounds__(64) k_ras_factor(RasGeom T, const double *__re
 // waits for a step's loads leave the later ones in flight (vector memory
 // operations return in order).  Bound by the step chain (two shuffles, three
 // products, backward a division) and, from a few hundred tiles on, by HBM.
-// 125x125x47, both sweeps: 41.7 us with two steps in flight, 33.7 / 32.6 / 32.4
-// us with 4 / 6 / 8; 500x500x100: 1189, 1159 / 1164 / 1153 us (with unconditional
-// stores, idle lanes writing to idle slots, 1258 us).
+// 125x125x47, both sweeps: 39.2 us with two steps in flight, 30.9 / 29.1 / 29.1 us
+// with 3 / 4 / 6; 500x500x100: with unconditional stores, idle lanes writing to
+// idle slots, 1258 us, and 1159.  Tiles of fewer steps than the ring holds load
+// nothing but repeats beyond them (1000x1000x1 in tiles of 1x1, one step: 430, 471,
+// 638 and 1168 us with 1 / 2 / 3 / 6; of 2x2, three steps: 223, 216, 356 with 2 / 3 / 6).
 constexpr int kRasAhead = 6;
 struct RasStep {
     double2 f0, f1;
@@ -151,7 +154,7 @@ __global__ void __launch_bounds__(64) k_ras_forward(RasGeom T, const double2 *__
         F.v = r[act ? c0 + (size_t)(sc - ab) * nxy : 0];
     };
     double yp = 0.0;  // this lane's y of the previous step (the -z neighbour)
-    auto step = [&](int s, RasStep &F) {
+    auto step = [&](int s, const RasStep &F) {
         const double yx = __shfl(yp, lx, 64), yy = __shfl(yp, ly, 64);
         double y = F.v;
         if (s - ab > 0) y = y - F.f0.x * yp;
@@ -160,16 +163,8 @@ __global__ void __launch_bounds__(64) k_ras_forward(RasGeom T, const double2 *__
         const bool act = active(s);
         yp = act ? y : 0.0;
         if (act) Yt[(size_t)s * 64] = yp;
-        fetch(s + AH, F);
     };
-#pragma unroll
-    for (int u = 0; u < AH; u++) fetch(u, ring[u]);
-    for (int s0 = 0; s0 < T.ns; s0 += AH)
-#pragma unroll
-        for (int u = 0; u < AH; u++) {
-            if (s0 + u >= T.ns) return;
-            step(s0 + u, ring[u]);
-        }
+    ring_steps<AH>(T.ns, ring, step, fetch);
 }
 
 // backward sweep: x (cell order) from y (slot order); only lanes with one of the
@@ -195,7 +190,7 @@ __global__ void __launch_bounds__(64) k_ras_backward(RasGeom T, const double2 *_
         F.v = Yt[(size_t)sc * 64 + tl];
     };
     double xp = 0.0;  // this lane's x of the later step (the +z neighbour)
-    auto step = [&](int s, RasStep &F) {
+    auto step = [&](int s, const RasStep &F) {
         const double xx = __shfl(xp, lx, 64), xy = __shfl(xp, ly, 64);
         const bool act = active(s);
         double v = F.v;
@@ -204,17 +199,10 @@ __global__ void __launch_bounds__(64) k_ras_backward(RasGeom T, const double2 *_
         if (s - ab + 1 < T.nz) v = v - F.f1.y * xp;
         xp = act ? v / F.f0.x : 0.0;
         if (act && L.own) x[c0 + (size_t)(s - ab) * nxy] = xp;
-        fetch(s - AH, F);
     };
     const int e = T.ns - 1;
-#pragma unroll
-    for (int u = 0; u < AH; u++) fetch(e - u, ring[u]);
-    for (int s0 = e; s0 >= 0; s0 -= AH)
-#pragma unroll
-        for (int u = 0; u < AH; u++) {
-            if (s0 - u < 0) return;
-            step(s0 - u, ring[u]);
-        }
+    ring_steps<AH>(
+        T.ns, ring, [&](int q, const RasStep &F) { step(e - q, F); }, [&](int q, RasStep &F) { fetch(e - q, F); });
 }
 
 __global__ void k_check_finite1(long long n, const double *__restrict__ v, int32_t *__restrict__ bad) {
@@ -246,11 +234,19 @@ bo_status scalar_spmv(const Grid &g, const double *A, double alpha, const double
 bo_status ras_apply(bo_cpr *pc, const double *r, double *z, hipStream_t s) {
     const RasGeom T = ras_geom(pc);
     const int tiles = T.ntx * T.nty;
-    k_ras_forward<kRasAhead><<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, pc->ilu_w.p);
-    BO_HIP(hipGetLastError());
-    k_ras_backward<kRasAhead><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, pc->ilu_w.p, z);
-    BO_HIP(hipGetLastError());
-    return BO_OK;
+    auto sweeps = [&](auto ah_) -> bo_status {
+        constexpr int AH = decltype(ah_)::value;
+        k_ras_forward<AH><<<tiles, 64, 0, s>>>(T, pc->ilu_f.p, r, pc->ilu_w.p);
+        BO_HIP(hipGetLastError());
+        k_ras_backward<AH><<<tiles, 64, 0, s>>>(T, pc->ilu_b.p, pc->ilu_w.p, z);
+        BO_HIP(hipGetLastError());
+        return BO_OK;
+    };
+    // (a ring of the tile's steps at most)
+    if (T.ns >= kRasAhead) return sweeps(std::integral_constant<int, kRasAhead>{});
+    if (T.ns >= 3) return sweeps(std::integral_constant<int, 3>{});
+    if (T.ns == 2) return sweeps(std::integral_constant<int, 2>{});
+    return sweeps(std::integral_constant<int, 1>{});
 }
 
 static bo_status ras_setup_impl(const bo_grid *grid, const double *coef, const bo_ras_opts *o, bo_cpr *pc,

@@ -66,6 +66,21 @@ def test_ras_apply_matches_oracle(B, tile, overlap):
         assert np.array_equal(to_host(z), ras.apply(r))
 
 
+@pytest.mark.parametrize("tile,overlap", [((1, 1), 0), ((2, 1), 0)])
+def test_ras_sweeps_of_few_steps(B, tile, overlap):
+    """Tiles of one step up to four rounds of the sweeps' ring of loads and every
+    remainder: nz steps with one column a tile, nz + 1 with two."""
+    import torch
+    for nz in range(1, 26):
+        c = cg.pressure_case(5, 4, nz, seed=17)
+        opts = B.bo_ras_default_opts(tile_x=tile[0], tile_y=tile[1], overlap=overlap)
+        pc = B.bo_ras_setup(grid_of(c), to_dev(c.coef.reshape(-1)), opts)
+        r = np.random.default_rng(nz).standard_normal(c.n)
+        z = torch.zeros(c.n, dtype=torch.float64, device="cuda")
+        B.bo_cpr_apply(pc, to_dev(r), z)
+        assert np.array_equal(to_host(z), PR.Ras(c.nx, c.ny, c.nz, c.coef, tile, overlap).apply(r)), nz
+
+
 def test_ras_setup_refusals(B):
     c = cg.pressure_case(9, 7, 3, seed=13)
     coef = to_dev(c.coef.reshape(-1))
