@@ -283,11 +283,11 @@ __device__ inline double block_sum(double v, double *sh) {
 // Steps 0 .. n - 1 over a ring of AH buffers, each filled once, AH steps ahead: the
 // whole rounds without a test inside (one that may leave the loop makes every step of
 // the unrolled round wait for all loads: 10 % of a two-phase sweep), the last two rounds
-// with.
+// with.  No step past the last is loaded: rings that went on loading took up to
+// 2.8 times as long on tiles of few steps.  ring_go: the first AH buffers are filled
+// already.
 template <int AH, typename Buf, typename Step, typename Fetch>
-__device__ __forceinline__ void ring_steps(int n, Buf (&R)[AH], Step step, Fetch fetch) {
-#pragma unroll
-    for (int u = 0; u < AH; u++) fetch(u, R[u]);
+__device__ __forceinline__ void ring_go(int n, Buf (&R)[AH], Step step, Fetch fetch) {
     int q = 0;
     for (; q + 2 * AH <= n; q += AH)
 #pragma unroll
@@ -303,6 +303,12 @@ __device__ __forceinline__ void ring_steps(int n, Buf (&R)[AH], Step step, Fetch
 #pragma unroll
     for (int u = 0; u + 1 < AH; u++)
         if (q + AH + u < n) step(q + AH + u, R[u]);
+}
+template <int AH, typename Buf, typename Step, typename Fetch>
+__device__ __forceinline__ void ring_steps(int n, Buf (&R)[AH], Step step, Fetch fetch) {
+#pragma unroll
+    for (int u = 0; u < AH; u++) fetch(u, R[u]);
+    ring_go<AH>(n, R, step, fetch);
 }
 
 // ---- process-lifetime scratch ------------------------------------------------------

@@ -447,15 +447,14 @@ struct Factors {
 // statically, so one that some paths skip makes later waits take in the next
 // steps' loads too.  (With conditional output stores and two wavefronts
 // joined by two barriers a step took one memory latency whatever the ring's
-// length: 1.17 us backward and 0.57 us forward on one tile, 0.46 us now; both
-// sweeps of a 104x104x31 grid 77.8 -> 54.4 us, of a 100x100x50 grid 115 -> 94
-// us, where 169 tiles on 256 CUs reach 3.4 TB/s.)
+// length: 1.17 us backward and 0.57 us forward on one tile, 0.46 us so; both
+// sweeps of a 104x104x31 grid 76 and now 46 us, of a 100x100x50 grid 112 and 80
+// us, where 169 tiles on 256 CUs reach 4 TB/s.)
 // Idle slots read the data of a lane that has a cell, which is loaded anyway: lane
 // 0's lines, where lane 0 is idle too, are a fifth of a one-layer grid's traffic
-// (both sweeps of 1000x1000x1 in FP64 1045 and now 950 us, in BF16 384 and 346 us;
-// 200x200x50 in FP64 273 and 266 us).  Finding that lane costs the mixed forms with
-// few tiles more than the lines do (100x100x50 in BF16 61 us, 63 so).
-template <int St, int AH> constexpr bool kShare = St == ST_F64 || AH == 2;
+// (both sweeps of 1000x1000x1 in FP64 1045 and 950 us, in BF16 384 and 346 us).
+// Finding that lane costs the mixed forms with few tiles, bound by the chain, more
+// than the lines do (100x100x50 in BF16 55.8 us, 57.1 so).
 struct SweepLane {
     int t, a, b, ab;  // ab: first step of the column, out of reach for a lane without one
     size_t c0;        // the column's cell in layer 0
@@ -507,12 +506,12 @@ __global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__re
     } ring[AH];
     auto fetch = [&](int s, Slot &Q) {
         const int sc = min(s, ns - 1);
-        Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + L.template load_lane<kShare<St, AH>>(G, sc));
+        Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + L.template load_lane<AH == 2>(G, sc));
         const double *rg = r + 3 * L.cell(G, sc);
         Q.r[0] = rg[0]; Q.r[1] = rg[1]; Q.r[2] = rg[2];
     };
     T wp[3] = {0, 0, 0};
-    auto step = [&](int s, Slot &Q) {
+    auto step = [&](int s, const Slot &Q) {
         T wx[3], wy[3];
 #pragma unroll
         for (int c = 0; c < 3; c++) {
@@ -539,16 +538,8 @@ __global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__re
             wp[c] = act ? v[c] : (T)0;
             w[c * S] = wp[c];
         }
-        fetch(s + AH, Q);
     };
-#pragma unroll
-    for (int u = 0; u < AH; u++) fetch(u, ring[u]);
-    for (int s0 = 0; s0 < ns; s0 += AH)
-#pragma unroll
-        for (int u = 0; u < AH; u++) {
-            if (s0 + u >= ns) return;
-            step(s0 + u, ring[u]);
-        }
+    ring_steps<AH>(ns, ring, step, fetch);
 }
 
 // backward sweep: FP64: x_i = E_i^{-1}(y_i - sum_{upper} A_ij x_j); FP32 /
@@ -561,7 +552,7 @@ __global__ void __launch_bounds__(64) k_ilu_forward(TileGeom G, const void *__re
 // is complete once step s is.  Each result goes into the layer's LDS slot (k
 // mod D, 64 x 3 doubles); step s writes layer s + 1 to HBM as tile_y rows of 3
 // tile_x contiguous doubles, three values per lane (lanes beyond the tile's or
-// the grid's columns repeat the tile's first value; up to AH - 1 steps before
+// the grid's columns repeat the tile's first value; up to 2 AH - 1 steps before
 // the first finished layer write the last layer's places, in the ZIN form with
 // the values they hold).  Without staging (STAGE false, where D layers do not fit) every lane
 // writes its 24 bytes at its cell, and the partial lines cost HBM writes of more than twice the output's size.
@@ -601,7 +592,7 @@ __global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__r
     } ring[AH];
     const TD *dpl = dp ? dp : (const TD *)wq;  // without dp a load that is not used
     auto fetch = [&](int s, Slot &Q) {
-        const int sc = max(s, 0), tl = L.template load_lane<kShare<St, AH>>(G, sc);
+        const int sc = max(s, 0), tl = L.template load_lane<AH == 2>(G, sc);
         Q.f.template load<NT>(Ft + (size_t)sc * Fac::kStride * 64 + tl);
         const T *w = wt + (size_t)sc * 64 + tl;
         Q.w[0] = w[0]; Q.w[1] = w[S]; Q.w[2] = w[2 * S];
@@ -633,7 +624,7 @@ __global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__r
         }
     };
     // fl (a constant at each call): write layer s + 1 out
-    auto step = [&](int s, Slot &Q, bool fl) {
+    auto step = [&](int s, const Slot &Q, bool fl) {
         T xx[3], xy[3];
 #pragma unroll
         for (int c = 0; c < 3; c++) {
@@ -684,20 +675,19 @@ __global__ void __launch_bounds__(64) k_ilu_backward(TileGeom G, const void *__r
                 p[2] = ZIN ? Q.z[2] + (double)xp[2] : (double)xp[2];
             }
         }
-        fetch(s - AH, Q);
     };
+    // whole rounds in which no layer is finished yet, then the rest
 #pragma unroll
     for (int u = 0; u < AH; u++) fetch(e - u, ring[u]);
     int s0 = e;
-    for (; s0 - AH >= G.nz - 2; s0 -= AH)  // no layer finished yet
-#pragma unroll
-        for (int u = 0; u < AH; u++) step(s0 - u, ring[u], false);
-    for (; s0 >= 0; s0 -= AH)
+    for (; s0 - AH >= G.nz - 2 && s0 + 1 >= 2 * AH; s0 -= AH)
 #pragma unroll
         for (int u = 0; u < AH; u++) {
-            if (s0 - u < 0) break;
-            step(s0 - u, ring[u], true);
+            step(s0 - u, ring[u], false);
+            fetch(s0 - u - AH, ring[u]);
         }
+    ring_go<AH>(
+        s0 + 1, ring, [&](int q, const Slot &Q) { step(s0 - q, Q, true); }, [&](int q, Slot &Q) { fetch(s0 - q, Q); });
     if constexpr (STAGE) {
         // layer 0, complete with the last step
         double o[3], z[3] = {0.0, 0.0, 0.0};
@@ -903,14 +893,18 @@ inline int stage_layers(const TileGeom &G) {
     return D * kStageBytes <= 32768 ? D : 0;
 }
 
-// One wavefront per tile: up to one per SIMD (1024 tiles) a longer ring of
-// loads pays for its registers (104x104x31, both sweeps: 54.4 us with 4 and 3
-// steps, 58.4 us with 2 and 2, 64.0 us with 6 and 4), beyond that more
-// tiles per SIMD do (400x400x100: 2.16 ms either way, HBM bound).
+// Steps in flight.  The mixed forms' chain is short of loads while every tile has
+// a SIMD of its own (1024 tiles): 100x100x50 in BF16, both sweeps, forward / backward
+// steps 4/3, 3/3, 2/2: 55.8, 57.2, 62.0 us, 104x104x31 in FP32 35.9, 36.3, 39.5 us;
+// with more tiles two are enough (300x300x60 in FP32 449, 449, 442 us).  In FP64 more
+// than two only take registers (104x104x31 4/3, 3/3, 2/2: 49.8, 49.0, 47.4 us;
+// 300x300x60 794, 769, 742 us; 400x400x100 2148, 2174, 2109 us).  Before the loads
+// were static 104x104x31 took 76 us in FP64, 400x400x100 2184.
 constexpr int kFewTiles = 1024, kAheadF = 4, kAheadB = 3;
+template <int St> bool few_tiles(const TileGeom &G) { return St != ST_F64 && G.ntx * G.nty <= kFewTiles; }
 // Factors larger than the last-level cache are read past it: they are gone
 // before the next sweep reads them, and leave it to what the products and the
-// V-cycle read again (400x400x100 in FP64, both sweeps: 2156 and now 2119 us).
+// V-cycle read again (400x400x100 in FP64, both sweeps: 2156 us through it, 2119 past it).
 // Factors that stay in part must not be: 100x100x50 in FP64, 155 MB, forward
 // sweep 41 us cached and 70 us past the cache.
 // What counts is what is read: tiles of 4x4 columns on the same grid store 501 MB of
@@ -919,14 +913,17 @@ template <int St, bool FWD> bool past_cache(const TileGeom &G) {
     typedef Factors<St, FWD> Fac;
     return tile_bytes_read(G.ntx * G.nty, G.tx, G.ty, G.nz, Fac::kCount, sizeof(typename Fac::Raw)) > kCacheBytes;
 }
+template <int St, typename T, int AH>
+void launch_forward_ah(const TileGeom &G, const void *F, const double *r, T *wq, hipStream_t s) {
+    const int nb = G.ntx * G.nty;
+    if (past_cache<St, true>(G)) k_ilu_forward<St, T, AH, true><<<nb, 64, 0, s>>>(G, F, r, wq);
+    else k_ilu_forward<St, T, AH, false><<<nb, 64, 0, s>>>(G, F, r, wq);
+}
 template <int St, typename T>
 void launch_forward(const TileGeom &G, const void *F, const double *r, T *wq, hipStream_t s) {
-    const int nb = G.ntx * G.nty;
-    const bool few = nb <= kFewTiles, nt = past_cache<St, true>(G);
-    if (few && nt) k_ilu_forward<St, T, kAheadF, true><<<nb, 64, 0, s>>>(G, F, r, wq);
-    else if (few) k_ilu_forward<St, T, kAheadF, false><<<nb, 64, 0, s>>>(G, F, r, wq);
-    else if (nt) k_ilu_forward<St, T, 2, true><<<nb, 64, 0, s>>>(G, F, r, wq);
-    else k_ilu_forward<St, T, 2, false><<<nb, 64, 0, s>>>(G, F, r, wq);
+    if constexpr (St != ST_F64)
+        if (few_tiles<St>(G)) return launch_forward_ah<St, T, kAheadF>(G, F, r, wq, s);
+    launch_forward_ah<St, T, 2>(G, F, r, wq, s);
 }
 template <int St, typename T, typename TD, int AH, bool NT, bool ZIN>
 void launch_backward_ah(const TileGeom &G, const void *F, T *wq, const TD *dp, double *out, const double *zin,
@@ -939,10 +936,14 @@ void launch_backward_ah(const TileGeom &G, const void *F, T *wq, const TD *dp, d
 template <int St, typename T, typename TD, bool ZIN>
 void launch_backward_zin(const TileGeom &G, const void *F, T *wq, const TD *dp, double *out, const double *zin,
                          hipStream_t s) {
-    const bool few = G.ntx * G.nty <= kFewTiles, nt = past_cache<St, false>(G);
-    if (few && nt) launch_backward_ah<St, T, TD, kAheadB, true, ZIN>(G, F, wq, dp, out, zin, s);
-    else if (few) launch_backward_ah<St, T, TD, kAheadB, false, ZIN>(G, F, wq, dp, out, zin, s);
-    else if (nt) launch_backward_ah<St, T, TD, 2, true, ZIN>(G, F, wq, dp, out, zin, s);
+    const bool nt = past_cache<St, false>(G);
+    if constexpr (St != ST_F64)
+        if (few_tiles<St>(G)) {
+            if (nt) launch_backward_ah<St, T, TD, kAheadB, true, ZIN>(G, F, wq, dp, out, zin, s);
+            else launch_backward_ah<St, T, TD, kAheadB, false, ZIN>(G, F, wq, dp, out, zin, s);
+            return;
+        }
+    if (nt) launch_backward_ah<St, T, TD, 2, true, ZIN>(G, F, wq, dp, out, zin, s);
     else launch_backward_ah<St, T, TD, 2, false, ZIN>(G, F, wq, dp, out, zin, s);
 }
 template <int St, typename T, typename TD>

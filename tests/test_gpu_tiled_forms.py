@@ -67,6 +67,21 @@ def test_sweeps_at_every_line_of_the_dispatch(B, O, shape, tile, prec):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("shape,tile", [((5, 4), (1, 1)), ((33, 32), (1, 1)), ((6, 4), (3, 2))])
+def test_sweeps_of_few_steps(B, O, shape, tile, prec):
+    """Tiles of one step (four with 3x2 columns) up to four rounds of the sweeps'
+    rings of loads and every remainder, few tiles and more than 1024."""
+    v = np.random.default_rng(77)
+    for nz in range(1, 14):
+        case = case_of((*shape, nz), 78)
+        r = v.standard_normal(3 * case.n)
+        for fpf in (0, 1):
+            _, _, _, _, _, opc, gpc = setup_both(B, O, case, tile=tile, precision=prec, use_amg=0, fpf=fpf)
+            got = run_stage(B, gpc, B.bo_cpr_apply, r, 3 * case.n)
+            assert rel_err_parts(got, opc.apply(r)) <= TOL[prec], nz
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
 @pytest.mark.parametrize("tile", [(32, 2), (1, 64), (21, 1), (22, 1)])
 def test_sweeps_around_the_staging_limit(B, O, tile, prec):
     """Tiles of 21 layers in flight (the last that are staged) and more, with the
